@@ -4,11 +4,13 @@
 // the diagonal; streaming heads visit only the sink tiles and the local band, so whole tiles
 // outside the mask are never loaded.  Only the diagonal tile needs element-wise causal masking.
 //
-// Mapping to CDNA4: a workgroup of eight wavefronts owns 256 consecutive query rows of one head;
-// wavefronts 2t and 2t + 1 own the two 32-row halves of mask tile 4 * block + t.  Two wavefronts
+// Mapping to CDNA4: a workgroup of eight wavefronts works on four units, a unit being one mask tile of queries of one
+// head; wavefronts 2u and 2u + 1 own the two 32-row halves of unit u.  Units are query heads of a group before they
+// are neighbouring query tiles: heads of a group need exactly the same key tiles.  Two wavefronts
 // share each SIMD, so the matrix pipe of one overlaps the softmax arithmetic of the other.  K and
 // V tiles are brought into LDS once per workgroup by direct-to-LDS loads, double buffered, and
-// consumed by all eight wavefronts.  Scores are computed transposed,
+// consumed by all eight wavefronts.  A launch with few query rows has the pairs of wavefronts share out the key tiles
+// of fewer units instead (key slices, see sparse_prefill_kernel).  Scores are computed transposed,
 //   S^T (keys x queries) = K (keys x d) * Q^T (d x queries)          v_mfma_f32_32x32x16
 // so that a lane owns one query column: the softmax reductions over keys stay inside the lane
 // (plus one exchange between the two lane halves), and the exponentiated tile is already in the
@@ -18,6 +20,7 @@
 // transposing LDS read of gfx950 (ds_read_b64_tr_b16), which hands a lane four keys of one channel, so
 // there is no transposition pass and no transposed copy of V.
 #include <algorithm>
+#include <type_traits>
 
 #include "kernels.h"
 
@@ -29,12 +32,11 @@ typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf168_t __attribute__((ext_vector_type(8)));
 typedef float float16_t __attribute__((ext_vector_type(16)));
 
-constexpr int kTile = 64;                          // mask tile = key tile = page
+constexpr int kTileLog2 = 6;
+constexpr int kTile = 1 << kTileLog2;              // mask tile = key tile = page
 constexpr int kPrefillWaves = 8;                   // two per SIMD, each owning 32 query rows
 constexpr int kPrefillThreads = kPrefillWaves * kWave;
-constexpr int kTilesPerBlock = kPrefillWaves / 2;  // mask tiles of queries per workgroup
-constexpr int kRowsPerBlock = kTilesPerBlock * kTile;
-constexpr int kDmaLoads = 16 / kPrefillWaves;      // 1 KiB loads per wave, tile and operand
+constexpr int kPairs = kPrefillWaves / 2;          // wavefront pairs; a pair owns the two halves of a mask tile's rows
 constexpr int kAhead = 4;                          // operand reads in flight ahead of the score products
 constexpr int kKRowBytes = 256;                    // K tile row: 128 x 16 bit = 16 chunks of 16 B
 constexpr int kVRowBytes = 256;                    // V tile row (one key): the same
@@ -125,41 +127,73 @@ __device__ __forceinline__ uint2 lds_read_transposed(const unsigned char* p) {
     return __builtin_bit_cast(uint2, v);
 }
 
-// Work order of the launch.  Workgroup ids go round-robin over the eight XCDs, each with its own L2.
-// Dense heads come first (heaviest query blocks first), streaming heads after.  When the number of
+// Work order of the launch.  Workgroup ids go round-robin over the eight XCDs, each with its own L2, and inside an
+// XCD round-robin over its four shader engines.  Dense heads come first, streaming heads after.  When the number of
 // heads of a class divides 8, an XCD serves a single KV head of that class at a time, so the
 // workgroups resident on it (the query heads of one group, neighbouring query blocks) walk the
 // same K / V tiles together and share them in that L2.
 constexpr int kXcds = 8;
 struct HeadClass {
-    int heads;          // KV heads of this class
-    int slices;         // query-block slices per head spread over XCDs (1 when not swizzled)
-    int swizzled;       // 8 % heads == 0
-    int items_per_xcd;  // workgroups of this class per XCD
+    int heads;            // KV heads of this class
+    int slices;           // XCDs per head (1 when not swizzled)
+    int swizzled;         // 8 % heads == 0
+    int items_per_xcd;    // workgroups of this class per XCD
+    int heads_per_block;  // query heads of a group that share a workgroup (1, 2 or 4)
+    int qtiles_log2;      // log2 of the query tiles a workgroup owns
+    int fold;             // the key slices of the kernel share a unit (and are folded), or each group of waves has its own
+    int blocks_per_seq;   // query blocks of the longest sequence
+    int ordered;          // blocks are dealt out longest walk first over the whole batch (see block_of)
     unsigned char kv_head[64];
 };
 struct PrefillSchedule {
     HeadClass cls[2];  // dense, streaming
-    int qblocks_total; // batch * blocks_per_seq
 };
 
-// Decodes workgroup `li` of XCD `xcd` inside a class.  Returns false for padding workgroups.
-__device__ __forceinline__ bool decode_work(const HeadClass& hc, int n, int qblocks_total, int xcd, int li, int& hk,
-                                            int& hh, int& rank) {
+// Decodes workgroup `li` of XCD `xcd` inside a class of workgroups, `n` of them per (KV head, query block): KV head hk,
+// group of query heads hg, and the position of the query block in the order of blocks.
+__device__ __forceinline__ void decode_work(const HeadClass& hc, int n, int xcd, int li, int& hk, int& hg, int& rank) {
     int hidx;
     if (hc.swizzled) {
         hidx = xcd % hc.heads;
-        const int slice = xcd / hc.heads;
-        hh = li % n;
-        rank = (li / n) * hc.slices + slice;
+        hg = li % n;
+        rank = (li / n) * hc.slices + xcd / hc.heads;
     } else {
         const int t = li * kXcds + xcd;
-        hh = t % n;
+        hg = t % n;
         hidx = (t / n) % hc.heads;
         rank = t / (n * hc.heads);
     }
     hk = hc.kv_head[hidx];
-    return rank < qblocks_total;
+}
+
+// Sum over the wave of a value below 2^24 per lane and in total (exact in fp32).
+__device__ __forceinline__ int wave_count(int x) { return (int)rows4_sum(row16_sum((float)x)); }
+
+// The rank-th query block of the batch, blocks ordered by their position inside their sequence, farthest first (the
+// longest walks start first and the short ones fill in behind them); false past the last one.  One lane per sequence
+// (batch <= 64) holds the blocks [lo, hi) its queries span.  Nothing is left out in this order, and that matters
+// beyond the launches it saves: workgroups go to the shader engines of an XCD in strict turn, so an order with gaps
+// of a fixed stride (one long sequence among fifteen short ones, each block index of all sixteen in a row) puts the
+// real work of a launch on one of the four (sixteen prompts of 77 .. 3001 tokens: 745 us, in this order 190).
+__device__ __forceinline__ bool block_of(int rank, int lo, int hi, int& b, int& qblk) {
+    const int n = max(0, hi - lo);
+    auto at_or_past = [&](int level) { return wave_count(min(max(hi - level, 0), n)); };
+    if (rank >= wave_count(n)) return false;
+    int below = 0, above = __builtin_amdgcn_readfirstlane((int)wave_max((float)(n > 0 ? hi : 0)));
+    while (above - below > 1) {  // largest level with more than `rank` blocks at or past it
+        const int mid = (below + above) / 2;
+        if (at_or_past(mid) > rank)
+            below = mid;
+        else
+            above = mid;
+    }
+    const int i = rank - at_or_past(below + 1);
+    const bool member = lo <= below && below < hi;
+    const unsigned long long members = __ballot(member);
+    const unsigned long long lower = (1ull << (threadIdx.x % kWave)) - 1ull;
+    b = __builtin_ctzll(__ballot(member && __popcll(members & lower) == i));
+    qblk = below;
+    return true;
 }
 
 // General block mask (Sec. 3.1, Sec. 3.4): per mask and query tile, the ascending list of kept key
@@ -173,33 +207,42 @@ struct PrefillMask {
     int rows_per_mask;
     int* blk_list;            // merged lists; the list of a workgroup starts at row_ptr[its first row]
     int* blk_count;           // [num_masks][batch][blocks_per_seq]
+    int blocks_per_seq;
 };
+// A step of a walk that the four query tiles of a workgroup share against a step in which each takes a tile of its own
+// (four times the staging): 2.0 us against 3.0.
+constexpr int kSharedWalkCost = 2, kOwnWalkCost = 3;
 constexpr int kKeepShift = 24;  // list entry = key tile | keep bits << 24
 
 __global__ __launch_bounds__(kWave) void merge_mask_rows_kernel(PrefillMask mk, const int* __restrict__ cu_seqlens,
-                                                                int batch, int blocks_per_seq) {
+                                                                int batch) {
     extern __shared__ unsigned char keep_bits[];  // one byte per key tile of the sequence
     const int qblk = blockIdx.x, b = blockIdx.y, m = blockIdx.z, lane = threadIdx.x;
     const int len = cu_seqlens[b + 1] - cu_seqlens[b];
     const int n_tiles = ceil_div(len, kTile);
-    int* count = mk.blk_count + ((size_t)m * batch + b) * blocks_per_seq + qblk;
-    const int iq0 = qblk * kTilesPerBlock;
+    int* count = mk.blk_count + ((size_t)m * batch + b) * mk.blocks_per_seq + qblk;
+    const int iq0 = qblk * kPairs;
     if (iq0 >= n_tiles) {
         if (lane == 0) *count = 0;
         return;
     }
-    const int rows = min(kTilesPerBlock, n_tiles - iq0);
+    const int rows = min(kPairs, n_tiles - iq0);
     const int r0 = m * mk.rows_per_mask + mk.q_tile_start[b] + iq0;
     const int last = min(iq0 + rows, n_tiles);  // key tiles the block can keep: [0, last)
     for (int j = lane; j < last; j += kWave) keep_bits[j] = 0;
     __builtin_amdgcn_s_waitcnt(0);
     __builtin_amdgcn_wave_barrier();
+    int longest = 0;
     for (int t = 0; t < rows; ++t) {  // one row at a time: no two lanes touch the same byte
         const int lo = mk.row_ptr[r0 + t], hi = mk.row_ptr[r0 + t + 1];
-        for (int e = lo + lane; e < hi; e += kWave) {
-            const int j = mk.cols[e];
-            if (j >= 0 && j <= iq0 + t) keep_bits[j] |= (unsigned char)(1u << t);
+        int kept = 0;
+        for (int e0 = lo; e0 < hi; e0 += kWave) {
+            const int j = mk.cols[min(e0 + lane, hi - 1)];
+            const bool live = e0 + lane < hi && j >= 0 && j <= iq0 + t;
+            if (live) keep_bits[j] |= (unsigned char)(1u << t);
+            kept += __popcll(__ballot(live));
         }
+        longest = max(longest, kept);
         __builtin_amdgcn_s_waitcnt(0);
         __builtin_amdgcn_wave_barrier();
     }
@@ -212,7 +255,8 @@ __global__ __launch_bounds__(kWave) void merge_mask_rows_kernel(PrefillMask mk, 
         if (bits) dst[total + __popcll(live & ((1ull << lane) - 1ull))] = j | (int)(bits << kKeepShift);
         total += __popcll(live);
     }
-    if (lane == 0) *count = total;
+    // negative: the four rows keep such different tiles that a walk of its own for each is quicker
+    if (lane == 0) *count = longest * kOwnWalkCost < total * kSharedWalkCost ? -1 - total : total;
 }
 
 template <class T> struct Ones;
@@ -224,34 +268,77 @@ enum PrefillMode { kPlain = 0, kMasked = 1, kPaged = 2 };
 // BITS: width of the rows in the pages (16, or 8 / 4 for quantised pages, kPaged only).  Quantised tiles cannot take
 // the direct-to-LDS path: their codes travel through registers, are turned into the layer's 16-bit type as
 // code * scale + zero (fp32, then rounded) and are stored to the same LDS places the direct loads would fill.
-template <class T, int MODE, int BITS = 16>
+//
+// SL: key slices.  The four wavefront pairs of a workgroup are (query heads) x (query tiles) x (key slices): with
+// one slice all pairs walk the same key tiles; with two or four, slice s of a unit takes every SL-th tile of the walk
+// and the slices are folded through LDS at the end.  A launch with few query rows (a short prompt, a chunk over a long
+// history) then has SL times the workgroups, each with a walk SL times shorter, for SL times the staging per step
+// (see choose_slices).
+template <class T, int MODE, int BITS, int SL>
 __global__ __launch_bounds__(kPrefillThreads, 512 / kPrefillThreads) void sparse_prefill_kernel(
     LayerParams lp, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
-    const int* __restrict__ cu_seqlens, int batch, int blocks_per_seq, uint16_t* __restrict__ out,
+    const int* __restrict__ cu_seqlens, int batch, uint16_t* __restrict__ out,
     float* __restrict__ lse_out, int total_tokens, PrefillSchedule sched, PrefillMask mk, PrefillPaged pg) {
     constexpr bool MASKED = MODE == kMasked, PAGED = MODE == kPaged, QUANT = BITS != 16;
     static_assert(!QUANT || PAGED, "quantised rows live in pages");
-    // Two stages of (K tile, V tile).  Four separate arrays, and a loop unrolled over the two stages,
-    // so that the compiler can tell the tile being read from the tile being filled and does not wait
-    // for the loads in flight before every operand read.
-    __shared__ __attribute__((aligned(1024))) unsigned char k_lds0[kKTileBytes];
-    __shared__ __attribute__((aligned(1024))) unsigned char k_lds1[kKTileBytes];
-    __shared__ __attribute__((aligned(1024))) unsigned char v_lds0[kVTileBytes];
-    __shared__ __attribute__((aligned(1024))) unsigned char v_lds1[kVTileBytes];
+    static_assert(SL == 1 || SL == 2 || (SL == 4 && !QUANT), "slices");
+    // One or two slices: two stages of (K tiles, V tiles).  Four separate arrays, and a loop unrolled over the two
+    // stages, so that the compiler can tell the tile being read from the tile being filled and does not wait
+    // for the loads in flight before every operand read.  Four slices: 64 KiB of K and 64 KiB of V are one stage;
+    // K is refilled while V is in use and the other way round.
+    constexpr bool kOneStage = SL == 4;
+    constexpr int kSpare = kOneStage ? 16 : SL * kKTileBytes;
+    __shared__ __attribute__((aligned(1024))) unsigned char k_lds0[SL * kKTileBytes];
+    __shared__ __attribute__((aligned(1024))) unsigned char k_lds1[kSpare];
+    __shared__ __attribute__((aligned(1024))) unsigned char v_lds0[SL * kVTileBytes];
+    __shared__ __attribute__((aligned(1024))) unsigned char v_lds1[kSpare];
+    __shared__ float2 fold_ml[SL == 1 ? 1 : kPrefillWaves][32];  // (maximum, sum) of a wavefront's rows
+    __shared__ int walk_len[SL == 1 ? 1 : kPrefillWaves];
 
-    // heaviest query blocks first; see PrefillSchedule for the XCD-aware order
-    const int xcd = blockIdx.x % kXcds;
-    int li = blockIdx.x / kXcds, hk, hh, rank;
-    bool real;
-    if (li < sched.cls[0].items_per_xcd) {
-        real = decode_work(sched.cls[0], lp.group, sched.qblocks_total, xcd, li, hk, hh, rank);
-    } else {
-        li -= sched.cls[0].items_per_xcd;
-        real = decode_work(sched.cls[1], lp.group, sched.qblocks_total, xcd, li, hk, hh, rank);
+    // The arguments fill eight 64-byte lines that the code below wants in dependent rounds, each a miss of the scalar
+    // cache in a new workgroup; one word of every line is requested here, together.
+#if defined(__HIP_DEVICE_COMPILE__)
+    {
+        typedef const int __attribute__((address_space(4))) * kernarg_words;
+        const kernarg_words args = (kernarg_words)__builtin_amdgcn_kernarg_segment_ptr();
+        static_assert(sizeof(LayerParams) + sizeof(PrefillSchedule) + sizeof(PrefillMask) + sizeof(PrefillPaged) + 8 * sizeof(void*) >
+                      112 * sizeof(int), "the argument block must reach the last line touched");
+        const int a0 = args[0], a1 = args[16], a2 = args[32], a3 = args[48], a4 = args[64], a5 = args[80], a6 = args[96],
+                  a7 = args[112];
+        asm volatile("" ::"s"(a0), "s"(a1), "s"(a2), "s"(a3), "s"(a4), "s"(a5), "s"(a6), "s"(a7));
     }
-    if (!real) return;
-    const int h = hk * lp.group + hh;
-    const int b = rank % batch;
+#endif
+
+    // heaviest query blocks first; see HeadClass for the XCD-aware order
+    const int xcd = blockIdx.x % kXcds;
+    int li = blockIdx.x / kXcds, hk, hg, rank;
+    const bool second = li >= sched.cls[0].items_per_xcd;
+    if (second) li -= sched.cls[0].items_per_xcd;
+    const int heads_per_block = second ? sched.cls[1].heads_per_block : sched.cls[0].heads_per_block;
+    const int qtiles_log2 = second ? sched.cls[1].qtiles_log2 : sched.cls[0].qtiles_log2;
+    const bool fold = SL > 1 && (second ? sched.cls[1].fold : sched.cls[0].fold);
+    const int blocks_per_seq = second ? sched.cls[1].blocks_per_seq : sched.cls[0].blocks_per_seq;
+    decode_work(second ? sched.cls[1] : sched.cls[0], lp.group / heads_per_block, xcd, li, hk, hg, rank);
+    int b, qblk = 0;
+    if (second ? sched.cls[1].ordered : sched.cls[0].ordered) {
+        const int i = min((int)(threadIdx.x % kWave), batch - 1);
+        const int fresh = cu_seqlens[i + 1] - cu_seqlens[i];
+        const int past = PAGED ? pg.kv.seq_lens[i] - (pg.k_new ? 0 : fresh) : 0;
+        const bool mine = (int)(threadIdx.x % kWave) < batch && fresh > 0;
+        const int rows_log2 = kTileLog2 + qtiles_log2;
+        const int lo = past >> rows_log2, hi = mine ? ((past + fresh - 1) >> rows_log2) + 1 : 0;
+        if (batch == 1) {
+            b = 0;
+            qblk = __builtin_amdgcn_readfirstlane(hi) - 1 - rank;
+            if (qblk < __builtin_amdgcn_readfirstlane(lo)) return;
+        } else {
+            if (!block_of(rank, lo, hi, b, qblk)) return;
+            b = __builtin_amdgcn_readfirstlane(b);
+        }
+    } else {
+        if (rank >= blocks_per_seq * batch) return;
+        b = rank % batch;
+    }
     // start: row of the sequence's first query in q / out; len: keys of the sequence; first: position of
     // that first query (0 unless the keys come from a paged cache that already holds earlier tokens)
     const int start = cu_seqlens[b];
@@ -259,37 +346,257 @@ __global__ __launch_bounds__(kPrefillThreads, 512 / kPrefillThreads) void sparse
     const int cached = PAGED ? pg.kv.seq_lens[b] : 0;
     const int len = PAGED ? (pg.k_new ? cached + (cu_seqlens[b + 1] - start) : cached) : cu_seqlens[b + 1] - start;
     const int first = PAGED ? len - (cu_seqlens[b + 1] - start) : 0;
-    const int qblk = first / kRowsPerBlock + blocks_per_seq - 1 - rank / batch;
-    if (qblk * kRowsPerBlock >= len) return;
+    const int qtiles = 1 << qtiles_log2;  // query tiles of the workgroup
+    if (!(second ? sched.cls[1].ordered : sched.cls[0].ordered))
+        qblk = (first >> (kTileLog2 + qtiles_log2)) + blocks_per_seq - 1 - rank / batch;
+    const int iq0 = qblk << qtiles_log2;
+    if (iq0 * kTile >= len) return;
     if (PAGED && first >= len) return;  // a sequence without queries in this chunk
 
-    const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+    const int tid = threadIdx.x, lane = tid % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int n = lane % 32, half = lane / 32;
+    // This wave's pair: the slice of the staging space it works from, and its (query tile, query head).  Folded, the
+    // slices of a workgroup hold different key tiles of the same units; otherwise each slice walks for units of its own.
+    constexpr int kSliceUnits = kPairs / SL;
+    const int slice = (wave / 2) % SL, unit = wave / 2 / SL;
+    const int own = SL > 1 && !fold ? slice * kSliceUnits + unit : unit;
+    const int qt = own & (qtiles - 1);
+    const int h = hk * lp.group + hg * heads_per_block + (own >> qtiles_log2);
     const bool streaming = (lp.streaming_mask >> hk) & 1ull;
-    const int iq = qblk * kTilesPerBlock + wave / 2;  // this wave's mask tile; the wave owns one half of its rows
+    const int iq = iq0 + qt;             // this wave's mask tile; the wave owns one half of its rows
     const int row0 = (wave % 2) * 32;    // first row of the wave inside the mask tile
     const int n_qtiles = ceil_div(len, kTile);
-    const int iq_last = min(qblk * kTilesPerBlock + kTilesPerBlock - 1, n_qtiles - 1);  // last mask tile of the block that holds rows
     const bool wave_has_rows = iq * kTile + row0 < len && iq * kTile + row0 + 32 > first;
-
-    // key tiles the block visits: [0, sink_end) and [band_begin, iq_last]
+    // query tiles that share this wave's walk, and the key tiles it visits: [0, sink_end) and [band_begin, iq_last]
+    const int iq_first = iq0 + (SL > 1 && !fold ? (slice * kSliceUnits) & (qtiles - 1) : 0);
+    const int iq_last = min(iq_first + (SL > 1 ? min(qtiles, kSliceUnits) : qtiles) - 1, n_qtiles - 1);
     int sink_end, band_begin;
     if (streaming) {
-        band_begin = max(0, qblk * kTilesPerBlock - lp.local_pages + 1);
+        band_begin = max(0, iq_first - lp.local_pages + 1);
         sink_end = min(lp.sink_pages, band_begin);
     } else {
         band_begin = 0;
         sink_end = 0;
     }
-    int n_visit = sink_end + (iq_last - band_begin + 1);
-    // a listed mask replaces the closed form: the merged list of this workgroup's four query tiles
+    int n_visit = iq_first <= iq_last ? sink_end + (iq_last - band_begin + 1) : 0;  // 0: past the end of the sequence
+    // a listed mask replaces the closed form: the merged list of the query tiles of the walk, or, when it has a single
+    // one, the caller's row itself (its entries above the tile's own index are cut off)
     const int* lst = nullptr;
     if (MASKED) {
         const int m = mk.head_mask[h];
-        if (m >= 0) {
-            lst = mk.blk_list + mk.row_ptr[m * mk.rows_per_mask + mk.q_tile_start[b] + qblk * kTilesPerBlock];
-            n_visit = mk.blk_count[((size_t)m * batch + b) * blocks_per_seq + qblk];
+        // Two launches share the blocks of a merged mask: the second takes those that are quicker row by row, the first the
+        // others and the analytic patterns.  (A workgroup has one head and one merged list: all of it leaves or none.)
+        const int merged =
+            mk.blk_list && m >= 0 ? mk.blk_count[((size_t)m * batch + b) * mk.blocks_per_seq + qblk] : 0;
+        if (mk.blk_list && (merged < 0) != (SL > 1)) return;
+        if (m >= 0 && iq_first <= iq_last) {
+            const int row = m * mk.rows_per_mask + mk.q_tile_start[b] + iq_first;
+            if (SL == 1) {
+                lst = mk.blk_list + mk.row_ptr[row];
+                n_visit = merged;
+            } else {
+                const int lo = mk.row_ptr[row];
+                lst = mk.cols + lo;
+                n_visit = max(0, mk.row_ptr[row + 1] - lo);
+                if (n_visit > 0 && lst[n_visit - 1] > iq) {
+                    int below = 0;
+                    while (below < n_visit) {
+                        const int mid = (below + n_visit) / 2;
+                        if (lst[mid] <= iq)
+                            below = mid + 1;
+                        else
+                            n_visit = mid;
+                    }
+                }
+            }
         }
+    }
+
+    float16_t acc[4];
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[db][i] = 0.f;
+    float m_run = -INFINITY, l_run = 0.f;  // running maximum (scaled, base 2) and sum of this lane's query row
+    // The score products start from -m_run instead of 0 (the accumulator input of the first product), so a
+    // tile whose maxima do not exceed the running ones needs no subtraction before exp2; 0 while m_run = -inf.
+    float16_t neg_m;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) neg_m[i] = 0.f;
+
+    // ---- staging: the waves of a slice bring in its tile, two direct-to-LDS loads of 1 KiB per wave, operand and slice
+    // contiguous keys: tile jt starts jt * 64 rows after the sequence's first row; paged keys: tile jt is the
+    // slab of (its page, hk) in the pool the head lives in, rows 256 bytes apart; keys of a chunk that has not
+    // been written back: row u - cached of the chunk's own K / V
+    const bool ring = PAGED && in_stream_pool(lp, pg.kv, hk);  // a streaming head kept in its bounded pool
+    const int heads_in_pool = PAGED ? (ring ? pg.kv.stream_heads : pg.kv.pool_heads) : lp.Hkv;
+    constexpr size_t kSlabBytes = slab_chunks(kTile, BITS) * 16;  // one (page, head) of a pool
+    const size_t slab_in_page = PAGED ? (size_t)pool_rank(lp, pg.kv, hk, ring) * (kSlabBytes / 2) : 0;  // in 16-bit units
+    const uint16_t* kbase = PAGED ? reinterpret_cast<const uint16_t*>(ring ? pg.kv.k_stream : pg.kv.k_pool) + slab_in_page
+                                  : k + ((size_t)start * lp.Hkv + hk) * kHeadDim;
+    const uint16_t* vbase = PAGED ? reinterpret_cast<const uint16_t*>(ring ? pg.kv.v_stream : pg.kv.v_pool) + slab_in_page
+                                  : v + ((size_t)start * lp.Hkv + hk) * kHeadDim;
+    const int* page_row = !PAGED ? nullptr
+                          : ring ? pg.kv.ring_table + (size_t)b * pg.kv.ring
+                                 : pg.kv.page_table + (size_t)b * pg.kv.max_pages;
+    // page of key tile jt, for tiles that hold cached keys (0 otherwise: never used)
+    auto page_of = [&](int jt) {
+        if (!PAGED || jt * kTile >= cached) return 0;
+        return page_row[ring ? ring_slot(lp, jt) : jt];
+    };
+    // The waves of a slice share out its tile: wave w of them takes rows 8 SL w .. + 8 SL - 1, four rows per load, and
+    // lane `lane` of load i fills position lane % 16 of row 8 SL w + 4 i + lane / 16.  Addresses are a wave-uniform
+    // 64-bit base (scalar arithmetic) plus a 32-bit lane offset that does not depend on the tile, except in the last
+    // tile of a sequence, where rows past the end read the last row again (finite values; their softmax weights
+    // are 0).  Sixteen rows on the permutation of K repeats itself, four rows on that of V.
+    constexpr int kLoads = 2 * SL;  // 1 KiB loads per wave and operand
+    constexpr int kOfs = kLoads < 4 ? kLoads : 4;
+    const unsigned seq_row_bytes = (unsigned)__builtin_amdgcn_readfirstlane(lp.Hkv * kHeadDim * 2);  // [token][Hkv][D]
+    const unsigned k_row_bytes = PAGED ? kHeadDim * 2u : seq_row_bytes;
+    const unsigned long long k_page_bytes = (unsigned long long)heads_in_pool * kSlabBytes;
+    const int wave_row0 = (unit * 2 + wave % 2) * (8 * SL);
+    const int krow0 = wave_row0 + lane / 16;  // row of load 0; load i takes row + 4 i
+    unsigned kofs[kOfs];
+#pragma unroll
+    for (int i = 0; i < kOfs; ++i)
+        kofs[i] = (unsigned)(krow0 + 4 * i) * k_row_bytes + k_chunk_pos(krow0 + 4 * i, lane % 16) * 16;  // an involution
+    const unsigned vofs = (unsigned)krow0 * k_row_bytes + v_chunk_pos(krow0, lane % 16) * 16;           // likewise
+    const unsigned lds_slice = (unsigned)slice * kKTileBytes;
+    const unsigned lds_wave = (unsigned)__builtin_amdgcn_readfirstlane(lds_slice + wave_row0 * kKRowBytes);
+    const unsigned long long kbase_u = uniform64((unsigned long long)kbase), vbase_u = uniform64((unsigned long long)vbase);
+    // the chunk's own rows, addressed from its first token (the row of position `cached`)
+    const unsigned long long knew_u =
+        uniform64((unsigned long long)(PAGED && pg.k_new ? pg.k_new + ((size_t)start * lp.Hkv + hk) * kHeadDim : nullptr));
+    const unsigned long long vnew_u =
+        uniform64((unsigned long long)(PAGED && pg.v_new ? pg.v_new + ((size_t)start * lp.Hkv + hk) * kHeadDim : nullptr));
+    const int len_u = __builtin_amdgcn_readfirstlane(len), cached_u = __builtin_amdgcn_readfirstlane(cached);
+    // quantised rows on their way through registers: per load the codes of this lane's 16-byte place (8 channels), the
+    // (scale, zero) pair of the row, and whether the lane's row comes from the pages at all
+    constexpr int kRowCodeBytes = kHeadDim * BITS / 8, kPlaceCodeBytes = BITS;  // per row; per 8 channels
+    struct Staged {
+        uint2 codes[kLoads];
+        uint32_t sz[kLoads];
+        int from, left;  // of the tile in flight: rows that come from the pages; rows it has
+    };
+    Staged staged_k, staged_v;
+    staged_k.from = staged_v.from = 0;
+    staged_k.left = staged_v.left = 1;
+    // Requests this wave's share of key tile jt: of K, of V or of both, then in turn (K after K and V after V was 3 % slower
+    // on a prompt of 65536 tokens: the first rows of V come before the last rows of K are asked for).  kd, vd: arrays of
+    // the stage.
+    auto fetch = [&](auto operands, unsigned char* kd, unsigned char* vd, int jt, int phys) {
+        constexpr bool K = decltype(operands)::value & 1, V = decltype(operands)::value & 2;
+        jt = __builtin_amdgcn_readfirstlane(jt);
+        const unsigned lds_k = lds_address(kd) + lds_wave, lds_v = lds_address(vd) + lds_wave;
+        // Rows at or past the sequence length must not be read as they are: a page may hold anything there, and
+        // although their weights are 0 a non-finite value would still poison the second product.
+        const int rows_left = len_u - jt * kTile;
+        // rows of the tile below `from_pages` come from the page, the others from the chunk's own K / V: row r of the
+        // tile is then the chunk's token jt * 64 + r - cached
+        const int from_pages = PAGED ? cached_u - jt * kTile : kTile;
+        if (!QUANT && (!PAGED || from_pages >= min(rows_left, kTile))) {
+            const unsigned long long ktile =
+                PAGED ? kbase_u + (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane(phys) * k_page_bytes
+                      : kbase_u + (unsigned long long)jt * (kTile * k_row_bytes);
+            const unsigned long long vtile = ktile - kbase_u + vbase_u;  // K and V are laid out alike
+#pragma unroll
+            for (int i = 0; i < kLoads; ++i) {
+                const unsigned ldk = __builtin_amdgcn_readfirstlane(lds_k + i * 1024);
+                const unsigned ldv = __builtin_amdgcn_readfirstlane(lds_v + i * 1024);
+                if (rows_left < kTile) {
+                    const int row = krow0 + 4 * i;
+                    const unsigned at = (unsigned)min(row, rows_left - 1) * k_row_bytes;
+                    if (K) dma_load16(ktile, at + k_chunk_pos(row, lane % 16) * 16, ldk);
+                    if (V) dma_load16(vtile, at + v_chunk_pos(row, lane % 16) * 16, ldv);
+                } else {
+                    if (K) dma_load16(ktile + (unsigned)(i / 4) * (16u * k_row_bytes), kofs[i % 4], ldk);
+                    if (V) dma_load16(vtile + (unsigned)i * (4u * k_row_bytes), vofs, ldv);
+                }
+            }
+        } else if (PAGED && from_pages < min(rows_left, kTile)) {
+            // the tile holds rows of the chunk; rows of quantised pages come another way (fetch_codes)
+            const unsigned long long page = (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane(phys) * k_page_bytes;
+            const unsigned long long shift = (unsigned long long)((long long)jt * kTile - cached_u) * seq_row_bytes;
+#pragma unroll
+            for (int i = 0; i < kLoads; ++i) {
+                const int row = krow0 + 4 * i, r = min(row, rows_left - 1);
+                const unsigned kc = k_chunk_pos(row, lane % 16) * 16, vc = v_chunk_pos(row, lane % 16) * 16;
+                const unsigned ldk = __builtin_amdgcn_readfirstlane(lds_k + i * 1024);
+                const unsigned ldv = __builtin_amdgcn_readfirstlane(lds_v + i * 1024);
+                if (r >= from_pages) {
+                    if (K) dma_load16(knew_u + shift, (unsigned)r * seq_row_bytes + kc, ldk);
+                    if (V) dma_load16(vnew_u + shift, (unsigned)r * seq_row_bytes + vc, ldv);
+                } else if (!QUANT) {  // only in the one tile that straddles the end of the cache
+                    if (K) dma_load16(kbase_u + page, (unsigned)r * k_row_bytes + kc, ldk);
+                    if (V) dma_load16(vbase_u + page, (unsigned)r * k_row_bytes + vc, ldv);
+                }
+            }
+        }
+    };
+    constexpr std::integral_constant<int, 1> kOnlyK{};
+    constexpr std::integral_constant<int, 2> kOnlyV{};
+    constexpr std::integral_constant<int, 3> kBoth{};
+    // requests the codes of one operand's share of key tile jt (quantised pages)
+    auto fetch_codes = [&](auto operand, Staged& staged, int jt, int phys) {
+        constexpr bool K = decltype(operand)::value == 1;
+        if constexpr (QUANT) {
+            jt = __builtin_amdgcn_readfirstlane(jt);
+            staged.left = len_u - jt * kTile;
+            staged.from = cached_u - jt * kTile;
+            if (staged.from <= 0) return;
+            const unsigned char* slab = reinterpret_cast<const unsigned char*>(K ? kbase : vbase) +
+                                        (size_t)(unsigned)__builtin_amdgcn_readfirstlane(phys) * k_page_bytes;
+#pragma unroll
+            for (int i = 0; i < kLoads; ++i) {
+                // a row that does not come from the page reads the page's last valid row, for nothing
+                const int row = krow0 + 4 * i, r = min(min(row, staged.left - 1), min(staged.from, kTile) - 1);
+                const unsigned char* src =
+                    slab + (size_t)r * kRowCodeBytes + (K ? k_chunk_pos(row, lane % 16) : v_chunk_pos(row, lane % 16)) * kPlaceCodeBytes;
+                if constexpr (BITS == 8)
+                    staged.codes[i] = *reinterpret_cast<const uint2*>(src);
+                else
+                    staged.codes[i] = make_uint2(*reinterpret_cast<const uint32_t*>(src), 0u);
+                staged.sz[i] = reinterpret_cast<const uint32_t*>(slab + kTile * kRowCodeBytes)[r];
+            }
+        }
+    };
+    // Entry `it` of the walk: key tile in the low bits; with a listed mask also which query tiles keep it.
+    auto entry_of = [&](int it) {
+        if (MASKED && lst) {
+            const int e = lst[it];
+            if (SL == 1) return e;
+            const int jt = min(max(e, 0), iq);  // a row of the caller: anything outside the triangle is not kept
+            return e == jt ? jt | (1 << kKeepShift) : jt;
+        }
+        return it < sink_end ? it : band_begin + (it - sink_end);
+    };
+    constexpr int kTileMask = (1 << kKeepShift) - 1;
+    // the wave's entries: first, first + stride, ...
+    const int it_first = fold ? slice : 0, stride = fold ? SL : 1;
+    int e_cur = it_first < n_visit ? entry_of(it_first) : 0;
+    int e_nxt = it_first + stride < n_visit ? entry_of(it_first + stride) : 0;
+    // physical pages of the tiles to come, looked up two steps ahead of the loads that need them
+    const int ph_first = it_first < n_visit ? page_of(e_cur & kTileMask) : 0;
+    int ph_nxt = it_first + stride < n_visit ? page_of(e_nxt & kTileMask) : 0;
+    // quantised pages: the entry after that too, since codes are requested two steps ahead
+    int e_nx2 = QUANT && it_first + 2 * stride < n_visit ? entry_of(it_first + 2 * stride) : 0;
+    int ph_nx2 = QUANT && it_first + 2 * stride < n_visit ? page_of(e_nx2 & kTileMask) : 0;
+    // the first tiles travel while the queries are fetched
+    if (it_first < n_visit) {
+        fetch(kBoth, k_lds0, v_lds0, e_cur & kTileMask, ph_first);
+        fetch_codes(kOnlyK, staged_k, e_cur & kTileMask, ph_first);
+        fetch_codes(kOnlyV, staged_v, e_cur & kTileMask, ph_first);
+    }
+    // steps of the workgroup: every wave must reach every barrier, so the longest walk counts
+    int steps = fold ? ceil_div(n_visit, SL) : n_visit;
+    if (SL > 1 && !fold) {
+        if (lane == 0) walk_len[wave] = n_visit;
+        __syncthreads();
+        steps = 0;
+#pragma unroll
+        for (int i = 0; i < kPrefillWaves; ++i) steps = max(steps, walk_len[i]);
+        steps = __builtin_amdgcn_readfirstlane(steps);
     }
 
     // ---- Q^T operand: lane (n, half) holds Q[row][16 kk + 8 half .. + 8]
@@ -317,157 +624,11 @@ __global__ __launch_bounds__(kPrefillThreads, 512 / kPrefillThreads) void sparse
         }
     }
 
-    float16_t acc[4];
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[db][i] = 0.f;
-    float m_run = -INFINITY, l_run = 0.f;  // running maximum (scaled, base 2) and sum of this lane's query row
-    // The score products start from -m_run instead of 0 (the accumulator input of the first product), so a
-    // tile whose maxima do not exceed the running ones needs no subtraction before exp2; 0 while m_run = -inf.
-    float16_t neg_m;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) neg_m[i] = 0.f;
 
-    // ---- staging: every wave issues two direct-to-LDS loads of 1 KiB per tile and operand
-    // contiguous keys: tile jt starts jt * 64 rows after the sequence's first row; paged keys: tile jt is the
-    // slab of (its page, hk) in the pool the head lives in, rows 256 bytes apart; keys of a chunk that has not
-    // been written back: row u - cached of the chunk's own K / V
-    const bool ring = PAGED && in_stream_pool(lp, pg.kv, hk);  // a streaming head kept in its bounded pool
-    const int heads_in_pool = PAGED ? (ring ? pg.kv.stream_heads : pg.kv.pool_heads) : lp.Hkv;
-    constexpr size_t kSlabBytes = slab_chunks(kTile, BITS) * 16;  // one (page, head) of a pool
-    const size_t slab_in_page = PAGED ? (size_t)pool_rank(lp, pg.kv, hk, ring) * (kSlabBytes / 2) : 0;  // in 16-bit units
-    const uint16_t* kbase = PAGED ? reinterpret_cast<const uint16_t*>(ring ? pg.kv.k_stream : pg.kv.k_pool) + slab_in_page
-                                  : k + ((size_t)start * lp.Hkv + hk) * kHeadDim;
-    const uint16_t* vbase = PAGED ? reinterpret_cast<const uint16_t*>(ring ? pg.kv.v_stream : pg.kv.v_pool) + slab_in_page
-                                  : v + ((size_t)start * lp.Hkv + hk) * kHeadDim;
-    const int* page_row = !PAGED ? nullptr
-                          : ring ? pg.kv.ring_table + (size_t)b * pg.kv.ring
-                                 : pg.kv.page_table + (size_t)b * pg.kv.max_pages;
-    // page of key tile jt, for tiles that hold cached keys (0 otherwise: never used)
-    auto page_of = [&](int jt) {
-        if (!PAGED || jt * kTile >= cached) return 0;
-        return page_row[ring ? ring_slot(lp, jt) : jt];
-    };
-    // lane `lane` of load i of this wave fills slot (2 wave + i) * 64 + lane of the tile, i.e. position lane % 16
-    // of row 4 (2 wave + i) + lane / 16.  Addresses are a wave-uniform 64-bit tile base (scalar arithmetic) plus a
-    // 32-bit lane offset that does not depend on the tile, except in the last tile of a sequence, where rows
-    // past the end read the last row again (finite values; their softmax weights are 0).
-    const unsigned seq_row_bytes = (unsigned)__builtin_amdgcn_readfirstlane(lp.Hkv * kHeadDim * 2);  // [token][Hkv][D]
-    const unsigned k_row_bytes = PAGED ? kHeadDim * 2u : seq_row_bytes;
-    const unsigned long long k_page_bytes = (unsigned long long)heads_in_pool * kSlabBytes;
-    const int krow0 = wave * (4 * kDmaLoads) + lane / 16;  // K row of load 0; load i takes row + 4 i
-    unsigned kofs[kDmaLoads], vofs[kDmaLoads];
-#pragma unroll
-    for (int i = 0; i < kDmaLoads; ++i) {
-        kofs[i] = (unsigned)(krow0 + 4 * i) * k_row_bytes + k_chunk_pos(krow0 + 4 * i, lane % 16) * 16;  // an involution
-        vofs[i] = (unsigned)(krow0 + 4 * i) * k_row_bytes + v_chunk_pos(krow0 + 4 * i, lane % 16) * 16;  // likewise
-    }
-    const unsigned lds_wave = (unsigned)__builtin_amdgcn_readfirstlane(wave * kDmaLoads * 1024);
-    const unsigned long long kbase_u = uniform64((unsigned long long)kbase), vbase_u = uniform64((unsigned long long)vbase);
-    // the chunk's own rows, addressed from its first token (the row of position `cached`)
-    const unsigned long long knew_u =
-        uniform64((unsigned long long)(PAGED && pg.k_new ? pg.k_new + ((size_t)start * lp.Hkv + hk) * kHeadDim : nullptr));
-    const unsigned long long vnew_u =
-        uniform64((unsigned long long)(PAGED && pg.v_new ? pg.v_new + ((size_t)start * lp.Hkv + hk) * kHeadDim : nullptr));
-    const int len_u = __builtin_amdgcn_readfirstlane(len), cached_u = __builtin_amdgcn_readfirstlane(cached);
-    // quantised rows on their way through registers: per load the codes of this lane's 16-byte place (8 channels) of
-    // K and of V, the (scale, zero) pairs of the row, and whether the lane's row comes from the pages at all
-    constexpr int kRowCodeBytes = kHeadDim * BITS / 8, kPlaceCodeBytes = BITS;  // per row; per 8 channels
-    uint2 staged_k[kDmaLoads], staged_v[kDmaLoads];
-    uint32_t staged_ksz[kDmaLoads], staged_vsz[kDmaLoads];
-    int staged_from = 0, staged_left = 1;  // of the tile in flight: rows that come from the pages; rows it has
-    auto fetch = [&](unsigned char* kd, unsigned char* vd, int jt, int phys) {
-        jt = __builtin_amdgcn_readfirstlane(jt);
-        if constexpr (QUANT) {
-            const int rows_left = len_u - jt * kTile;
-            const int from_pages = cached_u - jt * kTile;  // rows of the tile below this come from the pages
-            staged_from = from_pages;
-            staged_left = rows_left;
-            const unsigned char* kslab = reinterpret_cast<const unsigned char*>(kbase) +
-                                         (size_t)(unsigned)__builtin_amdgcn_readfirstlane(phys) * k_page_bytes;
-            const unsigned char* vslab = kslab - reinterpret_cast<const unsigned char*>(kbase) +
-                                         reinterpret_cast<const unsigned char*>(vbase);
-            const unsigned long long shift = (unsigned long long)((long long)jt * kTile - cached_u) * seq_row_bytes;
-#pragma unroll
-            for (int i = 0; i < kDmaLoads; ++i) {
-                const int row = krow0 + 4 * i, r = min(row, rows_left - 1);
-                const int kplace = k_chunk_pos(row, lane % 16), vplace = v_chunk_pos(row, lane % 16);
-                if (r < from_pages) {
-                    const unsigned char* kr = kslab + (size_t)r * kRowCodeBytes + kplace * kPlaceCodeBytes;
-                    const unsigned char* vr = vslab + (size_t)r * kRowCodeBytes + vplace * kPlaceCodeBytes;
-                    if constexpr (BITS == 8) {
-                        staged_k[i] = *reinterpret_cast<const uint2*>(kr);
-                        staged_v[i] = *reinterpret_cast<const uint2*>(vr);
-                    } else {
-                        staged_k[i] = make_uint2(*reinterpret_cast<const uint32_t*>(kr), 0u);
-                        staged_v[i] = make_uint2(*reinterpret_cast<const uint32_t*>(vr), 0u);
-                    }
-                    staged_ksz[i] = reinterpret_cast<const uint32_t*>(kslab + kTile * kRowCodeBytes)[r];
-                    staged_vsz[i] = reinterpret_cast<const uint32_t*>(vslab + kTile * kRowCodeBytes)[r];
-                } else {  // a row of the chunk: 16-bit, straight to LDS
-                    dma_load16(knew_u + shift, (unsigned)r * seq_row_bytes + kplace * 16,
-                               __builtin_amdgcn_readfirstlane(lds_address(kd) + lds_wave + i * 1024));
-                    dma_load16(vnew_u + shift, (unsigned)r * seq_row_bytes + vplace * 16,
-                               __builtin_amdgcn_readfirstlane(lds_address(vd) + lds_wave + i * 1024));
-                }
-            }
-            return;
-        }
-        const unsigned long long ktile =
-            PAGED ? kbase_u + (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane(phys) * k_page_bytes
-                  : kbase_u + (unsigned long long)jt * (kTile * k_row_bytes);
-        const unsigned long long vtile = ktile - kbase_u + vbase_u;  // K and V are laid out alike
-        // Rows at or past the sequence length must not be read as they are: a page may hold anything there, and
-        // although their weights are 0 a non-finite value would still poison the second product.
-        const int rows_left = len_u - jt * kTile;
-        // rows of the tile below `from_pages` come from the page, the others from the chunk's own K / V
-        const int from_pages = PAGED ? cached_u - jt * kTile : kTile;
-        if (!PAGED || from_pages >= min(rows_left, kTile)) {
-#pragma unroll
-            for (int i = 0; i < kDmaLoads; ++i) {
-                unsigned ko = kofs[i], vo = vofs[i];
-                if (rows_left < kTile) {
-                    const int row = krow0 + 4 * i;
-                    ko = (unsigned)min(row, rows_left - 1) * k_row_bytes + k_chunk_pos(row, lane % 16) * 16;
-                    vo = (unsigned)min(row, rows_left - 1) * k_row_bytes + v_chunk_pos(row, lane % 16) * 16;
-                }
-                dma_load16(ktile, ko, __builtin_amdgcn_readfirstlane(lds_address(kd) + lds_wave + i * 1024));
-                dma_load16(vtile, vo, __builtin_amdgcn_readfirstlane(lds_address(vd) + lds_wave + i * 1024));
-            }
-        } else {
-            // the tile holds rows of the chunk: row r of the tile is the chunk's token jt * 64 + r - cached
-            const unsigned long long shift = (unsigned long long)((long long)jt * kTile - cached_u) * seq_row_bytes;
-            const unsigned long long ktile_new = knew_u + shift, vtile_new = vnew_u + shift;
-#pragma unroll
-            for (int i = 0; i < kDmaLoads; ++i) {
-                const int row = krow0 + 4 * i, r = min(row, rows_left - 1);
-                const unsigned kc = k_chunk_pos(row, lane % 16) * 16, vc = v_chunk_pos(row, lane % 16) * 16;
-                const unsigned lds_k = __builtin_amdgcn_readfirstlane(lds_address(kd) + lds_wave + i * 1024);
-                const unsigned lds_v = __builtin_amdgcn_readfirstlane(lds_address(vd) + lds_wave + i * 1024);
-                if (r < from_pages) {  // only in the one tile that straddles the end of the cache
-                    dma_load16(ktile, (unsigned)r * k_row_bytes + kc, lds_k);
-                    dma_load16(vtile, (unsigned)r * k_row_bytes + vc, lds_v);
-                } else {
-                    dma_load16(ktile_new, (unsigned)r * seq_row_bytes + kc, lds_k);
-                    dma_load16(vtile_new, (unsigned)r * seq_row_bytes + vc, lds_v);
-                }
-            }
-        }
-    };
-    // Entry `it` of the walk: key tile in the low bits; with a listed mask also which query tiles keep it.
-    auto entry_of = [&](int it) {
-        if (MASKED && lst) return lst[it];
-        return it < sink_end ? it : band_begin + (it - sink_end);
-    };
-    int e_cur = n_visit > 0 ? entry_of(0) : 0, e_nxt = n_visit > 1 ? entry_of(1) : 0;
-    // physical pages of the tiles to come, looked up two steps ahead of the loads that need them
-    int ph_cur = n_visit > 0 ? page_of(e_cur) : 0, ph_nxt = n_visit > 1 ? page_of(e_nxt) : 0;
-
-    // loop-invariant operand offsets of this lane inside a tile
+    // loop-invariant operand offsets of this lane inside a stage (its slice's tile)
     int koff[8], voff[4];
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) koff[kk] = n * kKRowBytes + k_chunk_pos(n, kk * 2 + half) * 16;
+    for (int kk = 0; kk < 8; ++kk) koff[kk] = (int)lds_slice + n * kKRowBytes + k_chunk_pos(n, kk * 2 + half) * 16;
     // V^T operand of (channel block db, 16-key step, half u of the lane's 8 keys): the lane's row of sixteen names
     // keys 16 step + 8 u + 4 half + s / 4 (s = lane % 16) and channels 32 db + 16 (n / 16) + 4 (s % 4) .. + 3, which
     // after the exchange leaves lane (n, half) with channel 32 db + n of keys 16 step + 8 u + 4 half + 0 .. 3: the
@@ -477,7 +638,7 @@ __global__ __launch_bounds__(kPrefillThreads, 512 / kPrefillThreads) void sparse
     for (int db = 0; db < 4; ++db) {
         const int s16 = lane % 16, rr = s16 / 4;
         const int chunk = 4 * db + 2 * (n / 16) + (s16 % 4) / 2;
-        voff[db] = half * 1024 + rr * kVRowBytes + v_chunk_pos(rr, chunk) * 16 + 8 * (s16 % 2);
+        voff[db] = (int)lds_slice + half * 1024 + rr * kVRowBytes + v_chunk_pos(rr, chunk) * 16 + 8 * (s16 % 2);
     }
 
     // Quantised rows fetched for the tile in flight: eight codes -> code * scale + zero -> eight 16-bit values at the
@@ -490,6 +651,16 @@ __global__ __launch_bounds__(kPrefillThreads, 512 / kPrefillThreads) void sparse
             hi = (codes.x >> 4) & 0x0f0f0f0fu;
             lo = codes.x & 0x0f0f0f0fu;
         }
+        if constexpr (std::is_same<T, F16>::value) {
+            // A code under the exponent byte 0x64 is the fp16 number 1024 + code, from which 1024 is taken off exactly; the
+            // packed fma then rounds code * scale + zero once, to fp16, at three instructions per two values.
+            const half2_t scale2 = {sz[0], sz[0]}, zero2 = {sz[1], sz[1]}, offset = {(_Float16)-1024.f, (_Float16)-1024.f};
+            auto pair = [&](uint32_t word, uint32_t select) {
+                const half2_t c = __builtin_bit_cast(half2_t, __builtin_amdgcn_perm(0x64646464u, word, select)) + offset;
+                return __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(c, scale2, zero2));
+            };
+            return make_uint4(pair(lo, 0x04010400u), pair(lo, 0x04030402u), pair(hi, 0x04010400u), pair(hi, 0x04030402u));
+        }
         float x[8];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -498,249 +669,494 @@ __global__ __launch_bounds__(kPrefillThreads, 512 / kPrefillThreads) void sparse
         }
         return pack8<T>(x);
     };
-    auto store_staged = [&](unsigned char* kd, unsigned char* vd) {
+    auto store_staged = [&](unsigned char* dst, const Staged& staged) {
         if constexpr (QUANT) {
-            if (staged_from <= 0) return;
+            if (staged.from <= 0) return;
 #pragma unroll
-            for (int i = 0; i < kDmaLoads; ++i) {
-                if (min(krow0 + 4 * i, staged_left - 1) < staged_from) {  // the lanes that fetch() gave codes
-                    *reinterpret_cast<uint4*>(kd + lds_wave + i * 1024 + lane * 16) = dequantise8(staged_k[i], staged_ksz[i]);
-                    *reinterpret_cast<uint4*>(vd + lds_wave + i * 1024 + lane * 16) = dequantise8(staged_v[i], staged_vsz[i]);
-                }
+            for (int i = 0; i < kLoads; ++i) {
+                if (min(krow0 + 4 * i, staged.left - 1) < staged.from)  // the lanes that fetch() gave codes
+                    *reinterpret_cast<uint4*>(dst + lds_wave + i * 1024 + lane * 16) =
+                        dequantise8(staged.codes[i], staged.sz[i]);
             }
         }
     };
 
-    auto tile_step = [&](int it, const unsigned char* ks, const unsigned char* vs, unsigned char* kd, unsigned char* vd) {
-        const int e_new = it + 2 < n_visit ? entry_of(it + 2) : 0;  // requested two steps ahead of its use
-        const int ph_new = it + 2 < n_visit ? page_of(e_new) : 0;
-        const int jt = e_cur & ((1 << kKeepShift) - 1);
-        if (it + 1 < n_visit) fetch(kd, vd, e_nxt & ((1 << kKeepShift) - 1), ph_nxt);
-        ph_nxt = ph_new;
-        // does this wave's mask tile keep key tile jt?
-        bool keep = wave_has_rows && jt <= iq;
+    // does this wave's mask tile keep the tile of entry e (entry `it` of the walk)?
+    auto keeps = [&](int it, int e) {
+        const int jt = e & kTileMask;
+        bool keep = wave_has_rows && jt <= iq && (SL == 1 || it < n_visit);
         if (MASKED && lst)
-            keep = keep && ((e_cur >> (kKeepShift + wave / 2)) & 1);
+            keep = keep && ((e >> (kKeepShift + iq - iq_first)) & 1);
         else if (streaming)
             keep = keep && (jt < lp.sink_pages || jt > iq - lp.local_pages);
-        e_cur = e_nxt;
-        e_nxt = e_new;
-        if (keep) {
-            const bool diagonal = jt == iq;
-            // S^T for the 64 keys of the tile, two blocks of 32 keys.  All operand reads of a block are
-            // issued before its products so that LDS latency is paid once, and the two blocks'
-            // accumulation chains alternate in the matrix pipe.
-            __builtin_amdgcn_s_setprio(2);  // products first: the other wavefront of the SIMD fills in with softmax work
-            float16_t s[2];
-            uint4 ka[8][2];
+        return keep;
+    };
+    // S^T for the 64 keys of a tile, two blocks of 32 keys.  All operand reads of a block are issued before its
+    // products so that LDS latency is paid once, and the two blocks' accumulation chains alternate in the matrix pipe.
+    auto scores = [&](float16_t (&s)[2], const unsigned char* ks, bool diagonal) {
+        __builtin_amdgcn_s_setprio(2);  // products first: the other wavefront of the SIMD fills in with softmax work
+        uint4 ka[8][2];
 #pragma unroll
-            for (int kk = 0; kk < 8; ++kk)
+        for (int kk = 0; kk < 8; ++kk)
 #pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
-                    ka[kk][kb] = *reinterpret_cast<const uint4*>(ks + kb * 32 * kKRowBytes + koff[kk]);
-            s[0] = Mfma<T>::run(ka[0][0], qreg[0], neg_m);
-            s[1] = Mfma<T>::run(ka[0][1], qreg[0], neg_m);
+            for (int kb = 0; kb < 2; ++kb)
+                ka[kk][kb] = *reinterpret_cast<const uint4*>(ks + kb * 32 * kKRowBytes + koff[kk]);
+        s[0] = Mfma<T>::run(ka[0][0], qreg[0], neg_m);
+        s[1] = Mfma<T>::run(ka[0][1], qreg[0], neg_m);
 #pragma unroll
-            for (int kk = 1; kk < 8; ++kk) {
-                s[0] = Mfma<T>::run(ka[kk][0], qreg[kk], s[0]);
-                s[1] = Mfma<T>::run(ka[kk][1], qreg[kk], s[1]);
-            }
-            // schedule: operand reads run four ahead of the products that consume them
-            __builtin_amdgcn_sched_group_barrier(0x100, kAhead, 0);
-#pragma unroll
-            for (int u = 0; u < 16 - kAhead; ++u) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            }
-            __builtin_amdgcn_sched_group_barrier(0x008, kAhead, 0);
-            __builtin_amdgcn_s_setprio(0);
-            if (diagonal) {  // causal mask inside the diagonal tile
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const int key = kb * 32 + 8 * (i / 4) + 4 * half + (i % 4);
-                        if (key > row0 + n) s[kb][i] = -INFINITY;
-                    }
-            }
-            // online softmax of this lane's query row (its keys are split between the two lane halves)
-            float mx = fmaxf(s[0][0], s[1][0]);
-#pragma unroll
-            for (int i = 1; i < 16; ++i) mx = __builtin_fmaxf(__builtin_fmaxf(mx, s[0][i]), s[1][i]);  // v_max3_f32
-            mx = halves_max(mx);  // relative to the running maximum (to 0 before the first kept tile)
-            if (__any(mx > 0.f || m_run == -INFINITY)) {  // some row's maximum moved: subtract and rescale
-                const float m_base = m_run == -INFINITY ? 0.f : m_run;
-                const float m_new = fmaxf(m_run, m_base + mx);
-                const float delta = m_new - m_base;                         // 0 for rows whose maximum stayed
-                const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);  // exp2(-inf) = 0 on the first tile
-                l_run *= alpha;
-#pragma unroll
-                for (int db = 0; db < 4; ++db)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) acc[db][i] *= alpha;
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) s[kb][i] -= delta;
-                m_run = m_new;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) neg_m[i] = -m_new;
-            }
-            uint4 pb[2][2];  // P^T packed to 16 bit: [key block][16-key step]
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb) {
-                float pf[16];
-#pragma unroll
-                for (int i = 0; i < 16; ++i) pf[i] = __builtin_amdgcn_exp2f(s[kb][i]);
-                pb[kb][0] = pack8<T>(pf);
-                pb[kb][1] = pack8<T>(pf + 8);
-                // row sum from the rounded weights, the same values the second product uses
-                const uint32_t w[8] = {pb[kb][0].x, pb[kb][0].y, pb[kb][0].z, pb[kb][0].w,
-                                       pb[kb][1].x, pb[kb][1].y, pb[kb][1].z, pb[kb][1].w};
-#pragma unroll
-                for (int u = 0; u < 8; ++u) l_run = Elem<T>::dot2(w[u], Ones<T>::pair, l_run);
-            }
-            // O^T += V^T * P^T, 16 keys per instruction; operand reads run one step ahead
-#pragma unroll
-            for (int step = 0; step < 4; ++step) {
-                const int kb = step / 2, j = step % 2;
-                uint4 va[4];
-#pragma unroll
-                for (int db = 0; db < 4; ++db) {
-                    const uint2 lo = lds_read_transposed(vs + (4 * step) * 1024 + voff[db]);
-                    const uint2 hi = lds_read_transposed(vs + (4 * step + 2) * 1024 + voff[db]);
-                    va[db] = make_uint4(lo.x, lo.y, hi.x, hi.y);
-                }
-#pragma unroll
-                for (int db = 0; db < 4; ++db) acc[db] = Mfma<T>::run(va[db], pb[kb][j], acc[db]);
-            }
+        for (int kk = 1; kk < 8; ++kk) {
+            s[0] = Mfma<T>::run(ka[kk][0], qreg[kk], s[0]);
+            s[1] = Mfma<T>::run(ka[kk][1], qreg[kk], s[1]);
         }
-        if (it + 1 < n_visit) store_staged(kd, vd);
-        dma_wait();
-        __syncthreads();  // the next tile has landed and this one is free
+        // schedule: operand reads run four ahead of the products that consume them
+        __builtin_amdgcn_sched_group_barrier(0x100, kAhead, 0);
+#pragma unroll
+        for (int u = 0; u < 16 - kAhead; ++u) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, kAhead, 0);
+        __builtin_amdgcn_s_setprio(0);
+        if (diagonal) {  // causal mask inside the diagonal tile
+            // (opaque, or the 32 comparisons are hoisted out of the loop into 64 scalar registers, and what the loop
+            // does need is then read back from spilled lanes in every step)
+            int last_key = row0 + n - 4 * half;
+            asm volatile("" : "+v"(last_key));
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int key = kb * 32 + 8 * (i / 4) + (i % 4);  // less 4 half
+                    if (key > last_key) s[kb][i] = -INFINITY;
+                }
+        }
+    };
+    // online softmax of this lane's query row (its keys are split between the two lane halves), then O^T += V^T P^T
+    auto weights_and_values = [&](float16_t (&s)[2], const unsigned char* vs) {
+        float mx = fmaxf(s[0][0], s[1][0]);
+#pragma unroll
+        for (int i = 1; i < 16; ++i) mx = __builtin_fmaxf(__builtin_fmaxf(mx, s[0][i]), s[1][i]);  // v_max3_f32
+        mx = halves_max(mx);  // relative to the running maximum (to 0 before the first kept tile)
+        if (__any(mx > 0.f || m_run == -INFINITY)) {  // some row's maximum moved: subtract and rescale
+            const float m_base = m_run == -INFINITY ? 0.f : m_run;
+            const float m_new = fmaxf(m_run, m_base + mx);
+            const float delta = m_new - m_base;                         // 0 for rows whose maximum stayed
+            const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);  // exp2(-inf) = 0 on the first tile
+            l_run *= alpha;
+#pragma unroll
+            for (int db = 0; db < 4; ++db)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[db][i] *= alpha;
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) s[kb][i] -= delta;
+            m_run = m_new;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) neg_m[i] = -m_new;
+        }
+        uint4 pb[2][2];  // P^T packed to 16 bit: [key block][16-key step]
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+            float pf[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) pf[i] = __builtin_amdgcn_exp2f(s[kb][i]);
+            pb[kb][0] = pack8<T>(pf);
+            pb[kb][1] = pack8<T>(pf + 8);
+            // row sum from the rounded weights, the same values the second product uses
+            const uint32_t w[8] = {pb[kb][0].x, pb[kb][0].y, pb[kb][0].z, pb[kb][0].w,
+                                   pb[kb][1].x, pb[kb][1].y, pb[kb][1].z, pb[kb][1].w};
+#pragma unroll
+            for (int u = 0; u < 8; ++u) l_run = Elem<T>::dot2(w[u], Ones<T>::pair, l_run);
+        }
+        // O^T += V^T * P^T, 16 keys per instruction; operand reads run one step ahead
+#pragma unroll
+        for (int step = 0; step < 4; ++step) {
+            const int kb = step / 2, j = step % 2;
+            uint4 va[4];
+#pragma unroll
+            for (int db = 0; db < 4; ++db) {
+                const uint2 lo = lds_read_transposed(vs + (4 * step) * 1024 + voff[db]);
+                const uint2 hi = lds_read_transposed(vs + (4 * step + 2) * 1024 + voff[db]);
+                va[db] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+            }
+#pragma unroll
+            for (int db = 0; db < 4; ++db) acc[db] = Mfma<T>::run(va[db], pb[kb][j], acc[db]);
+        }
+        // schedule: operand reads run one step (four products, eight reads) ahead
+        __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
+#pragma unroll
+        for (int u = 0; u < 12; ++u) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
     };
 
-    if (n_visit > 0) {
-        fetch(k_lds0, v_lds0, e_cur & ((1 << kKeepShift) - 1), ph_cur);
-        store_staged(k_lds0, v_lds0);
+    // One step of two-stage staging: the tiles of the next step are requested, those of this one are worked on.
+    auto tile_step = [&](int it, const unsigned char* ks, const unsigned char* vs, unsigned char* kd, unsigned char* vd) {
+        const bool more = it + stride < n_visit;
+        const int e = e_cur;
+        if constexpr (QUANT) {
+            // The codes of the next tile were requested a step ago; they are stored between the products of this one, and
+            // the registers then take the codes of the tile after it, which have until the same place of the next step.
+            const bool more2 = it + 2 * stride < n_visit, more3 = it + 3 * stride < n_visit;
+            const int e_new = more3 ? entry_of(it + 3 * stride) : 0;
+            const int ph_new = more3 ? page_of(e_new & kTileMask) : 0;
+            const bool own_rows = more && cached_u - (e_nxt & kTileMask) * kTile < kTile;
+            if (own_rows) fetch(kBoth, kd, vd, e_nxt & kTileMask, ph_nxt);
+            const bool keep = keeps(it, e);
+            float16_t s[2];
+            if (keep) scores(s, ks, (e & kTileMask) == iq);
+            if (more) store_staged(kd, staged_k);
+            if (more2) fetch_codes(kOnlyK, staged_k, e_nx2 & kTileMask, ph_nx2);
+            if (keep) weights_and_values(s, vs);
+            if (more) store_staged(vd, staged_v);
+            if (more2) fetch_codes(kOnlyV, staged_v, e_nx2 & kTileMask, ph_nx2);
+            e_cur = e_nxt;
+            e_nxt = e_nx2;
+            e_nx2 = e_new;
+            ph_nxt = ph_nx2;
+            ph_nx2 = ph_new;
+            if (own_rows) dma_wait();
+        } else {
+            const int e_new = it + 2 * stride < n_visit ? entry_of(it + 2 * stride) : 0;  // requested two steps ahead of its use
+            const int ph_new = it + 2 * stride < n_visit ? page_of(e_new & kTileMask) : 0;
+            if (more) fetch(kBoth, kd, vd, e_nxt & kTileMask, ph_nxt);
+            ph_nxt = ph_new;
+            e_cur = e_nxt;
+            e_nxt = e_new;
+            if (keeps(it, e)) {
+                float16_t s[2];
+                scores(s, ks, (e & kTileMask) == iq);
+                weights_and_values(s, vs);
+            }
+            dma_wait();
+        }
+        __syncthreads();  // the next tiles have landed and these are free
+    };
+
+    if (it_first < n_visit) {
+        store_staged(k_lds0, staged_k);
+        store_staged(v_lds0, staged_v);
+    }
+    if (QUANT && it_first + stride < n_visit) {
+        fetch_codes(kOnlyK, staged_k, e_nxt & kTileMask, ph_nxt);
+        fetch_codes(kOnlyV, staged_v, e_nxt & kTileMask, ph_nxt);
     }
     dma_wait();
     __syncthreads();
-    for (int it = 0; it < n_visit; it += 2) {
-        tile_step(it, k_lds0, v_lds0, k_lds1, v_lds1);
-        if (it + 1 >= n_visit) break;
-        tile_step(it + 1, k_lds1, v_lds1, k_lds0, v_lds0);
+    if constexpr (!kOneStage) {
+        for (int st = 0; st < steps; st += 2) {
+            tile_step(it_first + st * stride, k_lds0, v_lds0, k_lds1, v_lds1);
+            if (st + 1 >= steps) break;
+            tile_step(it_first + (st + 1) * stride, k_lds1, v_lds1, k_lds0, v_lds0);
+        }
+    } else {
+        // K of the next step is requested once every wave has its scores of this one, V once every wave is done with it
+        for (int st = 0; st < steps; ++st) {
+            const int it = it_first + st * stride;
+            const bool more = it + stride < n_visit;
+            const int e_new = it + 2 * stride < n_visit ? entry_of(it + 2 * stride) : 0;
+            const int ph_new = it + 2 * stride < n_visit ? page_of(e_new & kTileMask) : 0;
+            const bool keep = keeps(it, e_cur);
+            float16_t s[2];
+            if (keep) scores(s, k_lds0, (e_cur & kTileMask) == iq);
+            dma_wait();
+            __syncthreads();  // V of this step has landed, K is free
+            if (more) fetch(kOnlyK, k_lds0, v_lds0, e_nxt & kTileMask, ph_nxt);
+            if (keep) weights_and_values(s, v_lds0);
+            dma_wait();
+            __syncthreads();  // K of the next step has landed, V is free
+            if (more) fetch(kOnlyV, k_lds0, v_lds0, e_nxt & kTileMask, ph_nxt);
+            ph_nxt = ph_new;
+            e_cur = e_nxt;
+            e_nxt = e_new;
+        }
     }
 
-    if (!wave_has_rows) return;
     // ---- epilogue: lane (n, half) holds O^T[d][q] for d = 32 db + 8 (i / 4) + 4 half + i % 4
     const float lt = halves_sum(l_run);
     const int pos = iq * kTile + row0 + n;
-    if (pos >= len || pos < first) return;
     const int row = pos - first;
-    const float inv = lt > 0.f ? 1.f / lt : 0.f;  // a row that keeps nothing (possible with a listed mask) gives 0
-    uint16_t* dst = out + ((size_t)(start + row) * lp.H + h) * kHeadDim;
+    if (!fold) {
+        if (!wave_has_rows) return;
+        if (pos >= len || pos < first) return;
+        const float inv = lt > 0.f ? 1.f / lt : 0.f;  // a row that keeps nothing (possible with a listed mask) gives 0
+        uint16_t* dst = out + ((size_t)(start + row) * lp.H + h) * kHeadDim;
 #pragma unroll
-    for (int db = 0; db < 4; ++db)
+        for (int db = 0; db < 4; ++db)
 #pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4) {
-            const int d = db * 32 + 8 * g4 + 4 * half;
-            uint2 w;
-            w.x = Elem<T>::pack(acc[db][4 * g4] * inv, acc[db][4 * g4 + 1] * inv);
-            w.y = Elem<T>::pack(acc[db][4 * g4 + 2] * inv, acc[db][4 * g4 + 3] * inv);
-            *reinterpret_cast<uint2*>(dst + d) = w;
+            for (int g4 = 0; g4 < 4; ++g4) {
+                const int d = db * 32 + 8 * g4 + 4 * half;
+                uint2 w;
+                w.x = Elem<T>::pack(acc[db][4 * g4] * inv, acc[db][4 * g4 + 1] * inv);
+                w.y = Elem<T>::pack(acc[db][4 * g4 + 2] * inv, acc[db][4 * g4 + 3] * inv);
+                *reinterpret_cast<uint2*>(dst + d) = w;
+            }
+        if (lse_out && half == 0)
+            lse_out[(size_t)h * total_tokens + start + row] = lt > 0.f ? (m_run + __builtin_amdgcn_logf(lt)) * kLn2 : -INFINITY;
+    } else if constexpr (SL > 1) {
+        // The slices of a unit meet in LDS (the tiles are done with: the loop ended on a barrier): every wave leaves
+        // its accumulators, 4 KiB per channel block, and then finishes 4 / SL of the four channel blocks for its rows.
+        float4* const room[4] = {reinterpret_cast<float4*>(k_lds0),
+                                 reinterpret_cast<float4*>(kOneStage ? k_lds0 + kPrefillWaves * 4096 : k_lds1),
+                                 reinterpret_cast<float4*>(v_lds0),
+                                 reinterpret_cast<float4*>(kOneStage ? v_lds0 + kPrefillWaves * 4096 : v_lds1)};
+        static_assert(SL == 1 || SL * kKTileBytes >= kPrefillWaves * 4096, "a channel block of every wave fits an array");
+#pragma unroll
+        for (int db = 0; db < 4; ++db)
+#pragma unroll
+            for (int g4 = 0; g4 < 4; ++g4)
+                room[db][(wave * 4 + g4) * kWave + lane] =
+                    make_float4(acc[db][4 * g4], acc[db][4 * g4 + 1], acc[db][4 * g4 + 2], acc[db][4 * g4 + 3]);
+        if (half == 0) fold_ml[wave][n] = make_float2(m_run, lt);
+        __syncthreads();
+        if (!wave_has_rows) return;
+        if (pos >= len || pos < first) return;
+        const int peer0 = unit * SL * 2 + wave % 2;  // wave of slice 0 with the same rows; slice i is 2 i waves on
+        float2 ml[SL];
+        float m_all = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < SL; ++i) {
+            ml[i] = fold_ml[peer0 + 2 * i][n];
+            m_all = fmaxf(m_all, ml[i].x);
         }
-    if (lse_out && half == 0)
-        lse_out[(size_t)h * total_tokens + start + row] = lt > 0.f ? (m_run + __builtin_amdgcn_logf(lt)) * kLn2 : -INFINITY;
+        float f[SL], l_all = 0.f;
+#pragma unroll
+        for (int i = 0; i < SL; ++i) {
+            f[i] = ml[i].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[i].x - m_all);  // a slice without keys adds nothing
+            l_all = __builtin_fmaf(ml[i].y, f[i], l_all);
+        }
+        const float inv = l_all > 0.f ? 1.f / l_all : 0.f;
+        uint16_t* dst = out + ((size_t)(start + row) * lp.H + h) * kHeadDim;
+#pragma unroll
+        for (int u = 0; u < 4 / SL; ++u) {
+            const int db = slice * (4 / SL) + u;
+            const float4* from = db == 0 ? room[0] : db == 1 ? room[1] : db == 2 ? room[2] : room[3];
+#pragma unroll
+            for (int g4 = 0; g4 < 4; ++g4) {
+                float o[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int i = 0; i < SL; ++i) {
+                    const float4 x = from[((peer0 + 2 * i) * 4 + g4) * kWave + lane];
+                    o[0] = __builtin_fmaf(x.x, f[i], o[0]);
+                    o[1] = __builtin_fmaf(x.y, f[i], o[1]);
+                    o[2] = __builtin_fmaf(x.z, f[i], o[2]);
+                    o[3] = __builtin_fmaf(x.w, f[i], o[3]);
+                }
+                const int d = db * 32 + 8 * g4 + 4 * half;
+                *reinterpret_cast<uint2*>(dst + d) =
+                    make_uint2(Elem<T>::pack(o[0] * inv, o[1] * inv), Elem<T>::pack(o[2] * inv, o[3] * inv));
+            }
+        }
+        if (lse_out && slice == 0 && half == 0)
+            lse_out[(size_t)h * total_tokens + start + row] =
+                l_all > 0.f ? (m_all + __builtin_amdgcn_logf(l_all)) * kLn2 : -INFINITY;
+    }
 }
 
-PrefillSchedule make_schedule(const LayerParams& lp, int blocks_per_seq, int batch) {
+// ---- host side -----------------------------------------------------------------------------------
+
+constexpr int kComputeUnits = 256;  // one workgroup per compute unit is resident
+
+int count_streaming(const LayerParams& lp) {
+    int n = 0;
+    for (int hk = 0; hk < lp.Hkv; ++hk) n += (int)((lp.streaming_mask >> hk) & 1ull);
+    return n;
+}
+
+// What a launch is made of: the kernel's key slices, and per class of heads whether the slices share a unit.
+struct PrefillShape {
+    int slices;
+    bool fold[2];
+};
+
+// Key slices of a launch over `tiles` query tiles whose dense walks are `longest` key tiles at most and `mean` on
+// average.  The launch takes as long as its longest workgroup, or as all of them shared out over the chip plus a
+// part of the longest for the uneven end; a workgroup costs a fixed time (start, first tiles and queries, epilogue:
+// 1 + 3 + 2.5 us by time stamps) and its steps.  More slices shorten the walks and multiply the workgroups, but a step
+// then stages as many tiles as there are slices for the same products.  Measured with one / two / four slices: 512 new
+// tokens over a history of 32768, 932 / 547 / 381 us; one prompt of 4096 tokens, 125 / 129 / 157 us; of 65536 tokens,
+// 15.4 / 17.6 / 21.6 ms.  Quantised pages are not built for four (the codes on their way need more registers than
+// there are).
+PrefillShape choose_shape(const LayerParams& lp, double tiles, double longest, double mean, int bits) {
+    const double fixed = 7.0;                                                        // microseconds
+    static const double step_us[2][3] = {{2.0, 2.35, 3.0}, {2.3, 2.9, 0.0}};         // by log2(slices)
+    const int n_stream = count_streaming(lp);
+    const double dense = tiles * (lp.Hkv - n_stream) * lp.group, stream = tiles * n_stream * lp.group;
+    const double band = std::min<double>(lp.sink_pages + lp.local_pages, longest);
+    PrefillShape best = {1, {false, false}};
+    double best_time = 1e300;
+    for (int i = 0; i < (bits == 16 ? 3 : 2); ++i) {
+        const int SL = 1 << i;
+        const double step = step_us[bits != 16][i];
+        const double dense_wgs = dense / kPairs * SL;
+        // the short walks of streaming heads are folded only while the chip has room for all of the launch at once
+        const bool fold_stream = dense_wgs + stream / kPairs * SL <= kComputeUnits;
+        const int stream_slices = fold_stream ? SL : 1;
+        const double work = (dense_wgs * (fixed + step * mean / SL) +
+                             stream / kPairs * stream_slices * (fixed + step * band / stream_slices)) / kComputeUnits;
+        const double last = fixed + step * (dense > 0 ? longest / SL : band / stream_slices);
+        const double time = std::max(last, work + 0.25 * last);
+        if (time < best_time) {
+            best_time = time;
+            best = {SL, {SL > 1, SL > 1 && fold_stream}};
+        }
+    }
+    return best;
+}
+
+// Query heads of a group that share a workgroup (they read the same keys, whole and at the same time, and all end on
+// the same diagonal tile, where query tiles side by side would not), then query tiles, to make up the units.
+// max_rows: rows of the longest sequence; any_start: they may start anywhere inside a block.
+PrefillSchedule make_schedule(const LayerParams& lp, const PrefillShape& shape, bool one_head, int max_rows, int total_rows,
+                              bool any_start, int batch) {
     PrefillSchedule sched;
-    sched.qblocks_total = blocks_per_seq * batch;
     for (int c = 0; c < 2; ++c) {
         HeadClass& hc = sched.cls[c];
+        hc.fold = shape.fold[c];
+        const int units = shape.fold[c] ? kPairs / shape.slices : kPairs;
+        int heads = 1;
+        while (!one_head && heads < units && lp.group % (2 * heads) == 0) heads *= 2;
+        hc.heads_per_block = heads;
+        hc.qtiles_log2 = 0;
+        while ((heads << hc.qtiles_log2) < units) ++hc.qtiles_log2;
+        const int rows = kTile << hc.qtiles_log2;
+        // rows that start anywhere inside a block reach into one block more than their number needs
+        hc.blocks_per_seq = (max_rows + rows - 1) / rows + (any_start ? 1 : 0);
+        hc.ordered = batch <= kWave;  // one lane per sequence
+        long long blocks = (long long)hc.blocks_per_seq * batch;
+        // n rows fill floor(n / rows) blocks and touch at most one more, two more if they start anywhere
+        if (hc.ordered) blocks = std::min(blocks, (long long)total_rows / rows + (any_start ? 2LL : 1LL) * batch);
         hc.heads = 0;
         for (int hk = 0; hk < lp.Hkv; ++hk)
             if ((int)((lp.streaming_mask >> hk) & 1ull) == c) hc.kv_head[hc.heads++] = (unsigned char)hk;
         hc.swizzled = hc.heads > 0 && kXcds % hc.heads == 0;
         hc.slices = hc.swizzled ? kXcds / hc.heads : 1;
+        const int per_block = lp.group / heads;
         if (hc.heads == 0)
             hc.items_per_xcd = 0;
         else if (hc.swizzled)
-            hc.items_per_xcd = lp.group * ((sched.qblocks_total + hc.slices - 1) / hc.slices);
+            hc.items_per_xcd = (int)(per_block * ((blocks + hc.slices - 1) / hc.slices));
         else
-            hc.items_per_xcd = (hc.heads * lp.group * sched.qblocks_total + kXcds - 1) / kXcds;
+            hc.items_per_xcd = (int)((hc.heads * per_block * blocks + kXcds - 1) / kXcds);
     }
     return sched;
 }
 
 size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
 
+// merged lists of a listed mask, one per block of four query tiles, of a sequence
+int mask_blocks(int max_seqlen) { return (max_seqlen + kPairs * kTile - 1) / (kPairs * kTile); }
+
+struct PrefillLaunch {
+    const LayerParams* lp;
+    const uint16_t *q, *k, *v;
+    const int* cu_seqlens;
+    int batch, total_tokens;
+    uint16_t* out;
+    float* lse_out;
+    PrefillSchedule sched;
+    PrefillMask mk;
+    PrefillPaged pg;
+    hipStream_t stream;
+};
+
+template <class T, int MODE, int BITS>
+hipError_t launch_slices(const PrefillLaunch& a, int slices) {
+    const int grid = kXcds * (a.sched.cls[0].items_per_xcd + a.sched.cls[1].items_per_xcd);
+#define LSERVE_PREFILL_SLICES(SL)                                                                                       \
+    hipLaunchKernelGGL((sparse_prefill_kernel<T, MODE, BITS, SL>), dim3(grid), dim3(kPrefillThreads), 0, a.stream, *a.lp, \
+                       a.q, a.k, a.v, a.cu_seqlens, a.batch, a.out, a.lse_out, a.total_tokens, a.sched, a.mk, a.pg)
+    if constexpr (BITS == 16) {
+        if (slices == 4) {
+            LSERVE_PREFILL_SLICES(4);
+            return hipGetLastError();
+        }
+    }
+    if (slices == 2)
+        LSERVE_PREFILL_SLICES(2);
+    else
+        LSERVE_PREFILL_SLICES(1);
+#undef LSERVE_PREFILL_SLICES
+    return hipGetLastError();
+}
+
 template <class T>
 hipError_t launch_prefill(const LayerParams& lp, const void* q, const void* k, const void* v, const int* cu_seqlens,
                           int batch, int total_tokens, int max_seqlen, void* out, float* lse_out, void* workspace,
                           const PrefillMaskArgs* mask, hipStream_t stream) {
     const int max_tiles = (max_seqlen + kTile - 1) / kTile;
-    hipError_t e = hipSuccess;
-    const int blocks_per_seq = (max_seqlen + kRowsPerBlock - 1) / kRowsPerBlock;
-    PrefillMask mk = {};
-    if (mask) {
-        unsigned char* ws = reinterpret_cast<unsigned char*>(workspace);
-        mk.head_mask = mask->head_mask;
-        mk.q_tile_start = mask->q_tile_start;
-        mk.row_ptr = mask->row_ptr;
-        mk.cols = mask->cols;
-        mk.rows_per_mask = mask->rows_per_mask;
-        mk.blk_list = reinterpret_cast<int*>(ws);
-        mk.blk_count = reinterpret_cast<int*>(ws + align16((size_t)mask->nnz * sizeof(int)));
-        hipLaunchKernelGGL(merge_mask_rows_kernel, dim3(blocks_per_seq, batch, mask->num_masks), dim3(kWave),
-                           (size_t)align16(max_tiles), stream, mk, cu_seqlens, batch, blocks_per_seq);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
+    PrefillLaunch a = {};
+    a.lp = &lp;
+    a.q = reinterpret_cast<const uint16_t*>(q);
+    a.k = reinterpret_cast<const uint16_t*>(k);
+    a.v = reinterpret_cast<const uint16_t*>(v);
+    a.cu_seqlens = cu_seqlens;
+    a.batch = batch;
+    a.total_tokens = total_tokens;
+    a.out = reinterpret_cast<uint16_t*>(out);
+    a.lse_out = lse_out;
+    a.stream = stream;
+    // half a tile of padding per sequence; walks are half as long as their sequence, and long sequences have more of them
+    const double tiles = (double)total_tokens / kTile + 0.5 * batch, mean_tiles = (double)total_tokens / kTile / batch;
+    PrefillShape shape = choose_shape(lp, tiles, max_tiles, 0.25 * (mean_tiles + max_tiles), 16);
+    if (!mask) {
+        a.sched = make_schedule(lp, shape, false, max_seqlen, total_tokens, false, batch);
+        return launch_slices<T, kPlain, 16>(a, shape.slices);
     }
-    const PrefillSchedule sched = make_schedule(lp, blocks_per_seq, batch);
-    const int grid = kXcds * (sched.cls[0].items_per_xcd + sched.cls[1].items_per_xcd);
-    const PrefillPaged pg = {};  // not read by these instantiations
-    if (mask)
-        hipLaunchKernelGGL((sparse_prefill_kernel<T, kMasked>), dim3(grid), dim3(kPrefillThreads), 0, stream, lp,
-                           reinterpret_cast<const uint16_t*>(q), reinterpret_cast<const uint16_t*>(k),
-                           reinterpret_cast<const uint16_t*>(v), cu_seqlens, batch, blocks_per_seq,
-                           reinterpret_cast<uint16_t*>(out), lse_out, total_tokens, sched, mk, pg);
-    else
-        hipLaunchKernelGGL((sparse_prefill_kernel<T, kPlain>), dim3(grid), dim3(kPrefillThreads), 0, stream, lp,
-                           reinterpret_cast<const uint16_t*>(q), reinterpret_cast<const uint16_t*>(k),
-                           reinterpret_cast<const uint16_t*>(v), cu_seqlens, batch, blocks_per_seq,
-                           reinterpret_cast<uint16_t*>(out), lse_out, total_tokens, sched, mk, pg);
-    return hipGetLastError();
+    PrefillMask& mk = a.mk;
+    mk.head_mask = mask->head_mask;
+    mk.q_tile_start = mask->q_tile_start;
+    mk.row_ptr = mask->row_ptr;
+    mk.cols = mask->cols;
+    mk.rows_per_mask = mask->rows_per_mask;
+    if (shape.slices > 1) {  // few blocks: the slices of a workgroup share out the caller's own rows
+        shape = {4, {true, true}};
+        a.sched = make_schedule(lp, shape, true, max_seqlen, total_tokens, false, batch);
+        return launch_slices<T, kMasked, 16>(a, 4);
+    }
+    // many: the rows of four query tiles are merged, and blocks whose rows have little in common go to a second launch
+    // that walks them row by row (12345 tokens under random masks of density 0.3: 508 us merged, 433 us by rows)
+    mk.blocks_per_seq = mask_blocks(max_seqlen);
+    mk.blk_list = reinterpret_cast<int*>(workspace);
+    mk.blk_count = reinterpret_cast<int*>(reinterpret_cast<unsigned char*>(workspace) + align16((size_t)mask->nnz * sizeof(int)));
+    hipLaunchKernelGGL(merge_mask_rows_kernel, dim3(mk.blocks_per_seq, batch, mask->num_masks), dim3(kWave),
+                       (size_t)align16(max_tiles), stream, mk, cu_seqlens, batch);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    a.sched = make_schedule(lp, shape, true, max_seqlen, total_tokens, false, batch);
+    e = launch_slices<T, kMasked, 16>(a, 1);
+    if (e != hipSuccess) return e;
+    return launch_slices<T, kMasked, 16>(a, 4);
 }
 
 template <class T>
 hipError_t launch_prefill_paged(const LayerParams& lp, const PagedParams& kv, const void* q, const void* k_new,
                                 const void* v_new, const int* cu_q, int total_new, int max_new_per_seq, int max_seqlen,
                                 void* out, float* lse_out, void* workspace, hipStream_t stream) {
-    PrefillPaged pg;
-    pg.kv = kv;
-    pg.k_new = reinterpret_cast<const uint16_t*>(k_new);
-    pg.v_new = reinterpret_cast<const uint16_t*>(v_new);
     (void)workspace;
     (void)max_seqlen;
-    // the chunk's rows start anywhere inside a 256-row block: one block more than the chunk length needs
-    const int blocks_per_seq = (max_new_per_seq + kRowsPerBlock - 1) / kRowsPerBlock + 1;
-    const PrefillSchedule sched = make_schedule(lp, blocks_per_seq, kv.batch);
-    const int grid = kXcds * (sched.cls[0].items_per_xcd + sched.cls[1].items_per_xcd);
-    const PrefillMask mk = {};
-#define LSERVE_PREFILL_PAGED(BITS)                                                                                     \
-    hipLaunchKernelGGL((sparse_prefill_kernel<T, kPaged, BITS>), dim3(grid), dim3(kPrefillThreads), 0, stream, lp,     \
-                       reinterpret_cast<const uint16_t*>(q), nullptr, nullptr, cu_q, kv.batch, blocks_per_seq,         \
-                       reinterpret_cast<uint16_t*>(out), lse_out, total_new, sched, mk, pg)
-    if (kv.kv_bits == 8)
-        LSERVE_PREFILL_PAGED(8);
-    else if (kv.kv_bits == 4)
-        LSERVE_PREFILL_PAGED(4);
-    else
-        LSERVE_PREFILL_PAGED(16);
-#undef LSERVE_PREFILL_PAGED
-    return hipGetLastError();
+    PrefillLaunch a = {};
+    a.lp = &lp;
+    a.q = reinterpret_cast<const uint16_t*>(q);
+    a.cu_seqlens = cu_q;
+    a.batch = kv.batch;
+    a.total_tokens = total_new;
+    a.out = reinterpret_cast<uint16_t*>(out);
+    a.lse_out = lse_out;
+    a.pg.kv = kv;
+    a.pg.k_new = reinterpret_cast<const uint16_t*>(k_new);
+    a.pg.v_new = reinterpret_cast<const uint16_t*>(v_new);
+    a.stream = stream;
+    // the history is not known on the host: the walks are taken to be as long as the page table allows
+    const double walk = kv.max_pages;
+    const PrefillShape shape = choose_shape(lp, (double)total_new / kTile + 0.5 * kv.batch, walk, walk, kv.kv_bits);
+    a.sched = make_schedule(lp, shape, false, max_new_per_seq, total_new, true, kv.batch);
+    if (kv.kv_bits == 8) return launch_slices<T, kPaged, 8>(a, shape.slices);
+    if (kv.kv_bits == 4) return launch_slices<T, kPaged, 4>(a, shape.slices);
+    return launch_slices<T, kPaged, 16>(a, shape.slices);
 }
 
 }  // namespace
@@ -778,7 +1194,7 @@ size_t prefill_workspace_bytes(const LayerParams& lp, int total_tokens, int batc
 // query rows).
 size_t masked_prefill_workspace_bytes(const LayerParams& lp, int total_tokens, int batch, int max_seqlen, int num_masks,
                                       int nnz) {
-    const int blocks_per_seq = (max_seqlen + kRowsPerBlock - 1) / kRowsPerBlock;
+    const int blocks_per_seq = mask_blocks(max_seqlen);
     (void)lp;
     (void)total_tokens;
     return align16((size_t)nnz * sizeof(int)) +

@@ -1,0 +1,108 @@
+"""Prefill launches of every shape the host chooses (one, two and four key slices, heads or query tiles as the units of a
+workgroup, blocks in order over the batch or per sequence), sampled rows against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from workloads import Workload, make_prefill_inputs
+
+from parity import LSE_TOL_PREFILL, assert_attention_close, assert_lse_close
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(w, lengths, mask=None, head_mask=None, past_diagonal=0):
+    import paper_2502_14866_amd as L
+
+    L.load_library()
+    dev = torch.device("cuda:0")
+    pin = make_prefill_inputs(w, lengths=lengths)
+    desc = L.AttnDesc(w.num_q_heads, w.num_kv_heads, w.streaming_flags(), dtype=w.torch_dtype,
+                      sink_tokens=w.sink_tokens, local_tokens=w.local_tokens)
+    q, k, v, cu = pin.q.to(dev), pin.k.to(dev), pin.v.to(dev), pin.cu_seqlens.to(dev)
+    out = torch.full_like(q, float("nan"))
+    lse = torch.full((w.num_q_heads, q.shape[0]), float("nan"), dtype=torch.float32, device=dev)
+    if mask is None:
+        L.lserve_sparse_prefill(desc, q, k, v, cu, max(lengths), out, lse)
+        csr = None
+    else:
+        from helpers import block_mask_csr
+        qts, rp, cl, rows = csr = block_mask_csr(mask, lengths)
+        if past_diagonal:  # entries above a row's own tile, to be ignored: the same for both sides but for these
+            tile = np.concatenate([np.arange(b - a) for a, b in zip(qts[:-1], qts[1:])] * len(mask))
+            last = np.concatenate([np.full(b - a, b - a) for a, b in zip(qts[:-1], qts[1:])] * len(mask))
+            more = [list(cl[rp[r]:rp[r + 1]]) + list(range(tile[r] + 1, min(tile[r] + past_diagonal, last[r])))
+                    for r in range(len(tile))]
+            rp = np.concatenate([[0], np.cumsum([len(x) for x in more])])
+            cl = np.concatenate(more)
+        i32 = lambda a: torch.as_tensor(np.asarray(a, dtype=np.int32)).to(dev)
+        bm = L.BlockMask(i32(head_mask), i32(qts), i32(rp), i32(cl), len(mask), rows)
+        need = L.lserve_masked_prefill_workspace_bytes(desc, len(lengths), q.shape[0], max(lengths), len(mask), len(cl))
+        ws = torch.empty((need,), dtype=torch.uint8, device=dev)
+        L.lserve_sparse_prefill_masked(desc, bm, q, k, v, cu, max(lengths), out, lse, ws)
+    torch.cuda.synchronize()
+    assert not torch.isnan(out).any() and not torch.isnan(lse).any()
+    return pin, out, lse, csr
+
+
+def _sample(lengths, per_seq, seed):
+    """First, last and random rows of every sequence, tile edges among them."""
+    rng = np.random.default_rng(seed)
+    tok, at = [], 0
+    for n in lengths:
+        rows = {0, n - 1, min(63, n - 1), min(64, n - 1), (n - 1) // 64 * 64} | set(rng.integers(0, n, per_seq).tolist())
+        tok += [at + r for r in sorted(rows)]
+        at += n
+    return np.asarray(tok, dtype=np.int32)
+
+
+def _check(w, lengths, pin, out, lse, ref, lse_ref, tok, what):
+    H = w.num_q_heads
+    got = out[torch.from_numpy(tok).long().to(out.device)]
+    assert_attention_close(got, ref.reshape(len(tok), H, -1), what)
+    got_lse = lse.t()[torch.from_numpy(tok).long().to(out.device)].contiguous()
+    assert_lse_close(got_lse, lse_ref.reshape(len(tok), H), what + " lse", LSE_TOL_PREFILL[w.dtype])
+
+
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+@pytest.mark.parametrize("heads,kv_heads,lengths", [
+    (8, 2, (65,)),                                # four slices, streaming heads folded too
+    (32, 8, (2047,)),                             # two slices, streaming heads in units of their own
+    (32, 8, (4097,)),                             # one slice, four heads of a group per workgroup
+    (8, 8, (4500, 1)),                            # no groups: query tiles as units, one-token sequence
+    (12, 4, (3000, 700)),                         # three heads per group: neither two nor four divide it
+    (12, 2, (1500, 333, 64)),                     # six: two heads and two query tiles
+    (64, 8, (1100, 77, 640)),                     # eight
+    (8, 2, tuple(3 + 17 * i for i in range(64))),  # the largest batch dealt out in order, one lane per sequence
+    (8, 2, tuple(5 + 16 * i for i in range(67))),  # a batch beyond that
+])
+def test_prefill_launch_shapes(dtype, heads, kv_heads, lengths):
+    w = Workload(name="ps", batch=len(lengths), num_q_heads=heads, num_kv_heads=kv_heads, dtype=dtype,
+                 streaming_kv_heads=tuple(range(kv_heads // 2)), sink_tokens=64, local_tokens=192, seed=53)
+    pin, out, lse, _ = _run(w, lengths)
+    tok = _sample(lengths, 6 if len(lengths) > 8 else 24, 5)
+    t, h = np.repeat(tok, heads), np.tile(np.arange(heads, dtype=np.int32), len(tok))
+    ref, lse_ref = oracle.sparse_prefill_rows(pin.q, pin.k, pin.v, pin.cu_seqlens, w.streaming_flags(), 64, w.sink_tokens,
+                                              w.local_tokens, t, h)
+    _check(w, lengths, pin, out, lse, ref, lse_ref, tok, f"prefill {dtype} {heads}/{kv_heads} {len(lengths)} sequences")
+
+
+@pytest.mark.parametrize("lengths", [(4160, 1000), (300, 129)])
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+def test_masked_prefill_splits_its_blocks_between_merged_and_row_by_row_walks(dtype, lengths):
+    """Large enough for merged lists: mask 0 keeps the same tiles in neighbouring rows (merged walks), mask 1 others in
+    every row (walked row by row), mask 2 mixes the two by block; one head keeps the analytic pattern; row lists that go
+    on past the diagonal are cut there.  The small batch takes the caller's rows as they are, in four key slices."""
+    w = Workload(name="pm3", batch=2, num_q_heads=32, num_kv_heads=8, dtype=dtype, streaming_kv_heads=(0, 1, 2, 3),
+                 sink_tokens=128, local_tokens=512, seed=59)
+    same = lambda b, i: [j for j in range(i + 1) if j % 3 == 0 or j == i]
+    other = lambda b, i: [j for j in range(i + 1) if (j + i) % 4 == 0 or j == i]
+    mixed = lambda b, i: same(b, i) if (i // 4) % 2 else other(b, i)
+    head_mask = [-1 if h < 13 else h % 3 for h in range(32)]
+    pin, out, lse, (qts, rp, cl, rows) = _run(w, lengths, [same, other, mixed], head_mask, past_diagonal=7)
+    tok = _sample(lengths, 40, 9)
+    t, h = np.repeat(tok, 32), np.tile(np.arange(32, dtype=np.int32), len(tok))
+    ref, lse_ref = oracle.block_mask_prefill_rows(pin.q, pin.k, pin.v, pin.cu_seqlens, w.streaming_flags(), 64,
+                                                  w.sink_tokens, w.local_tokens, head_mask, qts, rp, cl, rows, t, h)
+    _check(w, lengths, pin, out, lse, ref, lse_ref, tok, f"masked prefill {dtype}")
