@@ -19,7 +19,7 @@
 //
 // Pages may also hold quantised rows (Sec. 3.2: 8- or 4-bit codes with one fp16 scale and zero point per
 // token, stored after the page's rows).  The kernel is the same with the slab loads and the per-page
-// arithmetic swapped (template parameter BITS); see process_quantised_quarter_page.
+// arithmetic swapped (template parameter BITS); see quantised_quarter_page.
 #include <algorithm>
 
 #include "kernels.h"
@@ -91,9 +91,10 @@ template <int NP, int BITS> struct Slabs;
 template <int NP> struct Slabs<NP, 16> {
     uint4 k[KeyMap<NP>::ITS], v[KeyMap<NP>::ITS];
 };
-// Quantised pages (N_P = 64 only): a token row is 128 one-byte codes.  The key map keeps four lanes per token,
-// each with two 16-byte chunks; the value map keeps 16 lanes per token row, each with eight codes.  The
-// (scale, zero) pairs of both the K and the V row of a token travel with the key map's lane of that token.
+// Quantised pages (N_P = 64 only): a token row is 128 one-byte codes.  Lane (t, g) = (lane % 16, lane / 16) reads, as
+// the matrix instructions take their operands, two 16-byte chunks of the key row of token t, and eight codes (its
+// t-th eight channels) of the value rows of tokens 4 g .. 4 g + 3.  The (scale, zero) pairs of both the K and the V
+// row of token t travel with it.
 template <> struct Slabs<64, 8> {
     uint4 k[2];
     uint2 v[4];
@@ -108,70 +109,88 @@ template <> struct Slabs<64, 4> {
     uint32_t ksz, vsz;
 };
 
+// Slab loads: a wave-uniform slab address plus a 32-bit lane offset (and a constant), which is the form the load
+// instruction takes as it is; with 64-bit lane addresses the additions were a third of the vector instructions of the
+// quantised kernels.  live: all ones, or 0 for a request that only keeps the count of loads in flight what it is (see
+// the page loop): every lane then reads the slab's first bytes.
+template <class V> __device__ __forceinline__ V load_at(const uint4* slab, unsigned lane_bytes, unsigned constant_bytes) {
+    return *reinterpret_cast<const V*>(reinterpret_cast<const char*>(slab) + lane_bytes + constant_bytes);
+}
+
 template <int NP>
-__device__ __forceinline__ void load_k(Slabs<NP, 16>& s, const uint4* kslab, int tok0, int lane) {
+__device__ __forceinline__ void load_k(Slabs<NP, 16>& s, const uint4* kslab, int tok0, int lane, unsigned live) {
     using M = KeyMap<NP>;
+    const unsigned at = (unsigned)((tok0 + lane / M::LPT) * (kHeadDim / 8) + lane % M::LPT) * 16u & live;
 #pragma unroll
     for (int ps = 0; ps < M::PASSES; ++ps)
 #pragma unroll
         for (int j = 0; j < M::KLOADS; ++j)
-            s.k[ps * M::KLOADS + j] =
-                kslab[(size_t)(tok0 + ps * M::TPP + lane / M::LPT) * (kHeadDim / 8) + M::LPT * j + lane % M::LPT];
+            s.k[ps * M::KLOADS + j] = load_at<uint4>(kslab, at, (ps * M::TPP * (kHeadDim / 8) + M::LPT * j) * 16u);
 }
 
 template <int NP>
-__device__ __forceinline__ void load_v(Slabs<NP, 16>& s, const uint4* vslab, int tok0, int r, int c, int) {
+__device__ __forceinline__ void load_v(Slabs<NP, 16>& s, const uint4* vslab, int tok0, int r, int c, int, unsigned live) {
+    const unsigned at = (unsigned)((tok0 + r) * (kHeadDim / 8) + c) * 16u & live;
 #pragma unroll
-    for (int it = 0; it < KeyMap<NP>::ITS; ++it) s.v[it] = vslab[(size_t)(tok0 + 4 * it + r) * (kHeadDim / 8) + c];
+    for (int it = 0; it < KeyMap<NP>::ITS; ++it) s.v[it] = load_at<uint4>(vslab, at, 4 * it * kHeadDim * 2u);
 }
 
-__device__ __forceinline__ void load_k(Slabs<64, 4>& s, const uint4* kslab, int tok0, int lane) {
-    const int tok = tok0 + lane / 4;
-    s.k[0] = kslab[(size_t)tok * (kHeadDim / 32) + lane % 4];
-    s.ksz = reinterpret_cast<const uint32_t*>(kslab + 64 * (kHeadDim / 32))[tok];
+__device__ __forceinline__ void load_k(Slabs<64, 4>& s, const uint4* kslab, int tok0, int lane, unsigned live) {
+    const int tok = tok0 + lane % 16;
+    s.k[0] = load_at<uint4>(kslab, (unsigned)(tok * (kHeadDim / 32) + lane / 16) * 16u & live, 0);
+    s.ksz = load_at<uint32_t>(kslab + 64 * (kHeadDim / 32), (unsigned)tok * 4u & live, 0);
 }
-__device__ __forceinline__ void load_v(Slabs<64, 4>& s, const uint4* vslab, int tok0, int r, int c, int lane) {
-    const uint32_t* rows = reinterpret_cast<const uint32_t*>(vslab);
+__device__ __forceinline__ void load_v(Slabs<64, 4>& s, const uint4* vslab, int tok0, int r, int c, int lane, unsigned live) {
+    const unsigned at = (unsigned)((tok0 + 4 * r) * (kHeadDim / 8) + c) * 4u & live;
 #pragma unroll
-    for (int it = 0; it < 4; ++it) s.v[it] = rows[(size_t)(tok0 + 4 * it + r) * (kHeadDim / 8) + c];
-    s.vsz = reinterpret_cast<const uint32_t*>(vslab + 64 * (kHeadDim / 32))[tok0 + lane / 4];
+    for (int it = 0; it < 4; ++it) s.v[it] = load_at<uint32_t>(vslab, at, it * kHeadDim / 2u);
+    s.vsz = load_at<uint32_t>(vslab + 64 * (kHeadDim / 32), (unsigned)(tok0 + lane % 16) * 4u & live, 0);
 }
-__device__ __forceinline__ void load_k(Slabs<64, 8>& s, const uint4* kslab, int tok0, int lane) {
-    const int tok = tok0 + lane / 4;
+__device__ __forceinline__ void load_k(Slabs<64, 8>& s, const uint4* kslab, int tok0, int lane, unsigned live) {
+    const int tok = tok0 + lane % 16;
+    const unsigned at = (unsigned)(tok * (kHeadDim / 16) + lane / 16) * 16u & live;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) s.k[j] = kslab[(size_t)tok * (kHeadDim / 16) + 4 * j + lane % 4];
-    s.ksz = reinterpret_cast<const uint32_t*>(kslab + 64 * (kHeadDim / 16))[tok];
+    for (int j = 0; j < 2; ++j) s.k[j] = load_at<uint4>(kslab, at, 4 * j * 16u);
+    s.ksz = load_at<uint32_t>(kslab + 64 * (kHeadDim / 16), (unsigned)tok * 4u & live, 0);
 }
-__device__ __forceinline__ void load_v(Slabs<64, 8>& s, const uint4* vslab, int tok0, int r, int c, int lane) {
-    const uint2* rows = reinterpret_cast<const uint2*>(vslab);
+__device__ __forceinline__ void load_v(Slabs<64, 8>& s, const uint4* vslab, int tok0, int r, int c, int lane, unsigned live) {
+    const unsigned at = (unsigned)((tok0 + 4 * r) * (kHeadDim / 8) + c) * 8u & live;
 #pragma unroll
-    for (int it = 0; it < 4; ++it) s.v[it] = rows[(size_t)(tok0 + 4 * it + r) * (kHeadDim / 8) + c];
-    s.vsz = reinterpret_cast<const uint32_t*>(vslab + 64 * (kHeadDim / 16))[tok0 + lane / 4];
+    for (int it = 0; it < 4; ++it) s.v[it] = load_at<uint2>(vslab, at, it * kHeadDim);
+    s.vsz = load_at<uint32_t>(vslab + 64 * (kHeadDim / 16), (unsigned)(tok0 + lane % 16) * 4u & live, 0);
 }
 
-template <int N> struct WaveState {
-    float m[N], l[N], o[N][8];
-    float z[N];  // quantised values only: sum of weight * zero point, the same for every channel
-    // Quantised pages keep the softmax of a token in the four lanes that read its key, one query head (two for
-    // groups above four) per lane: lane l of a wave owns heads l % 4 and l % 4 + 4.  Running maximum, sum of weights
-    // and zero-point sum of those heads; w_sum: per head, the sum of the 16-bit weights this lane fed to `o`.
+typedef float floatx4_t __attribute__((ext_vector_type(4)));
+
+template <int N, int BITS> struct WaveState {
+    // Quantised pages: lane (t, g) keeps the softmax of query heads g and g + 4 (the latter for groups above four): their
+    // running maxima (equal over the sixteen lanes of g), and its token's share of the sums of weights and of weight *
+    // zero point.  acc[m][j] is the output of head g + 4 j in channel 8 t + m, in units of the stored weights and codes
+    // (see quantised_quarter_page); acc[m][2], acc[m][3] belong to no head.  q: the queries as matrix operands.
     static constexpr int kHeadsPerLane = (N + 3) / 4;
-    float lane_m[kHeadsPerLane], lane_l[kHeadsPerLane], lane_z[kHeadsPerLane], w_sum[N];
+    float m[kHeadsPerLane], l[kHeadsPerLane], z[kHeadsPerLane], q_sum[kHeadsPerLane];
+    floatx4_t acc[8];
+    uint4 q[4];
+    __device__ __forceinline__ void reset() {
+#pragma unroll
+        for (int j = 0; j < kHeadsPerLane; ++j) {
+            m[j] = -INFINITY;
+            l[j] = 0.f;
+            z[j] = 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[i] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+    }
+};
+template <int N> struct WaveState<N, 16> {
+    float m[N], l[N], o[N][8];
     __device__ __forceinline__ void reset() {
 #pragma unroll
         for (int hh = 0; hh < N; ++hh) {
             m[hh] = -INFINITY;
             l[hh] = 0.f;
-            z[hh] = 0.f;
-            w_sum[hh] = 0.f;
 #pragma unroll
             for (int i = 0; i < 8; ++i) o[hh][i] = 0.f;
-        }
-#pragma unroll
-        for (int g = 0; g < kHeadsPerLane; ++g) {
-            lane_m[g] = -INFINITY;
-            lane_l[g] = 0.f;
-            lane_z[g] = 0.f;
         }
     }
 };
@@ -197,7 +216,7 @@ __device__ __forceinline__ float wave_max_of_quads(float x) {
 // One quarter page.  q_lds: [N][16] 16-byte chunks of the group's queries; p_lds: this wave's
 // [NP / 4][p_row(N)] weight buffer.  `valid` = tokens of the page below the sequence length.
 template <class T, int N, int NP>
-__device__ __forceinline__ void process_quarter_page(WaveState<N>& st, const uint4* q_lds, const float*, float* p_lds,
+__device__ __forceinline__ void process_quarter_page(WaveState<N, 16>& st, const uint4* q_lds, float* p_lds,
                                                      Slabs<NP, 16>& cur, int valid, int tok0, int lane,
                                                      float scale_log2) {
     using M = KeyMap<NP>;
@@ -243,7 +262,6 @@ __device__ __forceinline__ void process_quarter_page(WaveState<N>& st, const uin
             const float alpha = __builtin_amdgcn_exp2f(st.m[hh] - pm);
             st.m[hh] = pm;
             st.l[hh] *= alpha;
-            st.z[hh] *= alpha;
 #pragma unroll
             for (int i = 0; i < 8; ++i) st.o[hh][i] *= alpha;
         }
@@ -289,204 +307,160 @@ __device__ __forceinline__ void process_quarter_page(WaveState<N>& st, const uin
     __builtin_amdgcn_wave_barrier();
 }
 
-// Value of lane k of the caller's group of four lanes.
-__device__ __forceinline__ float quad_lane(float x, int k) {
-    switch (k) {
-        case 0: return dpp_f<0x00>(x);
-        case 1: return dpp_f<0x55>(x);
-        case 2: return dpp_f<0xAA>(x);
-        default: return dpp_f<0xFF>(x);
-    }
-}
+constexpr float kWeightScale = 64.f;   // keeps weight * scale clear of the fp16 subnormals, and below 65504 for any fp16 row
+constexpr float kCodeUnit = 0x1p-24f;  // value of the fp16 number whose bits are 1
 
-// Sums x0 .. x3 over the four lanes that share a token; lane k of the four receives the total of x_k.
-__device__ __forceinline__ float quad_sum_scatter(float x0, float x1, float x2, float x3, int lane) {
-    const bool odd = lane & 1, upper = lane & 2;
-    float a0 = odd ? x1 : x0, a1 = odd ? x3 : x2;
-    const float b0 = odd ? x0 : x1, b1 = odd ? x2 : x3;
-    a0 += dpp_f<kDppXor1>(b0);
-    a1 += dpp_f<kDppXor1>(b1);
-    const float keep = upper ? a1 : a0, send = upper ? a0 : a1;
-    return keep + dpp_f<kDppXor2>(send);
-}
+typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 
-// Maximum over the sixteen lanes of a wave that have the caller's lane % 4; all of them receive it.
-__device__ __forceinline__ float wave_max_same_quarter(float x) {
-    x = fmaxf(x, dpp_f<0x124>(x));  // row_ror:4
-    x = fmaxf(x, dpp_f<0x128>(x));  // row_ror:8
-    return rows4_max(x);
-}
-
-constexpr float kWeightScale = 64.f;  // keeps weight * scale clear of the fp16 subnormals, and below 65504 for any fp16 row
-
-// The same over a quantised quarter page.  q_lds holds the queries as fp16 whatever the storage type and
-// q_sum[h] the sum of query h's channels.  With k = code * scale + zero the logit of a token is
-//   q . k = scale * (q . code) + zero * sum(q).
-// Codes become fp16 without a conversion: byte c under the exponent byte 0x64 is the fp16 number 1024 + c,
-// so one byte permute yields two operands of the packed dot instruction, and the 1024 * sum(q) this adds
-// to every dot product is taken off again.  For values the weight is folded into the scale,
+// The same over a quantised quarter page, on the matrix cores.  With k = code * scale + zero the logit of a token is
+//   q . k = scale * (q . code) + zero * sum(q),
+// and with the weight folded into the scale of a value row,
 //   sum_t p_t v_t = sum_t (p_t scale_t) code_t + sum_t p_t zero_t,
-// and the second sum, which no channel distinguishes, is kept as one number per query head.
-//
-// The instruction count, not the memory system, bounds this path (a page is half or a quarter of the bytes for the
-// same number of tokens), so it is arranged to issue as little as possible per token:
-//   - after the dot products the four lanes of a token hold four partial sums for each of N heads; a reduce-scatter
-//     leaves lane k with the total of head k, and maximum, exponential, sums and scales are then computed once
-//     per (token, head) instead of four times;
-//   - the weights go to LDS as fp16 (times kWeightScale), two tokens of a value row side by side, so that the
-//     value side reads ready-made pairs and takes two tokens per packed dot instruction, with the codes of the
-//     two tokens interleaved by byte permutes and lifted to 1024 + code like the keys; the 1024 * (sum of the
-//     rounded weights) this adds to every channel is subtracted, and the scale undone, once per piece of a list
-//     (lane_state_to_wave_state).  A weight is rounded to fp16 (2^-11 relative) before it meets the codes; the
-//     denominator keeps the unrounded weights.
-// p_lds is read as 16-bit [token pair][value row r][p_row(N) heads][2 tokens].
-template <class T, int N, int BITS>
-__device__ __forceinline__ void process_quantised_quarter_page(WaveState<N>& st, const uint4* q_lds, const float* q_sum,
-                                                     float* p_lds, Slabs<64, BITS>& cur, int valid, int tok0, int lane,
-                                                     float scale_log2) {
+// whose second sum no channel distinguishes: one number per query head.  Both first sums are products of small
+// matrices over the sixteen tokens of a wavefront's quarter page,
+//   scores (heads x tokens) = Q (heads x 128) * codes (128 x tokens)    v_mfma_f32_16x16x32_f16, four of them
+//   out (heads x channels) += weights (heads x 16) * codes (16 x 128)   v_mfma_f32_16x16x16_f16, one per 16 channels
+// with query head g + 4 j in row 4 g + j, so that lane (t, g) receives the scores of its own heads g and g + 4 and, later,
+// their outputs; the other rows hold copies whose results nobody reads.
+// A code needs no conversion: a byte (or nibble) alone in the low bits of a 16-bit half is the fp16 subnormal
+// code * 2^-24, which the matrix instructions of gfx950 take at its value, so one byte permute (or mask) yields two operands
+// and the unit is folded into factors that are there anyway.  Nibbles four bits up stand for 16 * code: they get products
+// (keys) or output channels (values) of their own.  Weights are rounded to fp16 (2^-11 relative), times kWeightScale, before
+// they meet the codes, and cross lanes through LDS; the denominator keeps the unrounded weights.
+// The instruction count, not the memory system, bounds this path (a page is half or a quarter of the bytes for the same
+// number of tokens): with packed dot products it took about 215 vector instructions per quarter page and four heads, now
+// about 90.  64 sequences of 9K .. 24K tokens, 32 / 8 heads, 4096-token budget: 60.0 -> 39 us over 4-bit pages, 65.3 ->
+// 58 us over 8-bit ones (324 MB: 5.6 TB/s); eight heads per group at batch 16: 31.7 -> 19.6 and 40.1 -> 21.9 us.
+// p_lds is read as fp16 [heads][16 tokens].
+template <int N, int BITS>
+__device__ __forceinline__ void quantised_quarter_page(WaveState<N, BITS>& st, float* p_lds, Slabs<64, BITS>& cur, int valid,
+                                                       int tok0, int lane, float scale_log2) {
     static_assert(BITS == 8 || BITS == 4, "quantised pages");
-    constexpr int PR = p_row(N), HPL = WaveState<N>::kHeadsPerLane;
-    const int r = lane / 16, qd = lane % 4;
-    float s[4 * HPL];
+    constexpr int HPL = WaveState<N, BITS>::kHeadsPerLane;
+    const int t = lane % 16, g = lane / 16;
+    auto mfma_k = [](uint4 a, uint4 b, floatx4_t c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a), __builtin_bit_cast(half8_t, b), c, 0, 0, 0);
+    };
+    floatx4_t s = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (BITS == 8) {
 #pragma unroll
-    for (int hh = 0; hh < 4 * HPL; ++hh) s[hh] = 0.f;
-    // 16 channels at a time: four bytes-per-code words (two of the 8-bit chunk's words, or the low and the high
-    // halves of two of the 4-bit chunk's words) become eight fp16 pairs and meet two 8-channel query chunks
+        for (int j = 0; j < 2; ++j) {
+            const uint32_t w[4] = {cur.k[j].x, cur.k[j].y, cur.k[j].z, cur.k[j].w};
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        uint32_t kw[4];
-        int qc;  // first of the two query chunks
-        if constexpr (BITS == 8) {
-            kw[0] = cur.k[j].x, kw[1] = cur.k[j].y, kw[2] = cur.k[j].z, kw[3] = cur.k[j].w;
-            qc = 2 * (4 * j + lane % 4);  // 16-byte chunk 4 j + lane % 4 of the row = channels 16 cb .. 16 cb + 15
-        } else {
-            const uint32_t w0 = j == 0 ? cur.k[0].x : cur.k[0].z, w1 = j == 0 ? cur.k[0].y : cur.k[0].w;
-            kw[0] = w0 & 0x0f0f0f0fu, kw[1] = (w0 >> 4) & 0x0f0f0f0fu;  // channels 8 g .. 8 g + 3, 8 g + 4 .. 8 g + 7
-            kw[2] = w1 & 0x0f0f0f0fu, kw[3] = (w1 >> 4) & 0x0f0f0f0fu;
-            qc = 4 * (lane % 4) + 2 * j;  // word g = 4 (lane % 4) + 2 j + {0, 1} of the row = channels 8 g .. 8 g + 7
-        }
-        uint32_t kh[8];  // 16 codes as eight fp16 pairs (1024 + code)
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            kh[2 * d] = __builtin_amdgcn_perm(0x64646464u, kw[d], 0x04010400u);
-            kh[2 * d + 1] = __builtin_amdgcn_perm(0x64646464u, kw[d], 0x04030402u);
-        }
-#pragma unroll
-        for (int hh = 0; hh < N; ++hh) {
-            const uint4 qa = q_lds[hh * 16 + qc], qb = q_lds[hh * 16 + qc + 1];
-            const uint32_t qw[8] = {qa.x, qa.y, qa.z, qa.w, qb.x, qb.y, qb.z, qb.w};
-#pragma unroll
-            for (int u = 0; u < 8; ++u) s[hh] = Elem<F16>::dot2(qw[u], kh[u], s[hh]);
-        }
-    }
-    const bool dead = valid < 64 && tok0 + lane / 4 >= valid;
-    const half2_t ksz = __builtin_bit_cast(half2_t, cur.ksz), vsz = __builtin_bit_cast(half2_t, cur.vsz);
-    const float k_scale = (float)ksz[0] * scale_log2, k_zero = (float)ksz[1] * scale_log2;
-    // slots past the end may hold anything
-    const float v_scale = dead ? 0.f : (float)vsz[0] * kWeightScale, v_zero = dead ? 0.f : (float)vsz[1];
-    // this lane's place in the weight buffer: token lane / 4 of the quarter page is member (t / 4) % 2 of pair t / 8 of
-    // value row t % 4
-    const int t = lane / 4;
-    _Float16* w_lds = reinterpret_cast<_Float16*>(p_lds) + (((t / 8) * 4 + t % 4) * PR + qd) * 2 + (t / 4) % 2;
-#pragma unroll
-    for (int g = 0; g < HPL; ++g) {
-        const bool mine = 4 * g + qd < N;  // lanes without a head of their own carry zeros along
-        const float qs = mine ? q_sum[4 * g + qd] : 0.f;
-        const float dot = quad_sum_scatter(s[4 * g], s[4 * g + 1], s[4 * g + 2], s[4 * g + 3], lane) - 1024.f * qs;
-        const float x = dead ? -INFINITY : __builtin_fmaf(k_scale, dot, k_zero * qs);
-        const float pm = wave_max_same_quarter(x);
-        const bool moved = pm > st.lane_m[g];
-        if (__any(moved)) {  // rare after the first pages: some head's running maximum moves
-            const float alpha = moved ? __builtin_amdgcn_exp2f(st.lane_m[g] - pm) : 1.f;
-            st.lane_m[g] = moved ? pm : st.lane_m[g];
-            st.lane_l[g] *= alpha;
-            st.lane_z[g] *= alpha;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                if (4 * g + k >= N) continue;
-                const float a = quad_lane(alpha, k);
-                st.w_sum[4 * g + k] *= a;
-#pragma unroll
-                for (int i = 0; i < 8; ++i) st.o[4 * g + k][i] *= a;
+            for (int u = 0; u < 2; ++u) {  // selector byte 0x0c: zero
+                const uint4 c = make_uint4(__builtin_amdgcn_perm(0u, w[2 * u], 0x0c010c00u), __builtin_amdgcn_perm(0u, w[2 * u], 0x0c030c02u),
+                                           __builtin_amdgcn_perm(0u, w[2 * u + 1], 0x0c010c00u), __builtin_amdgcn_perm(0u, w[2 * u + 1], 0x0c030c02u));
+                s = mfma_k(st.q[2 * j + u], c, s);
             }
         }
-        const float m_safe = st.lane_m[g] == -INFINITY ? 0.f : st.lane_m[g];
-        const float p = dead ? 0.f : __builtin_amdgcn_exp2f(x - m_safe);
-        st.lane_l[g] += p;
-        st.lane_z[g] = __builtin_fmaf(p, v_zero, st.lane_z[g]);
-        w_lds[8 * g] = (_Float16)(p * v_scale);  // head 4 g + qd: four heads = four token pairs = eight halves on
-    }
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int pr = 0; pr < 2; ++pr) {
-        uint32_t ta[2], tb[2];  // one byte per code, channels 0 .. 3 and 4 .. 7 of the pair's two tokens
-        if constexpr (BITS == 8) {
-            ta[0] = cur.v[2 * pr].x, ta[1] = cur.v[2 * pr].y;
-            tb[0] = cur.v[2 * pr + 1].x, tb[1] = cur.v[2 * pr + 1].y;
-        } else {
-            ta[0] = cur.v[2 * pr] & 0x0f0f0f0fu, ta[1] = (cur.v[2 * pr] >> 4) & 0x0f0f0f0fu;
-            tb[0] = cur.v[2 * pr + 1] & 0x0f0f0f0fu, tb[1] = (cur.v[2 * pr + 1] >> 4) & 0x0f0f0f0fu;
-        }
-        uint32_t wp[PR];  // (weight of the first token, weight of the second) per head, fp16
-#pragma unroll
-        for (int x4 = 0; x4 < PR / 4; ++x4) {
-            const uint4 w4 = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(p_lds) + (pr * 4 + r) * PR + 4 * x4);
-            wp[4 * x4] = w4.x, wp[4 * x4 + 1] = w4.y, wp[4 * x4 + 2] = w4.z, wp[4 * x4 + 3] = w4.w;
-        }
-        uint32_t ch[8];  // channel i of both tokens as an fp16 pair (1024 + code)
+    } else {
+        const uint32_t w[4] = {cur.k[0].x, cur.k[0].y, cur.k[0].z, cur.k[0].w};
+        floatx4_t s16 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            const uint32_t lo = __builtin_amdgcn_perm(tb[u], ta[u], 0x05010400u);  // a0 b0 a1 b1
-            const uint32_t hi = __builtin_amdgcn_perm(tb[u], ta[u], 0x07030602u);  // a2 b2 a3 b3
-            ch[4 * u] = __builtin_amdgcn_perm(0x64646464u, lo, 0x04010400u);
-            ch[4 * u + 1] = __builtin_amdgcn_perm(0x64646464u, lo, 0x04030402u);
-            ch[4 * u + 2] = __builtin_amdgcn_perm(0x64646464u, hi, 0x04010400u);
-            ch[4 * u + 3] = __builtin_amdgcn_perm(0x64646464u, hi, 0x04030402u);
+            const uint32_t a = w[2 * u], b = w[2 * u + 1], a8 = a >> 8, b8 = b >> 8;
+            s = mfma_k(st.q[2 * u], make_uint4(a & 0x000f000fu, a8 & 0x000f000fu, b & 0x000f000fu, b8 & 0x000f000fu), s);
+            s16 = mfma_k(st.q[2 * u + 1], make_uint4(a & 0x00f000f0u, a8 & 0x00f000f0u, b & 0x00f000f0u, b8 & 0x00f000f0u), s16);
         }
 #pragma unroll
-        for (int hh = 0; hh < N; ++hh) {
-            st.w_sum[hh] = Elem<F16>::dot2(wp[hh], 0x3c003c00u, st.w_sum[hh]);
+        for (int j = 0; j < HPL; ++j) s[j] = __builtin_fmaf(0.0625f, s16[j], s[j]);
+    }
+    const bool dead = valid < 64 && tok0 + t >= valid;
+    const half2_t ksz = __builtin_bit_cast(half2_t, cur.ksz), vsz = __builtin_bit_cast(half2_t, cur.vsz);
+    const float k_scale = (float)ksz[0] * (scale_log2 / kCodeUnit), k_zero = (float)ksz[1] * scale_log2;
+    // slots past the end may hold anything
+    const float v_scale = dead ? 0.f : (float)vsz[0] * kWeightScale, v_zero = dead ? 0.f : (float)vsz[1];
+    _Float16* w_lds = reinterpret_cast<_Float16*>(p_lds);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) st.o[hh][i] = Elem<F16>::dot2(wp[hh], ch[i], st.o[hh][i]);
+    for (int j = 0; j < HPL; ++j) {
+        const float x = dead ? -INFINITY : __builtin_fmaf(k_scale, s[j], k_zero * st.q_sum[j]);
+        float pm = x;  // maximum over the sixteen tokens
+        pm = fmaxf(pm, dpp_f<kDppXor1>(pm));
+        pm = fmaxf(pm, dpp_f<kDppXor2>(pm));
+        pm = fmaxf(pm, dpp_f<kDppHalfMirror>(pm));
+        pm = fmaxf(pm, dpp_f<kDppMirror>(pm));
+        const bool moved = pm > st.m[j];
+        if (__any(moved)) {  // rare after the first pages: some head's running maximum moves
+            const float alpha = moved ? __builtin_amdgcn_exp2f(st.m[j] - pm) : 1.f;
+            st.m[j] = moved ? pm : st.m[j];
+            st.l[j] *= alpha;
+            st.z[j] *= alpha;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) st.acc[i][j] *= alpha;
+        }
+        const float m_safe = st.m[j] == -INFINITY ? 0.f : st.m[j];
+        const float p = dead ? 0.f : __builtin_amdgcn_exp2f(x - m_safe);
+        st.l[j] += p;
+        st.z[j] = __builtin_fmaf(p, v_zero, st.z[j]);
+        w_lds[(4 * j + g) * 16 + t] = (_Float16)(p * v_scale);
+    }
+    __builtin_amdgcn_wave_barrier();
+    // row t of the operand: query head t / 4 + 4 (t % 4), tokens 4 g .. 4 g + 3 (rows without a head repeat one)
+    const int head = t / 4 + 4 * (t % 4 < HPL ? t % 4 : 0);
+    const half4_t weights = __builtin_bit_cast(half4_t, *reinterpret_cast<const uint2*>(w_lds + head * 16 + 4 * g));
+    auto mfma_v = [&](uint32_t lo, uint32_t hi, floatx4_t c) {
+        return __builtin_amdgcn_mfma_f32_16x16x16f16(weights, __builtin_bit_cast(half4_t, make_uint2(lo, hi)), c, 0, 0, 0);
+    };
+    if constexpr (BITS == 8) {
+        const uint32_t v[4][2] = {{cur.v[0].x, cur.v[0].y}, {cur.v[1].x, cur.v[1].y}, {cur.v[2].x, cur.v[2].y}, {cur.v[3].x, cur.v[3].y}};
+        constexpr uint32_t pick[4] = {0x0c040c00u, 0x0c050c01u, 0x0c060c02u, 0x0c070c03u};  // byte i of two tokens
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            st.acc[i] = mfma_v(__builtin_amdgcn_perm(v[1][i / 4], v[0][i / 4], pick[i % 4]),
+                               __builtin_amdgcn_perm(v[3][i / 4], v[2][i / 4], pick[i % 4]), st.acc[i]);
+    } else {
+        constexpr uint32_t pick[4] = {0x0c040c00u, 0x0c050c01u, 0x0c060c02u, 0x0c070c03u};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t lo = __builtin_amdgcn_perm(cur.v[1], cur.v[0], pick[i]), hi = __builtin_amdgcn_perm(cur.v[3], cur.v[2], pick[i]);
+            st.acc[i] = mfma_v(lo & 0x000f000fu, hi & 0x000f000fu, st.acc[i]);
+            st.acc[4 + i] = mfma_v(lo & 0x00f000f0u, hi & 0x00f000f0u, st.acc[4 + i]);
         }
     }
     __builtin_amdgcn_wave_barrier();
 }
 
-// Turns the per-lane softmax state of the quantised path into the form flush_block() folds: per head a wave-uniform
-// maximum, per-lane sums that add up (over the wave) to four times the head's total, and outputs with the code
-// offset and the weight scale taken off.
-template <int N>
-__device__ __forceinline__ void lane_state_to_wave_state(WaveState<N>& st, int lane) {
-    const int qd = lane % 4;
+// The queries of a list as this lane's matrix operands, from the fp16 rows stage_query() left in LDS: row t holds query
+// head t / 4 + 4 (t % 4) (rows without a head repeat one), channels in the order in which the codes of a key row come.
+template <int N, int BITS>
+__device__ __forceinline__ void load_query_operands(WaveState<N, BITS>& st, const uint4* q_lds, const float* q_sum, int lane) {
+    constexpr int HPL = WaveState<N, BITS>::kHeadsPerLane;
+    const int t = lane % 16, g = lane / 16;
+    const int head = min(t / 4 + 4 * (t % 4 < HPL ? t % 4 : 0), N - 1);
+    if constexpr (BITS == 8) {
 #pragma unroll
-    for (int hh = 0; hh < N; ++hh) {
-        const int g = hh / 4, k = hh % 4;
-        st.m[hh] = quad_lane(st.lane_m[g], k);
-        st.l[hh] = qd == k ? 4.f * st.lane_l[g] : 0.f;
-        st.z[hh] = qd == k ? 4.f * st.lane_z[g] : 0.f;
+        for (int m = 0; m < 4; ++m) st.q[m] = q_lds[head * 16 + 2 * (4 * (m / 2) + g) + m % 2];
+    } else {
+        auto low = [](uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); };   // even elements of two words
+        auto high = [](uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); };  // odd ones
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-            st.o[hh][i] = __builtin_fmaf(-1024.f, st.w_sum[hh], st.o[hh][i]) * (1.f / kWeightScale);
+        for (int u = 0; u < 2; ++u) {
+            const uint4 a = q_lds[head * 16 + 4 * g + 2 * u], b = q_lds[head * 16 + 4 * g + 2 * u + 1];
+            st.q[2 * u] = make_uint4(low(a.x, a.y), high(a.x, a.y), low(b.x, b.y), high(b.x, b.y));
+            st.q[2 * u + 1] = make_uint4(low(a.z, a.w), high(a.z, a.w), low(b.z, b.w), high(b.z, b.w));
+        }
     }
+#pragma unroll
+    for (int j = 0; j < HPL; ++j) st.q_sum[j] = q_sum[min(g + 4 * j, N - 1)];
 }
 
 template <class T, int N, int NP, int BITS>
-__device__ __forceinline__ void process_quarter(WaveState<N>& st, const uint4* q_lds, const float* q_sum, float* p_lds,
+__device__ __forceinline__ void process_quarter(WaveState<N, BITS>& st, const uint4* q_lds, float* p_lds,
                                                 Slabs<NP, BITS>& cur, int valid, int tok0, int lane, float scale_log2) {
     if constexpr (BITS == 16)
-        process_quarter_page<T, N, NP>(st, q_lds, q_sum, p_lds, cur, valid, tok0, lane, scale_log2);
+        process_quarter_page<T, N, NP>(st, q_lds, p_lds, cur, valid, tok0, lane, scale_log2);
     else
-        process_quantised_quarter_page<T, N, BITS>(st, q_lds, q_sum, p_lds, cur, valid, tok0, lane, scale_log2);
+        quantised_quarter_page<N, BITS>(st, p_lds, cur, valid, tok0, lane, scale_log2);
 }
 
 // Shared memory of a decode workgroup.
 template <int N, int NP> struct DecodeShared {
-    float o[kDecodeWaves][N][kHeadDim];   // cross-wave merge
+    alignas(16) float o[kDecodeWaves][N][kHeadDim];   // cross-wave merge
     float m[kDecodeWaves][N], l[kDecodeWaves][N], z[kDecodeWaves][N];
     uint4 q[N * 16];                      // queries of the current group
     float q_sum[kMaxGroup];               // quantised pages only: sum over the channels of each query
-    float p[kDecodeWaves][(NP / 4) * p_row(N)];
+    alignas(16) float p[kDecodeWaves][(NP / 4) * p_row(N)];
     unsigned arrived;                     // pieces of a cut list that were in before this workgroup's
 };
 
@@ -547,42 +521,59 @@ __device__ __forceinline__ float2 load_shared_across_chip(const float* p) {
                                                         __HIP_MEMORY_SCOPE_AGENT));
 }
 
-// Folds the four token rows of every wave, then the four waves of the workgroup, and writes either
-// the final rows (out / lse) or a partial (part_o / part_ml).  Must be called by all 256 threads.
-template <class T, int N, int NP, int BITS>
-__device__ __forceinline__ void flush_block(WaveState<N>& st, DecodeShared<N, NP>& sm, bool final_result, int H,
-                                            int b, int hk, uint16_t* out, float* lse_out, float* part_o,
-                                            float* part_ml, size_t part_slot) {
-    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+// Leaves a wave's maxima, sums and outputs in shared memory.  16-bit pages: the four token rows of the wave are folded
+// on the way, four values at a time so that row r ends up with the total of the r-th.
+template <int N, int NP>
+__device__ __forceinline__ void deposit_wave(WaveState<N, 16>& st, DecodeShared<N, NP>& sm, int wave, int lane) {
     const int r = lane / 16, c = lane % 16;
-    // Sums over the four token rows of the wave, four values at a time: row r ends up with the total of the r-th.
     constexpr int kQuads = (N + 3) / 4;
-    float lrow[4 * kQuads], zrow[4 * kQuads];
+    float lrow[4 * kQuads];
 #pragma unroll
-    for (int hh = 0; hh < 4 * kQuads; ++hh) {
-        // every lane of a token added the token's weight (and, for quantised values, its share of the zero-point
-        // term, which belongs to every channel): the 64 lanes hold LPT copies of each sum
-        lrow[hh] = hh < N ? row16_sum(st.l[hh]) : 0.f;
-        zrow[hh] = hh < N && BITS != 16 ? row16_sum(st.z[hh]) : 0.f;
-    }
+    for (int hh = 0; hh < 4 * kQuads; ++hh)
+        lrow[hh] = hh < N ? row16_sum(st.l[hh]) : 0.f;  // every lane of a token added the token's weight: LPT copies of the sum
 #pragma unroll
-    for (int g = 0; g < kQuads; ++g) {
-        const float lsum = rows4_sum_scatter(lrow[4 * g], lrow[4 * g + 1], lrow[4 * g + 2], lrow[4 * g + 3]);
-        float zsum = 0.f;
-        if (BITS != 16) zsum = rows4_sum_scatter(zrow[4 * g], zrow[4 * g + 1], zrow[4 * g + 2], zrow[4 * g + 3]);
-        if (c == 0 && 4 * g + r < N) {
-            sm.l[wave][4 * g + r] = lsum * (1.0f / KeyMap<NP>::LPT);
-            sm.z[wave][4 * g + r] = zsum * (1.0f / KeyMap<NP>::LPT);
-        }
+    for (int q = 0; q < kQuads; ++q) {
+        const float lsum = rows4_sum_scatter(lrow[4 * q], lrow[4 * q + 1], lrow[4 * q + 2], lrow[4 * q + 3]);
+        if (c == 0 && 4 * q + r < N) sm.l[wave][4 * q + r] = lsum * (1.0f / KeyMap<NP>::LPT);
     }
 #pragma unroll
     for (int hh = 0; hh < N; ++hh) {
 #pragma unroll
-        for (int g = 0; g < 2; ++g)  // lane (r, c) receives channel 8 c + 4 g + r
-            sm.o[wave][hh][8 * c + 4 * g + r] =
-                rows4_sum_scatter(st.o[hh][4 * g], st.o[hh][4 * g + 1], st.o[hh][4 * g + 2], st.o[hh][4 * g + 3]);
+        for (int q = 0; q < 2; ++q)  // lane (r, c) receives channel 8 c + 4 q + r
+            sm.o[wave][hh][8 * c + 4 * q + r] =
+                rows4_sum_scatter(st.o[hh][4 * q], st.o[hh][4 * q + 1], st.o[hh][4 * q + 2], st.o[hh][4 * q + 3]);
         if (lane == 0) sm.m[wave][hh] = st.m[hh];
     }
+}
+// Quantised pages: the outputs are whole already and take their unit here, the sums are added over the sixteen tokens.
+template <int N, int NP, int BITS>
+__device__ __forceinline__ void deposit_wave(WaveState<N, BITS>& st, DecodeShared<N, NP>& sm, int wave, int lane) {
+    const int t = lane % 16, g = lane / 16;
+    constexpr float unit = 1.f / (kCodeUnit * kWeightScale), upper = BITS == 4 ? unit / 16.f : unit;
+#pragma unroll
+    for (int j = 0; j < WaveState<N, BITS>::kHeadsPerLane; ++j) {
+        const float l = row16_sum(st.l[j]), z = row16_sum(st.z[j]);
+        const int hh = g + 4 * j;
+        if (hh < N) {
+            if (t == 0) {
+                sm.m[wave][hh] = st.m[j];
+                sm.l[wave][hh] = l;
+                sm.z[wave][hh] = z;
+            }
+            float4* dst = reinterpret_cast<float4*>(&sm.o[wave][hh][8 * t]);
+            dst[0] = make_float4(st.acc[0][j] * unit, st.acc[1][j] * unit, st.acc[2][j] * unit, st.acc[3][j] * unit);
+            dst[1] = make_float4(st.acc[4][j] * upper, st.acc[5][j] * upper, st.acc[6][j] * upper, st.acc[7][j] * upper);
+        }
+    }
+}
+
+// Folds the four waves of the workgroup, and writes either
+// the final rows (out / lse) or a partial (part_o / part_ml).  Must be called by all 256 threads.
+template <class T, int N, int NP, int BITS>
+__device__ __forceinline__ void flush_block(WaveState<N, BITS>& st, DecodeShared<N, NP>& sm, bool final_result, int H,
+                                            int b, int hk, uint16_t* out, float* lse_out, float* part_o,
+                                            float* part_ml, size_t part_slot) {
+    deposit_wave(st, sm, threadIdx.x / kWave, threadIdx.x % kWave);
     __syncthreads();
     // one thread per (query head, four channels): N * 32 <= 256 work items
     if (threadIdx.x < N * (kHeadDim / 4)) {
@@ -715,7 +706,7 @@ __device__ __forceinline__ void fold_pieces(int list, int j0, int j1, int hh, in
 // agent-scope accesses with a wait for the stores in between; no cache-wide fence (a device-scope fence here was
 // measured at three times the whole kernel: it writes back and invalidates the L2).  Called by all threads.
 template <class T, int N, int NP, int BITS>
-__device__ __forceinline__ void end_piece(WaveState<N>& st, DecodeShared<N, NP>& sm, const DecodePlan& plan, int blk,
+__device__ __forceinline__ void end_piece(WaveState<N, BITS>& st, DecodeShared<N, NP>& sm, const DecodePlan& plan, int blk,
                                           int lo, int hi, int list, int len, int H, int Hkv,
                                           unsigned long long streaming_mask, uint16_t* out,
                                           float* lse_out, float* part_o, float* part_ml, unsigned* arrivals) {
@@ -723,7 +714,6 @@ __device__ __forceinline__ void end_piece(WaveState<N>& st, DecodeShared<N, NP>&
     const int n0 = b * plan.per_seq + first_entry(plan, streaming_mask, hk);
     const int n_end = n0 + min(len, nominal_len(plan, streaming_mask, hk));
     const bool whole = n0 >= lo && n_end <= hi;
-    if constexpr (BITS != 16) lane_state_to_wave_state<N>(st, threadIdx.x % kWave);
     flush_block<T, N, NP, BITS>(st, sm, whole, H, b, hk, out, lse_out, part_o, part_ml, (size_t)blk + list);
     if (whole) return;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this thread's part of the piece has reached memory
@@ -757,13 +747,12 @@ __device__ __forceinline__ void end_piece(WaveState<N>& st, DecodeShared<N, NP>&
             cur_b = list / lp.Hkv;                                                                                   \
             cur_hk = list % lp.Hkv;                                                                                  \
             stage_query<T, N, NP, BITS>(sm, q, cur_b, lp.H, cur_hk, list, q_ahead);                                  \
+            if constexpr (BITS != 16) load_query_operands<N, BITS>(st, sm.q, sm.q_sum, lane);                        \
             st.reset();                                                                                              \
         }                                                                                                            \
-        const int L = __builtin_amdgcn_readlane(my_L, (IDX));                                                        \
-        const int pos = __builtin_amdgcn_readlane(my_pos, (IDX));                                                    \
-        process_quarter<T, N, NP, BITS>(st, sm.q, sm.q_sum, sm.p[wave], CUR, L - pos * NP, tok0, lane, lp.sm_scale_log2); \
-        const int extra = __builtin_amdgcn_readlane(my_extra, (IDX));                                                \
-        if (extra > 0) {                                                                                             \
+        process_quarter<T, N, NP, BITS>(st, sm.q, sm.p[wave], CUR, __builtin_amdgcn_readlane(my_left, (IDX)), tok0, lane, lp.sm_scale_log2); \
+        if ((outgrown >> (IDX)) & 1) {                                                                               \
+            const int extra = __builtin_amdgcn_readlane(my_extra, (IDX)), L = __builtin_amdgcn_readlane(my_L, (IDX)); \
             const int nominal = nominal_len(plan, lp.streaming_mask, cur_hk);                                        \
             const int tail = __builtin_amdgcn_readlane(my_tail, (IDX));                                              \
             for (int e = 0; e < extra; ++e) {                                                                        \
@@ -771,12 +760,19 @@ __device__ __forceinline__ void end_piece(WaveState<N>& st, DecodeShared<N, NP>&
                 const int ephys = kv.page_table[(size_t)cur_b * kv.max_pages + epos];                                \
                 const uint4 *ke, *ve;                                                                                \
                 slab_of(ephys, cur_hk, ke, ve);                                                                      \
-                load_k(CUR, ke, tok0, lane);                                                                         \
-                load_v(CUR, ve, tok0, r, c, lane);                                                                   \
-                process_quarter<T, N, NP, BITS>(st, sm.q, sm.q_sum, sm.p[wave], CUR, L - epos * NP, tok0, lane, lp.sm_scale_log2);\
+                load_k(CUR, ke, tok0, lane, ~0u);                                                                     \
+                load_v(CUR, ve, tok0, r, c, lane, ~0u);                                                                \
+                process_quarter<T, N, NP, BITS>(st, sm.q, sm.p[wave], CUR, L - epos * NP, tok0, lane, lp.sm_scale_log2);\
             }                                                                                                        \
         }                                                                                                            \
     }
+
+// The pointer that lane `lane` holds, wave-uniform.
+__device__ __forceinline__ const uint4* pointer_of_lane(const uint4* p, int lane) {
+    const unsigned long long x = reinterpret_cast<unsigned long long>(p);
+    return reinterpret_cast<const uint4*>(((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(x >> 32), lane) << 32) |
+                                          (unsigned)__builtin_amdgcn_readlane((int)x, lane));
+}
 
 template <class T, int N, int NP, int BITS>
 __global__ __launch_bounds__(kDecodeThreads) void sparse_decode_kernel(
@@ -827,7 +823,7 @@ __global__ __launch_bounds__(kDecodeThreads) void sparse_decode_kernel(
     q_ahead.list = -4;  // matches no list
     q_ahead.x[0] = q_ahead.x[1] = make_uint4(0, 0, 0, 0);
 
-    WaveState<N> st;
+    WaveState<N, BITS> st;
     int cur_list = -1, cur_b = 0, cur_hk = 0, cur_len = 0;
     // with every head streaming there is no selection: the loads below then read a valid word of the lengths
     const int* sel_table = sel_pages ? sel_pages : kv.seq_lens;
@@ -882,70 +878,71 @@ __global__ __launch_bounds__(kDecodeThreads) void sparse_decode_kernel(
                                                  : kv.page_table[(size_t)b * kv.max_pages + my_pos];
         unsigned long long todo = __ballot(my_valid);
         if (todo == 0) continue;
+        // Everything the page loop needs of an entry is worked out here, by its lane, for all entries at once: in the
+        // loop the same arithmetic (a remainder by the head count, head ranks, 64-bit products) is a chain of scalar
+        // instructions per page.
+        const uint4 *my_k, *my_v;
+        slab_of(my_phys, hk, my_k, my_v);
+        const int my_left = my_L - my_pos * NP;  // tokens of the page below the sequence length (or more than a page)
+        const unsigned long long outgrown = __ballot(my_valid && my_extra > 0);
+        // The two workgroups of a compute unit take turns at the higher wave priority, page by page
+        // (workgroups j and j + G / 2 share a unit); measured 0.4 us per call on the 32K benchmark shape.
+        auto take_turn = [&] {
+            if ((__builtin_popcountll(todo) + (blk >= (int)gridDim.x / 2)) & 1)
+                __builtin_amdgcn_s_setprio(1);
+            else
+                __builtin_amdgcn_s_setprio(0);
+        };
         if constexpr (BITS == 16) {
             // one page in flight behind the one being worked on
             Slabs<NP, BITS> cur, nxt;
             {
                 const int idx0 = __builtin_ctzll(todo);
-                const uint4 *k0, *v0;
-                slab_of(__builtin_amdgcn_readlane(my_phys, idx0), __builtin_amdgcn_readlane(my_list, idx0) % lp.Hkv, k0, v0);
-                load_k(cur, k0, tok0, lane);
-                load_v(cur, v0, tok0, r, c, lane);
+                load_k(cur, pointer_of_lane(my_k, idx0), tok0, lane, ~0u);
+                load_v(cur, pointer_of_lane(my_v, idx0), tok0, r, c, lane, ~0u);
             }
             while (todo) {
                 const int idx = __builtin_ctzll(todo);
                 todo &= todo - 1;
                 if (todo) {
                     const int idx1 = __builtin_ctzll(todo);
-                    const uint4 *k1, *v1;
-                    slab_of(__builtin_amdgcn_readlane(my_phys, idx1), __builtin_amdgcn_readlane(my_list, idx1) % lp.Hkv, k1, v1);
-                    load_k(nxt, k1, tok0, lane);
-                    load_v(nxt, v1, tok0, r, c, lane);
+                    load_k(nxt, pointer_of_lane(my_k, idx1), tok0, lane, ~0u);
+                    load_v(nxt, pointer_of_lane(my_v, idx1), tok0, r, c, lane, ~0u);
                 }
-                // The two workgroups of a compute unit take turns at the higher wave priority, page by page
-                // (workgroups j and j + G / 2 share a unit); measured 0.4 us per call on the 32K benchmark shape.
-                if ((__builtin_popcountll(todo) + (blk >= (int)gridDim.x / 2)) & 1)
-                    __builtin_amdgcn_s_setprio(1);
-                else
-                    __builtin_amdgcn_s_setprio(0);
+                take_turn();
                 LSERVE_DECODE_VISIT(idx, cur)
                 cur = nxt;
             }
         } else {
-            // Quantised pages are half the bytes, so two are kept in flight to cover the same latency.  The
-            // three stages rotate by name (a copy of a register whose load is still in flight would wait for it).
+            // One page in flight here too (two to six changed nothing over 4-bit pages and cost up to a quarter over 8-bit
+            // ones); the stages rotate by name (a copy of a register whose load is in flight would wait for it).  Over
+            // 4-bit pages a request goes out with every page, past the last one too: the wait for a page's slabs is a
+            // count of the loads behind them, and where a request may or may not have been made the compiler can only
+            // wait for all of them (batch 16, no groups: 40.4 us without, 39.1 with; 8-bit pages lose 2 to 5 % instead).
+            constexpr bool kAlways = BITS == 4;
             unsigned long long ahead = todo;  // entries whose slabs have not been requested yet
-#define LSERVE_REQUEST(DST)                                                                                              \
-    {                                                                                                                    \
-        const int nx = __builtin_ctzll(ahead);                                                                           \
-        ahead &= ahead - 1;                                                                                              \
-        const uint4 *k1, *v1;                                                                                            \
-        slab_of(__builtin_amdgcn_readlane(my_phys, nx), __builtin_amdgcn_readlane(my_list, nx) % lp.Hkv, k1, v1);        \
-        load_k(DST, k1, tok0, lane);                                                                                     \
-        load_v(DST, v1, tok0, r, c, lane);                                                                               \
-    }
-#define LSERVE_TURN(CUR, FILL)                                                                                           \
-    {                                                                                                                    \
-        const int idx = __builtin_ctzll(todo);                                                                           \
-        todo &= todo - 1;                                                                                                \
-        if (ahead) LSERVE_REQUEST(FILL)                                                                                  \
-        if ((__builtin_popcountll(todo) + (blk >= (int)gridDim.x / 2)) & 1)                                              \
-            __builtin_amdgcn_s_setprio(1);                                                                               \
-        else                                                                                                             \
-            __builtin_amdgcn_s_setprio(0);                                                                               \
-        LSERVE_DECODE_VISIT(idx, CUR)                                                                                    \
-        if (!todo) break;                                                                                                \
-    }
-            Slabs<NP, BITS> s0, s1, s2;
-            LSERVE_REQUEST(s0)
-            if (ahead) LSERVE_REQUEST(s1)
-            for (;;) {
-                LSERVE_TURN(s0, s2)
-                LSERVE_TURN(s1, s0)
-                LSERVE_TURN(s2, s1)
+            auto request = [&](Slabs<NP, BITS>& dst, int current) {
+                if (!kAlways && !ahead) return;
+                const unsigned live = ahead ? ~0u : 0u;
+                const int nx = ahead ? __builtin_ctzll(ahead) : current;
+                ahead &= ahead - 1;
+                load_k(dst, pointer_of_lane(my_k, nx), tok0, lane, live);
+                load_v(dst, pointer_of_lane(my_v, nx), tok0, r, c, lane, live);
+            };
+            constexpr int kStages = 2;
+            Slabs<NP, BITS> stage[kStages];
+            request(stage[0], __builtin_ctzll(todo));
+            while (todo) {
+#pragma unroll
+                for (int u = 0; u < kStages; ++u) {
+                    if (!todo) break;
+                    const int idx = __builtin_ctzll(todo);
+                    todo &= todo - 1;
+                    request(stage[(u + 1) % kStages], idx);
+                    take_turn();
+                    LSERVE_DECODE_VISIT(idx, stage[u])
+                }
             }
-#undef LSERVE_TURN
-#undef LSERVE_REQUEST
         }
     }
     if (cur_list < 0) return;  // no real entry in this range
