@@ -653,48 +653,97 @@ __device__ __forceinline__ int head_of_entry(const DecodePlan& plan, unsigned lo
     return hk;
 }
 
-// Folds the pieces of one list, in slot order, kBatch at a time so that their loads are in flight together, for
-// four channels `ch .. ch + 3` of query head `hh` of the group.  Every range between j0 and j1 holds a real entry
-// of the list and wrote a piece (ranges there are never empty: an empty range implies quot = 0, and then no list
-// spans two ranges).
-template <class T, int N, int kBatch>
-__device__ __forceinline__ void fold_pieces(int list, int j0, int j1, int hh, int ch, int H, int b, int hk,
-                                            uint16_t* out, float* lse_out, const float* part_o,
-                                            const float* part_ml) {
-    float M = -INFINITY, lt = 0.f, acc[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int jb = j0; jb <= j1; jb += kBatch) {
+// Maximum, sum and four channels `ch .. ch + 3` of query head `hh`, folded over pieces ja .. jb of a list, in slot order,
+// kBatch at a time so that their loads are in flight together.  Every range between a list's first and last holds a
+// real entry of the list and wrote a piece (empty ranges come after all others).
+struct Folded {
+    float m, l, acc[4];
+};
+template <int N, int kBatch>
+__device__ __forceinline__ Folded fold_pieces(int list, int ja, int jb, int hh, int ch, const float* part_o,
+                                              const float* part_ml) {
+    Folded f = {-INFINITY, 0.f, {0.f, 0.f, 0.f, 0.f}};
+    for (int j = ja; j <= jb; j += kBatch) {
         float2 ml[kBatch], lo[kBatch], hi[kBatch];
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
-            const size_t pi = ((size_t)min(jb + u, j1) + list) * N + hh;  // past the end: the last piece again, unused
+            const size_t pi = ((size_t)min(j + u, jb) + list) * N + hh;  // past the end: the last piece again, unused
             ml[u] = load_shared_across_chip(part_ml + pi * 2);
             lo[u] = load_shared_across_chip(part_o + pi * kHeadDim + ch);
             hi[u] = load_shared_across_chip(part_o + pi * kHeadDim + ch + 2);
         }
         float bm = -INFINITY;
 #pragma unroll
-        for (int u = 0; u < kBatch; ++u) bm = fmaxf(bm, jb + u <= j1 ? ml[u].x : -INFINITY);
+        for (int u = 0; u < kBatch; ++u) bm = fmaxf(bm, j + u <= jb ? ml[u].x : -INFINITY);
         if (bm == -INFINITY) continue;  // only if every logit of these pieces was -inf
-        const float m_new = fmaxf(M, bm);
-        const float keep = __builtin_amdgcn_exp2f(M - m_new);  // 0 for the first batch (M = -inf)
-        lt *= keep;
+        const float m_new = fmaxf(f.m, bm);
+        const float keep = __builtin_amdgcn_exp2f(f.m - m_new);  // 0 for the first batch (m = -inf)
+        f.l *= keep;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) acc[i] *= keep;
+        for (int i = 0; i < 4; ++i) f.acc[i] *= keep;
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
-            const float f = jb + u <= j1 ? __builtin_amdgcn_exp2f(ml[u].x - m_new) : 0.f;
-            lt += ml[u].y * f;
-            acc[0] += lo[u].x * f;
-            acc[1] += lo[u].y * f;
-            acc[2] += hi[u].x * f;
-            acc[3] += hi[u].y * f;
+            const float w = j + u <= jb ? __builtin_amdgcn_exp2f(ml[u].x - m_new) : 0.f;
+            f.l += ml[u].y * w;
+            f.acc[0] += lo[u].x * w;
+            f.acc[1] += lo[u].y * w;
+            f.acc[2] += hi[u].x * w;
+            f.acc[3] += hi[u].y * w;
         }
-        M = m_new;
+        f.m = m_new;
     }
+    return f;
+}
+
+// Folds pieces j0 .. j1 of a list and writes its rows.  Called by all threads.  Up to eight pieces (the lists of a large
+// batch) are one round of loads by one thread per (query head, four channels).  A small batch cuts its lists into as many
+// as sixty: eight at a time they were seven rounds, one after the other (6 of the call's 15 us at one sequence of 4000
+// tokens); then the pieces are shared out over all threads, sixteen at a time, and met in shared memory.
+template <class T, int N, int NP>
+__device__ __forceinline__ void fold_list(DecodeShared<N, NP>& sm, int list, int j0, int j1, int H, int b, int hk,
+                                          uint16_t* out, float* lse_out, const float* part_o, const float* part_ml) {
+    constexpr int kItems = N * (kHeadDim / 4), kParts = N <= 2 ? 4 : N <= 4 ? 2 : 1;
+    const int item = threadIdx.x % kItems, part = threadIdx.x / kItems;
+    const int hh = item / (kHeadDim / 4), ch = item % (kHeadDim / 4) * 4;
+    Folded f;
+    if (j1 - j0 < 8) {
+        if (part == 0) f = fold_pieces<N, 8>(list, j0, j1, hh, ch, part_o, part_ml);
+    } else {
+        const int share = (j1 - j0 + kParts) / kParts, ja = j0 + part * share;
+        if (part < kParts) f = fold_pieces<N, 16>(list, ja, min(ja + share - 1, j1), hh, ch, part_o, part_ml);
+        if (kParts > 1) {
+            if (part > 0 && part < kParts) {
+                *reinterpret_cast<float4*>(&sm.o[part][hh][ch]) = make_float4(f.acc[0], f.acc[1], f.acc[2], f.acc[3]);
+                if (ch == 0) sm.m[part][hh] = f.m, sm.l[part][hh] = f.l;
+            }
+            __syncthreads();
+            if (part == 0) {
+                float m_all = f.m;
+#pragma unroll
+                for (int i = 1; i < kParts; ++i) m_all = fmaxf(m_all, sm.m[i][hh]);
+                const float w0 = f.m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(f.m - m_all);
+                f.l *= w0;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) f.acc[i] *= w0;
+#pragma unroll
+                for (int i = 1; i < kParts; ++i) {  // a part without pieces, or without a finite logit, adds nothing
+                    const float w = sm.m[i][hh] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sm.m[i][hh] - m_all);
+                    const float4 o = *reinterpret_cast<const float4*>(&sm.o[i][hh][ch]);
+                    f.l += sm.l[i][hh] * w;
+                    f.acc[0] += o.x * w;
+                    f.acc[1] += o.y * w;
+                    f.acc[2] += o.z * w;
+                    f.acc[3] += o.w * w;
+                }
+                f.m = m_all;
+            }
+        }
+    }
+    if (part > 0) return;
     const int h = hk * N + hh;
-    const uint2 packed = make_uint2(Elem<T>::pack(acc[0] / lt, acc[1] / lt), Elem<T>::pack(acc[2] / lt, acc[3] / lt));
+    const uint2 packed = make_uint2(Elem<T>::pack(f.acc[0] / f.l, f.acc[1] / f.l), Elem<T>::pack(f.acc[2] / f.l, f.acc[3] / f.l));
     *reinterpret_cast<uint2*>(out + ((size_t)b * H + h) * kHeadDim + ch) = packed;
-    if (lse_out && ch == 0) lse_out[b * H + h] = (M + __builtin_amdgcn_logf(lt)) * kLn2;
+    if (lse_out && ch == 0) lse_out[b * H + h] = (f.m + __builtin_amdgcn_logf(f.l)) * kLn2;
 }
 
 // Ends a (workgroup, list) piece.  `len` is the real length of the list, so its real entries occupy the nominal
@@ -723,9 +772,7 @@ __device__ __forceinline__ void end_piece(WaveState<N, BITS>& st, DecodeShared<N
     __syncthreads();
     const int j0 = range_of(plan, n0), j1 = range_of(plan, n_end - 1);
     if ((int)sm.arrived != j1 - j0) return;  // somebody else will fold
-    if (threadIdx.x < N * (kHeadDim / 4))
-        fold_pieces<T, N, 8>(list, j0, j1, threadIdx.x / (kHeadDim / 4), threadIdx.x % (kHeadDim / 4) * 4, H, b, hk, out,
-                             lse_out, part_o, part_ml);
+    fold_list<T, N, NP>(sm, list, j0, j1, H, b, hk, out, lse_out, part_o, part_ml);
     if (threadIdx.x == 0) __hip_atomic_store(arrivals + list, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -1013,11 +1060,15 @@ hipError_t launch_decode_kernels(const LayerParams& lp, const PagedParams& kv, c
         return nb < 1 ? 1 : (nb > kBlocksPerCU ? kBlocksPerCU : nb);
     }();
     // two workgroups per compute unit, unless that leaves fewer than four entries each: a small launch is all
-    // start-up and fold, and half as many workgroups with twice the pages do less of each (measured)
-    int G = num_compute_units() * per_cu;
+    // start-up and fold, and half as many workgroups with twice the pages do less of each (measured).  A very small one
+    // whose lists are long (no list is longer than the page table) gives every workgroup two entries, so that half as
+    // many pieces are counted in and folded (one sequence of 4000 tokens: 12.9 us with one entry each, 11.2 with two,
+    // 12.8 with three); short lists take one (1000 tokens: 8.9 us with one entry, 10.1 with two).
+    const int cus = num_compute_units();
+    int G = cus * per_cu;
     DecodePlan plan = make_plan(lp, kv.batch, sel_stride, G, 0);
     if (per_cu > 1 && plan.quot < 4) {
-        G = num_compute_units();
+        G = std::min(plan.select_len, kv.max_pages) > 32 && plan.total < 2 * cus ? (plan.total + 1) / 2 : cus;
         plan = make_plan(lp, kv.batch, sel_stride, G, 0);
     } else if (plan.quot >= kSlackFromEntries) {
         plan = make_plan(lp, kv.batch, sel_stride, G, 1);
