@@ -168,34 +168,37 @@ class PagedKV:
     kv_bits: int = 16
 
     def c(self):
-        num_pages = 0
-        for t in (self.k_pool, self.v_pool, self.stats):
-            if t is not None:
-                num_pages = t.shape[0]
-        num_pages_stream = 0 if self.k_pool_stream is None else self.k_pool_stream.shape[0]
+        sized = self.stats if self.stats is not None else self.v_pool if self.v_pool is not None else self.k_pool
+        num_pages = 0 if sized is None else sized.size(0)
+        num_pages_stream = 0 if self.k_pool_stream is None else self.k_pool_stream.size(0)
         self._c = _CPagedKV(_ptr(self.k_pool), _ptr(self.v_pool), _ptr(self.stats), _ptr(self.page_table),
-                            _ptr(self.seq_lens), self.page_table.shape[0], self.page_table.shape[1], num_pages,
+                            _ptr(self.seq_lens), self.page_table.size(0), self.page_table.size(1), num_pages,
                             self.pool_heads, _ptr(self.k_pool_stream), _ptr(self.v_pool_stream),
                             _ptr(self.ring_table), num_pages_stream, self.kv_bits)
         return ctypes.byref(self._c)
 
 
-def _ptr(t: Optional[torch.Tensor]):
+# A decode step of a small batch is four calls of some ten microseconds of GPU work each, so the marshalling is kept to
+# what a call cannot do without: addresses travel as plain integers (the argument types make pointers of them), and the
+# current stream is asked for as a handle, without the stream object around it.
+def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     if t is None:
         return None
     if not t.is_contiguous():
         raise ValueError("lserve binding takes contiguous tensors")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
-def _stream(stream) -> ctypes.c_void_p:
+def _stream(stream) -> int:
     if stream is None:
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _check(rc: int, where: str) -> None:
-    if rc != 0:
+    if rc:
         raise LserveError(rc, where)
 
 
