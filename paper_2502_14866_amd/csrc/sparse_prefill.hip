@@ -175,8 +175,16 @@ __device__ __forceinline__ int wave_count(int x) { return (int)rows4_sum(row16_s
 // beyond the launches it saves: workgroups go to the shader engines of an XCD in strict turn, so an order with gaps
 // of a fixed stride (one long sequence among fifteen short ones, each block index of all sixteen in a row) puts the
 // real work of a launch on one of the four (sixteen prompts of 77 .. 3001 tokens: 745 us, in this order 190).
-__device__ __forceinline__ bool block_of(int rank, int lo, int hi, int& b, int& qblk) {
+__device__ __forceinline__ bool block_of(int rank, int lo, int hi, int batch, int& b, int& qblk) {
     const int n = max(0, hi - lo);
+    // All sequences alike: no search.
+    const int n_seq = __popcll(__ballot(n > 0)), lo0 = __builtin_amdgcn_readfirstlane(lo), hi0 = __builtin_amdgcn_readfirstlane(hi);
+    if (n_seq == batch && __ballot(n > 0 && (lo != lo0 || hi != hi0)) == 0) {
+        const int level = rank / batch;
+        b = rank - level * batch;
+        qblk = hi0 - 1 - level;
+        return qblk >= lo0;
+    }
     auto at_or_past = [&](int level) { return wave_count(min(max(hi - level, 0), n)); };
     if (rank >= wave_count(n)) return false;
     int below = 0, above = __builtin_amdgcn_readfirstlane((int)wave_max((float)(n > 0 ? hi : 0)));
@@ -332,7 +340,7 @@ __global__ __launch_bounds__(kPrefillThreads, 512 / kPrefillThreads) void sparse
             qblk = __builtin_amdgcn_readfirstlane(hi) - 1 - rank;
             if (qblk < __builtin_amdgcn_readfirstlane(lo)) return;
         } else {
-            if (!block_of(rank, lo, hi, b, qblk)) return;
+            if (!block_of(rank, lo, hi, batch, b, qblk)) return;
             b = __builtin_amdgcn_readfirstlane(b);
         }
     } else {
@@ -980,9 +988,12 @@ struct PrefillShape {
 // tokens over a history of 32768, 932 / 547 / 381 us; one prompt of 4096 tokens, 125 / 129 / 157 us; of 65536 tokens,
 // 15.4 / 17.6 / 21.6 ms.  Quantised pages are not built for four (the codes on their way need more registers than
 // there are).
+constexpr double kFixedUs = 7.0, kFoldUs = 1.0;                        // of a workgroup; and if it folds slices
+constexpr double kStepUs[2][3] = {{2.0, 2.35, 3.0}, {2.3, 3.5, 0.0}};  // 16-bit / quantised pages, by log2(slices)
+
+double launch_time(double work, double last) { return std::max(last, work / kComputeUnits + 0.35 * last); }
+
 PrefillShape choose_shape(const LayerParams& lp, double tiles, double longest, double mean, int bits) {
-    const double fixed = 7.0;                                                        // microseconds
-    static const double step_us[2][3] = {{2.0, 2.35, 3.0}, {2.3, 2.9, 0.0}};         // by log2(slices)
     const int n_stream = count_streaming(lp);
     const double dense = tiles * (lp.Hkv - n_stream) * lp.group, stream = tiles * n_stream * lp.group;
     const double band = std::min<double>(lp.sink_pages + lp.local_pages, longest);
@@ -990,21 +1001,39 @@ PrefillShape choose_shape(const LayerParams& lp, double tiles, double longest, d
     double best_time = 1e300;
     for (int i = 0; i < (bits == 16 ? 3 : 2); ++i) {
         const int SL = 1 << i;
-        const double step = step_us[bits != 16][i];
-        const double dense_wgs = dense / kPairs * SL;
-        // the short walks of streaming heads are folded only while the chip has room for all of the launch at once
-        const bool fold_stream = dense_wgs + stream / kPairs * SL <= kComputeUnits;
-        const int stream_slices = fold_stream ? SL : 1;
-        const double work = (dense_wgs * (fixed + step * mean / SL) +
-                             stream / kPairs * stream_slices * (fixed + step * band / stream_slices)) / kComputeUnits;
-        const double last = fixed + step * (dense > 0 ? longest / SL : band / stream_slices);
-        const double time = std::max(last, work + 0.25 * last);
-        if (time < best_time) {
-            best_time = time;
-            best = {SL, {SL > 1, SL > 1 && fold_stream}};
+        const double step = kStepUs[bits != 16][i], fold_us = SL > 1 ? kFoldUs : 0.;
+        for (int fold_stream = 0; fold_stream <= (SL > 1); ++fold_stream) {
+            const double stream_slices = fold_stream ? SL : 1, stream_us = kFixedUs + fold_stream * fold_us + step * band / stream_slices;
+            const double dense_us = kFixedUs + fold_us;
+            const double work = dense / kPairs * SL * (dense_us + step * mean / SL) + stream / kPairs * stream_slices * stream_us;
+            const double last = std::max(dense > 0 ? dense_us + step * longest / SL : 0., stream > 0 ? stream_us : 0.);
+            const double time = launch_time(work, last);
+            // (a tie goes to the shorter walks)
+            if (time < best_time || (fold_stream && time == best_time)) best_time = time, best = {SL, {SL > 1, fold_stream != 0}};
         }
     }
     return best;
+}
+
+// How a listed mask is walked: by merged lists of four query tiles (and row by row where those have little in common: two
+// launches behind the merging pass), by the caller's rows with four units to a workgroup, or by the caller's rows with
+// four key slices to a unit.  `row`: mean number of tiles kept by a row of the lists.  Rows of neighbouring query tiles are
+// taken to have little in common, which is the dearer case of the merged lists.  (12345 tokens, 32 / 8 heads, random masks of
+// density 0.3: 485 / 433 / 540 us; 2234 tokens at 0.23: 52 us merged, 66 sliced; 5101 tokens, 8 / 2 heads: 119 merged,
+// 54 sliced.)
+enum MaskWalk { kMergedRows, kOwnRows, kSlicedRows };
+MaskWalk choose_mask_walk(const LayerParams& lp, double tiles, double longest, double row) {
+    const int n_stream = count_streaming(lp);
+    const double dense = tiles * (lp.Hkv - n_stream) * lp.group, stream = tiles * n_stream * lp.group;
+    const double band = std::min<double>(lp.sink_pages + lp.local_pages, longest);
+    const double rows4 = kFixedUs + kStepUs[0][2] * 1.15 * row;                 // the longest of four rows counts
+    const double last = kFixedUs + kStepUs[0][2] * std::min(2.3 * row, longest);
+    const double merged = 10. + launch_time((dense * rows4 + stream * (kFixedUs + kStepUs[0][0] * (band + 3))) / kPairs, last);
+    const double own = launch_time((dense * rows4 + stream * (kFixedUs + kStepUs[0][2] * band)) / kPairs, last);
+    const double sliced = launch_time(dense * (kFixedUs + kFoldUs + kStepUs[0][2] * row / 4) +
+                                          stream * (kFixedUs + kFoldUs + kStepUs[0][2] * band / 4),
+                                      kFixedUs + kFoldUs + kStepUs[0][2] * std::min(2 * row, longest) / 4);
+    return sliced <= std::min(merged, own) ? kSlicedRows : own < merged ? kOwnRows : kMergedRows;
 }
 
 // Query heads of a group that share a workgroup (they read the same keys, whole and at the same time, and all end on
@@ -1101,8 +1130,8 @@ hipError_t launch_prefill(const LayerParams& lp, const void* q, const void* k, c
     a.stream = stream;
     // half a tile of padding per sequence; walks are half as long as their sequence, and long sequences have more of them
     const double tiles = (double)total_tokens / kTile + 0.5 * batch, mean_tiles = (double)total_tokens / kTile / batch;
-    PrefillShape shape = choose_shape(lp, tiles, max_tiles, 0.25 * (mean_tiles + max_tiles), 16);
     if (!mask) {
+        const PrefillShape shape = choose_shape(lp, tiles, max_tiles, 0.25 * (mean_tiles + max_tiles), 16);
         a.sched = make_schedule(lp, shape, false, max_seqlen, total_tokens, false, batch);
         return launch_slices<T, kPlain, 16>(a, shape.slices);
     }
@@ -1112,13 +1141,15 @@ hipError_t launch_prefill(const LayerParams& lp, const void* q, const void* k, c
     mk.row_ptr = mask->row_ptr;
     mk.cols = mask->cols;
     mk.rows_per_mask = mask->rows_per_mask;
-    if (shape.slices > 1) {  // few blocks: the slices of a workgroup share out the caller's own rows
-        shape = {4, {true, true}};
-        a.sched = make_schedule(lp, shape, true, max_seqlen, total_tokens, false, batch);
+    const double row = (double)mask->nnz / ((double)mask->num_masks * mask->rows_per_mask);
+    const MaskWalk walk = choose_mask_walk(lp, tiles, max_tiles, row);
+    if (walk != kMergedRows) {
+        a.sched = make_schedule(lp, {4, {walk == kSlicedRows, walk == kSlicedRows}}, true, max_seqlen, total_tokens, false, batch);
         return launch_slices<T, kMasked, 16>(a, 4);
     }
-    // many: the rows of four query tiles are merged, and blocks whose rows have little in common go to a second launch
-    // that walks them row by row (12345 tokens under random masks of density 0.3: 508 us merged, 433 us by rows)
+    // The rows of four query tiles are merged; blocks whose rows have little in common are left to a second launch, which
+    // walks them row by row.
+    const PrefillShape shape = {1, {false, false}};
     mk.blocks_per_seq = mask_blocks(max_seqlen);
     mk.blk_list = reinterpret_cast<int*>(workspace);
     mk.blk_count = reinterpret_cast<int*>(reinterpret_cast<unsigned char*>(workspace) + align16((size_t)mask->nnz * sizeof(int)));

@@ -72,6 +72,7 @@ def _check(w, lengths, pin, out, lse, ref, lse_ref, tok, what):
     (32, 8, (4097,)),                             # one slice, four heads of a group per workgroup
     (8, 8, (4500, 1)),                            # no groups: query tiles as units, one-token sequence
     (12, 4, (3000, 700)),                         # three heads per group: neither two nor four divide it
+    (16, 4, (1000, 1000, 1000)),                  # equal lengths are not searched
     (12, 2, (1500, 333, 64)),                     # six: two heads and two query tiles
     (64, 8, (1100, 77, 640)),                     # eight
     (8, 2, tuple(3 + 17 * i for i in range(64))),  # the largest batch dealt out in order, one lane per sequence
@@ -88,12 +89,13 @@ def test_prefill_launch_shapes(dtype, heads, kv_heads, lengths):
     _check(w, lengths, pin, out, lse, ref, lse_ref, tok, f"prefill {dtype} {heads}/{kv_heads} {len(lengths)} sequences")
 
 
-@pytest.mark.parametrize("lengths", [(4160, 1000), (300, 129)])
+@pytest.mark.parametrize("lengths", [(10300, 333), (4160, 1000), (300, 129)])
 @pytest.mark.parametrize("dtype", ["fp16", "bf16"])
 def test_masked_prefill_splits_its_blocks_between_merged_and_row_by_row_walks(dtype, lengths):
     """Large enough for merged lists: mask 0 keeps the same tiles in neighbouring rows (merged walks), mask 1 others in
     every row (walked row by row), mask 2 mixes the two by block; one head keeps the analytic pattern; row lists that go
-    on past the diagonal are cut there.  The small batch takes the caller's rows as they are, in four key slices."""
+    on past the diagonal are cut there.  The smaller batches take the caller's rows as they are, four units to a workgroup
+    or in four key slices."""
     w = Workload(name="pm3", batch=2, num_q_heads=32, num_kv_heads=8, dtype=dtype, streaming_kv_heads=(0, 1, 2, 3),
                  sink_tokens=128, local_tokens=512, seed=59)
     same = lambda b, i: [j for j in range(i + 1) if j % 3 == 0 or j == i]
