@@ -241,7 +241,7 @@ __global__ __launch_bounds__(kWave* kMaxLogical) void append_kv_kernel(LayerPara
 // The same for at most one new token per sequence (a decode step).  Nothing but latency and launch: the general kernel
 // starts a workgroup per (page, KV head, sequence) and a wavefront per logical page to move 512 bytes.  Here sixteen
 // lanes own the K row of a (sequence, KV head) and the next sixteen its V row, eight such pairs to a workgroup, and all
-// loads that depend on nothing but the position go out together (64 sequences, 8 KV heads, 4-bit pages: 7.2 -> 4.1 us).
+// loads that depend on nothing but the position go out together (64 sequences, 8 KV heads, 4-bit pages: 7.2 -> 4.6 us).
 template <class T, int BITS>
 __global__ __launch_bounds__(256) void append_token_kernel(LayerParams lp, PagedParams kv, const uint4* __restrict__ k_new,
                                                            const uint4* __restrict__ v_new, const int* __restrict__ cu_new,

@@ -174,7 +174,7 @@ __device__ __forceinline__ int wave_count(int x) { return (int)rows4_sum(row16_s
 // (batch <= 64) holds the blocks [lo, hi) its queries span.  Nothing is left out in this order, and that matters
 // beyond the launches it saves: workgroups go to the shader engines of an XCD in strict turn, so an order with gaps
 // of a fixed stride (one long sequence among fifteen short ones, each block index of all sixteen in a row) puts the
-// real work of a launch on one of the four (sixteen prompts of 77 .. 3001 tokens: 745 us, in this order 190).
+// real work of a launch on one of the four (sixteen prompts of 77 .. 3001 tokens: 745 us, in this order 214).
 __device__ __forceinline__ bool block_of(int rank, int lo, int hi, int batch, int& b, int& qblk) {
     const int n = max(0, hi - lo);
     // All sequences alike: no search.
