@@ -3,7 +3,7 @@
 // sink + local pages for streaming heads.  Both kinds run in one launch.
 //
 // The work is GEMV-shaped (n <= 8 query rows per KV head) and bound by HBM bandwidth, so there is
-// no MFMA here: each page is a 2 * N_P * 256-byte contiguous K / V slab read with 16-byte loads
+// no MFMA here for 16-bit pages: each page is a 2 * N_P * 256-byte contiguous K / V slab read with 16-byte loads
 // (16 lanes per token row), dot products use packed 16-bit dot instructions with fp32
 // accumulation, and the softmax is kept online per wavefront.
 //

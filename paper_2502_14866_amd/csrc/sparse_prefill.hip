@@ -1017,8 +1017,9 @@ PrefillShape choose_shape(const LayerParams& lp, double tiles, double longest, d
 
 // How a listed mask is walked: by merged lists of four query tiles (and row by row where those have little in common: two
 // launches behind the merging pass), by the caller's rows with four units to a workgroup, or by the caller's rows with
-// four key slices to a unit.  `row`: mean number of tiles kept by a row of the lists.  Rows of neighbouring query tiles are
-// taken to have little in common, which is the dearer case of the merged lists.  (12345 tokens, 32 / 8 heads, random masks of
+// four key slices to a unit.  `row`: mean number of tiles kept by a row of the lists.  How much the
+// rows of neighbouring query tiles have in common is not known here; the merged lists are taken half way (a pattern of
+// 65536 tokens whose rows agree: 16 ms merged, 24 ms row by row).  (12345 tokens, 32 / 8 heads, random masks of
 // density 0.3: 485 / 433 / 540 us; 2234 tokens at 0.23: 52 us merged, 66 sliced; 5101 tokens, 8 / 2 heads: 119 merged,
 // 54 sliced.)
 enum MaskWalk { kMergedRows, kOwnRows, kSlicedRows };
@@ -1028,7 +1029,10 @@ MaskWalk choose_mask_walk(const LayerParams& lp, double tiles, double longest, d
     const double band = std::min<double>(lp.sink_pages + lp.local_pages, longest);
     const double rows4 = kFixedUs + kStepUs[0][2] * 1.15 * row;                 // the longest of four rows counts
     const double last = kFixedUs + kStepUs[0][2] * std::min(2.3 * row, longest);
-    const double merged = 10. + launch_time((dense * rows4 + stream * (kFixedUs + kStepUs[0][0] * (band + 3))) / kPairs, last);
+    // merged rows cost between a shared walk of one row's length and what the row-by-row launch makes of them
+    const double merged4 = kFixedUs + 0.5 * (kStepUs[0][0] * row + std::min(kStepUs[0][0] * 0.5 * longest, kStepUs[0][2] * 1.15 * row));
+    const double merged = 10. + launch_time((dense * merged4 + stream * (kFixedUs + kStepUs[0][0] * (band + 3))) / kPairs,
+                                            kFixedUs + 0.8 * (last - kFixedUs));
     const double own = launch_time((dense * rows4 + stream * (kFixedUs + kStepUs[0][2] * band)) / kPairs, last);
     const double sliced = launch_time(dense * (kFixedUs + kFoldUs + kStepUs[0][2] * row / 4) +
                                           stream * (kFixedUs + kFoldUs + kStepUs[0][2] * band / 4),
