@@ -217,9 +217,6 @@ struct PrefillMask {
     int* blk_count;           // [num_masks][batch][blocks_per_seq]
     int blocks_per_seq;
 };
-// A step of a walk that the four query tiles of a workgroup share against a step in which each takes a tile of its own
-// (four times the staging): 2.0 us against 3.0.
-constexpr int kSharedWalkCost = 2, kOwnWalkCost = 3;
 constexpr int kKeepShift = 24;  // list entry = key tile | keep bits << 24
 
 __global__ __launch_bounds__(kWave) void merge_mask_rows_kernel(PrefillMask mk, const int* __restrict__ cu_seqlens,
@@ -240,17 +237,12 @@ __global__ __launch_bounds__(kWave) void merge_mask_rows_kernel(PrefillMask mk, 
     for (int j = lane; j < last; j += kWave) keep_bits[j] = 0;
     __builtin_amdgcn_s_waitcnt(0);
     __builtin_amdgcn_wave_barrier();
-    int longest = 0;
     for (int t = 0; t < rows; ++t) {  // one row at a time: no two lanes touch the same byte
         const int lo = mk.row_ptr[r0 + t], hi = mk.row_ptr[r0 + t + 1];
-        int kept = 0;
-        for (int e0 = lo; e0 < hi; e0 += kWave) {
-            const int j = mk.cols[min(e0 + lane, hi - 1)];
-            const bool live = e0 + lane < hi && j >= 0 && j <= iq0 + t;
-            if (live) keep_bits[j] |= (unsigned char)(1u << t);
-            kept += __popcll(__ballot(live));
+        for (int e = lo + lane; e < hi; e += kWave) {
+            const int j = mk.cols[e];
+            if (j >= 0 && j <= iq0 + t) keep_bits[j] |= (unsigned char)(1u << t);
         }
-        longest = max(longest, kept);
         __builtin_amdgcn_s_waitcnt(0);
         __builtin_amdgcn_wave_barrier();
     }
@@ -263,8 +255,7 @@ __global__ __launch_bounds__(kWave) void merge_mask_rows_kernel(PrefillMask mk, 
         if (bits) dst[total + __popcll(live & ((1ull << lane) - 1ull))] = j | (int)(bits << kKeepShift);
         total += __popcll(live);
     }
-    // negative: the four rows keep such different tiles that a walk of its own for each is quicker
-    if (lane == 0) *count = longest * kOwnWalkCost < total * kSharedWalkCost ? -1 - total : total;
+    if (lane == 0) *count = total;
 }
 
 template <class T> struct Ones;
@@ -393,16 +384,11 @@ __global__ __launch_bounds__(kPrefillThreads, 512 / kPrefillThreads) void sparse
     const int* lst = nullptr;
     if (MASKED) {
         const int m = mk.head_mask[h];
-        // Two launches share the blocks of a merged mask: the second takes those that are quicker row by row, the first the
-        // others and the analytic patterns.  (A workgroup has one head and one merged list: all of it leaves or none.)
-        const int merged =
-            mk.blk_list && m >= 0 ? mk.blk_count[((size_t)m * batch + b) * mk.blocks_per_seq + qblk] : 0;
-        if (mk.blk_list && (merged < 0) != (SL > 1)) return;
         if (m >= 0 && iq_first <= iq_last) {
             const int row = m * mk.rows_per_mask + mk.q_tile_start[b] + iq_first;
             if (SL == 1) {
                 lst = mk.blk_list + mk.row_ptr[row];
-                n_visit = merged;
+                n_visit = mk.blk_count[((size_t)m * batch + b) * mk.blocks_per_seq + qblk];
             } else {
                 const int lo = mk.row_ptr[row];
                 lst = mk.cols + lo;
@@ -1015,29 +1001,25 @@ PrefillShape choose_shape(const LayerParams& lp, double tiles, double longest, d
     return best;
 }
 
-// How a listed mask is walked: by merged lists of four query tiles (and row by row where those have little in common: two
-// launches behind the merging pass), by the caller's rows with four units to a workgroup, or by the caller's rows with
-// four key slices to a unit.  `row`: mean number of tiles kept by a row of the lists.  How much the
-// rows of neighbouring query tiles have in common is not known here; the merged lists are taken half way (a pattern of
-// 65536 tokens whose rows agree: 16 ms merged, 24 ms row by row).  (12345 tokens, 32 / 8 heads, random masks of
-// density 0.3: 485 / 433 / 540 us; 2234 tokens at 0.23: 52 us merged, 66 sliced; 5101 tokens, 8 / 2 heads: 119 merged,
-// 54 sliced.)
-enum MaskWalk { kMergedRows, kOwnRows, kSlicedRows };
-MaskWalk choose_mask_walk(const LayerParams& lp, double tiles, double longest, double row) {
+// Is a listed mask walked by the caller's rows as they are, four key slices to a unit, rather than by merged lists of four
+// query tiles?  `row`: mean number of tiles kept by a row of the lists.  How much neighbouring rows have in common is not
+// known here: merged lists are taken half way between a row and the union of four random ones, and the sliced walk has to be
+// quicker by a margin.  (5101 tokens at density 0.35, 8 / 2 heads: 119 us merged, 54 sliced; 588 tokens at 0.17, 32 / 16 heads:
+// 27 and 20; 519 tokens, twice, at 0.4: 28 and 32; a pattern of 65536 tokens whose rows agree: 16 and 24 ms.  A second launch
+// that walked blocks of little common row by row gained 2 to 9 % above 10000 tokens and lost up to 30 % below.)
+bool choose_sliced_rows(const LayerParams& lp, double tiles, double longest, double row) {
     const int n_stream = count_streaming(lp);
     const double dense = tiles * (lp.Hkv - n_stream) * lp.group, stream = tiles * n_stream * lp.group;
     const double band = std::min<double>(lp.sink_pages + lp.local_pages, longest);
-    const double rows4 = kFixedUs + kStepUs[0][2] * 1.15 * row;                 // the longest of four rows counts
-    const double last = kFixedUs + kStepUs[0][2] * std::min(2.3 * row, longest);
-    // merged rows cost between a shared walk of one row's length and what the row-by-row launch makes of them
-    const double merged4 = kFixedUs + 0.5 * (kStepUs[0][0] * row + std::min(kStepUs[0][0] * 0.5 * longest, kStepUs[0][2] * 1.15 * row));
-    const double merged = 10. + launch_time((dense * merged4 + stream * (kFixedUs + kStepUs[0][0] * (band + 3))) / kPairs,
-                                            kFixedUs + 0.8 * (last - kFixedUs));
-    const double own = launch_time((dense * rows4 + stream * (kFixedUs + kStepUs[0][2] * band)) / kPairs, last);
+    const double keep = std::min(1., row / (0.5 * longest)), drop = 1. - keep, joint = 1. - drop * drop * drop * drop;
+    const double walk = 0.5 * (row + 0.5 * longest * joint), merge_us = 5.;
+    const double merged = merge_us + launch_time((dense * (kFixedUs + kStepUs[0][0] * walk) +
+                                                  stream * (kFixedUs + kStepUs[0][0] * (band + 3))) / kPairs,
+                                                 kFixedUs + kStepUs[0][0] * longest * joint);
     const double sliced = launch_time(dense * (kFixedUs + kFoldUs + kStepUs[0][2] * row / 4) +
                                           stream * (kFixedUs + kFoldUs + kStepUs[0][2] * band / 4),
                                       kFixedUs + kFoldUs + kStepUs[0][2] * std::min(2 * row, longest) / 4);
-    return sliced <= std::min(merged, own) ? kSlicedRows : own < merged ? kOwnRows : kMergedRows;
+    return 1.15 * sliced < merged;
 }
 
 // Query heads of a group that share a workgroup (they read the same keys, whole and at the same time, and all end on
@@ -1146,25 +1128,19 @@ hipError_t launch_prefill(const LayerParams& lp, const void* q, const void* k, c
     mk.cols = mask->cols;
     mk.rows_per_mask = mask->rows_per_mask;
     const double row = (double)mask->nnz / ((double)mask->num_masks * mask->rows_per_mask);
-    const MaskWalk walk = choose_mask_walk(lp, tiles, max_tiles, row);
-    if (walk != kMergedRows) {
-        a.sched = make_schedule(lp, {4, {walk == kSlicedRows, walk == kSlicedRows}}, true, max_seqlen, total_tokens, false, batch);
+    if (choose_sliced_rows(lp, tiles, max_tiles, row)) {
+        a.sched = make_schedule(lp, {4, {true, true}}, true, max_seqlen, total_tokens, false, batch);
         return launch_slices<T, kMasked, 16>(a, 4);
     }
-    // The rows of four query tiles are merged; blocks whose rows have little in common are left to a second launch, which
-    // walks them row by row.
-    const PrefillShape shape = {1, {false, false}};
     mk.blocks_per_seq = mask_blocks(max_seqlen);
     mk.blk_list = reinterpret_cast<int*>(workspace);
     mk.blk_count = reinterpret_cast<int*>(reinterpret_cast<unsigned char*>(workspace) + align16((size_t)mask->nnz * sizeof(int)));
     hipLaunchKernelGGL(merge_mask_rows_kernel, dim3(mk.blocks_per_seq, batch, mask->num_masks), dim3(kWave),
                        (size_t)align16(max_tiles), stream, mk, cu_seqlens, batch);
-    hipError_t e = hipGetLastError();
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    a.sched = make_schedule(lp, shape, true, max_seqlen, total_tokens, false, batch);
-    e = launch_slices<T, kMasked, 16>(a, 1);
-    if (e != hipSuccess) return e;
-    return launch_slices<T, kMasked, 16>(a, 4);
+    a.sched = make_schedule(lp, {1, {false, false}}, true, max_seqlen, total_tokens, false, batch);
+    return launch_slices<T, kMasked, 16>(a, 1);
 }
 
 template <class T>

@@ -91,11 +91,10 @@ def test_prefill_launch_shapes(dtype, heads, kv_heads, lengths):
 
 @pytest.mark.parametrize("lengths", [(10300, 333), (2100, 64), (300, 129)])
 @pytest.mark.parametrize("dtype", ["fp16", "bf16"])
-def test_masked_prefill_splits_its_blocks_between_merged_and_row_by_row_walks(dtype, lengths):
-    """Large enough for merged lists: mask 0 keeps the same tiles in neighbouring rows (merged walks), mask 1 others in
-    every row (walked row by row), mask 2 mixes the two by block; one head keeps the analytic pattern; row lists that go
-    on past the diagonal are cut there.  The smaller batches take the caller's rows as they are, four units to a workgroup
-    or in four key slices."""
+def test_masked_prefill_walks_merged_lists_and_the_callers_rows(dtype, lengths):
+    """Mask 0 keeps the same tiles in neighbouring rows, mask 1 others in every row, mask 2 mixes the two by block; one head
+    keeps the analytic pattern; row lists go on past the diagonal and are cut there.  The larger batches take merged lists,
+    the smallest the caller's rows in four key slices."""
     w = Workload(name="pm3", batch=2, num_q_heads=32, num_kv_heads=8, dtype=dtype, streaming_kv_heads=(0, 1, 2, 3),
                  sink_tokens=128, local_tokens=512, seed=59)
     same = lambda b, i: [j for j in range(i + 1) if j % 3 == 0 or j == i]
