@@ -332,7 +332,11 @@ __global__ __launch_bounds__(kPrefillThreads, 512 / kPrefillThreads) void sparse
             if (qblk < __builtin_amdgcn_readfirstlane(lo)) return;
         } else {
             if (!block_of(rank, lo, hi, batch, b, qblk)) return;
+            // Both come out of lane arithmetic.  Left in a vector register, the block's position takes the length of the walk,
+            // the key tile of every step and the page look-ups there with it, and each branch on them runs under a mask of
+            // lanes (a step of one slice 1.71 us, 1.65 with both in scalar registers: 512 tokens over 32768).
             b = __builtin_amdgcn_readfirstlane(b);
+            qblk = __builtin_amdgcn_readfirstlane(qblk);
         }
     } else {
         if (rank >= blocks_per_seq * batch) return;
