@@ -393,6 +393,20 @@ int lserve_probe_decode_read(const lserve_attn_desc *desc, const lserve_paged_kv
                              void *stream);
 
 /*
+ * Test and measurement aid, not part of the attention path: how a prefill launch of these sizes is laid out on the
+ * current device (as on 256 compute units without one).  Launches nothing.
+ *   total_rows, max_rows  query rows of all sequences, of the longest
+ *   pages      0: prompts (lserve_sparse_prefill); else chunks (lserve_sparse_prefill_chunk, lserve_sparse_prefill_paged)
+ *              whose sequences have up to this many pages of keys: max_pages_per_seq, and for the paged call no more
+ *              than max_seqlen needs
+ *   kv_bits    of the pages
+ *   shape      HOST, [4] out: key slices (1, 2 or 4); 1 if the slices of a dense head's query rows are folded; the same of
+ *              a streaming head's; 1 if a workgroup's units are query tiles of one head, 0 if they are heads of a group first
+ */
+int lserve_probe_prefill_shape(const lserve_attn_desc *desc, int32_t batch, int32_t total_rows, int32_t max_rows,
+                               int32_t pages, int32_t kv_bits, int32_t *shape);
+
+/*
  * Bytes of device workspace a call needs (Sec. 3.6 / 3.5.2 calls keep partial results there).
  *   batch, max_pages_per_seq: as in lserve_paged_kv (ignored for prefill)
  *   sel_stride_or_budget_pages: K for select, sel_stride for decode (ignored otherwise)

@@ -36,6 +36,7 @@ EXPORTED_SYMBOLS = (
     "lserve_init",
     "lserve_sparse_decode_noalloc",
     "lserve_probe_decode_read",
+    "lserve_probe_prefill_shape",
 )
 
 
@@ -115,6 +116,8 @@ def load_library():
         lib.lserve_sparse_decode_noalloc.restype = ctypes.c_int
         lib.lserve_probe_decode_read.argtypes = [dp, kp, vp, vp, vp, i32, vp]
         lib.lserve_probe_decode_read.restype = ctypes.c_int
+        lib.lserve_probe_prefill_shape.argtypes = [dp, i32, i32, i32, i32, i32, ctypes.POINTER(i32)]
+        lib.lserve_probe_prefill_shape.restype = ctypes.c_int
         lib.lserve_init.argtypes = []
         lib.lserve_init.restype = ctypes.c_int
         for name in ("lserve_build_page_stats", "lserve_select_pages", "lserve_sparse_prefill",
@@ -340,3 +343,12 @@ def lserve_probe_decode_read(desc: AttnDesc, kv: PagedKV, sel_pages: Optional[to
     sel_stride = 0 if sel_pages is None else sel_pages.shape[-1]
     _check(load_library().lserve_probe_decode_read(desc.c(), kv.c(), _ptr(sel_pages), _ptr(sel_count), _ptr(sel_seq_len),
                                                    sel_stride, _stream(stream)), "lserve_probe_decode_read")
+
+
+def lserve_probe_prefill_shape(desc: AttnDesc, batch: int, total_rows: int, max_rows: int, pages: int = 0,
+                               kv_bits: int = 16) -> tuple:
+    """(key slices, dense heads folded, streaming heads folded, units are query tiles of one head) of a prefill launch."""
+    shape = (ctypes.c_int32 * 4)()
+    _check(load_library().lserve_probe_prefill_shape(desc.c(), batch, total_rows, max_rows, pages, kv_bits, shape),
+           "lserve_probe_prefill_shape")
+    return tuple(shape)

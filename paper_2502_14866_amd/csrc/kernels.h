@@ -23,6 +23,13 @@ hipError_t launch_select_pages(int dtype, const LayerParams& lp, const PagedPara
                                float* scores, bool scores_is_user_buffer, const HeadList& selecting,
                                hipStream_t stream);
 
+// Compute units of the device that is current at the first call (256 without one).
+int num_compute_units();
+
+// {key slices, dense heads' slices share a unit, streaming heads' do, units are query tiles of one head} of a prefill launch:
+// of prompts with pages = 0, else of chunks whose sequences have up to `pages` pages of keys.
+void prefill_shape(const LayerParams& lp, int batch, int total_rows, int max_rows, int pages, int kv_bits, int (&out)[4]);
+
 size_t paged_prefill_workspace_bytes(const LayerParams& lp, int batch, int max_pages);
 // k_new / v_new: the chunk's own K / V when they have not been written back yet (the cache is then the chunk's
 // history), or null when the cache already holds the chunk.

@@ -10,6 +10,19 @@
 
 using namespace lserve;
 
+int lserve::num_compute_units() {
+    static const int cus = [] {
+        int dev = 0, n = 0;
+        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+            n <= 0) {
+            (void)hipGetLastError();
+            return 256;
+        }
+        return n;
+    }();
+    return cus;
+}
+
 // Scratch of lserve_sparse_decode_noalloc: the partial results the decode kernels exchange, which the other
 // decode entry point keeps in the caller's workspace.  One copy per GPU for the life of the process.  In host code
 // the name is only a handle: the address on a device comes from hipGetSymbolAddress (scratch_on_current_device).
@@ -291,6 +304,20 @@ int lserve_sparse_prefill_chunk(const lserve_attn_desc* desc, const lserve_paged
     hipError_t e = launch_sparse_prefill_paged(desc->dtype, lp, pp, q, k_new, v_new, cu_new, total_new, max_new_per_seq, 0,
                                                out, lse_out, nullptr, (hipStream_t)stream);
     return e == hipSuccess ? LSERVE_OK : fail_hip(e);
+}
+
+int lserve_probe_prefill_shape(const lserve_attn_desc* desc, int32_t batch, int32_t total_rows, int32_t max_rows, int32_t pages,
+                               int32_t kv_bits, int32_t* shape) {
+    LayerParams lp;
+    const int rc = make_layer(desc, &lp);
+    if (rc) return rc;
+    if (!shape || batch <= 0 || total_rows <= 0 || max_rows <= 0 || max_rows > total_rows || pages < 0) return LSERVE_ERR_INVALID_ARG;
+    if (kv_bits != 0 && kv_bits != 16 && kv_bits != 8 && kv_bits != 4) return LSERVE_ERR_INVALID_ARG;
+    if (lp.NP != 64) return LSERVE_ERR_UNSUPPORTED;
+    int out[4];
+    prefill_shape(lp, batch, total_rows, max_rows, pages, kv_bits == 0 ? 16 : kv_bits, out);
+    for (int i = 0; i < 4; ++i) shape[i] = out[i];
+    return LSERVE_OK;
 }
 
 size_t lserve_paged_prefill_workspace_bytes(const lserve_attn_desc* desc, int32_t batch, int32_t max_pages_per_seq) {

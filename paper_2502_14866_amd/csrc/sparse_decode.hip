@@ -1001,16 +1001,6 @@ __global__ __launch_bounds__(kDecodeThreads) void sparse_decode_kernel(
 
 // ---- host side -----------------------------------------------------------------------------------
 
-int num_compute_units() {
-    static int cus = [] {
-        int dev = 0, n = 0;
-        if (hipGetDevice(&dev) != hipSuccess) return 256;
-        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) return 256;
-        return n;
-    }();
-    return cus;
-}
-
 // `slack`: nominal entries added to a streaming head's list beyond its s + w pages.  They are never real, so they
 // cost the workgroup that holds them nothing, which makes up for what a list boundary inside a range costs it
 // (the piece of the list that ends there is folded and delivered, the next list's queries are staged: about

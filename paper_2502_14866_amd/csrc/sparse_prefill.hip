@@ -20,6 +20,7 @@
 // transposing LDS read of gfx950 (ds_read_b64_tr_b16), which hands a lane four keys of one channel, so
 // there is no transposition pass and no transposed copy of V.
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "kernels.h"
@@ -272,7 +273,7 @@ enum PrefillMode { kPlain = 0, kMasked = 1, kPaged = 2 };
 // one slice all pairs walk the same key tiles; with two or four, slice s of a unit takes every SL-th tile of the walk
 // and the slices are folded through LDS at the end.  A launch with few query rows (a short prompt, a chunk over a long
 // history) then has SL times the workgroups, each with a walk SL times shorter, for SL times the staging per step
-// (see choose_slices).
+// (see choose_shape).
 template <class T, int MODE, int BITS, int SL>
 __global__ __launch_bounds__(kPrefillThreads, 512 / kPrefillThreads) void sparse_prefill_kernel(
     LayerParams lp, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
@@ -963,53 +964,185 @@ __global__ __launch_bounds__(kPrefillThreads, 512 / kPrefillThreads) void sparse
 
 // ---- host side -----------------------------------------------------------------------------------
 
-constexpr int kComputeUnits = 256;  // one workgroup per compute unit is resident
-
 int count_streaming(const LayerParams& lp) {
     int n = 0;
     for (int hk = 0; hk < lp.Hkv; ++hk) n += (int)((lp.streaming_mask >> hk) & 1ull);
     return n;
 }
 
-// What a launch is made of: the kernel's key slices, and per class of heads whether the slices share a unit.
+// What a launch is made of: the kernel's key slices, per class of heads whether the slices share a unit, and whether the
+// units of a workgroup are query tiles of one head instead of heads of a group.
 struct PrefillShape {
     int slices;
     bool fold[2];
+    bool one_head;
 };
 
-// Key slices of a launch over `tiles` query tiles whose dense walks are `longest` key tiles at most and `mean` on
-// average.  The launch takes as long as its longest workgroup, or as all of them shared out over the chip plus a
-// part of the longest for the uneven end; a workgroup costs a fixed time (start, first tiles and queries, epilogue:
-// 1 + 3 + 2.5 us by time stamps) and its steps.  More slices shorten the walks and multiply the workgroups, but a step
-// then stages as many tiles as there are slices for the same products.  Measured with one / two / four slices: 512 new
-// tokens over a history of 32768, 932 / 547 / 381 us; one prompt of 4096 tokens, 125 / 129 / 157 us; of 65536 tokens,
-// 15.4 / 17.6 / 21.6 ms.  Quantised pages are not built for four (the codes on their way need more registers than
-// there are).
-constexpr double kFixedUs = 7.0, kFoldUs = 1.0;                        // of a workgroup; and if it folds slices
-constexpr double kStepUs[2][3] = {{2.0, 2.35, 3.0}, {2.3, 3.5, 0.0}};  // 16-bit / quantised pages, by log2(slices)
+// The queries of a launch as far as the host knows them.
+struct PrefillRows {
+    int batch, total, longest;
+    int history_pages;  // bound of the key tiles in front of them, of every sequence; -1: none (a prompt)
+};
 
-double launch_time(double work, double last) { return std::max(last, work / kComputeUnits + 0.35 * last); }
+int units_of(const PrefillShape& shape, int cls) { return shape.fold[cls] ? kPairs / shape.slices : kPairs; }
+// Query heads of a group that share a workgroup: they read the same keys, whole and at the same time, and all end on the
+// same diagonal tile, where query tiles side by side would not.  Query tiles make up the rest of the units.
+int heads_per_block(const LayerParams& lp, const PrefillShape& shape, int cls) {
+    int heads = 1;
+    while (!shape.one_head && heads < units_of(shape, cls) && lp.group % (2 * heads) == 0) heads *= 2;
+    return heads;
+}
 
-PrefillShape choose_shape(const LayerParams& lp, double tiles, double longest, double mean, int bits) {
-    const int n_stream = count_streaming(lp);
-    const double dense = tiles * (lp.Hkv - n_stream) * lp.group, stream = tiles * n_stream * lp.group;
-    const double band = std::min<double>(lp.sink_pages + lp.local_pages, longest);
-    PrefillShape best = {1, {false, false}};
-    double best_time = 1e300;
-    for (int i = 0; i < (bits == 16 ? 3 : 2); ++i) {
-        const int SL = 1 << i;
-        const double step = kStepUs[bits != 16][i], fold_us = SL > 1 ? kFoldUs : 0.;
-        for (int fold_stream = 0; fold_stream <= (SL > 1); ++fold_stream) {
-            const double stream_slices = fold_stream ? SL : 1, stream_us = kFixedUs + fold_stream * fold_us + step * band / stream_slices;
-            const double dense_us = kFixedUs + fold_us;
-            const double work = dense / kPairs * SL * (dense_us + step * mean / SL) + stream / kPairs * stream_slices * stream_us;
-            const double last = std::max(dense > 0 ? dense_us + step * longest / SL : 0., stream > 0 ? stream_us : 0.);
-            const double time = launch_time(work, last);
-            // (a tie goes to the shorter walks)
-            if (time < best_time || (fold_stream && time == best_time)) best_time = time, best = {SL, {SL > 1, fold_stream != 0}};
+// The estimate behind the choice of a shape: a compute unit holds one workgroup at a time, an XCD deals its workgroups out
+// longest walk first, and a workgroup costs a fixed time and its steps.  Constants in microseconds, fitted to 2100 launches
+// (211 chunks and 90 prompts of 1 .. 24 sequences in every shape; two thirds of the estimates are within 9 %):
+// a step of 64 keys with one / two / four slices takes 1.75 / 2.16 / 2.91, 2.21 / 2.85 over quantised pages (not built for
+// four: the codes on their way need more registers than there are); with most wavefronts without rows 22 % less.
+constexpr float kStepUs[2][3] = {{1.75f, 2.16f, 2.91f}, {2.21f, 2.85f, 2.85f}};
+constexpr float kStepWithoutRows = 0.78f;
+constexpr float kStartUs[2] = {5.2f, 5.8f}, kStartOfSlices[3] = {0.f, 0.5f, 0.55f}, kFoldUs = 0.44f, kLaunchUs = 2.2f;
+// past the even share of the work: a part of the last streaming walk, or of the longest dense one
+constexpr float kTailOfStream = 0.55f, kTailOfDense = 0.14f;
+
+// One class of heads of a launch: workgroups per XCD and what they cost.
+struct ClassCost {
+    float count, start, step;  // step: of a workgroup's own share of the keys
+    int qtiles;
+};
+
+// Smallest whole number not below x >= 0.
+float whole(float x) {
+    const float i = (float)(int)x;
+    return i < x ? i + 1.f : i;
+}
+
+// side: -1 / 1 for a few blocks less / more than the mean where their number is an estimate, 0 where it is known.
+ClassCost class_cost(const LayerParams& lp, const PrefillShape& shape, const PrefillRows& rows, int cls, int heads, bool quant,
+                     int side, float spread) {
+    ClassCost c = {};
+    if (heads == 0) return c;
+    const int per_block = heads_per_block(lp, shape, cls);
+    c.qtiles = units_of(shape, cls) / per_block;
+    const int block = kTile * c.qtiles, log2_slices = shape.slices == 4 ? 2 : shape.slices == 2 ? 1 : 0;
+    const float n = (float)rows.batch;
+    const bool alike = (long long)rows.batch * rows.longest == rows.total;
+    float blocks;
+    if (rows.history_pages < 0 ? alike : alike && side < 0 && rows.longest % kTile == 0)
+        blocks = n * (float)((rows.longest + block - 1) / block);  // chunks of whole tiles mostly follow others
+    else if (rows.history_pages >= 0)  // rows that start anywhere inside a block touch (rows - 1) / block + 1 blocks on average
+        blocks = std::max(std::max(n, (float)rows.total / block), (float)(rows.total - rows.batch) / block + n + side * spread);
+    else
+        blocks = std::max(n, (float)rows.total / block + 0.5f * n + side * spread);
+    const int n_per_block = lp.group / per_block;
+    c.count = kXcds % heads == 0 ? n_per_block * whole(blocks * heads / kXcds - 1e-4f)
+                                 : whole(heads * n_per_block * blocks / kXcds - 1e-4f);
+    const float halves = ((float)rows.total + 31.f * n) / 32.f;  // halves of tiles with rows
+    const float active = std::min(1.f, halves / (blocks * c.qtiles * 2));
+    c.step = kStepUs[quant][log2_slices] * (kStepWithoutRows + (1.f - kStepWithoutRows) * active) / (shape.fold[cls] ? shape.slices : 1);
+    c.start = kStartUs[quant] + kStartOfSlices[log2_slices] + (shape.fold[cls] ? kFoldUs : 0.f);
+    return c;
+}
+
+// Time until the last of n workgroups is through, n dealt out to m units longest first, their times falling evenly from
+// `longest` to `shortest`: the unit that ends a round first takes the longest of the next, so every two rounds are even.
+float rounds_time(float n, float longest, float shortest, int m) {
+    const float fall = (longest - shortest) / std::max(1.f, n - 1.f);
+    auto of = [&](float k) { return longest - fall * std::min(k, n - 1.f); };
+    const int pairs = (int)(n / (2 * m));
+    float t = 0.f;
+    if (pairs > 8)
+        t = pairs * (longest + shortest);
+    else
+        for (int i = 0; i < pairs; ++i) t += of(2.f * m * i) + of(2.f * m * i + 2 * m - 1);
+    const float done = 2.f * m * pairs, left = n - done;
+    if (left < 0.5f) return t;
+    return t + (left <= m ? of(done) : std::max(of(done), of(done + m - 1) + of(done + m)));
+}
+
+// Estimated time of a launch whose history is `history` key tiles long.
+float launch_time(const LayerParams& lp, const PrefillRows& rows, float history, const ClassCost (&c)[2], int units_per_xcd) {
+    const float longest_tiles = (float)rows.longest / kTile, mean_tiles = (float)rows.total / rows.batch / kTile;
+    const float other = rows.batch > 1 ? (float)(rows.total - rows.longest) / (rows.batch - 1) / kTile : longest_tiles;
+    float longest[2] = {}, shortest[2] = {}, mean[2] = {};
+    for (int cls = 0; cls < 2; ++cls) {
+        if (c[cls].count == 0.f) continue;
+        const float qt = (float)c[cls].qtiles;
+        float hi, lo, mid;  // key tiles of the walks
+        if (rows.history_pages >= 0) {
+            hi = history + longest_tiles + 0.5f;
+            lo = history + std::min(qt, other + 0.5f);
+            mid = history + 0.25f * (longest_tiles + mean_tiles) + 0.5f * std::min(qt, longest_tiles);
+        } else {
+            hi = whole(longest_tiles);
+            lo = std::min(qt, hi);
+            mid = 0.25f * (longest_tiles + mean_tiles) + 0.5f * std::min(qt, other + 0.5f);
         }
+        if (cls == 1) {
+            const float band = (float)(lp.sink_pages + lp.local_pages) + qt - 1.f;
+            hi = std::min(hi, band);
+            lo = std::min(lo, band);
+        }
+        mid = std::min(hi, std::max(lo, mid));
+        longest[cls] = c[cls].start + c[cls].step * hi;
+        shortest[cls] = c[cls].start + c[cls].step * lo;
+        mean[cls] = c[cls].start + c[cls].step * mid;
     }
-    return best;
+    float t = longest[1];
+    if (c[0].count > 0.f) t = std::max(t, rounds_time(c[0].count, longest[0], shortest[0], units_per_xcd));
+    if (c[0].count + c[1].count > units_per_xcd) {
+        const float even = (c[0].count * mean[0] + c[1].count * mean[1]) / units_per_xcd;
+        t = std::max(t, even + std::max(kTailOfStream * longest[1], kTailOfDense * longest[0]));
+    }
+    return t + kLaunchUs;
+}
+
+// The shape of a launch.  Measured with one / two / four slices: 512 new tokens over a history of 32768, 849 / 520 / 363 us;
+// 2635 over 45405, 1229 / 1480 / 1513 us (one round of workgroups, or two of half the length at more per step); one prompt of
+// 4096 tokens, 119 / 116 / 146 us; of 65536, 15.4 / 17.6 / 21.6 ms.  Heads or query tiles as units of one slice: 5 sequences of
+// 7 .. 123 tokens, 12.4 and 9.3 us (fewer wavefronts at work on a compute unit); 8 of 100 .. 1500, 60 and 73 us.
+// The history of a chunk is not known on the host.  It may be as long as the page table allows, which a caller that
+// allocates what it needs sees to, or far shorter, in a table as wide as the longest context: the shape is the one that on
+// average costs least over what it could have been for histories of that length (counted four times), a quarter, a
+// sixteenth and a sixty-fourth of it (490 chunks: 1.5 % over the best shape with a tight table and 2.2 % with one 32 times as
+// wide; by the length of the table alone 1.1 and 3.3 %, and up to half the speed lost).  Where the number of blocks is an
+// estimate, near the end of a round of workgroups, so is the time: the mean of a few blocks less and a few more.
+PrefillShape choose_shape(const LayerParams& lp, const PrefillRows& rows, bool quant) {
+    constexpr PrefillShape kShapes[] = {{1, {false, false}, false}, {1, {false, false}, true}, {2, {true, true}, true},
+                                        {2, {true, true}, false},   {2, {true, false}, false}, {4, {true, true}, false}};
+    constexpr int kCount = (int)(sizeof(kShapes) / sizeof(kShapes[0]));
+    constexpr float kWeight[4] = {4.f, 1.f, 1.f, 1.f};
+    const int n_stream = count_streaming(lp), heads[2] = {lp.Hkv - n_stream, n_stream};
+    const int units_per_xcd = std::max(1, num_compute_units() / kXcds);
+    const bool prompt = rows.history_pages < 0, exact = prompt && (long long)rows.batch * rows.longest == rows.total;
+    // a walk of one or two tiles leaves nothing to share out; quantised pages are not built for four slices
+    const int count = prompt && rows.longest <= 2 * kTile ? 2 : quant ? kCount - 1 : kCount;
+    const int guesses = prompt ? 1 : 4;
+    const float spread = 0.4f * std::sqrt((float)rows.batch);
+    float time[kCount][4] = {};
+    for (int i = 0; i < count; ++i)
+        for (int side = exact ? 0 : -1; side <= 1; side += 2) {
+            const ClassCost c[2] = {class_cost(lp, kShapes[i], rows, 0, heads[0], quant, exact ? 0 : side, spread),
+                                    class_cost(lp, kShapes[i], rows, 1, heads[1], quant, exact ? 0 : side, spread)};
+            float history = prompt ? 0.f : (float)rows.history_pages;
+            for (int g = 0; g < guesses; ++g, history *= 0.25f) time[i][g] += launch_time(lp, rows, history, c, units_per_xcd);
+        }
+    int best = 0;
+    float best_score = 0.f;
+    for (int i = 0; i < count; ++i) {
+        float score = 0.f;
+        for (int g = 0; g < guesses; ++g) {
+            float least = time[0][g];
+            for (int k = 1; k < count; ++k) least = std::min(least, time[k][g]);
+            score += kWeight[g] * time[i][g] / least;
+        }
+        if (i == 0 || score < best_score) best = i, best_score = score;
+    }
+    return kShapes[best];
+}
+
+// Rows of a chunk in front of which up to `pages` pages of keys may lie, its own among them.
+PrefillRows chunk_rows(int batch, int total_new, int max_new_per_seq, int pages) {
+    return {batch, total_new, max_new_per_seq, std::max(0, pages - max_new_per_seq / kTile)};
 }
 
 // Is a listed mask walked by the caller's rows as they are, four key slices to a unit, rather than by merged lists of four
@@ -1019,32 +1152,29 @@ PrefillShape choose_shape(const LayerParams& lp, double tiles, double longest, d
 // 27 and 20; 519 tokens, twice, at 0.4: 28 and 32; a pattern of 65536 tokens whose rows agree: 16 and 24 ms.  A second launch
 // that walked blocks of little common row by row gained 2 to 9 % above 10000 tokens and lost up to 30 % below.)
 bool choose_sliced_rows(const LayerParams& lp, double tiles, double longest, double row) {
+    constexpr double kFixedUs = 7., kFoldedUs = 8., kStepUs = 2., kSlicedStepUs = 3.;  // of a workgroup, rounded up
+    const double units = num_compute_units();
+    auto launch_time = [&](double work, double last) { return std::max(last, work / units + 0.35 * last); };
     const int n_stream = count_streaming(lp);
     const double dense = tiles * (lp.Hkv - n_stream) * lp.group, stream = tiles * n_stream * lp.group;
     const double band = std::min<double>(lp.sink_pages + lp.local_pages, longest);
     const double keep = std::min(1., row / (0.5 * longest)), drop = 1. - keep, joint = 1. - drop * drop * drop * drop;
     const double walk = 0.5 * (row + 0.5 * longest * joint), merge_us = 5.;
-    const double merged = merge_us + launch_time((dense * (kFixedUs + kStepUs[0][0] * walk) +
-                                                  stream * (kFixedUs + kStepUs[0][0] * (band + 3))) / kPairs,
-                                                 kFixedUs + kStepUs[0][0] * longest * joint);
-    const double sliced = launch_time(dense * (kFixedUs + kFoldUs + kStepUs[0][2] * row / 4) +
-                                          stream * (kFixedUs + kFoldUs + kStepUs[0][2] * band / 4),
-                                      kFixedUs + kFoldUs + kStepUs[0][2] * std::min(2 * row, longest) / 4);
+    const double merged = merge_us + launch_time((dense * (kFixedUs + kStepUs * walk) + stream * (kFixedUs + kStepUs * (band + 3))) / kPairs,
+                                                 kFixedUs + kStepUs * longest * joint);
+    const double sliced = launch_time(dense * (kFoldedUs + kSlicedStepUs * row / 4) + stream * (kFoldedUs + kSlicedStepUs * band / 4),
+                                      kFoldedUs + kSlicedStepUs * std::min(2 * row, longest) / 4);
     return 1.15 * sliced < merged;
 }
 
-// Query heads of a group that share a workgroup (they read the same keys, whole and at the same time, and all end on
-// the same diagonal tile, where query tiles side by side would not), then query tiles, to make up the units.
 // max_rows: rows of the longest sequence; any_start: they may start anywhere inside a block.
-PrefillSchedule make_schedule(const LayerParams& lp, const PrefillShape& shape, bool one_head, int max_rows, int total_rows,
-                              bool any_start, int batch) {
+PrefillSchedule make_schedule(const LayerParams& lp, const PrefillShape& shape, int max_rows, int total_rows, bool any_start,
+                              int batch) {
     PrefillSchedule sched;
     for (int c = 0; c < 2; ++c) {
         HeadClass& hc = sched.cls[c];
         hc.fold = shape.fold[c];
-        const int units = shape.fold[c] ? kPairs / shape.slices : kPairs;
-        int heads = 1;
-        while (!one_head && heads < units && lp.group % (2 * heads) == 0) heads *= 2;
+        const int units = units_of(shape, c), heads = heads_per_block(lp, shape, c);
         hc.heads_per_block = heads;
         hc.qtiles_log2 = 0;
         while ((heads << hc.qtiles_log2) < units) ++hc.qtiles_log2;
@@ -1125,11 +1255,9 @@ hipError_t launch_prefill(const LayerParams& lp, const void* q, const void* k, c
     a.out = reinterpret_cast<uint16_t*>(out);
     a.lse_out = lse_out;
     a.stream = stream;
-    // half a tile of padding per sequence; walks are half as long as their sequence, and long sequences have more of them
-    const double tiles = (double)total_tokens / kTile + 0.5 * batch, mean_tiles = (double)total_tokens / kTile / batch;
     if (!mask) {
-        const PrefillShape shape = choose_shape(lp, tiles, max_tiles, 0.25 * (mean_tiles + max_tiles), 16);
-        a.sched = make_schedule(lp, shape, false, max_seqlen, total_tokens, false, batch);
+        const PrefillShape shape = choose_shape(lp, {batch, total_tokens, max_seqlen, -1}, false);
+        a.sched = make_schedule(lp, shape, max_seqlen, total_tokens, false, batch);
         return launch_slices<T, kPlain, 16>(a, shape.slices);
     }
     PrefillMask& mk = a.mk;
@@ -1139,8 +1267,9 @@ hipError_t launch_prefill(const LayerParams& lp, const void* q, const void* k, c
     mk.cols = mask->cols;
     mk.rows_per_mask = mask->rows_per_mask;
     const double row = (double)mask->nnz / ((double)mask->num_masks * mask->rows_per_mask);
+    const double tiles = (double)total_tokens / kTile + 0.5 * batch;  // half a tile of padding per sequence
     if (choose_sliced_rows(lp, tiles, max_tiles, row)) {
-        a.sched = make_schedule(lp, {4, {true, true}}, true, max_seqlen, total_tokens, false, batch);
+        a.sched = make_schedule(lp, {4, {true, true}, true}, max_seqlen, total_tokens, false, batch);
         return launch_slices<T, kMasked, 16>(a, 4);
     }
     mk.blocks_per_seq = mask_blocks(max_seqlen);
@@ -1150,7 +1279,7 @@ hipError_t launch_prefill(const LayerParams& lp, const void* q, const void* k, c
                        (size_t)align16(max_tiles), stream, mk, cu_seqlens, batch);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    a.sched = make_schedule(lp, {1, {false, false}}, true, max_seqlen, total_tokens, false, batch);
+    a.sched = make_schedule(lp, {1, {false, false}, true}, max_seqlen, total_tokens, false, batch);
     return launch_slices<T, kMasked, 16>(a, 1);
 }
 
@@ -1159,7 +1288,6 @@ hipError_t launch_prefill_paged(const LayerParams& lp, const PagedParams& kv, co
                                 const void* v_new, const int* cu_q, int total_new, int max_new_per_seq, int max_seqlen,
                                 void* out, float* lse_out, void* workspace, hipStream_t stream) {
     (void)workspace;
-    (void)max_seqlen;
     PrefillLaunch a = {};
     a.lp = &lp;
     a.q = reinterpret_cast<const uint16_t*>(q);
@@ -1172,10 +1300,9 @@ hipError_t launch_prefill_paged(const LayerParams& lp, const PagedParams& kv, co
     a.pg.k_new = reinterpret_cast<const uint16_t*>(k_new);
     a.pg.v_new = reinterpret_cast<const uint16_t*>(v_new);
     a.stream = stream;
-    // the history is not known on the host: the walks are taken to be as long as the page table allows
-    const double walk = kv.max_pages;
-    const PrefillShape shape = choose_shape(lp, (double)total_new / kTile + 0.5 * kv.batch, walk, walk, kv.kv_bits);
-    a.sched = make_schedule(lp, shape, false, max_new_per_seq, total_new, true, kv.batch);
+    const int pages = max_seqlen > 0 ? std::min(kv.max_pages, (max_seqlen - 1) / kTile + 1) : kv.max_pages;
+    const PrefillShape shape = choose_shape(lp, chunk_rows(kv.batch, total_new, max_new_per_seq, pages), kv.kv_bits != 16);
+    a.sched = make_schedule(lp, shape, max_new_per_seq, total_new, true, kv.batch);
     if (kv.kv_bits == 8) return launch_slices<T, kPaged, 8>(a, shape.slices);
     if (kv.kv_bits == 4) return launch_slices<T, kPaged, 4>(a, shape.slices);
     return launch_slices<T, kPaged, 16>(a, shape.slices);
@@ -1186,6 +1313,15 @@ hipError_t launch_prefill_paged(const LayerParams& lp, const PagedParams& kv, co
 hipError_t preload_prefill_kernels() {
     hipFuncAttributes attr;
     return hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(&merge_mask_rows_kernel));
+}
+
+void prefill_shape(const LayerParams& lp, int batch, int total_rows, int max_rows, int pages, int kv_bits, int (&out)[4]) {
+    const PrefillShape shape = pages > 0 ? choose_shape(lp, chunk_rows(batch, total_rows, max_rows, pages), kv_bits != 16)
+                                         : choose_shape(lp, {batch, total_rows, max_rows, -1}, false);
+    out[0] = shape.slices;
+    out[1] = shape.fold[0];
+    out[2] = shape.fold[1];
+    out[3] = shape.one_head;
 }
 
 size_t paged_prefill_workspace_bytes(const LayerParams& lp, int batch, int max_pages) {

@@ -107,3 +107,29 @@ def test_masked_prefill_walks_merged_lists_and_the_callers_rows(dtype, lengths):
     ref, lse_ref = oracle.block_mask_prefill_rows(pin.q, pin.k, pin.v, pin.cu_seqlens, w.streaming_flags(), 64,
                                                   w.sink_tokens, w.local_tokens, head_mask, qts, rp, cl, rows, t, h)
     _check(w, lengths, pin, out, lse, ref, lse_ref, tok, f"masked prefill {dtype}")
+
+
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+def test_paged_prefill_goes_by_the_stated_length_not_by_the_width_of_the_table(dtype):
+    """The same cache behind a table of 32 and of 2048 pages per sequence: the launch, and so every bit, is the same."""
+    import paper_2502_14866_amd as L
+
+    L.load_library()
+    dev = torch.device("cuda:0")
+    n = 2047
+    w = Workload(name="width", batch=1, num_q_heads=32, num_kv_heads=8, dtype=dtype, streaming_kv_heads=(0, 1, 2, 3),
+                 sink_tokens=128, local_tokens=512, seed=83)
+    pin = make_prefill_inputs(w, lengths=(n,))
+    desc = L.AttnDesc(32, 8, w.streaming_flags(), dtype=w.torch_dtype, sink_tokens=128, local_tokens=512)
+    pool = lambda t: torch.cat([t, t[:1]]).reshape(32, 64, 8, 128).transpose(1, 2).contiguous().to(dev)
+    k, v, q, cu = pool(pin.k), pool(pin.v), pin.q.to(dev), pin.cu_seqlens.to(dev)
+    outs = []
+    for width in (32, 2048):
+        table = torch.zeros((1, width), dtype=torch.int32)
+        table[0, :32] = torch.arange(32)
+        kv = L.PagedKV(k, v, None, table.to(dev), torch.tensor([n], dtype=torch.int32, device=dev))
+        out, lse = torch.empty_like(q), torch.empty((32, n), dtype=torch.float32, device=dev)
+        L.lserve_sparse_prefill_paged(desc, kv, q, cu, n, n, out, lse, None)
+        outs.append((out, lse))
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
