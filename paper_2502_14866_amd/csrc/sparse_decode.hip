@@ -162,16 +162,23 @@ __device__ __forceinline__ void load_v(Slabs<64, 8>& s, const uint4* vslab, int 
 
 typedef float floatx4_t __attribute__((ext_vector_type(4)));
 
+// Factor of weight * scale on its way to fp16: clear of the subnormals, and below 65504 for scales up to 1023.  The quantiser
+// makes larger ones (4-bit rows that span more than 15350, 8-bit ones more than 260000): from the first weight that would
+// not fit on, the wave does without the factor, which fits any weight (at most 1) times any scale.
+constexpr float kWeightScale = 64.f, kMaxWeight = 65504.f;
+
 template <int N, int BITS> struct WaveState {
     // Quantised pages: lane (t, g) keeps the softmax of query heads g and g + 4 (the latter for groups above four): their
     // running maxima (equal over the sixteen lanes of g), and its token's share of the sums of weights and of weight *
     // zero point.  acc[m][j] is the output of head g + 4 j in channel 8 t + m, in units of the stored weights and codes
     // (see quantised_quarter_page); acc[m][2], acc[m][3] belong to no head.  q: the queries as matrix operands.
     static constexpr int kHeadsPerLane = (N + 3) / 4;
-    float m[kHeadsPerLane], l[kHeadsPerLane], z[kHeadsPerLane], q_sum[kHeadsPerLane];
+    // weight_scale: the factor the weights are stored with, one for the wave (kWeightScale or 1).
+    float m[kHeadsPerLane], l[kHeadsPerLane], z[kHeadsPerLane], q_sum[kHeadsPerLane], weight_scale;
     floatx4_t acc[8];
     uint4 q[4];
     __device__ __forceinline__ void reset() {
+        weight_scale = kWeightScale;
 #pragma unroll
         for (int j = 0; j < kHeadsPerLane; ++j) {
             m[j] = -INFINITY;
@@ -307,7 +314,6 @@ __device__ __forceinline__ void process_quarter_page(WaveState<N, 16>& st, const
     __builtin_amdgcn_wave_barrier();
 }
 
-constexpr float kWeightScale = 64.f;   // keeps weight * scale clear of the fp16 subnormals, and below 65504 for any fp16 row
 constexpr float kCodeUnit = 0x1p-24f;  // value of the fp16 number whose bits are 1
 
 typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
@@ -370,8 +376,9 @@ __device__ __forceinline__ void quantised_quarter_page(WaveState<N, BITS>& st, f
     const half2_t ksz = __builtin_bit_cast(half2_t, cur.ksz), vsz = __builtin_bit_cast(half2_t, cur.vsz);
     const float k_scale = (float)ksz[0] * (scale_log2 / kCodeUnit), k_zero = (float)ksz[1] * scale_log2;
     // slots past the end may hold anything
-    const float v_scale = dead ? 0.f : (float)vsz[0] * kWeightScale, v_zero = dead ? 0.f : (float)vsz[1];
+    const float v_scale = dead ? 0.f : (float)vsz[0] * st.weight_scale, v_zero = dead ? 0.f : (float)vsz[1];
     _Float16* w_lds = reinterpret_cast<_Float16*>(p_lds);
+    float w[HPL];
 #pragma unroll
     for (int j = 0; j < HPL; ++j) {
         const float x = dead ? -INFINITY : __builtin_fmaf(k_scale, s[j], k_zero * st.q_sum[j]);
@@ -393,8 +400,23 @@ __device__ __forceinline__ void quantised_quarter_page(WaveState<N, BITS>& st, f
         const float p = dead ? 0.f : __builtin_amdgcn_exp2f(x - m_safe);
         st.l[j] += p;
         st.z[j] = __builtin_fmaf(p, v_zero, st.z[j]);
-        w_lds[(4 * j + g) * 16 + t] = (_Float16)(p * v_scale);
+        w[j] = p * v_scale;
     }
+    float w_max = w[0];
+#pragma unroll
+    for (int j = 1; j < HPL; ++j) w_max = fmaxf(w_max, w[j]);
+    if (__any(w_max > kMaxWeight)) {  // hardly ever: a value row of a very large scale
+        const float down = 1.f / kWeightScale;  // (a second time cannot be: without the factor every weight fits)
+        st.weight_scale = 1.f;
+#pragma unroll
+        for (int j = 0; j < HPL; ++j) {
+            w[j] *= down;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) st.acc[i][j] *= down;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < HPL; ++j) w_lds[(4 * j + g) * 16 + t] = (_Float16)w[j];
     __builtin_amdgcn_wave_barrier();
     // row t of the operand: query head t / 4 + 4 (t % 4), tokens 4 g .. 4 g + 3 (rows without a head repeat one)
     const int head = t / 4 + 4 * (t % 4 < HPL ? t % 4 : 0);
@@ -549,7 +571,8 @@ __device__ __forceinline__ void deposit_wave(WaveState<N, 16>& st, DecodeShared<
 template <int N, int NP, int BITS>
 __device__ __forceinline__ void deposit_wave(WaveState<N, BITS>& st, DecodeShared<N, NP>& sm, int wave, int lane) {
     const int t = lane % 16, g = lane / 16;
-    constexpr float unit = 1.f / (kCodeUnit * kWeightScale), upper = BITS == 4 ? unit / 16.f : unit;
+    const float unit = st.weight_scale == kWeightScale ? 1.f / (kCodeUnit * kWeightScale) : 1.f / kCodeUnit;
+    const float upper = BITS == 4 ? unit * 0.0625f : unit;
 #pragma unroll
     for (int j = 0; j < WaveState<N, BITS>::kHeadsPerLane; ++j) {
         const float l = row16_sum(st.l[j]), z = row16_sum(st.z[j]);

@@ -185,3 +185,46 @@ def test_covered_sequences_take_no_scores_but_their_statistics_are_brought_up_to
         picked.append((sel, cnt, ssl))
     assert all(torch.equal(a, b) for a, b in zip(*picked))
     assert cnt[:3, 0].tolist() == [11, 1, 3] and cnt[3].tolist() == [16, 16]
+
+
+@pytest.mark.parametrize("group", [1, 4, 8])
+@pytest.mark.parametrize("dtype,kv_bits,span", [(torch.float16, 4, 20000.0), (torch.float16, 4, 65504.0), (torch.bfloat16, 4, 60000.0),
+                                                (torch.bfloat16, 8, 3e5), (torch.bfloat16, 8, 6e6)])
+def test_quantised_decode_over_value_rows_of_any_scale(dtype, kv_bits, span, group):
+    """A few value rows spanning `span` either way among rows of N(0, 1), anywhere in the list: their scales times the weights
+    times the factor that suits the other rows are beyond fp16."""
+    L = _lib()
+    dev = torch.device("cuda:0")
+    n, heads = 3000, 2
+    g = torch.Generator().manual_seed(97 + group)
+    k = torch.randn((n, heads, 128), generator=g)
+    v = torch.randn((n, heads, 128), generator=g)
+    loud = torch.randint(0, n, (40,), generator=g)
+    k[loud] *= 2.5  # and they take the largest weights
+    v[loud] = (torch.rand((40, heads, 128), generator=g) * 2 - 1) * span
+    k, v = k.to(dtype), v.to(dtype)
+    q = torch.randn((1, heads * group, 128), generator=g).to(dtype)
+    pages = -(-n // 64)
+    shape = (pages, heads, 64 * 128 * kv_bits // 8 + 256)
+    seq = torch.tensor([n], dtype=torch.int32)
+    kv = L.PagedKV(torch.zeros(shape, dtype=torch.uint8, device=dev), torch.zeros(shape, dtype=torch.uint8, device=dev),
+                   torch.zeros((pages, heads, 4, 2, 128), dtype=dtype, device=dev),
+                   torch.arange(pages, dtype=torch.int32, device=dev).reshape(1, -1), seq.to(dev), kv_bits=kv_bits)
+    desc = L.AttnDesc(heads * group, heads, [0, 0], dtype=dtype)
+    L.lserve_append_kv(desc, kv, k.to(dev), v.to(dev), torch.tensor([0, n], dtype=torch.int32, device=dev),
+                       torch.zeros(1, dtype=torch.int32, device=dev), n)
+    sel = torch.arange(pages, dtype=torch.int32).repeat(1, heads, 1)
+    cnt = torch.full((1, heads), pages, dtype=torch.int32)
+    out = torch.full((1, heads * group, 128), float("nan"), dtype=dtype, device=dev)
+    L.lserve_sparse_decode_noalloc(desc, kv, q.to(dev), sel.to(dev), cnt.to(dev), seq.to(dev), out, None)
+    torch.cuda.synchronize()
+    from test_gpu_quant import _values
+    ref, _ = oracle.sparse_decode_values(q, _values(kv.k_pool.cpu(), kv_bits), _values(kv.v_pool.cpu(), kv_bits),
+                                         torch.arange(pages, dtype=torch.int32).reshape(1, -1), seq, sel.numpy(), cnt.numpy(),
+                                         seq.numpy(), [0, 0], 64, 64)
+    ref = np.asarray(ref).reshape(heads * group, 128)
+    got = out.double().cpu().numpy().reshape(heads * group, 128)
+    assert np.isfinite(got).all()
+    # weights are rounded to fp16 (2^-11 relative), outputs to their type (2^-11 or 2^-8): the row bound of the other tests
+    rel = np.linalg.norm(got - ref, axis=1) / np.linalg.norm(ref, axis=1)
+    assert rel.max() <= 1e-2, rel.max()
