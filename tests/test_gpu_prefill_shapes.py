@@ -1,5 +1,6 @@
-"""Prefill launches of every shape the host chooses (one, two and four key slices, heads or query tiles as the units of a
-workgroup, blocks in order over the batch or per sequence), sampled rows against the oracle."""
+"""Prefill of prompts in every launch shape the host chooses (one, two and four key slices, heads or query tiles as the units
+of a workgroup, blocks in order over the batch or per sequence), sampled rows against the oracle.  Chunks over pages:
+test_gpu_paged_shapes.py."""
 import numpy as np
 import pytest
 import torch
@@ -66,21 +67,25 @@ def _check(w, lengths, pin, out, lse, ref, lse_ref, tok, what):
 
 
 @pytest.mark.parametrize("dtype", ["fp16", "bf16"])
-@pytest.mark.parametrize("heads,kv_heads,lengths", [
-    (8, 2, (65,)),                                # four slices, streaming heads folded too
-    (32, 8, (2047,)),                             # two slices, streaming heads in units of their own
-    (32, 8, (4097,)),                             # one slice, four heads of a group per workgroup
-    (8, 8, (4500, 1)),                            # no groups: query tiles as units, one-token sequence
-    (12, 4, (3000, 700)),                         # three heads per group: neither two nor four divide it
-    (16, 4, (1000, 1000, 1000)),                  # equal lengths are not searched
-    (12, 2, (1500, 333, 64)),                     # six: two heads and two query tiles
-    (64, 8, (1100, 77, 640)),                     # eight
-    (8, 2, tuple(3 + 17 * i for i in range(64))),  # the largest batch dealt out in order, one lane per sequence
-    (8, 2, tuple(5 + 16 * i for i in range(67))),  # a batch beyond that
+@pytest.mark.parametrize("heads,kv_heads,lengths,shape", [  # (slices, dense folded, streaming folded, units are query tiles)
+    (8, 2, (65,), (1, 0, 0, 1)),                    # walks of one or two tiles
+    (32, 8, (1500,), (2, 1, 1, 1)),
+    (32, 8, (2047,), (2, 1, 1, 0)),                 # two slices, streaming heads folded too
+    (32, 8, (4097,), (2, 1, 0, 0)),                 # streaming heads in units of their own
+    (8, 8, (4500, 1), (4, 1, 1, 0)),                # no groups; one-token sequence
+    (12, 4, (3000, 700), (4, 1, 1, 0)),             # three heads per group: neither two nor four divide it
+    (16, 4, (1000, 1000, 1000), (2, 1, 0, 0)),      # equal lengths are not searched
+    (12, 2, (1500, 333, 64), (4, 1, 1, 0)),         # six: two heads and two query tiles, where four units share a walk
+    (64, 8, (1100, 77, 640), (1, 0, 0, 0)),         # eight: four heads of a group per workgroup
+    (8, 2, tuple(3 + 17 * i for i in range(64)), (1, 0, 0, 0)),  # the largest batch dealt out in order, one lane per sequence
+    (8, 2, tuple(5 + 16 * i for i in range(67)), (1, 0, 0, 0)),  # a batch beyond that
 ])
-def test_prefill_launch_shapes(dtype, heads, kv_heads, lengths):
+def test_prefill_launch_shapes(dtype, heads, kv_heads, lengths, shape):
     w = Workload(name="ps", batch=len(lengths), num_q_heads=heads, num_kv_heads=kv_heads, dtype=dtype,
                  streaming_kv_heads=tuple(range(kv_heads // 2)), sink_tokens=64, local_tokens=192, seed=53)
+    import paper_2502_14866_amd as L
+    desc = L.AttnDesc(heads, kv_heads, w.streaming_flags(), dtype=w.torch_dtype, sink_tokens=64, local_tokens=192)
+    assert L.lserve_probe_prefill_shape(desc, len(lengths), sum(lengths), max(lengths)) == shape
     pin, out, lse, _ = _run(w, lengths)
     tok = _sample(lengths, 6 if len(lengths) > 8 else 24, 5)
     t, h = np.repeat(tok, heads), np.tile(np.arange(heads, dtype=np.int32), len(tok))
