@@ -192,10 +192,14 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return t.data_ptr()
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # private names: the public way where they are gone
+_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream) -> int:
     if stream is None:
-        if torch.cuda.is_initialized():
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        if _raw_stream and _device and torch.cuda.is_initialized():
+            return _raw_stream(_device())
         stream = torch.cuda.current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
