@@ -170,25 +170,50 @@ __device__ __forceinline__ void decode_work(const HeadClass& hc, int n, int xcd,
 // Sum over the wave of a value below 2^24 per lane and in total (exact in fp32).
 __device__ __forceinline__ int wave_count(int x) { return (int)rows4_sum(row16_sum((float)x)); }
 
+// Batches of up to kOrderedSeqs sequences are dealt out in one order, which a lane's registers hold: four sequences to a lane.
+// (Beyond, the blocks of each index follow one another sequence by sequence, gaps and all; up to 64, one to a lane, was too
+// few: 128 prompts of 20 .. 2500 tokens, 8 / 2 heads, took 432 us that way.)
+constexpr int kSeqGroups = 4, kOrderedSeqs = kSeqGroups * kWave;
+struct BlockSpans {
+    int lo[kSeqGroups], hi[kSeqGroups];  // blocks [lo, hi) of sequence 64 g + lane
+};
+
 // The rank-th query block of the batch, blocks ordered by their position inside their sequence, farthest first (the
-// longest walks start first and the short ones fill in behind them); false past the last one.  One lane per sequence
-// (batch <= 64) holds the blocks [lo, hi) its queries span.  Nothing is left out in this order, and that matters
+// longest walks start first and the short ones fill in behind them); false past the last one.
+// Nothing is left out in this order, and that matters
 // beyond the launches it saves: workgroups go to the shader engines of an XCD in strict turn, so an order with gaps
 // of a fixed stride (one long sequence among fifteen short ones, each block index of all sixteen in a row) puts the
 // real work of a launch on one of the four (sixteen prompts of 77 .. 3001 tokens: 745 us, in this order 214).
-__device__ __forceinline__ bool block_of(int rank, int lo, int hi, int batch, int& b, int& qblk) {
-    const int n = max(0, hi - lo);
+__device__ __forceinline__ bool block_of(int rank, const BlockSpans& s, int batch, int& b, int& qblk) {
+    // calls f(g, blocks of this lane's sequence) for every group in use
+    auto each = [&](auto f) {
+#pragma unroll
+        for (int g = 0; g < kSeqGroups; ++g)
+            if (g == 0 || g * kWave < batch) f(g, max(0, s.hi[g] - s.lo[g]));
+    };
     // All sequences alike: no search.
-    const int n_seq = __popcll(__ballot(n > 0)), lo0 = __builtin_amdgcn_readfirstlane(lo), hi0 = __builtin_amdgcn_readfirstlane(hi);
-    if (n_seq == batch && __ballot(n > 0 && (lo != lo0 || hi != hi0)) == 0) {
+    const int lo0 = __builtin_amdgcn_readfirstlane(s.lo[0]), hi0 = __builtin_amdgcn_readfirstlane(s.hi[0]);
+    int n_seq = 0, own = 0, top = 0;
+    unsigned long long unlike = 0;
+    each([&](int g, int n) {
+        n_seq += __popcll(__ballot(n > 0));
+        unlike |= __ballot(n > 0 && (s.lo[g] != lo0 || s.hi[g] != hi0));
+        own += n;
+        top = max(top, n > 0 ? s.hi[g] : 0);
+    });
+    if (n_seq == batch && unlike == 0) {
         const int level = rank / batch;
         b = rank - level * batch;
         qblk = hi0 - 1 - level;
         return qblk >= lo0;
     }
-    auto at_or_past = [&](int level) { return wave_count(min(max(hi - level, 0), n)); };
-    if (rank >= wave_count(n)) return false;
-    int below = 0, above = __builtin_amdgcn_readfirstlane((int)wave_max((float)(n > 0 ? hi : 0)));
+    auto at_or_past = [&](int level) {
+        int count = 0;
+        each([&](int g, int n) { count += min(max(s.hi[g] - level, 0), n); });
+        return wave_count(count);
+    };
+    if (rank >= wave_count(own)) return false;
+    int below = 0, above = __builtin_amdgcn_readfirstlane((int)wave_max((float)top));
     while (above - below > 1) {  // largest level with more than `rank` blocks at or past it
         const int mid = (below + above) / 2;
         if (at_or_past(mid) > rank)
@@ -196,11 +221,15 @@ __device__ __forceinline__ bool block_of(int rank, int lo, int hi, int batch, in
         else
             above = mid;
     }
-    const int i = rank - at_or_past(below + 1);
-    const bool member = lo <= below && below < hi;
-    const unsigned long long members = __ballot(member);
+    int i = rank - at_or_past(below + 1);
     const unsigned long long lower = (1ull << (threadIdx.x % kWave)) - 1ull;
-    b = __builtin_ctzll(__ballot(member && __popcll(members & lower) == i));
+    b = -1;
+    each([&](int g, int) {
+        const bool member = s.lo[g] <= below && below < s.hi[g];
+        const unsigned long long members = __ballot(member), hit = __ballot(member && __popcll(members & lower) == i);
+        if (b < 0 && hit) b = g * kWave + __builtin_ctzll(hit);
+        i -= __popcll(members);
+    });
     qblk = below;
     return true;
 }
@@ -321,18 +350,24 @@ __global__ __launch_bounds__(kPrefillThreads, 512 / kPrefillThreads) void sparse
     decode_work(second ? sched.cls[1] : sched.cls[0], lp.group / heads_per_block, xcd, li, hk, hg, rank);
     int b, qblk = 0;
     if (second ? sched.cls[1].ordered : sched.cls[0].ordered) {
-        const int i = min((int)(threadIdx.x % kWave), batch - 1);
-        const int fresh = cu_seqlens[i + 1] - cu_seqlens[i];
-        const int past = PAGED ? pg.kv.seq_lens[i] - (pg.k_new ? 0 : fresh) : 0;
-        const bool mine = (int)(threadIdx.x % kWave) < batch && fresh > 0;
         const int rows_log2 = kTileLog2 + qtiles_log2;
-        const int lo = past >> rows_log2, hi = mine ? ((past + fresh - 1) >> rows_log2) + 1 : 0;
+        BlockSpans spans;
+#pragma unroll
+        for (int g = 0; g < kSeqGroups; ++g) {
+            spans.lo[g] = spans.hi[g] = 0;
+            if (g > 0 && g * kWave >= batch) continue;
+            const int seq = g * kWave + threadIdx.x % kWave, i = min(seq, batch - 1);
+            const int fresh = cu_seqlens[i + 1] - cu_seqlens[i];
+            const int past = PAGED ? pg.kv.seq_lens[i] - (pg.k_new ? 0 : fresh) : 0;
+            spans.lo[g] = past >> rows_log2;
+            spans.hi[g] = seq < batch && fresh > 0 ? ((past + fresh - 1) >> rows_log2) + 1 : 0;
+        }
         if (batch == 1) {
             b = 0;
-            qblk = __builtin_amdgcn_readfirstlane(hi) - 1 - rank;
-            if (qblk < __builtin_amdgcn_readfirstlane(lo)) return;
+            qblk = __builtin_amdgcn_readfirstlane(spans.hi[0]) - 1 - rank;
+            if (qblk < __builtin_amdgcn_readfirstlane(spans.lo[0])) return;
         } else {
-            if (!block_of(rank, lo, hi, batch, b, qblk)) return;
+            if (!block_of(rank, spans, batch, b, qblk)) return;
             // Both come out of lane arithmetic.  Left in a vector register, the block's position takes the length of the walk,
             // the key tile of every step and the page look-ups there with it, and each branch on them runs under a mask of
             // lanes (a step of one slice 1.71 us, 1.65 with both in scalar registers: 512 tokens over 32768).
@@ -1181,7 +1216,7 @@ PrefillSchedule make_schedule(const LayerParams& lp, const PrefillShape& shape, 
         const int rows = kTile << hc.qtiles_log2;
         // rows that start anywhere inside a block reach into one block more than their number needs
         hc.blocks_per_seq = (max_rows + rows - 1) / rows + (any_start ? 1 : 0);
-        hc.ordered = batch <= kWave;  // one lane per sequence
+        hc.ordered = batch <= kOrderedSeqs;
         long long blocks = (long long)hc.blocks_per_seq * batch;
         // n rows fill floor(n / rows) blocks and touch at most one more, two more if they start anywhere
         if (hc.ordered) blocks = std::min(blocks, (long long)total_rows / rows + (any_start ? 2LL : 1LL) * batch);

@@ -77,8 +77,12 @@ def _check(w, lengths, pin, out, lse, ref, lse_ref, tok, what):
     (16, 4, (1000, 1000, 1000), (2, 1, 0, 0)),      # equal lengths are not searched
     (12, 2, (1500, 333, 64), (4, 1, 1, 0)),         # six: two heads and two query tiles, where four units share a walk
     (64, 8, (1100, 77, 640), (1, 0, 0, 0)),         # eight: four heads of a group per workgroup
-    (8, 2, tuple(3 + 17 * i for i in range(64)), (1, 0, 0, 0)),  # the largest batch dealt out in order, one lane per sequence
-    (8, 2, tuple(5 + 16 * i for i in range(67)), (1, 0, 0, 0)),  # a batch beyond that
+    (8, 2, tuple(3 + 17 * i for i in range(64)), (1, 0, 0, 0)),  # one sequence to every lane
+    (8, 2, tuple(5 + 16 * i for i in range(67)), (1, 0, 0, 0)),  # two to some
+    (4, 2, tuple(1 + (37 * i) % 400 for i in range(200)), (1, 0, 0, 0)),  # four to some
+    (4, 2, (130,) * 200, (1, 0, 0, 0)),                                   # and all alike
+    (4, 2, tuple(1 + (37 * i) % 300 for i in range(256)), (1, 0, 0, 0)),  # the largest batch dealt out in order
+    (4, 2, tuple(1 + (37 * i) % 300 for i in range(257)), (1, 0, 0, 0)),  # a batch beyond that
 ])
 def test_prefill_launch_shapes(dtype, heads, kv_heads, lengths, shape):
     w = Workload(name="ps", batch=len(lengths), num_q_heads=heads, num_kv_heads=kv_heads, dtype=dtype,
@@ -87,7 +91,7 @@ def test_prefill_launch_shapes(dtype, heads, kv_heads, lengths, shape):
     desc = L.AttnDesc(heads, kv_heads, w.streaming_flags(), dtype=w.torch_dtype, sink_tokens=64, local_tokens=192)
     assert L.lserve_probe_prefill_shape(desc, len(lengths), sum(lengths), max(lengths)) == shape
     pin, out, lse, _ = _run(w, lengths)
-    tok = _sample(lengths, 6 if len(lengths) > 8 else 24, 5)
+    tok = _sample(lengths, 1 if len(lengths) > 99 else 6 if len(lengths) > 8 else 24, 5)
     t, h = np.repeat(tok, heads), np.tile(np.arange(heads, dtype=np.int32), len(tok))
     ref, lse_ref = oracle.sparse_prefill_rows(pin.q, pin.k, pin.v, pin.cu_seqlens, w.streaming_flags(), 64, w.sink_tokens,
                                               w.local_tokens, t, h)
