@@ -721,7 +721,9 @@ __device__ __forceinline__ Folded fold_pieces(int list, int ja, int jb, int hh, 
 // Folds pieces j0 .. j1 of a list and writes its rows.  Called by all threads.  Up to eight pieces (the lists of a large
 // batch) are one round of loads by one thread per (query head, four channels).  A small batch cuts its lists into as many
 // as sixty: eight at a time they were seven rounds, one after the other (6 of the call's 15 us at one sequence of 4000
-// tokens); then the pieces are shared out over all threads, sixteen at a time, and met in shared memory.
+// tokens); then the pieces are shared out over all threads, sixteen at a time, and met in shared memory.  Pages of 128 tokens
+// make half as many pieces and fill the registers: sixteen at a time left room for one workgroup to a compute unit instead
+// of two (57 sequences of 290 .. 6691 tokens, 32 / 8 heads: 440 us for four steps, eight at a time 298).
 template <class T, int N, int NP>
 __device__ __forceinline__ void fold_list(DecodeShared<N, NP>& sm, int list, int j0, int j1, int H, int b, int hk,
                                           uint16_t* out, float* lse_out, const float* part_o, const float* part_ml) {
@@ -729,7 +731,7 @@ __device__ __forceinline__ void fold_list(DecodeShared<N, NP>& sm, int list, int
     const int item = threadIdx.x % kItems, part = threadIdx.x / kItems;
     const int hh = item / (kHeadDim / 4), ch = item % (kHeadDim / 4) * 4;
     Folded f;
-    if (j1 - j0 < 8) {
+    if (NP == 128 || j1 - j0 < 8) {
         if (part == 0) f = fold_pieces<N, 8>(list, j0, j1, hh, ch, part_o, part_ml);
     } else {
         const int share = (j1 - j0 + kParts) / kParts, ja = j0 + part * share;
@@ -950,9 +952,17 @@ __global__ __launch_bounds__(kDecodeThreads) void sparse_decode_kernel(
         if (todo == 0) continue;
         // Everything the page loop needs of an entry is worked out here, by its lane, for all entries at once: in the
         // loop the same arithmetic (a remainder by the head count, head ranks, 64-bit products) is a chain of scalar
-        // instructions per page.
+        // instructions per page.  Pages of 128 tokens are four times the work, and have no registers left for addresses.
         const uint4 *my_k, *my_v;
         slab_of(my_phys, hk, my_k, my_v);
+        auto slabs_of = [&](int idx, const uint4*& k, const uint4*& v) {
+            if constexpr (NP == 128) {
+                slab_of(__builtin_amdgcn_readlane(my_phys, idx), __builtin_amdgcn_readlane(my_list, idx) % lp.Hkv, k, v);
+            } else {
+                k = pointer_of_lane(my_k, idx);
+                v = pointer_of_lane(my_v, idx);
+            }
+        };
         const int my_left = my_L - my_pos * NP;  // tokens of the page below the sequence length (or more than a page)
         const unsigned long long outgrown = __ballot(my_valid && my_extra > 0);
         // The two workgroups of a compute unit take turns at the higher wave priority, page by page
@@ -967,17 +977,19 @@ __global__ __launch_bounds__(kDecodeThreads) void sparse_decode_kernel(
             // one page in flight behind the one being worked on
             Slabs<NP, BITS> cur, nxt;
             {
-                const int idx0 = __builtin_ctzll(todo);
-                load_k(cur, pointer_of_lane(my_k, idx0), tok0, lane, ~0u);
-                load_v(cur, pointer_of_lane(my_v, idx0), tok0, r, c, lane, ~0u);
+                const uint4 *k0, *v0;
+                slabs_of(__builtin_ctzll(todo), k0, v0);
+                load_k(cur, k0, tok0, lane, ~0u);
+                load_v(cur, v0, tok0, r, c, lane, ~0u);
             }
             while (todo) {
                 const int idx = __builtin_ctzll(todo);
                 todo &= todo - 1;
                 if (todo) {
-                    const int idx1 = __builtin_ctzll(todo);
-                    load_k(nxt, pointer_of_lane(my_k, idx1), tok0, lane, ~0u);
-                    load_v(nxt, pointer_of_lane(my_v, idx1), tok0, r, c, lane, ~0u);
+                    const uint4 *k1, *v1;
+                    slabs_of(__builtin_ctzll(todo), k1, v1);
+                    load_k(nxt, k1, tok0, lane, ~0u);
+                    load_v(nxt, v1, tok0, r, c, lane, ~0u);
                 }
                 take_turn();
                 LSERVE_DECODE_VISIT(idx, cur)
@@ -996,8 +1008,10 @@ __global__ __launch_bounds__(kDecodeThreads) void sparse_decode_kernel(
                 const unsigned live = ahead ? ~0u : 0u;
                 const int nx = ahead ? __builtin_ctzll(ahead) : current;
                 ahead &= ahead - 1;
-                load_k(dst, pointer_of_lane(my_k, nx), tok0, lane, live);
-                load_v(dst, pointer_of_lane(my_v, nx), tok0, r, c, lane, live);
+                const uint4 *k1, *v1;
+                slabs_of(nx, k1, v1);
+                load_k(dst, k1, tok0, lane, live);
+                load_v(dst, v1, tok0, r, c, lane, live);
             };
             constexpr int kStages = 2;
             Slabs<NP, BITS> stage[kStages];
