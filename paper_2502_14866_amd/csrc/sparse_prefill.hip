@@ -144,7 +144,7 @@ struct HeadClass {
     int fold;             // the key slices of the kernel share a unit (and are folded), or each group of waves has its own
     int blocks_per_seq;   // query blocks of the longest sequence
     int ordered;          // blocks are dealt out longest walk first over the whole batch (see block_of)
-    unsigned char kv_head[64];
+    unsigned kv_head[16];  // four to a word: a byte of its own is a vector load, one more trip to memory in a start
 };
 struct PrefillSchedule {
     HeadClass cls[2];  // dense, streaming
@@ -164,7 +164,7 @@ __device__ __forceinline__ void decode_work(const HeadClass& hc, int n, int xcd,
         hidx = (t / n) % hc.heads;
         rank = t / (n * hc.heads);
     }
-    hk = hc.kv_head[hidx];
+    hk = (int)(hc.kv_head[hidx / 4] >> (8 * (hidx % 4))) & 0xff;
 }
 
 // Sum over the wave of a value below 2^24 per lane and in total (exact in fp32).
@@ -1221,8 +1221,12 @@ PrefillSchedule make_schedule(const LayerParams& lp, const PrefillShape& shape, 
         // n rows fill floor(n / rows) blocks and touch at most one more, two more if they start anywhere
         if (hc.ordered) blocks = std::min(blocks, (long long)total_rows / rows + (any_start ? 2LL : 1LL) * batch);
         hc.heads = 0;
+        for (unsigned& w : hc.kv_head) w = 0;
         for (int hk = 0; hk < lp.Hkv; ++hk)
-            if ((int)((lp.streaming_mask >> hk) & 1ull) == c) hc.kv_head[hc.heads++] = (unsigned char)hk;
+            if ((int)((lp.streaming_mask >> hk) & 1ull) == c) {
+                hc.kv_head[hc.heads / 4] |= (unsigned)hk << (8 * (hc.heads % 4));
+                ++hc.heads;
+            }
         hc.swizzled = hc.heads > 0 && kXcds % hc.heads == 0;
         hc.slices = hc.swizzled ? kXcds / hc.heads : 1;
         const int per_block = lp.group / heads;
