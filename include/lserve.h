@@ -231,6 +231,13 @@ int lserve_select_pages(const lserve_attn_desc *desc, const lserve_paged_kv *kv,
  *   workspace    unused: lserve_workspace_bytes(LSERVE_CALL_SPARSE_PREFILL, ...) is 0 (Q, K and V are read where
  *                they are); NULL is accepted
  * Requires desc->page_size == 64 (the mask tile).
+ *
+ * Bits of the results, here and in the two calls over a paged cache below.  The same call on the same data gives the same
+ * bits.  How a launch shares out the keys of a row is chosen from the sizes of the whole call (heads, batch, total_tokens,
+ * max_seqlen; over a cache also max_pages_per_seq, max_seqlen and kv_bits) and the compute units of the device, and the
+ * sums of a row are taken in that order: a row computed next to other sequences, in other chunks or through another of the
+ * three calls agrees within the rounding of its type, and bit for bit where lserve_probe_prefill_shape names one shape for
+ * both.
  */
 int lserve_sparse_prefill(const lserve_attn_desc *desc, const void *q, const void *k, const void *v,
                           const int32_t *cu_seqlens, int32_t batch, int32_t total_tokens,
@@ -243,12 +250,13 @@ int lserve_sparse_prefill(const lserve_attn_desc *desc, const void *q, const voi
  * kv; sequence b has L_b = kv->seq_lens[b] tokens and the chunk is its last n_b = cu_q[b+1] - cu_q[b]
  * tokens, so query j sits at position t = L_b - n_b + j and attends the positions u <= t that the analytic
  * mask of `desc` allows, tiles counted from position 0.  With n_b = L_b this equals lserve_sparse_prefill on
- * the same tokens; with n_b = 1 it equals a decode step with nothing left out for dense heads.
+ * the same tokens (see there for what differs by rounding); with n_b = 1 it equals a decode step with nothing left out for dense heads.
  *
  *   kv           one pool holding every KV head (pool_heads 0 or Hkv, no streaming pool), N_P = 64;
  *                stats are not used
  *   q            device [total_new][H][D], cu_q device [batch + 1] (batch = kv->batch), n_b >= 0
- *   max_new_per_seq  host bound of n_b (> 0); max_seqlen host bound of L_b
+ *   max_new_per_seq  host bound of n_b (> 0); max_seqlen host bound of L_b (the launch is laid out for walks of up to
+ *                this length, or of max_pages_per_seq where that is shorter: a bound far too wide costs time)
  *   out          device [total_new][H][D]; lse_out device [H][total_new] fp32 or NULL
  *   workspace    unused: lserve_paged_prefill_workspace_bytes() is 0 (keys and values are read from the pages as
  *                they are); NULL is accepted
@@ -268,14 +276,16 @@ size_t lserve_paged_prefill_workspace_bytes(const lserve_attn_desc *desc, int32_
  * new tokens whose Q, K and V arrive contiguously.  Query j sits at position t = S_b + j and attends the positions
  * u <= t that the analytic mask of `desc` allows, tiles counted from position 0: keys u < S_b are read from the cache,
  * keys u >= S_b from k_new / v_new.  Nothing is written to the cache: call lserve_append_kv with the same k_new, v_new,
- * cu_new (and start_pos = the lengths) afterwards.  With S_b = 0 everywhere this equals lserve_sparse_prefill.
+ * cu_new (and start_pos = the lengths) afterwards.  With S_b = 0 everywhere this equals lserve_sparse_prefill (see
+ * there for what differs by rounding).  The lengths of the histories are not known on the host: the launch is laid out
+ * for histories of up to max_pages_per_seq pages.
  *
  *   kv           the history, N_P = 64: one pool holding every KV head, or the two-way cache (dense heads in the
  *                main pool, streaming heads in their ring: the ring of a sequence of S_b tokens holds the sink pages
  *                and the last w pages, which is every history key a streaming query of the chunk may attend; the keys
  *                between come from the chunk itself).  Pages of 16-bit rows or quantised pages (kv_bits 8 or 4): a
- *                history key / value is then the number its code stands for, code * scale + zero, computed in fp32
- *                and rounded to the layer's 16-bit type on its way to the matrix cores.  stats are not used.
+ *                history key / value is then the number its code stands for, code * scale + zero, rounded once to
+ *                fp16, or computed in fp32 and rounded to bf16, on its way to the matrix cores.  stats are not used.
  *   q            device [total_new][H][D]; k_new, v_new device [total_new][Hkv][D]
  *   cu_new       device [batch + 1] (batch = kv->batch), cu_new[0] = 0, n_b >= 0
  *   max_new_per_seq  host bound of n_b (> 0)

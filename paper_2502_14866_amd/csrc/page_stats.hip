@@ -97,7 +97,8 @@ __device__ __forceinline__ void quantize_row(const uint4& x, uint32_t (&c)[8], u
     // code = rint of the fp32 quotient.  An IEEE division is some ten instructions, and eight of them per lane and row were
     // most of the write-back of quantised pages.  The product with the reciprocal is within 3 units in the last place of
     // the quotient, which for quotients up to 256 is less than 1e-4, so the two round to the same whole number unless the
-    // product lies that close to a half; those lanes (two in ten thousand) divide.
+    // product lies that close to a half.  That is two quotients in ten thousand, one lane in 600 (of eight quotients) and
+    // one wavefront in ten (of 512), which then divides.
     const float inv = __builtin_amdgcn_rcpf(scale);
     float t[8];
     bool close = false;

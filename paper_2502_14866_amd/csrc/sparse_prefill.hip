@@ -235,8 +235,10 @@ __device__ __forceinline__ bool block_of(int rank, const BlockSpans& s, int batc
 }
 
 // General block mask (Sec. 3.1, Sec. 3.4): per mask and query tile, the ascending list of kept key
-// tiles.  A workgroup owns four query tiles; a pre-pass merges their rows into one ascending list of
-// (key tile, which of the four query tiles keep it) so that the main loop walks a single list.
+// tiles.  A workgroup of one slice owns four query tiles; a pre-pass merges their rows into one ascending list of
+// (key tile, which of the four query tiles keep it) so that the main loop walks a single list.  A workgroup of four
+// slices owns one query tile and walks the caller's row as it is (see choose_sliced_rows); the last three members are
+// then not used.
 struct PrefillMask {
     const int* head_mask;     // [H]: mask of query head h, -1 = analytic mask of the layer description
     const int* q_tile_start;  // [batch + 1]: first row of sequence b inside one mask
@@ -296,7 +298,8 @@ enum PrefillMode { kPlain = 0, kMasked = 1, kPaged = 2 };
 
 // BITS: width of the rows in the pages (16, or 8 / 4 for quantised pages, kPaged only).  Quantised tiles cannot take
 // the direct-to-LDS path: their codes travel through registers, are turned into the layer's 16-bit type as
-// code * scale + zero (fp32, then rounded) and are stored to the same LDS places the direct loads would fill.
+// code * scale + zero (fp16: rounded once; bf16: fp32, then rounded) and are stored to the same LDS places the direct loads
+// would fill.
 //
 // SL: key slices.  The four wavefront pairs of a workgroup are (query heads) x (query tiles) x (key slices): with
 // one slice all pairs walk the same key tiles; with two or four, slice s of a unit takes every SL-th tile of the walk
