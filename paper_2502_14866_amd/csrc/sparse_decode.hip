@@ -402,10 +402,8 @@ __device__ __forceinline__ void quantised_quarter_page(WaveState<N, BITS>& st, f
         st.z[j] = __builtin_fmaf(p, v_zero, st.z[j]);
         w[j] = p * v_scale;
     }
-    float w_max = w[0];
-#pragma unroll
-    for (int j = 1; j < HPL; ++j) w_max = fmaxf(w_max, w[j]);
-    if (__any(w_max > kMaxWeight)) {  // hardly ever: a value row of a very large scale
+    // Hardly ever: a value row of a very large scale (known before the weights are), and a weight for it that does not fit.
+    if (__any(v_scale > kMaxWeight) && __any(HPL == 1 ? w[0] > kMaxWeight : fmaxf(w[0], w[HPL - 1]) > kMaxWeight)) {
         const float down = 1.f / kWeightScale;  // (a second time cannot be: without the factor every weight fits)
         st.weight_scale = 1.f;
 #pragma unroll
