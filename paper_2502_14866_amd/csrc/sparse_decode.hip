@@ -336,7 +336,7 @@ typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 // they meet the codes, and cross lanes through LDS; the denominator keeps the unrounded weights.
 // The instruction count, not the memory system, bounds this path (a page is half or a quarter of the bytes for the same
 // number of tokens): with packed dot products it took about 215 vector instructions per quarter page and four heads, now
-// about 90.  64 sequences of 9K .. 24K tokens, 32 / 8 heads, 4096-token budget: 60.0 -> 39 us over 4-bit pages, 65.3 ->
+// about 90.  64 sequences of 9K .. 24K tokens, 32 / 8 heads, 4096-token budget: 60.0 -> 40 us over 4-bit pages, 65.3 ->
 // 58 us over 8-bit ones (324 MB: 5.6 TB/s); eight heads per group at batch 16: 31.7 -> 19.6 and 40.1 -> 21.9 us.
 // p_lds is read as fp16 [heads][16 tokens].
 template <int N, int BITS>
