@@ -234,10 +234,10 @@ int lserve_select_pages(const lserve_attn_desc *desc, const lserve_paged_kv *kv,
  *
  * Bits of the results, here and in the two calls over a paged cache below.  The same call on the same data gives the same
  * bits.  How a launch shares out the keys of a row is chosen from the sizes of the whole call (heads, batch, total_tokens,
- * max_seqlen; over a cache also max_pages_per_seq, max_seqlen and kv_bits) and the compute units of the device, and the
- * sums of a row are taken in that order: a row computed next to other sequences, in other chunks or through another of the
- * three calls agrees within the rounding of its type, and bit for bit where lserve_probe_prefill_shape names one shape for
- * both.
+ * max_seqlen; over a cache also max_pages_per_seq, max_seqlen and kv_bits), the scratch and the compute units of the device,
+ * and the sums of a row are taken in that order: a row computed next to other sequences, in other chunks or through another
+ * of the three calls agrees within the rounding of its type, and bit for bit where lserve_probe_prefill_shape names one
+ * shape for both and neither had scratch.
  */
 int lserve_sparse_prefill(const lserve_attn_desc *desc, const void *q, const void *k, const void *v,
                           const int32_t *cu_seqlens, int32_t batch, int32_t total_tokens,
@@ -258,8 +258,9 @@ int lserve_sparse_prefill(const lserve_attn_desc *desc, const void *q, const voi
  *   max_new_per_seq  host bound of n_b (> 0); max_seqlen host bound of L_b (the launch is laid out for walks of up to
  *                this length, or of max_pages_per_seq where that is shorter: a bound far too wide costs time)
  *   out          device [total_new][H][D]; lse_out device [H][total_new] fp32 or NULL
- *   workspace    unused: lserve_paged_prefill_workspace_bytes() is 0 (keys and values are read from the pages as
- *                they are); NULL is accepted
+ *   workspace    none needed: lserve_paged_prefill_workspace_bytes() is 0 (keys and values are read from the pages as
+ *                they are), NULL is accepted.  With lserve_chunk_scratch_bytes(...) or more, of any contents, a chunk over
+ *                a long history is shared out over more of the chip
  */
 int lserve_sparse_prefill_paged(const lserve_attn_desc *desc, const lserve_paged_kv *kv, const void *q,
                                 const int32_t *cu_q, int32_t total_new, int32_t max_new_per_seq,
@@ -295,6 +296,22 @@ size_t lserve_paged_prefill_workspace_bytes(const lserve_attn_desc *desc, int32_
 int lserve_sparse_prefill_chunk(const lserve_attn_desc *desc, const lserve_paged_kv *kv, const void *q,
                                 const void *k_new, const void *v_new, const int32_t *cu_new, int32_t total_new,
                                 int32_t max_new_per_seq, void *out, float *lse_out, void *stream);
+
+/* The same with scratch of lserve_chunk_scratch_bytes(...) (device, any contents; NULL or less: done without). */
+int lserve_sparse_prefill_chunk_scratch(const lserve_attn_desc *desc, const lserve_paged_kv *kv, const void *q,
+                                        const void *k_new, const void *v_new, const int32_t *cu_new,
+                                        int32_t total_new, int32_t max_new_per_seq, void *out, float *lse_out,
+                                        void *scratch, size_t scratch_bytes, void *stream);
+
+/*
+ * Bytes of scratch with which chunks of these sizes are quicker; 0: none, also on invalid arguments.  Few query rows over a
+ * long history leave most of the chip idle; with scratch the walks over the history are cut into pieces that a workgroup each
+ * works on, and a second kernel puts the pieces together.
+ *   total_new, max_new_per_seq: as in the call
+ *   pages      width of the page table; for lserve_sparse_prefill_paged min(width, ceil(max_seqlen / 64))
+ */
+size_t lserve_chunk_scratch_bytes(const lserve_attn_desc *desc, int32_t batch, int32_t total_new, int32_t max_new_per_seq,
+                                  int32_t pages, int32_t kv_bits);
 
 /*
  * Block-sparse prefill under a general block mask (Sec. 3.1: every tile of the attention map is skipped or

@@ -27,6 +27,8 @@ EXPORTED_SYMBOLS = (
     "lserve_sparse_prefill_masked",
     "lserve_sparse_prefill_paged",
     "lserve_sparse_prefill_chunk",
+    "lserve_sparse_prefill_chunk_scratch",
+    "lserve_chunk_scratch_bytes",
     "lserve_paged_prefill_workspace_bytes",
     "lserve_masked_prefill_workspace_bytes",
     "BlockMask",
@@ -105,6 +107,10 @@ def load_library():
         lib.lserve_sparse_prefill_paged.restype = ctypes.c_int
         lib.lserve_sparse_prefill_chunk.argtypes = [dp, kp, vp, vp, vp, vp, i32, i32, vp, vp, vp]
         lib.lserve_sparse_prefill_chunk.restype = ctypes.c_int
+        lib.lserve_sparse_prefill_chunk_scratch.argtypes = [dp, kp, vp, vp, vp, vp, i32, i32, vp, vp, vp, sz, vp]
+        lib.lserve_sparse_prefill_chunk_scratch.restype = ctypes.c_int
+        lib.lserve_chunk_scratch_bytes.argtypes = [dp, i32, i32, i32, i32, i32]
+        lib.lserve_chunk_scratch_bytes.restype = sz
         lib.lserve_paged_prefill_workspace_bytes.argtypes = [dp, i32, i32]
         lib.lserve_paged_prefill_workspace_bytes.restype = ctypes.c_size_t
         lib.lserve_workspace_bytes.argtypes = [ctypes.c_int, dp, i32, i32, i32, i32]
@@ -250,6 +256,26 @@ def lserve_select_pages(desc: AttnDesc, kv: PagedKV, q: torch.Tensor, budget_tok
                                               _ptr(workspace), ws_bytes, _stream(stream)), "lserve_select_pages")
 
 
+def lserve_chunk_scratch_bytes(desc: AttnDesc, batch: int, total_new: int, max_new_per_seq: int, pages: int,
+                               kv_bits: int = 16) -> int:
+    return int(load_library().lserve_chunk_scratch_bytes(desc.c(), batch, total_new, max_new_per_seq, pages, kv_bits))
+
+
+def _chunk_scratch(desc: AttnDesc, q: torch.Tensor, batch: int, max_new_per_seq: int, pages: int, kv_bits: int,
+                   stream) -> Optional[torch.Tensor]:
+    """Scratch for a call on chunks, from torch's allocator, which hands freed memory on in the order of the stream it was
+    taken on: only for calls on the current stream, and not under capture, where an allocation may not be allowed."""
+    if stream is not None or not q.is_cuda:
+        return None
+    need = lserve_chunk_scratch_bytes(desc, batch, q.shape[0], max_new_per_seq, pages, kv_bits)
+    if need == 0 or torch.cuda.is_current_stream_capturing():
+        return None
+    try:
+        return torch.empty((need,), dtype=torch.uint8, device=q.device)
+    except torch.cuda.OutOfMemoryError:
+        return None
+
+
 def lserve_sparse_prefill(desc: AttnDesc, q: torch.Tensor, k: torch.Tensor, v: torch.Tensor,
                           cu_seqlens: torch.Tensor, max_seqlen: int, out: torch.Tensor,
                           lse_out: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None,
@@ -307,6 +333,9 @@ def lserve_sparse_prefill_paged(desc: AttnDesc, kv: PagedKV, q: torch.Tensor, cu
                                 max_new_per_seq: int, max_seqlen: int, out: torch.Tensor,
                                 lse_out: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None,
                                 stream=None) -> None:
+    if workspace is None and max_seqlen > 0:
+        pages = min(kv.page_table.shape[1], (max_seqlen - 1) // 64 + 1)
+        workspace = _chunk_scratch(desc, q, cu_q.shape[0] - 1, max_new_per_seq, pages, 16, stream)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(load_library().lserve_sparse_prefill_paged(desc.c(), kv.c(), _ptr(q), _ptr(cu_q), q.shape[0],
                                                       max_new_per_seq, max_seqlen, _ptr(out), _ptr(lse_out),
@@ -317,9 +346,11 @@ def lserve_sparse_prefill_paged(desc: AttnDesc, kv: PagedKV, q: torch.Tensor, cu
 def lserve_sparse_prefill_chunk(desc: AttnDesc, kv: PagedKV, q: torch.Tensor, k_new: torch.Tensor, v_new: torch.Tensor,
                                 cu_new: torch.Tensor, max_new_per_seq: int, out: torch.Tensor,
                                 lse_out: Optional[torch.Tensor] = None, stream=None) -> None:
-    _check(load_library().lserve_sparse_prefill_chunk(desc.c(), kv.c(), _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(cu_new),
-                                                      q.shape[0], max_new_per_seq, _ptr(out), _ptr(lse_out),
-                                                      _stream(stream)), "lserve_sparse_prefill_chunk")
+    scratch = _chunk_scratch(desc, q, cu_new.shape[0] - 1, max_new_per_seq, kv.page_table.shape[1], kv.kv_bits, stream)
+    _check(load_library().lserve_sparse_prefill_chunk_scratch(
+        desc.c(), kv.c(), _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(cu_new), q.shape[0], max_new_per_seq, _ptr(out),
+        _ptr(lse_out), _ptr(scratch), 0 if scratch is None else scratch.numel(), _stream(stream)),
+        "lserve_sparse_prefill_chunk")
 
 
 def lserve_sparse_decode(desc: AttnDesc, kv: PagedKV, q: torch.Tensor, sel_pages: Optional[torch.Tensor],

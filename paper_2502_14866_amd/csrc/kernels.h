@@ -30,13 +30,16 @@ int num_compute_units();
 // of prompts with pages = 0, else of chunks whose sequences have up to `pages` pages of keys.
 void prefill_shape(const LayerParams& lp, int batch, int total_rows, int max_rows, int pages, int kv_bits, int (&out)[4]);
 
+// Scratch with which a launch of chunks is quicker (dense walks in pieces); 0: none.  `pages` as above.
+size_t chunk_scratch_bytes(const LayerParams& lp, int batch, int total_rows, int max_rows, int pages, int kv_bits);
+
 size_t paged_prefill_workspace_bytes(const LayerParams& lp, int batch, int max_pages);
 // k_new / v_new: the chunk's own K / V when they have not been written back yet (the cache is then the chunk's
 // history), or null when the cache already holds the chunk.
 hipError_t launch_sparse_prefill_paged(int dtype, const LayerParams& lp, const PagedParams& kv, const void* q,
                                        const void* k_new, const void* v_new, const int* cu_q, int total_new,
                                        int max_new_per_seq, int max_seqlen, void* out, float* lse_out, void* workspace,
-                                       hipStream_t stream);
+                                       size_t workspace_bytes, hipStream_t stream);
 
 size_t decode_workspace_bytes(const LayerParams& lp, int batch, int sel_stride);
 

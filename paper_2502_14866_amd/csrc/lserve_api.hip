@@ -282,13 +282,21 @@ int lserve_sparse_prefill_paged(const lserve_attn_desc* desc, const lserve_paged
     const size_t need = paged_prefill_workspace_bytes(lp, pp.batch, pp.max_pages);
     if (need > 0 && (!workspace || workspace_bytes < need)) return LSERVE_ERR_WORKSPACE;
     hipError_t e = launch_sparse_prefill_paged(desc->dtype, lp, pp, q, nullptr, nullptr, cu_q, total_new, max_new_per_seq,
-                                               max_seqlen, out, lse_out, workspace, (hipStream_t)stream);
+                                               max_seqlen, out, lse_out, workspace, workspace_bytes, (hipStream_t)stream);
     return e == hipSuccess ? LSERVE_OK : fail_hip(e);
 }
 
 int lserve_sparse_prefill_chunk(const lserve_attn_desc* desc, const lserve_paged_kv* kv, const void* q, const void* k_new,
                                 const void* v_new, const int32_t* cu_new, int32_t total_new, int32_t max_new_per_seq,
                                 void* out, float* lse_out, void* stream) {
+    return lserve_sparse_prefill_chunk_scratch(desc, kv, q, k_new, v_new, cu_new, total_new, max_new_per_seq, out, lse_out,
+                                               nullptr, 0, stream);
+}
+
+int lserve_sparse_prefill_chunk_scratch(const lserve_attn_desc* desc, const lserve_paged_kv* kv, const void* q,
+                                        const void* k_new, const void* v_new, const int32_t* cu_new, int32_t total_new,
+                                        int32_t max_new_per_seq, void* out, float* lse_out, void* scratch,
+                                        size_t scratch_bytes, void* stream) {
     LayerParams lp;
     PagedParams pp;
     int rc = make_layer(desc, &lp);
@@ -299,11 +307,19 @@ int lserve_sparse_prefill_chunk(const lserve_attn_desc* desc, const lserve_paged
     if (!q || !k_new || !v_new || !cu_new || !out) return LSERVE_ERR_INVALID_ARG;
     if (total_new <= 0 || max_new_per_seq <= 0 || max_new_per_seq > total_new) return LSERVE_ERR_INVALID_ARG;
     if (!aligned16(q) || !aligned16(k_new) || !aligned16(v_new) || !aligned16(cu_new) || !aligned16(out) ||
-        !aligned16(lse_out))
+        !aligned16(lse_out) || !aligned16(scratch))
         return LSERVE_ERR_INVALID_ARG;
     hipError_t e = launch_sparse_prefill_paged(desc->dtype, lp, pp, q, k_new, v_new, cu_new, total_new, max_new_per_seq, 0,
-                                               out, lse_out, nullptr, (hipStream_t)stream);
+                                               out, lse_out, scratch, scratch_bytes, (hipStream_t)stream);
     return e == hipSuccess ? LSERVE_OK : fail_hip(e);
+}
+
+size_t lserve_chunk_scratch_bytes(const lserve_attn_desc* desc, int32_t batch, int32_t total_new, int32_t max_new_per_seq,
+                                  int32_t pages, int32_t kv_bits) {
+    LayerParams lp;
+    if (make_layer(desc, &lp) != LSERVE_OK || lp.NP != 64) return 0;
+    if (batch <= 0 || total_new <= 0 || max_new_per_seq <= 0 || max_new_per_seq > total_new || pages <= 0) return 0;
+    return chunk_scratch_bytes(lp, batch, total_new, max_new_per_seq, pages, kv_bits == 0 ? 16 : kv_bits);
 }
 
 int lserve_probe_prefill_shape(const lserve_attn_desc* desc, int32_t batch, int32_t total_rows, int32_t max_rows, int32_t pages,

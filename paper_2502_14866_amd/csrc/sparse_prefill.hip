@@ -143,17 +143,23 @@ struct HeadClass {
     int qtiles_log2;      // log2 of the query tiles a workgroup owns
     int fold;             // the key slices of the kernel share a unit (and are folded), or each group of waves has its own
     int blocks_per_seq;   // query blocks of the longest sequence
+    int blocks;           // query blocks of the batch, at most
     int ordered;          // blocks are dealt out longest walk first over the whole batch (see block_of)
     unsigned kv_head[16];  // four to a word: a byte of its own is a vector load, one more trip to memory in a start
 };
+// Dense walks cut into pieces (see PiecePlan); partials is null where blocks are whole.
+struct PrefillPieces {
+    float* partials;  // kPieceFloats for every piece, pieces of a (KV head, group of query heads) next to each other
+    int target;       // pieces of a (KV head, group of query heads) in the launch, at most
+};
 struct PrefillSchedule {
     HeadClass cls[2];  // dense, streaming
+    PrefillPieces pieces;
 };
 
-// Decodes workgroup `li` of XCD `xcd` inside a class of workgroups, `n` of them per (KV head, query block): KV head hk,
-// group of query heads hg, and the position of the query block in the order of blocks.
-__device__ __forceinline__ void decode_work(const HeadClass& hc, int n, int xcd, int li, int& hk, int& hg, int& rank) {
-    int hidx;
+// Decodes workgroup `li` of XCD `xcd` inside a class of workgroups, `n` of them per (KV head, query block): KV head hk (the
+// hidx-th of its class), group of query heads hg, and the position of the query block in the order of blocks.
+__device__ __forceinline__ void decode_work(const HeadClass& hc, int n, int xcd, int li, int& hidx, int& hk, int& hg, int& rank) {
     if (hc.swizzled) {
         hidx = xcd % hc.heads;
         hg = li % n;
@@ -168,7 +174,7 @@ __device__ __forceinline__ void decode_work(const HeadClass& hc, int n, int xcd,
 }
 
 // Sum over the wave of a value below 2^24 per lane and in total (exact in fp32).
-__device__ __forceinline__ int wave_count(int x) { return (int)rows4_sum(row16_sum((float)x)); }
+__device__ __forceinline__ int wave_count(int x) { return __builtin_amdgcn_readfirstlane((int)rows4_sum(row16_sum((float)x))); }
 
 // Batches of up to kOrderedSeqs sequences are dealt out in one order, which a lane's registers hold: four sequences to a lane.
 // (Beyond, the blocks of each index follow one another sequence by sequence, gaps and all; up to 64, one to a lane, was too
@@ -178,61 +184,175 @@ struct BlockSpans {
     int lo[kSeqGroups], hi[kSeqGroups];  // blocks [lo, hi) of sequence 64 g + lane
 };
 
-// The rank-th query block of the batch, blocks ordered by their position inside their sequence, farthest first (the
-// longest walks start first and the short ones fill in behind them); false past the last one.
+// The query blocks of a batch, ordered by their position inside their sequence, farthest first (the
+// longest walks start first and the short ones fill in behind them).
 // Nothing is left out in this order, and that matters
 // beyond the launches it saves: workgroups go to the shader engines of an XCD in strict turn, so an order with gaps
 // of a fixed stride (one long sequence among fifteen short ones, each block index of all sixteen in a row) puts the
 // real work of a launch on one of the four (sixteen prompts of 77 .. 3001 tokens: 745 us, in this order 214).
-__device__ __forceinline__ bool block_of(int rank, const BlockSpans& s, int batch, int& b, int& qblk) {
+struct BlockOrder {
+    BlockSpans s;
+    int batch, lo0, hi0;  // blocks of the first sequence
+    bool alike;           // and of every other
+
     // calls f(g, blocks of this lane's sequence) for every group in use
-    auto each = [&](auto f) {
+    template <class F> __device__ __forceinline__ void each(F f) const {
 #pragma unroll
         for (int g = 0; g < kSeqGroups; ++g)
             if (g == 0 || g * kWave < batch) f(g, max(0, s.hi[g] - s.lo[g]));
-    };
-    // All sequences alike: no search.
-    const int lo0 = __builtin_amdgcn_readfirstlane(s.lo[0]), hi0 = __builtin_amdgcn_readfirstlane(s.hi[0]);
-    int n_seq = 0, own = 0, top = 0;
-    unsigned long long unlike = 0;
-    each([&](int g, int n) {
-        n_seq += __popcll(__ballot(n > 0));
-        unlike |= __ballot(n > 0 && (s.lo[g] != lo0 || s.hi[g] != hi0));
-        own += n;
-        top = max(top, n > 0 ? s.hi[g] : 0);
-    });
-    if (n_seq == batch && unlike == 0) {
-        const int level = rank / batch;
-        b = rank - level * batch;
-        qblk = hi0 - 1 - level;
-        return qblk >= lo0;
     }
-    auto at_or_past = [&](int level) {
+    // blocks of the batch at position `level` of their sequence or past it
+    __device__ __forceinline__ int at_or_past(int level) const {
+        if (alike) return batch * max(0, hi0 - max(lo0, level));
         int count = 0;
         each([&](int g, int n) { count += min(max(s.hi[g] - level, 0), n); });
         return wave_count(count);
-    };
-    if (rank >= wave_count(own)) return false;
-    int below = 0, above = __builtin_amdgcn_readfirstlane((int)wave_max((float)top));
-    while (above - below > 1) {  // largest level with more than `rank` blocks at or past it
-        const int mid = (below + above) / 2;
-        if (at_or_past(mid) > rank)
-            below = mid;
-        else
-            above = mid;
     }
-    int i = rank - at_or_past(below + 1);
-    const unsigned long long lower = (1ull << (threadIdx.x % kWave)) - 1ull;
-    b = -1;
-    each([&](int g, int) {
-        const bool member = s.lo[g] <= below && below < s.hi[g];
-        const unsigned long long members = __ballot(member), hit = __ballot(member && __popcll(members & lower) == i);
-        if (b < 0 && hit) b = g * kWave + __builtin_ctzll(hit);
-        i -= __popcll(members);
-    });
-    qblk = below;
-    return true;
+    // past the last block of any sequence
+    __device__ __forceinline__ int top() const {
+        if (alike) return hi0;
+        int t = 0;
+        each([&](int g, int n) { t = max(t, n > 0 ? s.hi[g] : 0); });
+        return __builtin_amdgcn_readfirstlane((int)wave_max((float)t));
+    }
+    // The rank-th block of the batch; false past the last one.
+    __device__ __forceinline__ bool find(int rank, int& b, int& qblk) const {
+        if (alike) {
+            const int level = batch == 1 ? rank : rank / batch;
+            b = rank - level * batch;
+            qblk = hi0 - 1 - level;
+            return qblk >= lo0;
+        }
+        if (rank >= at_or_past(0)) return false;
+        int below = 0, above = top();
+        while (above - below > 1) {  // largest level with more than `rank` blocks at or past it
+            const int mid = (below + above) / 2;
+            if (at_or_past(mid) > rank)
+                below = mid;
+            else
+                above = mid;
+        }
+        int i = rank - at_or_past(below + 1);
+        const unsigned long long lower = (1ull << (threadIdx.x % kWave)) - 1ull;
+        int found = -1;
+        each([&](int g, int) {
+            const bool member = s.lo[g] <= below && below < s.hi[g];
+            const unsigned long long members = __ballot(member), hit = __ballot(member && __popcll(members & lower) == i);
+            if (found < 0 && hit) found = g * kWave + __builtin_ctzll(hit);
+            i -= __popcll(members);
+        });
+        b = found;
+        qblk = below;
+        return true;
+    }
+};
+
+// seq_lens: tokens in the pages, or null without pages; alongside: the batch's new tokens are not among them yet.
+__device__ __forceinline__ BlockOrder block_order(const int* cu_seqlens, const int* seq_lens, bool alongside, int batch, int rows_log2) {
+    BlockOrder o;
+    o.batch = batch;
+#pragma unroll
+    for (int g = 0; g < kSeqGroups; ++g) {
+        o.s.lo[g] = o.s.hi[g] = 0;
+        if (g > 0 && g * kWave >= batch) continue;
+        const int seq = g * kWave + threadIdx.x % kWave, i = min(seq, batch - 1);
+        const int fresh = cu_seqlens[i + 1] - cu_seqlens[i];
+        const int past = seq_lens ? seq_lens[i] - (alongside ? 0 : fresh) : 0;
+        o.s.lo[g] = past >> rows_log2;
+        o.s.hi[g] = seq < batch && fresh > 0 ? ((past + fresh - 1) >> rows_log2) + 1 : 0;
+    }
+    o.lo0 = __builtin_amdgcn_readfirstlane(o.s.lo[0]);
+    o.hi0 = __builtin_amdgcn_readfirstlane(o.s.hi[0]);
+    o.alike = true;
+    if (batch > 1) {  // all sequences alike: no search
+        int n_seq = 0;
+        unsigned long long unlike = 0;
+        o.each([&](int g, int n) {
+            n_seq += __popcll(__ballot(n > 0));
+            unlike |= __ballot(n > 0 && (o.s.lo[g] != o.lo0 || o.s.hi[g] != o.hi0));
+        });
+        o.alike = n_seq == batch && unlike == 0;
+    }
+    return o;
 }
+
+// Pieces of dense walks.  A launch of few blocks with long walks (a chunk over a long history: 32 workgroups of 516 steps on
+// 256 compute units) leaves most of the chip idle.  A walk may therefore be cut: block qblk of a sequence, counted from the start of the sequence, is ceil((qblk + 1) / span) pieces of
+// nearly equal length, worked on by a workgroup each.  A piece leaves its unnormalised outputs, maxima and sums in
+// PrefillPieces::partials, and fold_pieces_kernel puts the pieces of a block together.  The span is the smallest that needs no
+// more pieces than the launch has workgroups for; every workgroup works it out from the lengths, which the host does not know.
+// Measured, whole walks in the best shape and pieces: 512 tokens over 32768, 32 / 8 heads, 372 and 161 us (7 pieces to a block:
+// 74 steps of 1.85 us with every compute unit at work, then 10 us to put 29 MB of pieces together); 17 over 42116, twice, 436 and
+// 65; 108 over 73893, 32 / 16 heads, 976 and 259.  Prompts are not cut: one of 4096 tokens takes 119 us whole and 124 or more in any
+// number of pieces, one of 8192 313 and 340, because what they gain in balance (42 steps a compute unit where the longest walk has
+// 64) goes into the starts of the pieces and into putting them together.
+// A position in the launch stands for a piece: last pieces first (none is shorter than half a span), then the last but one,
+// and so on, each kind farthest block first; whole blocks of less than a span come at the end.
+constexpr int kLeastSpanTiles = 8;  // key tiles: a piece costs about three steps of its own
+constexpr int kPieceFloats = kPrefillWaves * (32 * kHeadDim + 64);  // accumulators as the lanes hold them; (maximum, sum) per row
+
+constexpr int kManyPieces = 1 << 15;  // of a sequence: no launch has as many, and wave_count adds up 256 times that exactly
+
+// x / y for 0 <= x < 2^22, 0 < y, by the reciprocal (a whole division is four times the instructions, and the search below,
+// in front of everything else a workgroup does, is a chain of them).
+__device__ __forceinline__ int divide(int x, int y, float reciprocal) {
+    int k = (int)((float)x * reciprocal);
+    const int r = x - k * y;
+    k += r >= y;
+    return k - (r < 0);
+}
+
+struct PiecePlan {
+    int span, total;
+    // pieces of x blocks at the start of a sequence
+    static __device__ __forceinline__ int prefix(int x, int span, float reciprocal) {
+        const int k = divide(x, span, reciprocal), r = x - k * span;
+        return span * (k * (k + 1) / 2) + r * (k + 1);
+    }
+    static __device__ __forceinline__ int pieces_of_batch(const BlockOrder& o, int span) {
+        const float rec = __builtin_amdgcn_rcpf((float)span);
+        if (o.alike) return __builtin_amdgcn_readfirstlane(o.batch * min(prefix(o.hi0, span, rec) - prefix(o.lo0, span, rec), kManyPieces));
+        int count = 0;
+        o.each([&](int g, int n) { count += n > 0 ? min(prefix(o.s.hi[g], span, rec) - prefix(o.s.lo[g], span, rec), kManyPieces) : 0; });
+        return wave_count(count);
+    }
+    static __device__ __forceinline__ PiecePlan make(const BlockOrder& o, int target, int least) {
+        // A walk of x is ceil(x / span) pieces: with a sum of w over n blocks, at least w / span in all and less than
+        // w / span + n.  (fp32 sums, so one to spare on either side.)
+        const int blocks = o.at_or_past(0);
+        float w = 0.f;
+        if (o.alike) {
+            w = 0.5f * (float)o.batch * (float)(o.hi0 - o.lo0) * (float)(o.hi0 + o.lo0 + 1);
+        } else {
+            o.each([&](int g, int n) { w += 0.5f * (float)n * (float)(o.s.hi[g] + o.s.lo[g] + 1); });
+            w = rows4_sum(row16_sum(w));
+        }
+        int low = max(least, (int)(w * __builtin_amdgcn_rcpf((float)target)) - 1) - 1;
+        int high = target > blocks ? (int)min(1e6f, w * __builtin_amdgcn_rcpf((float)(target - blocks))) + 2 : 1 << 20;
+        low = __builtin_amdgcn_readfirstlane(low);
+        high = __builtin_amdgcn_readfirstlane(max(min(high, max(o.top(), 1)), low + 1));
+        while (high - low > 1) {
+            const int mid = (low + high) / 2;
+            if (pieces_of_batch(o, mid) <= target)
+                high = mid;
+            else
+                low = mid;
+        }
+        return {high, pieces_of_batch(o, high)};
+    }
+    // Position `rank` of the launch, below `total`: which piece it is of which block in the order of blocks, and the slot of
+    // the piece.
+    __device__ __forceinline__ void find(const BlockOrder& o, int& rank, int& piece, int& slot) const {
+        int before = total;  // pieces with numbers up to the one looked at
+        for (piece = __builtin_amdgcn_readfirstlane(divide(o.top() - 1, span, __builtin_amdgcn_rcpf((float)span))); piece > 0; --piece) {
+            const int n = o.at_or_past(piece * span);
+            before -= n;
+            if (rank < n) break;
+            rank -= n;
+        }
+        slot = (piece > 0 ? before : 0) + rank;
+    }
+};
 
 // General block mask (Sec. 3.1, Sec. 3.4): per mask and query tile, the ascending list of kept key
 // tiles.  A workgroup of one slice owns four query tiles; a pre-pass merges their rows into one ascending list of
@@ -306,12 +426,14 @@ enum PrefillMode { kPlain = 0, kMasked = 1, kPaged = 2 };
 // and the slices are folded through LDS at the end.  A launch with few query rows (a short prompt, a chunk over a long
 // history) then has SL times the workgroups, each with a walk SL times shorter, for SL times the staging per step
 // (see choose_shape).
-template <class T, int MODE, int BITS, int SL>
-__global__ __launch_bounds__(kPrefillThreads, 512 / kPrefillThreads) void sparse_prefill_kernel(
-    LayerParams lp, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+// CUT: the dense walks come in pieces (see PiecePlan).
+template <class T, int MODE, int BITS, int SL, bool CUT>
+__device__ __forceinline__ void prefill_workgroup(
+    const LayerParams& lp, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int* __restrict__ cu_seqlens, int batch, uint16_t* __restrict__ out,
-    float* __restrict__ lse_out, int total_tokens, PrefillSchedule sched, PrefillMask mk, PrefillPaged pg) {
+    float* __restrict__ lse_out, int total_tokens, const PrefillSchedule& sched, const PrefillMask& mk, const PrefillPaged& pg) {
     constexpr bool MASKED = MODE == kMasked, PAGED = MODE == kPaged, QUANT = BITS != 16;
+    static_assert(!CUT || (SL == 1 && PAGED), "chunks");
     static_assert(!QUANT || PAGED, "quantised rows live in pages");
     static_assert(SL == 1 || SL == 2 || (SL == 4 && !QUANT), "slices");
     // One or two slices: two stages of (K tiles, V tiles).  Four separate arrays, and a loop unrolled over the two
@@ -343,39 +465,37 @@ __global__ __launch_bounds__(kPrefillThreads, 512 / kPrefillThreads) void sparse
 
     // heaviest query blocks first; see HeadClass for the XCD-aware order
     const int xcd = blockIdx.x % kXcds;
-    int li = blockIdx.x / kXcds, hk, hg, rank;
+    int li = blockIdx.x / kXcds, hidx, hk, hg, rank;
     const bool second = li >= sched.cls[0].items_per_xcd;
     if (second) li -= sched.cls[0].items_per_xcd;
     const int heads_per_block = second ? sched.cls[1].heads_per_block : sched.cls[0].heads_per_block;
     const int qtiles_log2 = second ? sched.cls[1].qtiles_log2 : sched.cls[0].qtiles_log2;
     const bool fold = SL > 1 && (second ? sched.cls[1].fold : sched.cls[0].fold);
     const int blocks_per_seq = second ? sched.cls[1].blocks_per_seq : sched.cls[0].blocks_per_seq;
-    decode_work(second ? sched.cls[1] : sched.cls[0], lp.group / heads_per_block, xcd, li, hk, hg, rank);
+    decode_work(second ? sched.cls[1] : sched.cls[0], lp.group / heads_per_block, xcd, li, hidx, hk, hg, rank);
     int b, qblk = 0;
+    int piece = 0, pieces = 1, slot = 0, span = 0x7fffffff;  // of a cut walk: which piece of how many, and where it goes
     if (second ? sched.cls[1].ordered : sched.cls[0].ordered) {
-        const int rows_log2 = kTileLog2 + qtiles_log2;
-        BlockSpans spans;
-#pragma unroll
-        for (int g = 0; g < kSeqGroups; ++g) {
-            spans.lo[g] = spans.hi[g] = 0;
-            if (g > 0 && g * kWave >= batch) continue;
-            const int seq = g * kWave + threadIdx.x % kWave, i = min(seq, batch - 1);
-            const int fresh = cu_seqlens[i + 1] - cu_seqlens[i];
-            const int past = PAGED ? pg.kv.seq_lens[i] - (pg.k_new ? 0 : fresh) : 0;
-            spans.lo[g] = past >> rows_log2;
-            spans.hi[g] = seq < batch && fresh > 0 ? ((past + fresh - 1) >> rows_log2) + 1 : 0;
+        const BlockOrder order =
+            block_order(cu_seqlens, PAGED ? pg.kv.seq_lens : nullptr, PAGED && pg.k_new, batch, kTileLog2 + qtiles_log2);
+        if (CUT && !second) {
+            const PiecePlan plan = PiecePlan::make(order, sched.pieces.target, kLeastSpanTiles >> qtiles_log2);
+            if (rank >= plan.total) return;
+            plan.find(order, rank, piece, slot);
+            slot += (hidx * (lp.group / heads_per_block) + hg) * sched.pieces.target;
+            span = plan.span;
         }
-        if (batch == 1) {
-            b = 0;
-            qblk = __builtin_amdgcn_readfirstlane(spans.hi[0]) - 1 - rank;
-            if (qblk < __builtin_amdgcn_readfirstlane(spans.lo[0])) return;
-        } else {
-            if (!block_of(rank, spans, batch, b, qblk)) return;
-            // Both come out of lane arithmetic.  Left in a vector register, the block's position takes the length of the walk,
-            // the key tile of every step and the page look-ups there with it, and each branch on them runs under a mask of
-            // lanes (a step of one slice 1.71 us, 1.65 with both in scalar registers: 512 tokens over 32768).
-            b = __builtin_amdgcn_readfirstlane(b);
-            qblk = __builtin_amdgcn_readfirstlane(qblk);
+        if (!order.find(rank, b, qblk)) return;
+        // All of it comes out of lane arithmetic.  Left in a vector register, the block's position takes the length of the
+        // walk, the key tile of every step and the page look-ups there with it, and each branch on them runs under a mask of
+        // lanes (a step of one slice 1.71 us, 1.65 with all in scalar registers: 512 tokens over 32768).
+        b = __builtin_amdgcn_readfirstlane(b);
+        qblk = __builtin_amdgcn_readfirstlane(qblk);
+        if (CUT) {
+            piece = __builtin_amdgcn_readfirstlane(piece);
+            pieces = qblk >= span ? __builtin_amdgcn_readfirstlane(divide(qblk, span, __builtin_amdgcn_rcpf((float)span)) + 1) : 1;
+            slot = pieces > 1 ? slot : -1;
+            asm volatile("" : "+v"(slot));  // wanted at the very end: a vector register, of which there are some left
         }
     } else {
         if (rank >= blocks_per_seq * batch) return;
@@ -448,6 +568,12 @@ __global__ __launch_bounds__(kPrefillThreads, 512 / kPrefillThreads) void sparse
                 }
             }
         }
+    }
+
+    int it_begin = 0;
+    if (CUT && pieces > 1) {
+        it_begin = n_visit * piece / pieces;
+        n_visit = n_visit * (piece + 1) / pieces;
     }
 
     float16_t acc[4];
@@ -610,7 +736,7 @@ __global__ __launch_bounds__(kPrefillThreads, 512 / kPrefillThreads) void sparse
     };
     constexpr int kTileMask = (1 << kKeepShift) - 1;
     // the wave's entries: first, first + stride, ...
-    const int it_first = fold ? slice : 0, stride = fold ? SL : 1;
+    const int it_first = CUT ? it_begin : fold ? slice : 0, stride = fold ? SL : 1;
     int e_cur = it_first < n_visit ? entry_of(it_first) : 0;
     int e_nxt = it_first + stride < n_visit ? entry_of(it_first + stride) : 0;
     // physical pages of the tiles to come, looked up two steps ahead of the loads that need them
@@ -626,7 +752,7 @@ __global__ __launch_bounds__(kPrefillThreads, 512 / kPrefillThreads) void sparse
         fetch_codes(kOnlyV, staged_v, e_cur & kTileMask, ph_first);
     }
     // steps of the workgroup: every wave must reach every barrier, so the longest walk counts
-    int steps = fold ? ceil_div(n_visit, SL) : n_visit;
+    int steps = fold ? ceil_div(n_visit, SL) : n_visit - (CUT ? it_begin : 0);
     if (SL > 1 && !fold) {
         if (lane == 0) walk_len[wave] = n_visit;
         __syncthreads();
@@ -919,10 +1045,23 @@ __global__ __launch_bounds__(kPrefillThreads, 512 / kPrefillThreads) void sparse
         }
     }
 
+    if (CUT) slot = __builtin_amdgcn_readfirstlane(slot);
     // ---- epilogue: lane (n, half) holds O^T[d][q] for d = 32 db + 8 (i / 4) + 4 half + i % 4
     const float lt = halves_sum(l_run);
     const int pos = iq * kTile + row0 + n;
     const int row = pos - first;
+    if (CUT && slot >= 0) {  // a piece: as the lanes hold it, 1 KiB at a time
+        if (!wave_has_rows) return;
+        float4* dst = reinterpret_cast<float4*>(sched.pieces.partials + (size_t)slot * kPieceFloats) + wave * (kPieceFloats / 4 / kPrefillWaves);
+#pragma unroll
+        for (int db = 0; db < 4; ++db)
+#pragma unroll
+            for (int g4 = 0; g4 < 4; ++g4)
+                dst[(db * 4 + g4) * kWave + lane] =
+                    make_float4(acc[db][4 * g4], acc[db][4 * g4 + 1], acc[db][4 * g4 + 2], acc[db][4 * g4 + 3]);
+        if (half == 0) reinterpret_cast<float2*>(dst + 16 * kWave)[n] = make_float2(m_run, lt);
+        return;
+    }
     if (!fold) {
         if (!wave_has_rows) return;
         if (pos >= len || pos < first) return;
@@ -1000,6 +1139,99 @@ __global__ __launch_bounds__(kPrefillThreads, 512 / kPrefillThreads) void sparse
     }
 }
 
+template <class T, int MODE, int BITS, int SL>
+__global__ __launch_bounds__(kPrefillThreads, 512 / kPrefillThreads) void sparse_prefill_kernel(
+    LayerParams lp, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+    const int* __restrict__ cu_seqlens, int batch, uint16_t* __restrict__ out,
+    float* __restrict__ lse_out, int total_tokens, PrefillSchedule sched, PrefillMask mk, PrefillPaged pg) {
+    prefill_workgroup<T, MODE, BITS, SL, false>(lp, q, k, v, cu_seqlens, batch, out, lse_out, total_tokens, sched, mk, pg);
+}
+// (a kernel of its own: the search for a piece takes scalar registers from the walk, 2 to 5 % of a launch of whole walks)
+template <class T, int BITS>
+__global__ __launch_bounds__(kPrefillThreads, 512 / kPrefillThreads) void prefill_pieces_kernel(
+    LayerParams lp, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+    const int* __restrict__ cu_seqlens, int batch, uint16_t* __restrict__ out,
+    float* __restrict__ lse_out, int total_tokens, PrefillSchedule sched, PrefillMask mk, PrefillPaged pg) {
+    prefill_workgroup<T, kPaged, BITS, 1, true>(lp, q, k, v, cu_seqlens, batch, out, lse_out, total_tokens, sched, mk, pg);
+}
+
+// Puts the pieces of cut walks together.  One workgroup per block and wavefront of its workgroups, one wavefront per 32
+// channels, which reads 4 KiB of every piece, kBatch pieces at a time.
+template <class T>
+__global__ __launch_bounds__(256) void fold_pieces_kernel(LayerParams lp, const int* __restrict__ cu_seqlens, const int* __restrict__ seq_lens,
+                                                          int alongside, int batch, uint16_t* __restrict__ out, float* __restrict__ lse_out,
+                                                          int total_tokens, PrefillSchedule sched) {
+    constexpr int kBatch = 8;
+    const HeadClass& hc = sched.cls[0];
+    const int wave = blockIdx.x % kPrefillWaves, rank = blockIdx.x / kPrefillWaves, hidx = blockIdx.y, hg = blockIdx.z;
+    const int hk = (int)(hc.kv_head[hidx / 4] >> (8 * (hidx % 4))) & 0xff;
+    const BlockOrder order = block_order(cu_seqlens, seq_lens, alongside, batch, kTileLog2 + hc.qtiles_log2);
+    const PiecePlan plan = PiecePlan::make(order, sched.pieces.target, kLeastSpanTiles >> hc.qtiles_log2);
+    int b, qblk;
+    if (!order.find(rank, b, qblk)) return;
+    const int pieces = __builtin_amdgcn_readfirstlane(divide(qblk, plan.span, __builtin_amdgcn_rcpf((float)plan.span))) + 1;
+    if (pieces == 1) return;
+    const int start = cu_seqlens[b], fresh = cu_seqlens[b + 1] - start;
+    const int len = seq_lens[b] + (alongside ? fresh : 0), first = len - fresh;
+    const int lane = threadIdx.x % kWave, n = lane % 32, half = lane / 32;
+    const int db = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int unit = wave / 2;
+    const int h = hk * lp.group + hg * hc.heads_per_block + (unit >> hc.qtiles_log2);
+    const int pos = ((qblk << hc.qtiles_log2) + (unit & ((1 << hc.qtiles_log2) - 1))) * kTile + wave % 2 * 32 + n;
+    if (pos - n >= len || pos - n + 32 <= first) return;
+
+    const float4* base = reinterpret_cast<const float4*>(sched.pieces.partials) + wave * (kPieceFloats / 4 / kPrefillWaves);
+    const size_t slot0 = (size_t)(hidx * (lp.group / hc.heads_per_block) + hg) * sched.pieces.target + rank;
+    float m = -INFINITY, l = 0.f, o[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) o[i] = 0.f;
+    int before = 0;  // pieces with smaller numbers
+    for (int p = 0; p < pieces; p += kBatch) {
+        float2 ml[kBatch];
+        float4 x[kBatch][4];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const float4* src = base + (slot0 + before) * (kPieceFloats / 4);
+            ml[u] = reinterpret_cast<const float2*>(src + 16 * kWave)[n];
+#pragma unroll
+            for (int g4 = 0; g4 < 4; ++g4) x[u][g4] = src[(db * 4 + g4) * kWave + lane];
+            if (p + u + 1 < pieces) before += order.at_or_past((p + u) * plan.span);  // past the end: the last piece again, unused
+        }
+        float m_new = m;
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) m_new = fmaxf(m_new, p + u < pieces ? ml[u].x : -INFINITY);
+        const float m_safe = m_new == -INFINITY ? 0.f : m_new;
+        const float keep = __builtin_amdgcn_exp2f(m - m_safe);
+        l *= keep;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[i] *= keep;
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            if (p + u >= pieces) break;
+            const float f = __builtin_amdgcn_exp2f(ml[u].x - m_safe);
+            l = __builtin_fmaf(ml[u].y, f, l);
+#pragma unroll
+            for (int g4 = 0; g4 < 4; ++g4) {
+                o[4 * g4] = __builtin_fmaf(x[u][g4].x, f, o[4 * g4]);
+                o[4 * g4 + 1] = __builtin_fmaf(x[u][g4].y, f, o[4 * g4 + 1]);
+                o[4 * g4 + 2] = __builtin_fmaf(x[u][g4].z, f, o[4 * g4 + 2]);
+                o[4 * g4 + 3] = __builtin_fmaf(x[u][g4].w, f, o[4 * g4 + 3]);
+            }
+        }
+        m = m_new;
+    }
+    if (pos >= len || pos < first) return;
+    const int row = pos - first;
+    const float inv = l > 0.f ? 1.f / l : 0.f;
+    uint16_t* dst = out + ((size_t)(start + row) * lp.H + h) * kHeadDim + db * 32 + 4 * half;
+#pragma unroll
+    for (int g4 = 0; g4 < 4; ++g4)
+        *reinterpret_cast<uint2*>(dst + 8 * g4) = make_uint2(Elem<T>::pack(o[4 * g4] * inv, o[4 * g4 + 1] * inv),
+                                                             Elem<T>::pack(o[4 * g4 + 2] * inv, o[4 * g4 + 3] * inv));
+    if (lse_out && db == 0 && half == 0)
+        lse_out[(size_t)h * total_tokens + start + row] = l > 0.f ? (m + __builtin_amdgcn_logf(l)) * kLn2 : -INFINITY;
+}
+
 // ---- host side -----------------------------------------------------------------------------------
 
 int count_streaming(const LayerParams& lp) {
@@ -1014,6 +1246,7 @@ struct PrefillShape {
     int slices;
     bool fold[2];
     bool one_head;
+    int pieces;  // of dense walks per (KV head, group of query heads), at most (PrefillPieces::target); 0: whole walks
 };
 
 // The queries of a launch as far as the host knows them.
@@ -1036,6 +1269,7 @@ int heads_per_block(const LayerParams& lp, const PrefillShape& shape, int cls) {
 // (211 chunks and 90 prompts of 1 .. 24 sequences in every shape; two thirds of the estimates are within 9 %):
 // a step of 64 keys with one / two / four slices takes 1.75 / 2.16 / 2.91, 2.21 / 2.85 over quantised pages (not built for
 // four: the codes on their way need more registers than there are); with most wavefronts without rows 22 % less.
+constexpr int kMostPieces = 4096;  // per (KV head, group of query heads)
 constexpr float kStepUs[2][3] = {{1.75f, 2.16f, 2.91f}, {2.21f, 2.85f, 2.85f}};
 constexpr float kStepWithoutRows = 0.78f;
 constexpr float kStartUs[2] = {5.2f, 5.8f}, kStartOfSlices[3] = {0.f, 0.5f, 0.55f}, kFoldUs = 0.44f, kLaunchUs = 2.2f;
@@ -1097,41 +1331,68 @@ float rounds_time(float n, float longest, float shortest, int m) {
     return t + (left <= m ? of(done) : std::max(of(done), of(done + m - 1) + of(done + m)));
 }
 
-// Estimated time of a launch whose history is `history` key tiles long.
-float launch_time(const LayerParams& lp, const PrefillRows& rows, float history, const ClassCost (&c)[2], int units_per_xcd) {
+// Key tiles of the walks of one class of heads, and a workgroup's times for them.
+struct ClassWalks {
+    float hi, lo, mid;
+    float longest, shortest, mean;
+};
+ClassWalks class_walks(const LayerParams& lp, const PrefillRows& rows, float history, const ClassCost& c, int cls) {
     const float longest_tiles = (float)rows.longest / kTile, mean_tiles = (float)rows.total / rows.batch / kTile;
     const float other = rows.batch > 1 ? (float)(rows.total - rows.longest) / (rows.batch - 1) / kTile : longest_tiles;
-    float longest[2] = {}, shortest[2] = {}, mean[2] = {};
-    for (int cls = 0; cls < 2; ++cls) {
-        if (c[cls].count == 0.f) continue;
-        const float qt = (float)c[cls].qtiles;
-        float hi, lo, mid;  // key tiles of the walks
-        if (rows.history_pages >= 0) {
-            hi = history + longest_tiles + 0.5f;
-            lo = history + std::min(qt, other + 0.5f);
-            mid = history + 0.25f * (longest_tiles + mean_tiles) + 0.5f * std::min(qt, longest_tiles);
-        } else {
-            hi = whole(longest_tiles);
-            lo = std::min(qt, hi);
-            mid = 0.25f * (longest_tiles + mean_tiles) + 0.5f * std::min(qt, other + 0.5f);
-        }
-        if (cls == 1) {
-            const float band = (float)(lp.sink_pages + lp.local_pages) + qt - 1.f;
-            hi = std::min(hi, band);
-            lo = std::min(lo, band);
-        }
-        mid = std::min(hi, std::max(lo, mid));
-        longest[cls] = c[cls].start + c[cls].step * hi;
-        shortest[cls] = c[cls].start + c[cls].step * lo;
-        mean[cls] = c[cls].start + c[cls].step * mid;
+    ClassWalks w = {};
+    if (c.count == 0.f) return w;
+    const float qt = (float)c.qtiles;
+    if (rows.history_pages >= 0) {
+        w.hi = history + longest_tiles + 0.5f;
+        w.lo = history + std::min(qt, other + 0.5f);
+        w.mid = history + 0.25f * (longest_tiles + mean_tiles) + 0.5f * std::min(qt, longest_tiles);
+    } else {
+        w.hi = whole(longest_tiles);
+        w.lo = std::min(qt, w.hi);
+        w.mid = 0.25f * (longest_tiles + mean_tiles) + 0.5f * std::min(qt, other + 0.5f);
     }
-    float t = longest[1];
-    if (c[0].count > 0.f) t = std::max(t, rounds_time(c[0].count, longest[0], shortest[0], units_per_xcd));
+    if (cls == 1) {
+        const float band = (float)(lp.sink_pages + lp.local_pages) + qt - 1.f;
+        w.hi = std::min(w.hi, band);
+        w.lo = std::min(w.lo, band);
+    }
+    w.mid = std::min(w.hi, std::max(w.lo, w.mid));
+    w.longest = c.start + c.step * w.hi;
+    w.shortest = c.start + c.step * w.lo;
+    w.mean = c.start + c.step * w.mid;
+    return w;
+}
+
+// Estimated time of a launch whose history is `history` key tiles long.
+float launch_time(const LayerParams& lp, const PrefillRows& rows, float history, const ClassCost (&c)[2], int units_per_xcd) {
+    const ClassWalks w[2] = {class_walks(lp, rows, history, c[0], 0), class_walks(lp, rows, history, c[1], 1)};
+    float t = w[1].longest;
+    if (c[0].count > 0.f) t = std::max(t, rounds_time(c[0].count, w[0].longest, w[0].shortest, units_per_xcd));
     if (c[0].count + c[1].count > units_per_xcd) {
-        const float even = (c[0].count * mean[0] + c[1].count * mean[1]) / units_per_xcd;
-        t = std::max(t, even + std::max(kTailOfStream * longest[1], kTailOfDense * longest[0]));
+        const float even = (c[0].count * w[0].mean + c[1].count * w[1].mean) / units_per_xcd;
+        t = std::max(t, even + std::max(kTailOfStream * w[1].longest, kTailOfDense * w[0].longest));
     }
     return t + kLaunchUs;
+}
+
+// The same with dense walks in up to `pieces` pieces per XCD (see PiecePlan): the time of a piece beside its steps, of
+// putting pieces together, and of a step where every compute unit is at work on keys of its own.  Fitted to 95 drawn chunks: the
+// pieces taken come to 0.60 of the time of whole walks over one half of them and 0.81 over the other, the best to 0.57 and 0.79.
+constexpr float kPieceUs = 0.5f, kFoldLaunchUs = 1.f, kFoldPieceUs = 0.15f, kCutStep = 1.07f;
+float cut_launch_time(const LayerParams& lp, const PrefillRows& rows, float history, const ClassCost (&c)[2], int units_per_xcd,
+                      float pieces) {
+    const ClassWalks w[2] = {class_walks(lp, rows, history, c[0], 0), class_walks(lp, rows, history, c[1], 1)};
+    const float work = c[0].count * w[0].mid;
+    const float alike = w[0].hi / std::max(1.f, (float)(int)(pieces / c[0].count)), apart = work / (pieces - 0.5f * c[0].count);
+    const float span = std::min(w[0].hi, std::max((float)kLeastSpanTiles, std::max(apart, apart + (alike - apart) * w[0].lo / w[0].hi)));
+    const float count = std::max(c[0].count, std::min(pieces, work / span + 0.5f * c[0].count));
+    const float longest = c[0].start + kCutStep * c[0].step * span + kPieceUs;
+    float t = std::max(longest, w[1].longest);
+    if (count + c[1].count > units_per_xcd) {
+        const float even = (count * (c[0].start + kPieceUs) + work * kCutStep * c[0].step + c[1].count * w[1].mean) / units_per_xcd;
+        t = std::max(t, even + std::max(kTailOfStream * w[1].longest, 0.3f * longest));
+    }
+    return t + kLaunchUs + kFoldLaunchUs + kFoldPieceUs * count;
 }
 
 // The shape of a launch.  Measured with one / two / four slices: 512 new tokens over a history of 32768, 849 / 520 / 363 us;
@@ -1144,10 +1405,19 @@ float launch_time(const LayerParams& lp, const PrefillRows& rows, float history,
 // sixteenth and a sixty-fourth of it (490 chunks: 1.5 % over the best shape with a tight table and 2.2 % with one 32 times as
 // wide; by the length of the table alone 1.1 and 3.3 %, and up to half the speed lost).  Where the number of blocks is an
 // estimate, near the end of a round of workgroups, so is the time: the mean of a few blocks less and a few more.
-PrefillShape choose_shape(const LayerParams& lp, const PrefillRows& rows, bool quant) {
-    constexpr PrefillShape kShapes[] = {{1, {false, false}, false}, {1, {false, false}, true}, {2, {true, true}, true},
-                                        {2, {true, true}, false},   {2, {true, false}, false}, {4, {true, true}, false}};
-    constexpr int kCount = (int)(sizeof(kShapes) / sizeof(kShapes[0]));
+// May it pay to cut the walks of these chunks into pieces?  A first look, for the host's time: not where the history is short
+// or whole walks fill the chip.
+bool may_cut(const LayerParams& lp, const PrefillRows& rows) {
+    const int dense = lp.Hkv - count_streaming(lp);
+    return dense > 0 && rows.batch <= kOrderedSeqs && rows.history_pages >= 3 * kLeastSpanTiles &&
+           (long long)rows.total * dense * lp.group < (long long)num_compute_units() * kPairs * kTile;
+}
+
+// scratch: the launch may cut dense walks into pieces, so many that its workgroups are about one, two ... rounds of the chip.
+PrefillShape choose_shape(const LayerParams& lp, const PrefillRows& rows, bool quant, bool scratch) {
+    constexpr PrefillShape kShapes[] = {{1, {false, false}, false, 0}, {1, {false, false}, true, 0}, {2, {true, true}, true, 0},
+                                        {2, {true, true}, false, 0},   {2, {true, false}, false, 0}, {4, {true, true}, false, 0}};
+    constexpr int kCount = (int)(sizeof(kShapes) / sizeof(kShapes[0])), kRounds = 4;
     constexpr float kWeight[4] = {4.f, 1.f, 1.f, 1.f};
     const int n_stream = count_streaming(lp), heads[2] = {lp.Hkv - n_stream, n_stream};
     const int units_per_xcd = std::max(1, num_compute_units() / kXcds);
@@ -1156,17 +1426,38 @@ PrefillShape choose_shape(const LayerParams& lp, const PrefillRows& rows, bool q
     const int count = prompt && rows.longest <= 2 * kTile ? 2 : quant ? kCount - 1 : kCount;
     const int guesses = prompt ? 1 : 4;
     const float spread = 0.4f * std::sqrt((float)rows.batch);
-    float time[kCount][4] = {};
-    for (int i = 0; i < count; ++i)
-        for (int side = exact ? 0 : -1; side <= 1; side += 2) {
-            const ClassCost c[2] = {class_cost(lp, kShapes[i], rows, 0, heads[0], quant, exact ? 0 : side, spread),
-                                    class_cost(lp, kShapes[i], rows, 1, heads[1], quant, exact ? 0 : side, spread)};
-            float history = prompt ? 0.f : (float)rows.history_pages;
-            for (int g = 0; g < guesses; ++g, history *= 0.25f) time[i][g] += launch_time(lp, rows, history, c, units_per_xcd);
+    // pieces per (KV head, group of query heads), and per XCD, of launches of one, two ... rounds (0: not to be had)
+    int pieces[kRounds] = {};
+    float per_xcd[kRounds] = {};
+    if (scratch) {
+        const ClassCost dense = class_cost(lp, kShapes[0], rows, 0, heads[0], quant, 0, 0.f), stream = class_cost(lp, kShapes[0], rows, 1, heads[1], quant, -1, 0.f);
+        const int per_block = lp.group / heads_per_block(lp, kShapes[0], 0), block = kTile * dense.qtiles;
+        const long long blocks = std::min((long long)rows.batch * ((rows.longest + block - 1) / block + 1), (long long)rows.total / block + 2LL * rows.batch);
+        for (int r = 0; r < kRounds; ++r) {
+            const int room = (r + 1) * units_per_xcd - (int)stream.count;
+            const int n = kXcds % heads[0] == 0 ? room / per_block * (kXcds / heads[0]) : room * kXcds / (heads[0] * per_block);
+            if (room <= 0 || n < blocks + blocks / 4 || n > kMostPieces) continue;
+            pieces[r] = n;
+            per_xcd[r] = (float)(n * heads[0] * per_block) / kXcds;
         }
+    }
+    float time[kCount + kRounds][4] = {};
+    for (int side = exact ? 0 : -1; side <= 1; side += 2) {
+        for (int i = 0; i < kCount + kRounds; ++i) {
+            if (i < kCount ? i >= count : pieces[i - kCount] == 0) continue;
+            const PrefillShape& shape = kShapes[i < kCount ? i : 0];
+            const ClassCost c[2] = {class_cost(lp, shape, rows, 0, heads[0], quant, exact ? 0 : side, spread),
+                                    class_cost(lp, shape, rows, 1, heads[1], quant, exact ? 0 : side, spread)};
+            float history = prompt ? 0.f : (float)rows.history_pages;
+            for (int g = 0; g < guesses; ++g, history *= 0.25f)
+                time[i][g] += i < kCount ? launch_time(lp, rows, history, c, units_per_xcd)
+                                         : cut_launch_time(lp, rows, history, c, units_per_xcd, per_xcd[i - kCount]);
+        }
+    }
     int best = 0;
     float best_score = 0.f;
-    for (int i = 0; i < count; ++i) {
+    for (int i = 0; i < kCount + kRounds; ++i) {
+        if (i < kCount ? i >= count : pieces[i - kCount] == 0) continue;
         float score = 0.f;
         for (int g = 0; g < guesses; ++g) {
             float least = time[0][g];
@@ -1175,12 +1466,28 @@ PrefillShape choose_shape(const LayerParams& lp, const PrefillRows& rows, bool q
         }
         if (i == 0 || score < best_score) best = i, best_score = score;
     }
-    return kShapes[best];
+    PrefillShape shape = kShapes[best < kCount ? best : 0];
+    if (best >= kCount) shape.pieces = pieces[best - kCount];
+    return shape;
+}
+
+// Scratch of a launch in pieces.
+size_t pieces_bytes(const LayerParams& lp, const PrefillShape& shape) {
+    return (size_t)shape.pieces * (lp.Hkv - count_streaming(lp)) * (lp.group / heads_per_block(lp, shape, 0)) * kPieceFloats * sizeof(float);
 }
 
 // Rows of a chunk in front of which up to `pages` pages of keys may lie, its own among them.
 PrefillRows chunk_rows(int batch, int total_new, int max_new_per_seq, int pages) {
     return {batch, total_new, max_new_per_seq, std::max(0, pages - max_new_per_seq / kTile)};
+}
+
+// The shape of a launch that has this much scratch.
+PrefillShape shape_within(const LayerParams& lp, const PrefillRows& rows, bool quant, const void* scratch, size_t bytes) {
+    if (scratch && bytes > 0 && may_cut(lp, rows)) {
+        const PrefillShape shape = choose_shape(lp, rows, quant, true);
+        if (pieces_bytes(lp, shape) <= bytes) return shape;
+    }
+    return choose_shape(lp, rows, quant, false);
 }
 
 // Is a listed mask walked by the caller's rows as they are, four key slices to a unit, rather than by merged lists of four
@@ -1209,6 +1516,7 @@ bool choose_sliced_rows(const LayerParams& lp, double tiles, double longest, dou
 PrefillSchedule make_schedule(const LayerParams& lp, const PrefillShape& shape, int max_rows, int total_rows, bool any_start,
                               int batch) {
     PrefillSchedule sched;
+    sched.pieces = {nullptr, shape.pieces};
     for (int c = 0; c < 2; ++c) {
         HeadClass& hc = sched.cls[c];
         hc.fold = shape.fold[c];
@@ -1223,6 +1531,8 @@ PrefillSchedule make_schedule(const LayerParams& lp, const PrefillShape& shape, 
         long long blocks = (long long)hc.blocks_per_seq * batch;
         // n rows fill floor(n / rows) blocks and touch at most one more, two more if they start anywhere
         if (hc.ordered) blocks = std::min(blocks, (long long)total_rows / rows + (any_start ? 2LL : 1LL) * batch);
+        hc.blocks = (int)std::min(blocks, 0x7fffffffLL);
+        if (c == 0 && shape.pieces) blocks = shape.pieces;
         hc.heads = 0;
         for (unsigned& w : hc.kv_head) w = 0;
         for (int hk = 0; hk < lp.Hkv; ++hk)
@@ -1281,6 +1591,23 @@ hipError_t launch_slices(const PrefillLaunch& a, int slices) {
     return hipGetLastError();
 }
 
+// A launch over pages, in pieces if that is the shape.
+template <class T, int BITS>
+hipError_t launch_chunk(PrefillLaunch& a, const PrefillShape& shape, void* scratch) {
+    if (!shape.pieces) return launch_slices<T, kPaged, BITS>(a, shape.slices);
+    a.sched.pieces.partials = reinterpret_cast<float*>(scratch);
+    const HeadClass& dense = a.sched.cls[0];
+    hipLaunchKernelGGL((prefill_pieces_kernel<T, BITS>), dim3(kXcds * (dense.items_per_xcd + a.sched.cls[1].items_per_xcd)),
+                       dim3(kPrefillThreads), 0, a.stream, *a.lp, a.q, a.k, a.v, a.cu_seqlens, a.batch, a.out, a.lse_out, a.total_tokens,
+                       a.sched, a.mk, a.pg);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((fold_pieces_kernel<T>), dim3(dense.blocks * kPrefillWaves, dense.heads, a.lp->group / dense.heads_per_block), dim3(256),
+                       0, a.stream, *a.lp, a.cu_seqlens, a.pg.kv.seq_lens, a.pg.k_new != nullptr, a.batch, a.out, a.lse_out, a.total_tokens,
+                       a.sched);
+    return hipGetLastError();
+}
+
 template <class T>
 hipError_t launch_prefill(const LayerParams& lp, const void* q, const void* k, const void* v, const int* cu_seqlens,
                           int batch, int total_tokens, int max_seqlen, void* out, float* lse_out, void* workspace,
@@ -1298,7 +1625,7 @@ hipError_t launch_prefill(const LayerParams& lp, const void* q, const void* k, c
     a.lse_out = lse_out;
     a.stream = stream;
     if (!mask) {
-        const PrefillShape shape = choose_shape(lp, {batch, total_tokens, max_seqlen, -1}, false);
+        const PrefillShape shape = choose_shape(lp, {batch, total_tokens, max_seqlen, -1}, false, false);
         a.sched = make_schedule(lp, shape, max_seqlen, total_tokens, false, batch);
         return launch_slices<T, kPlain, 16>(a, shape.slices);
     }
@@ -1311,7 +1638,7 @@ hipError_t launch_prefill(const LayerParams& lp, const void* q, const void* k, c
     const double row = (double)mask->nnz / ((double)mask->num_masks * mask->rows_per_mask);
     const double tiles = (double)total_tokens / kTile + 0.5 * batch;  // half a tile of padding per sequence
     if (choose_sliced_rows(lp, tiles, max_tiles, row)) {
-        a.sched = make_schedule(lp, {4, {true, true}, true}, max_seqlen, total_tokens, false, batch);
+        a.sched = make_schedule(lp, {4, {true, true}, true, 0}, max_seqlen, total_tokens, false, batch);
         return launch_slices<T, kMasked, 16>(a, 4);
     }
     mk.blocks_per_seq = mask_blocks(max_seqlen);
@@ -1321,15 +1648,14 @@ hipError_t launch_prefill(const LayerParams& lp, const void* q, const void* k, c
                        (size_t)align16(max_tiles), stream, mk, cu_seqlens, batch);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    a.sched = make_schedule(lp, {1, {false, false}, true}, max_seqlen, total_tokens, false, batch);
+    a.sched = make_schedule(lp, {1, {false, false}, true, 0}, max_seqlen, total_tokens, false, batch);
     return launch_slices<T, kMasked, 16>(a, 1);
 }
 
 template <class T>
 hipError_t launch_prefill_paged(const LayerParams& lp, const PagedParams& kv, const void* q, const void* k_new,
                                 const void* v_new, const int* cu_q, int total_new, int max_new_per_seq, int max_seqlen,
-                                void* out, float* lse_out, void* workspace, hipStream_t stream) {
-    (void)workspace;
+                                void* out, float* lse_out, void* workspace, size_t workspace_bytes, hipStream_t stream) {
     PrefillLaunch a = {};
     a.lp = &lp;
     a.q = reinterpret_cast<const uint16_t*>(q);
@@ -1343,11 +1669,12 @@ hipError_t launch_prefill_paged(const LayerParams& lp, const PagedParams& kv, co
     a.pg.v_new = reinterpret_cast<const uint16_t*>(v_new);
     a.stream = stream;
     const int pages = max_seqlen > 0 ? std::min(kv.max_pages, (max_seqlen - 1) / kTile + 1) : kv.max_pages;
-    const PrefillShape shape = choose_shape(lp, chunk_rows(kv.batch, total_new, max_new_per_seq, pages), kv.kv_bits != 16);
+    const PrefillShape shape =
+        shape_within(lp, chunk_rows(kv.batch, total_new, max_new_per_seq, pages), kv.kv_bits != 16, workspace, workspace_bytes);
     a.sched = make_schedule(lp, shape, max_new_per_seq, total_new, true, kv.batch);
-    if (kv.kv_bits == 8) return launch_slices<T, kPaged, 8>(a, shape.slices);
-    if (kv.kv_bits == 4) return launch_slices<T, kPaged, 4>(a, shape.slices);
-    return launch_slices<T, kPaged, 16>(a, shape.slices);
+    if (kv.kv_bits == 8) return launch_chunk<T, 8>(a, shape, workspace);
+    if (kv.kv_bits == 4) return launch_chunk<T, 4>(a, shape, workspace);
+    return launch_chunk<T, 16>(a, shape, workspace);
 }
 
 }  // namespace
@@ -1358,12 +1685,17 @@ hipError_t preload_prefill_kernels() {
 }
 
 void prefill_shape(const LayerParams& lp, int batch, int total_rows, int max_rows, int pages, int kv_bits, int (&out)[4]) {
-    const PrefillShape shape = pages > 0 ? choose_shape(lp, chunk_rows(batch, total_rows, max_rows, pages), kv_bits != 16)
-                                         : choose_shape(lp, {batch, total_rows, max_rows, -1}, false);
+    const PrefillShape shape = pages > 0 ? choose_shape(lp, chunk_rows(batch, total_rows, max_rows, pages), kv_bits != 16, false)
+                                         : choose_shape(lp, {batch, total_rows, max_rows, -1}, false, false);
     out[0] = shape.slices;
     out[1] = shape.fold[0];
     out[2] = shape.fold[1];
     out[3] = shape.one_head;
+}
+
+size_t chunk_scratch_bytes(const LayerParams& lp, int batch, int total_rows, int max_rows, int pages, int kv_bits) {
+    const PrefillRows rows = chunk_rows(batch, total_rows, max_rows, pages);
+    return may_cut(lp, rows) ? pieces_bytes(lp, choose_shape(lp, rows, kv_bits != 16, true)) : 0;
 }
 
 size_t paged_prefill_workspace_bytes(const LayerParams& lp, int batch, int max_pages) {
@@ -1376,11 +1708,11 @@ size_t paged_prefill_workspace_bytes(const LayerParams& lp, int batch, int max_p
 hipError_t launch_sparse_prefill_paged(int dtype, const LayerParams& lp, const PagedParams& kv, const void* q,
                                        const void* k_new, const void* v_new, const int* cu_q, int total_new,
                                        int max_new_per_seq, int max_seqlen, void* out, float* lse_out, void* workspace,
-                                       hipStream_t stream) {
+                                       size_t workspace_bytes, hipStream_t stream) {
     return dtype == 0 ? launch_prefill_paged<F16>(lp, kv, q, k_new, v_new, cu_q, total_new, max_new_per_seq, max_seqlen,
-                                                  out, lse_out, workspace, stream)
+                                                  out, lse_out, workspace, workspace_bytes, stream)
                       : launch_prefill_paged<BF16>(lp, kv, q, k_new, v_new, cu_q, total_new, max_new_per_seq, max_seqlen,
-                                                   out, lse_out, workspace, stream);
+                                                   out, lse_out, workspace, workspace_bytes, stream);
 }
 
 size_t prefill_workspace_bytes(const LayerParams& lp, int total_tokens, int batch) {
