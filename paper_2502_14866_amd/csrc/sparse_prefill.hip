@@ -357,8 +357,8 @@ struct PiecePlan {
 // General block mask (Sec. 3.1, Sec. 3.4): per mask and query tile, the ascending list of kept key
 // tiles.  A workgroup of one slice owns four query tiles; a pre-pass merges their rows into one ascending list of
 // (key tile, which of the four query tiles keep it) so that the main loop walks a single list.  A workgroup of four
-// slices owns one query tile and walks the caller's row as it is (see choose_sliced_rows); the last three members are
-// then not used.
+// slices, or half a workgroup, owns one query tile and walks the caller's row as it is (see choose_mask_walk); the last three
+// members are then not used.
 struct PrefillMask {
     const int* head_mask;     // [H]: mask of query head h, -1 = analytic mask of the layer description
     const int* q_tile_start;  // [batch + 1]: first row of sequence b inside one mask
@@ -426,14 +426,19 @@ enum PrefillMode { kPlain = 0, kMasked = 1, kPaged = 2 };
 // and the slices are folded through LDS at the end.  A launch with few query rows (a short prompt, a chunk over a long
 // history) then has SL times the workgroups, each with a walk SL times shorter, for SL times the staging per step
 // (see choose_shape).
-// CUT: the dense walks come in pieces (see PiecePlan).
-template <class T, int MODE, int BITS, int SL, bool CUT>
+// KIND: kCut: the dense walks come in pieces (see PiecePlan); kHalf: a workgroup of four wavefronts and two units, two of them to
+// a compute unit.
+enum WorkgroupKind { kWhole = 0, kCut = 1, kHalf = 2 };
+template <class T, int MODE, int BITS, int SL, int KIND>
 __device__ __forceinline__ void prefill_workgroup(
     const LayerParams& lp, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int* __restrict__ cu_seqlens, int batch, uint16_t* __restrict__ out,
     float* __restrict__ lse_out, int total_tokens, const PrefillSchedule& sched, const PrefillMask& mk, const PrefillPaged& pg) {
     constexpr bool MASKED = MODE == kMasked, PAGED = MODE == kPaged, QUANT = BITS != 16;
+    constexpr bool CUT = KIND == kCut, HALF = KIND == kHalf, ROWS = MASKED && (SL > 1 || HALF);  // ROWS: lists are the caller's rows
+    constexpr int kWaves = HALF ? kPrefillWaves / 2 : kPrefillWaves;
     static_assert(!CUT || (SL == 1 && PAGED), "chunks");
+    static_assert(!HALF || SL == 1, "two units share a walk");
     static_assert(!QUANT || PAGED, "quantised rows live in pages");
     static_assert(SL == 1 || SL == 2 || (SL == 4 && !QUANT), "slices");
     // One or two slices: two stages of (K tiles, V tiles).  Four separate arrays, and a loop unrolled over the two
@@ -474,6 +479,12 @@ __device__ __forceinline__ void prefill_workgroup(
     const int blocks_per_seq = second ? sched.cls[1].blocks_per_seq : sched.cls[0].blocks_per_seq;
     decode_work(second ? sched.cls[1] : sched.cls[0], lp.group / heads_per_block, xcd, li, hidx, hk, hg, rank);
     int b, qblk = 0;
+    const int blocks = second ? sched.cls[1].blocks : sched.cls[0].blocks;
+    const bool again = MASKED && HALF && rank >= blocks;  // the second time over the blocks, for heads without a common mask
+    if (again) {
+        if (heads_per_block == 1) return;
+        rank -= blocks;
+    }
     int piece = 0, pieces = 1, slot = 0, span = 0x7fffffff;  // of a cut walk: which piece of how many, and where it goes
     if (second ? sched.cls[1].ordered : sched.cls[0].ordered) {
         const BlockOrder order =
@@ -524,12 +535,39 @@ __device__ __forceinline__ void prefill_workgroup(
     const int slice = (wave / 2) % SL, unit = wave / 2 / SL;
     const int own = SL > 1 && !fold ? slice * kSliceUnits + unit : unit;
     const int qt = own & (qtiles - 1);
-    const int h = hk * lp.group + hg * heads_per_block + (own >> qtiles_log2);
+    int h = hk * lp.group + hg * heads_per_block + (own >> qtiles_log2);
+    bool idle = false;  // a unit without work
+    if (MASKED && HALF) {
+        idle = unit > 0;
+        h = hk * lp.group + hg;  // of all wavefronts: they walk one list, and meet at its barriers
+        if (heads_per_block == 2) {
+            // The hg-th two of the group's heads in the order of their masks: one workgroup for both if they have one mask
+            // between them, one for each otherwise.
+            int head[2] = {0, 0}, mask[2] = {-1, -1};
+            const int* ids = mk.head_mask + hk * lp.group;
+#pragma unroll
+            for (int i = 0; i < kMaxGroup; ++i) {
+                if (i >= lp.group) break;
+                const int id = ids[i];
+                int before = 0;
+#pragma unroll
+                for (int j = 0; j < kMaxGroup; ++j)
+                    if (j < lp.group && j != i) before += j < i ? ids[j] <= id : ids[j] < id;
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+                    if (before == 2 * hg + u) head[u] = i, mask[u] = id;
+            }
+            const bool together = mask[0] == mask[1];
+            if (together && again) return;
+            idle = !together && unit > 0;
+            h = hk * lp.group + __builtin_amdgcn_readfirstlane((together ? unit > 0 : again) ? head[1] : head[0]);
+        }
+    }
     const bool streaming = (lp.streaming_mask >> hk) & 1ull;
     const int iq = iq0 + qt;             // this wave's mask tile; the wave owns one half of its rows
     const int row0 = (wave % 2) * 32;    // first row of the wave inside the mask tile
     const int n_qtiles = ceil_div(len, kTile);
-    const bool wave_has_rows = iq * kTile + row0 < len && iq * kTile + row0 + 32 > first;
+    const bool wave_has_rows = !idle && iq * kTile + row0 < len && iq * kTile + row0 + 32 > first;
     // query tiles that share this wave's walk, and the key tiles it visits: [0, sink_end) and [band_begin, iq_last]
     const int iq_first = iq0 + (SL > 1 && !fold ? (slice * kSliceUnits) & (qtiles - 1) : 0);
     const int iq_last = min(iq_first + (SL > 1 ? min(qtiles, kSliceUnits) : qtiles) - 1, n_qtiles - 1);
@@ -549,7 +587,7 @@ __device__ __forceinline__ void prefill_workgroup(
         const int m = mk.head_mask[h];
         if (m >= 0 && iq_first <= iq_last) {
             const int row = m * mk.rows_per_mask + mk.q_tile_start[b] + iq_first;
-            if (SL == 1) {
+            if (!ROWS) {
                 lst = mk.blk_list + mk.row_ptr[row];
                 n_visit = mk.blk_count[((size_t)m * batch + b) * mk.blocks_per_seq + qblk];
             } else {
@@ -608,17 +646,17 @@ __device__ __forceinline__ void prefill_workgroup(
         if (!PAGED || jt * kTile >= cached) return 0;
         return page_row[ring ? ring_slot(lp, jt) : jt];
     };
-    // The waves of a slice share out its tile: wave w of them takes rows 8 SL w .. + 8 SL - 1, four rows per load, and
-    // lane `lane` of load i fills position lane % 16 of row 8 SL w + 4 i + lane / 16.  Addresses are a wave-uniform
+    // The waves of a slice share out its tile: wave w of them takes the n = 64 SL / kWaves rows from n w, four rows per load, and
+    // lane `lane` of load i fills position lane % 16 of row n w + 4 i + lane / 16.  Addresses are a wave-uniform
     // 64-bit base (scalar arithmetic) plus a 32-bit lane offset that does not depend on the tile, except in the last
     // tile of a sequence, where rows past the end read the last row again (finite values; their softmax weights
     // are 0).  Sixteen rows on the permutation of K repeats itself, four rows on that of V.
-    constexpr int kLoads = 2 * SL;  // 1 KiB loads per wave and operand
+    constexpr int kLoads = SL * 16 / kWaves;  // 1 KiB loads per wave and operand
     constexpr int kOfs = kLoads < 4 ? kLoads : 4;
     const unsigned seq_row_bytes = (unsigned)__builtin_amdgcn_readfirstlane(lp.Hkv * kHeadDim * 2);  // [token][Hkv][D]
     const unsigned k_row_bytes = PAGED ? kHeadDim * 2u : seq_row_bytes;
     const unsigned long long k_page_bytes = (unsigned long long)heads_in_pool * kSlabBytes;
-    const int wave_row0 = (unit * 2 + wave % 2) * (8 * SL);
+    const int wave_row0 = (unit * 2 + wave % 2) * (kTile * SL / kWaves);
     const int krow0 = wave_row0 + lane / 16;  // row of load 0; load i takes row + 4 i
     unsigned kofs[kOfs];
 #pragma unroll
@@ -728,7 +766,7 @@ __device__ __forceinline__ void prefill_workgroup(
     auto entry_of = [&](int it) {
         if (MASKED && lst) {
             const int e = lst[it];
-            if (SL == 1) return e;
+            if (!ROWS) return e;
             const int jt = min(max(e, 0), iq);  // a row of the caller: anything outside the triangle is not kept
             return e == jt ? jt | (1 << kKeepShift) : jt;
         }
@@ -1144,7 +1182,7 @@ __global__ __launch_bounds__(kPrefillThreads, 512 / kPrefillThreads) void sparse
     LayerParams lp, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int* __restrict__ cu_seqlens, int batch, uint16_t* __restrict__ out,
     float* __restrict__ lse_out, int total_tokens, PrefillSchedule sched, PrefillMask mk, PrefillPaged pg) {
-    prefill_workgroup<T, MODE, BITS, SL, false>(lp, q, k, v, cu_seqlens, batch, out, lse_out, total_tokens, sched, mk, pg);
+    prefill_workgroup<T, MODE, BITS, SL, kWhole>(lp, q, k, v, cu_seqlens, batch, out, lse_out, total_tokens, sched, mk, pg);
 }
 // (a kernel of its own: the search for a piece takes scalar registers from the walk, 2 to 5 % of a launch of whole walks)
 template <class T, int BITS>
@@ -1152,7 +1190,20 @@ __global__ __launch_bounds__(kPrefillThreads, 512 / kPrefillThreads) void prefil
     LayerParams lp, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int* __restrict__ cu_seqlens, int batch, uint16_t* __restrict__ out,
     float* __restrict__ lse_out, int total_tokens, PrefillSchedule sched, PrefillMask mk, PrefillPaged pg) {
-    prefill_workgroup<T, kPaged, BITS, 1, true>(lp, q, k, v, cu_seqlens, batch, out, lse_out, total_tokens, sched, mk, pg);
+    prefill_workgroup<T, kPaged, BITS, 1, kCut>(lp, q, k, v, cu_seqlens, batch, out, lse_out, total_tokens, sched, mk, pg);
+}
+
+// Half workgroups: one does not have a compute unit to itself, so that its start and end, 5 us in which nothing else of it is under
+// way, and the time its wavefronts wait for each other at the end of a step go to the other's steps; short walks gain most, and
+// where heads of a group keep different tiles (listed masks) two share a walk more often than four.  It stages every tile for half
+// as many rows, which long walks pay for.  Whole and half, us: ten prompts of 327 tokens, 32 / 32 heads, 47 and 34; 16 of 527, 32 / 16,
+// 108 and 87; one of 4096, 32 / 8, 121 and 108; 16 of 77 .. 3001, 213 and 208; 65536, 15690 and 16220.
+template <class T, int MODE>
+__global__ __launch_bounds__(kPrefillThreads / 2, 2) void prefill_half_kernel(
+    LayerParams lp, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+    const int* __restrict__ cu_seqlens, int batch, uint16_t* __restrict__ out,
+    float* __restrict__ lse_out, int total_tokens, PrefillSchedule sched, PrefillMask mk, PrefillPaged pg) {
+    prefill_workgroup<T, MODE, 16, 1, kHalf>(lp, q, k, v, cu_seqlens, batch, out, lse_out, total_tokens, sched, mk, pg);
 }
 
 // Puts the pieces of cut walks together.  One workgroup per block and wavefront of its workgroups, one wavefront per 32
@@ -1246,6 +1297,7 @@ struct PrefillShape {
     int slices;
     bool fold[2];
     bool one_head;
+    bool half;   // workgroups of two units, two to a compute unit
     int pieces;  // of dense walks per (KV head, group of query heads), at most (PrefillPieces::target); 0: whole walks
 };
 
@@ -1255,7 +1307,9 @@ struct PrefillRows {
     int history_pages;  // bound of the key tiles in front of them, of every sequence; -1: none (a prompt)
 };
 
-int units_of(const PrefillShape& shape, int cls) { return shape.fold[cls] ? kPairs / shape.slices : kPairs; }
+int units_of(const PrefillShape& shape, int cls) {
+    return shape.half ? kPairs / 2 : shape.fold[cls] ? kPairs / shape.slices : kPairs;
+}
 // Query heads of a group that share a workgroup: they read the same keys, whole and at the same time, and all end on the
 // same diagonal tile, where query tiles side by side would not.  Query tiles make up the rest of the units.
 int heads_per_block(const LayerParams& lp, const PrefillShape& shape, int cls) {
@@ -1414,9 +1468,10 @@ bool may_cut(const LayerParams& lp, const PrefillRows& rows) {
 }
 
 // scratch: the launch may cut dense walks into pieces, so many that its workgroups are about one, two ... rounds of the chip.
-PrefillShape choose_shape(const LayerParams& lp, const PrefillRows& rows, bool quant, bool scratch) {
-    constexpr PrefillShape kShapes[] = {{1, {false, false}, false, 0}, {1, {false, false}, true, 0}, {2, {true, true}, true, 0},
-                                        {2, {true, true}, false, 0},   {2, {true, false}, false, 0}, {4, {true, true}, false, 0}};
+PrefillShape choose_shape(const LayerParams& lp, const PrefillRows& rows, bool quant, bool scratch, bool halves = true) {
+    constexpr PrefillShape kShapes[] = {{1, {false, false}, false, false, 0}, {1, {false, false}, true, false, 0},
+                                        {2, {true, true}, true, false, 0},    {2, {true, true}, false, false, 0},
+                                        {2, {true, false}, false, false, 0},  {4, {true, true}, false, false, 0}};
     constexpr int kCount = (int)(sizeof(kShapes) / sizeof(kShapes[0])), kRounds = 4;
     constexpr float kWeight[4] = {4.f, 1.f, 1.f, 1.f};
     const int n_stream = count_streaming(lp), heads[2] = {lp.Hkv - n_stream, n_stream};
@@ -1467,7 +1522,18 @@ PrefillShape choose_shape(const LayerParams& lp, const PrefillRows& rows, bool q
         if (i == 0 || score < best_score) best = i, best_score = score;
     }
     PrefillShape shape = kShapes[best < kCount ? best : 0];
-    if (best >= kCount) shape.pieces = pieces[best - kCount];
+    if (best >= kCount) {
+        shape.pieces = pieces[best - kCount];
+    } else if (halves && shape.slices == 1 && !quant) {
+        // The same walks by half workgroups (see prefill_half_kernel): the same sums in the same order, so the results are of
+        // the shape they were.  Over 160 batches of prompts half workgroups took 0.72 to 0.95 of the time where a dense walk is up to
+        // 30 tiles long on average, 0.84 to 1.01 up to 60, 0.92 to 1.03 beyond.  (Quantised pages are dequantised by every
+        // workgroup for itself, and half workgroups are twice as many.)
+        constexpr float kHalfWalkTiles = 60.f;
+        const PrefillShape half = {1, {false, false}, false, true, 0};
+        const ClassCost dense = class_cost(lp, half, rows, 0, heads[0], quant, 0, 0.f);
+        if (class_walks(lp, rows, prompt ? 0.f : (float)rows.history_pages, dense, 0).mid <= kHalfWalkTiles) shape = half;
+    }
     return shape;
 }
 
@@ -1490,14 +1556,22 @@ PrefillShape shape_within(const LayerParams& lp, const PrefillRows& rows, bool q
     return choose_shape(lp, rows, quant, false);
 }
 
-// Is a listed mask walked by the caller's rows as they are, four key slices to a unit, rather than by merged lists of four
-// query tiles?  `row`: mean number of tiles kept by a row of the lists.  How much neighbouring rows have in common is not
-// known here: merged lists are taken half way between a row and the union of four random ones, and the sliced walk has to be
-// quicker by a margin.  (5101 tokens at density 0.35, 8 / 2 heads: 119 us merged, 54 sliced; 588 tokens at 0.17, 32 / 16 heads:
-// 27 and 20; 519 tokens, twice, at 0.4: 28 and 32; a pattern of 65536 tokens whose rows agree: 16 and 24 ms.  A second launch
-// that walked blocks of little common row by row gained 2 to 9 % above 10000 tokens and lost up to 30 % below.)
-bool choose_sliced_rows(const LayerParams& lp, double tiles, double longest, double row) {
-    constexpr double kFixedUs = 7., kFoldedUs = 8., kStepUs = 2., kSlicedStepUs = 3.;  // of a workgroup, rounded up
+// How a listed mask is walked: by merged lists of four query tiles of a head, or by the caller's rows as they are, for a head
+// and a query tile at a time in four key slices, or by half workgroups, for two heads of a group where they have a mask in common.
+enum MaskWalk { kMergedRows, kRowSlices, kRowHalves };
+
+// `row`: mean number of tiles kept by a row of the lists.  How much neighbouring rows have in common is not known here: merged
+// lists are taken half way between a row and the union of four random ones, and a walk of single rows has to be quicker by a
+// margin.  Nor is it known which heads have a mask in common: in the order of their masks a group's heads make pairs, of which all
+// but one fewer than there are masks are of one mask, whoever has which.  (Merged, slices, halves: 12345 tokens at density 0.3, 32 / 8
+// heads, two masks in turn, 473, 530 and 329 us; 6330 tokens, twice, at 0.08, 64 / 8 heads, 466, 702 and 399; 5101 tokens at 0.35,
+// 8 / 2 heads, slices 54 where merged lists take 119; 519 tokens, twice, at 0.4, 32 and 28; a pattern of 65536 tokens whose rows
+// agree, 24 and 16 ms.  A second launch that walked blocks of little common row by row gained 2 to 9 % over merged lists above 10000
+// tokens and lost up to 30 % below.  Two heads to a row in two slices: 392 us at 12345 tokens, but 41 where halves take 47 at 2907,
+// twice, 8 / 2 heads; not kept for that.)
+MaskWalk choose_mask_walk(const LayerParams& lp, double tiles, double longest, double row, int masks) {
+    constexpr double kFixedUs = 7., kFoldedUs = 8., kStepUs = 2., kSlicedStepUs = 3., kHalfStartUs = 5.5, kHalfStepUs = 1.9,
+                     kAloneStepUs = 1.5, kNothingUs = 1.;  // of a workgroup, rounded up
     const double units = num_compute_units();
     auto launch_time = [&](double work, double last) { return std::max(last, work / units + 0.35 * last); };
     const int n_stream = count_streaming(lp);
@@ -1509,12 +1583,23 @@ bool choose_sliced_rows(const LayerParams& lp, double tiles, double longest, dou
                                                  kFixedUs + kStepUs * longest * joint);
     const double sliced = launch_time(dense * (kFoldedUs + kSlicedStepUs * row / 4) + stream * (kFoldedUs + kSlicedStepUs * band / 4),
                                       kFoldedUs + kSlicedStepUs * std::min(2 * row, longest) / 4);
-    return 1.15 * sliced < merged;
+    // two half workgroups to a compute unit; in groups of even size the second of a pair finds nothing to do where the first has both
+    const bool even = lp.group % 2 == 0;
+    const double pairs = even ? std::max(0., 1. - 2. * (masks - 1) / lp.group) : 0.;
+    auto halves_of = [&](double n, double joined, double steps) {
+        return n * (0.5 * joined * (kHalfStartUs + kHalfStepUs * steps) + (1. - joined) * (kHalfStartUs + kAloneStepUs * steps)) +
+               (even ? 0.5 * n * kNothingUs : 0.);
+    };
+    const double halves = launch_time(0.5 * (halves_of(dense, pairs, row) + halves_of(stream, even ? 1. : 0., band)),
+                                      kHalfStartUs + kAloneStepUs * std::min(2 * row, longest));
+    if (1.15 * std::min(sliced, halves) >= merged) return kMergedRows;
+    return halves < sliced ? kRowHalves : kRowSlices;
 }
 
-// max_rows: rows of the longest sequence; any_start: they may start anywhere inside a block.
+// max_rows: rows of the longest sequence; any_start: they may start anywhere inside a block; single_rows: a workgroup has one
+// query tile, whatever units that leaves without work.
 PrefillSchedule make_schedule(const LayerParams& lp, const PrefillShape& shape, int max_rows, int total_rows, bool any_start,
-                              int batch) {
+                              int batch, bool single_rows = false) {
     PrefillSchedule sched;
     sched.pieces = {nullptr, shape.pieces};
     for (int c = 0; c < 2; ++c) {
@@ -1523,7 +1608,7 @@ PrefillSchedule make_schedule(const LayerParams& lp, const PrefillShape& shape, 
         const int units = units_of(shape, c), heads = heads_per_block(lp, shape, c);
         hc.heads_per_block = heads;
         hc.qtiles_log2 = 0;
-        while ((heads << hc.qtiles_log2) < units) ++hc.qtiles_log2;
+        while (!single_rows && (heads << hc.qtiles_log2) < units) ++hc.qtiles_log2;
         const int rows = kTile << hc.qtiles_log2;
         // rows that start anywhere inside a block reach into one block more than their number needs
         hc.blocks_per_seq = (max_rows + rows - 1) / rows + (any_start ? 1 : 0);
@@ -1533,6 +1618,7 @@ PrefillSchedule make_schedule(const LayerParams& lp, const PrefillShape& shape, 
         if (hc.ordered) blocks = std::min(blocks, (long long)total_rows / rows + (any_start ? 2LL : 1LL) * batch);
         hc.blocks = (int)std::min(blocks, 0x7fffffffLL);
         if (c == 0 && shape.pieces) blocks = shape.pieces;
+        if (single_rows && shape.half && heads == 2) blocks *= 2;  // `again`
         hc.heads = 0;
         for (unsigned& w : hc.kv_head) w = 0;
         for (int hk = 0; hk < lp.Hkv; ++hk)
@@ -1591,9 +1677,20 @@ hipError_t launch_slices(const PrefillLaunch& a, int slices) {
     return hipGetLastError();
 }
 
+template <class T, int MODE>
+hipError_t launch_half(const PrefillLaunch& a) {
+    hipLaunchKernelGGL((prefill_half_kernel<T, MODE>), dim3(kXcds * (a.sched.cls[0].items_per_xcd + a.sched.cls[1].items_per_xcd)),
+                       dim3(kPrefillThreads / 2), 0, a.stream, *a.lp, a.q, a.k, a.v, a.cu_seqlens, a.batch, a.out, a.lse_out, a.total_tokens,
+                       a.sched, a.mk, a.pg);
+    return hipGetLastError();
+}
+
 // A launch over pages, in pieces if that is the shape.
 template <class T, int BITS>
 hipError_t launch_chunk(PrefillLaunch& a, const PrefillShape& shape, void* scratch) {
+    if constexpr (BITS == 16) {
+        if (shape.half) return launch_half<T, kPaged>(a);
+    }
     if (!shape.pieces) return launch_slices<T, kPaged, BITS>(a, shape.slices);
     a.sched.pieces.partials = reinterpret_cast<float*>(scratch);
     const HeadClass& dense = a.sched.cls[0];
@@ -1627,6 +1724,7 @@ hipError_t launch_prefill(const LayerParams& lp, const void* q, const void* k, c
     if (!mask) {
         const PrefillShape shape = choose_shape(lp, {batch, total_tokens, max_seqlen, -1}, false, false);
         a.sched = make_schedule(lp, shape, max_seqlen, total_tokens, false, batch);
+        if (shape.half) return launch_half<T, kPlain>(a);
         return launch_slices<T, kPlain, 16>(a, shape.slices);
     }
     PrefillMask& mk = a.mk;
@@ -1637,8 +1735,13 @@ hipError_t launch_prefill(const LayerParams& lp, const void* q, const void* k, c
     mk.rows_per_mask = mask->rows_per_mask;
     const double row = (double)mask->nnz / ((double)mask->num_masks * mask->rows_per_mask);
     const double tiles = (double)total_tokens / kTile + 0.5 * batch;  // half a tile of padding per sequence
-    if (choose_sliced_rows(lp, tiles, max_tiles, row)) {
-        a.sched = make_schedule(lp, {4, {true, true}, true, 0}, max_seqlen, total_tokens, false, batch);
+    const MaskWalk walk = choose_mask_walk(lp, tiles, max_tiles, row, mask->num_masks);
+    if (walk == kRowHalves) {
+        a.sched = make_schedule(lp, {1, {false, false}, false, true, 0}, max_seqlen, total_tokens, false, batch, true);
+        return launch_half<T, kMasked>(a);
+    }
+    if (walk == kRowSlices) {
+        a.sched = make_schedule(lp, {4, {true, true}, true, false, 0}, max_seqlen, total_tokens, false, batch);
         return launch_slices<T, kMasked, 16>(a, 4);
     }
     mk.blocks_per_seq = mask_blocks(max_seqlen);
@@ -1648,7 +1751,7 @@ hipError_t launch_prefill(const LayerParams& lp, const void* q, const void* k, c
                        (size_t)align16(max_tiles), stream, mk, cu_seqlens, batch);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    a.sched = make_schedule(lp, {1, {false, false}, true, 0}, max_seqlen, total_tokens, false, batch);
+    a.sched = make_schedule(lp, {1, {false, false}, true, false, 0}, max_seqlen, total_tokens, false, batch);
     return launch_slices<T, kMasked, 16>(a, 1);
 }
 
@@ -1685,8 +1788,8 @@ hipError_t preload_prefill_kernels() {
 }
 
 void prefill_shape(const LayerParams& lp, int batch, int total_rows, int max_rows, int pages, int kv_bits, int (&out)[4]) {
-    const PrefillShape shape = pages > 0 ? choose_shape(lp, chunk_rows(batch, total_rows, max_rows, pages), kv_bits != 16, false)
-                                         : choose_shape(lp, {batch, total_rows, max_rows, -1}, false, false);
+    const PrefillShape shape = pages > 0 ? choose_shape(lp, chunk_rows(batch, total_rows, max_rows, pages), kv_bits != 16, false, false)
+                                         : choose_shape(lp, {batch, total_rows, max_rows, -1}, false, false, false);
     out[0] = shape.slices;
     out[1] = shape.fold[0];
     out[2] = shape.fold[1];

@@ -1,0 +1,45 @@
+"""Masked prefill where two heads of a group share a workgroup and, if they have a mask in common, its rows (two key slices):
+masks given to the heads of a group in every way, streaming groups with listed masks, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from workloads import Workload
+
+from test_gpu_prefill_shapes import _check, _run, _sample
+
+pytestmark = pytest.mark.gpu
+
+ROWS = {
+    "few": lambda b, i: [j for j in range(i + 1) if (7 * j + 3 * i) % 5 == 0 or j == i],
+    "other": lambda b, i: [j for j in range(i + 1) if (j + i) % 3 == 0],  # the diagonal tile is kept by some rows only
+    "gaps": lambda b, i: [] if i % 4 == 3 else [j for j in range(i + 1) if j % 2 == 0 or j == i],  # rows that keep nothing
+}
+
+
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+@pytest.mark.parametrize("heads,kv_heads,lengths,masks,head_mask", [
+    (32, 8, (1500, 333), ("few", "other"), [-1] * 16 + [0, 1, 0, 1] * 4),         # two pairs, heads in turn
+    (32, 8, (1999,), ("few", "gaps"), [1] * 5 + [-1] * 11 + [0, 0, 0, 1, 1, 0, 1, 1, -1, 0, 1, -1, 0, 0, 0, 0]),
+    (16, 4, (1000, 65, 1), ("gaps",), [-1, 0, 0, -1, 0, 0, 0, 0, 0, -1, -1, -1, -1, 0, -1, 0]),  # one mask or none
+    (64, 8, (1300,), ("few", "other", "gaps"), [(5 * h + h // 7) % 4 - 1 for h in range(64)]),    # four pairs to a group
+    (24, 4, (2100, 700), ("other", "few", "gaps"), [(h * h) % 3 for h in range(24)]),             # three, listed masks on streaming heads
+    (4, 2, (3100,), ("few",), [0, 0, 0, 0]),
+])
+def test_two_heads_to_a_row(dtype, heads, kv_heads, lengths, masks, head_mask):
+    w = Workload(name="shared", batch=len(lengths), num_q_heads=heads, num_kv_heads=kv_heads, dtype=dtype,
+                 streaming_kv_heads=tuple(range(kv_heads // 2)), sink_tokens=64, local_tokens=256, seed=61)
+    pin, out, lse, (qts, rp, cl, rows) = _run(w, lengths, [ROWS[m] for m in masks], head_mask, past_diagonal=3)
+    tok = _sample(lengths, 30, 11)
+    t, h = np.repeat(tok, heads), np.tile(np.arange(heads, dtype=np.int32), len(tok))
+    ref, lse_ref = oracle.block_mask_prefill_rows(pin.q, pin.k, pin.v, pin.cu_seqlens, w.streaming_flags(), 64,
+                                                  w.sink_tokens, w.local_tokens, head_mask, qts, rp, cl, rows, t, h)
+    # rows that keep nothing: 0 and -inf on both sides (and out of the comparison of finite numbers)
+    at = torch.from_numpy(tok).long().to(out.device)
+    none = torch.from_numpy(np.isneginf(lse_ref.reshape(len(tok), heads))).to(out.device)
+    assert (lse.t()[at][none] == -np.inf).all() and (out[at][none] == 0).all() and torch.isfinite(lse.t()[at][~none]).all()
+    if none.any():
+        lse[:, at] = torch.where(none.t(), torch.zeros_like(lse[:, at]), lse[:, at])
+        lse_ref = np.where(np.isneginf(lse_ref), 0.0, lse_ref)
+    _check(w, lengths, pin, out, lse, ref, lse_ref, tok, f"masked prefill {dtype} {heads}/{kv_heads}")

@@ -59,3 +59,13 @@ def test_prefill_kernels_use_no_scratch(kernels):
     found = [k for name, k in kernels.items() if "sparse_prefill_kernel" in name]
     assert len(found) == 2 * (3 + 3 + 3 + 2 + 2)  # types, slices of each of the five kinds
     assert all(k[".private_segment_fixed_size"] == 0 and k[".vgpr_count"] <= 256 for k in found)
+
+
+def test_half_prefill_workgroups_go_two_to_a_compute_unit(kernels):
+    """Four wavefronts each, one to a SIMD, and no scratch; chunks in pieces: no scratch either."""
+    halves = [k for name, k in kernels.items() if "prefill_half_kernel" in name]
+    assert len(halves) == 2 * 3  # types, (prompts, listed masks, pages)
+    assert all(k[".vgpr_count"] <= 256 and k[".group_segment_fixed_size"] <= 80 * 1024 for k in halves)
+    pieces = [k for name, k in kernels.items() if "pieces_kernel" in name]
+    assert len(pieces) == 2 * (3 + 1)  # types, widths of the pages and the kernel that puts pieces together
+    assert all(k[".private_segment_fixed_size"] == 0 and k[".vgpr_count"] <= 256 for k in halves + pieces)
