@@ -306,7 +306,9 @@ int lserve_sparse_prefill_chunk_scratch(const lserve_attn_desc *desc, const lser
 /*
  * Bytes of scratch with which chunks of these sizes are quicker; 0: none, also on invalid arguments.  Few query rows over a
  * long history leave most of the chip idle; with scratch the walks over the history are cut into pieces that a workgroup each
- * works on, and a second kernel puts the pieces together.
+ * works on, and a second kernel puts the pieces together.  Many query rows over quantised pages have the history dequantised
+ * by every workgroup; with scratch it is turned into 16-bit pages once (up to 1 GiB of them; wider tables are left as they
+ * are).
  *   total_new, max_new_per_seq: as in the call
  *   pages      width of the page table; for lserve_sparse_prefill_paged min(width, ceil(max_seqlen / 64))
  */

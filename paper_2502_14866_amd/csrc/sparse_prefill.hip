@@ -410,6 +410,34 @@ __global__ __launch_bounds__(kWave) void merge_mask_rows_kernel(PrefillMask mk, 
     if (lane == 0) *count = total;
 }
 
+// Eight codes of a quantised row -> code * scale + zero -> eight values of the layer's 16-bit type.
+template <class T, int BITS> __device__ __forceinline__ uint4 dequantise8(uint2 codes, uint32_t scale_zero) {
+    const half2_t sz = __builtin_bit_cast(half2_t, scale_zero);
+    const float scale = (float)sz[0], zero = (float)sz[1];
+    uint32_t lo = codes.x, hi = codes.y;  // channels 0..3 and 4..7, one byte each
+    if constexpr (BITS == 4) {
+        hi = (codes.x >> 4) & 0x0f0f0f0fu;
+        lo = codes.x & 0x0f0f0f0fu;
+    }
+    if constexpr (std::is_same<T, F16>::value) {
+        // A code under the exponent byte 0x64 is the fp16 number 1024 + code, from which 1024 is taken off exactly; the
+        // packed fma then rounds code * scale + zero once, to fp16, at three instructions per two values.
+        const half2_t scale2 = {sz[0], sz[0]}, zero2 = {sz[1], sz[1]}, offset = {(_Float16)-1024.f, (_Float16)-1024.f};
+        auto pair = [&](uint32_t word, uint32_t select) {
+            const half2_t c = __builtin_bit_cast(half2_t, __builtin_amdgcn_perm(0x64646464u, word, select)) + offset;
+            return __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(c, scale2, zero2));
+        };
+        return make_uint4(pair(lo, 0x04010400u), pair(lo, 0x04030402u), pair(hi, 0x04010400u), pair(hi, 0x04030402u));
+    }
+    float x[8];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        x[j] = __builtin_fmaf((float)((lo >> (8 * j)) & 0xffu), scale, zero);
+        x[4 + j] = __builtin_fmaf((float)((hi >> (8 * j)) & 0xffu), scale, zero);
+    }
+    return pack8<T>(x);
+}
+
 template <class T> struct Ones;
 template <> struct Ones<F16> { static constexpr uint32_t pair = 0x3c003c00u; };
 template <> struct Ones<BF16> { static constexpr uint32_t pair = 0x3f803f80u; };
@@ -842,34 +870,6 @@ __device__ __forceinline__ void prefill_workgroup(
         voff[db] = (int)lds_slice + half * 1024 + rr * kVRowBytes + v_chunk_pos(rr, chunk) * 16 + 8 * (s16 % 2);
     }
 
-    // Quantised rows fetched for the tile in flight: eight codes -> code * scale + zero -> eight 16-bit values at the
-    // lane's place of the row in LDS (the place a direct load of the same row would have filled).
-    auto dequantise8 = [&](uint2 codes, uint32_t scale_zero) {
-        const half2_t sz = __builtin_bit_cast(half2_t, scale_zero);
-        const float scale = (float)sz[0], zero = (float)sz[1];
-        uint32_t lo = codes.x, hi = codes.y;  // channels 0..3 and 4..7, one byte each
-        if constexpr (BITS == 4) {
-            hi = (codes.x >> 4) & 0x0f0f0f0fu;
-            lo = codes.x & 0x0f0f0f0fu;
-        }
-        if constexpr (std::is_same<T, F16>::value) {
-            // A code under the exponent byte 0x64 is the fp16 number 1024 + code, from which 1024 is taken off exactly; the
-            // packed fma then rounds code * scale + zero once, to fp16, at three instructions per two values.
-            const half2_t scale2 = {sz[0], sz[0]}, zero2 = {sz[1], sz[1]}, offset = {(_Float16)-1024.f, (_Float16)-1024.f};
-            auto pair = [&](uint32_t word, uint32_t select) {
-                const half2_t c = __builtin_bit_cast(half2_t, __builtin_amdgcn_perm(0x64646464u, word, select)) + offset;
-                return __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(c, scale2, zero2));
-            };
-            return make_uint4(pair(lo, 0x04010400u), pair(lo, 0x04030402u), pair(hi, 0x04010400u), pair(hi, 0x04030402u));
-        }
-        float x[8];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            x[j] = __builtin_fmaf((float)((lo >> (8 * j)) & 0xffu), scale, zero);
-            x[4 + j] = __builtin_fmaf((float)((hi >> (8 * j)) & 0xffu), scale, zero);
-        }
-        return pack8<T>(x);
-    };
     auto store_staged = [&](unsigned char* dst, const Staged& staged) {
         if constexpr (QUANT) {
             if (staged.from <= 0) return;
@@ -877,7 +877,7 @@ __device__ __forceinline__ void prefill_workgroup(
             for (int i = 0; i < kLoads; ++i) {
                 if (min(krow0 + 4 * i, staged.left - 1) < staged.from)  // the lanes that fetch() gave codes
                     *reinterpret_cast<uint4*>(dst + lds_wave + i * 1024 + lane * 16) =
-                        dequantise8(staged.codes[i], staged.sz[i]);
+                        dequantise8<T, BITS>(staged.codes[i], staged.sz[i]);
             }
         }
     };
@@ -1283,6 +1283,69 @@ __global__ __launch_bounds__(256) void fold_pieces_kernel(LayerParams lp, const 
         lse_out[(size_t)h * total_tokens + start + row] = l > 0.f ? (m + __builtin_amdgcn_logf(l)) * kLn2 : -INFINITY;
 }
 
+// ---- quantised history as 16-bit pages ------------------------------------------------------------
+//
+// A chunk of many rows has every tile of a quantised history dequantised by every workgroup that walks it, next to the softmax
+// in the vector pipe: a step takes 2.21 us where 16-bit pages take 1.75.  With scratch for it the history is dequantised once,
+// into pages of the layer's type, and the chunk then walks those: the same values, rounded the same way.  Two chunks of 1500 and
+// 2048 tokens over 24001 of 8 bits, 32 / 8 heads: 930 -> 830 us, 40 of them for 98 MB of pages; 859 over 8966, five times, 64 / 8
+// heads: 672 -> 573; 1392 over 1055 of 4 bits, twice: 93 -> 83.
+struct ExpandedPages {
+    uint16_t *k, *v;            // [batch][max_pages][dense heads][64][D]
+    uint16_t *k_ring, *v_ring;  // [batch][ring][streaming heads][64][D]: sink and local pages
+    int *table, *ring_table;    // page and slot numbers of the above
+};
+
+// One workgroup per KV head, sequence and share of its pages; bound by memory (a slab of 8192 codes is 8.5 KB to read and 16 KB to
+// write).
+template <class T, int BITS>
+__global__ __launch_bounds__(256) void expand_pages_kernel(LayerParams lp, PagedParams kv, ExpandedPages to) {
+    const int hk = blockIdx.y, b = blockIdx.z, cached = kv.seq_lens[b], pages = ceil_div(cached, kTile);
+    const bool streaming = (lp.streaming_mask >> hk) & 1ull, ring = in_stream_pool(lp, kv, hk);
+    const int heads = streaming ? kv.stream_heads : lp.Hkv - kv.stream_heads;
+    const unsigned long long below = (1ull << hk) - 1ull;
+    const int rank = __popcll((streaming ? lp.streaming_mask : ~lp.streaming_mask) & below);
+    constexpr size_t kSlab = slab_chunks(kTile, BITS) * 16;
+    constexpr int kRowBytes = kHeadDim * BITS / 8;
+    const size_t page_bytes = (ring ? kv.stream_heads : kv.pool_heads) * kSlab, slab_in_page = pool_rank(lp, kv, hk, ring) * kSlab;
+    // pages a query of the chunk can reach: all, or the sink pages and the last local ones
+    const int first_local = streaming ? max(lp.sink_pages, pages - lp.local_pages) : 0;
+    const int sinks = streaming ? min(lp.sink_pages, pages) : 0, count = sinks + max(0, pages - first_local);
+    for (int i = blockIdx.x; i < count; i += gridDim.x) {
+        const int p = i < sinks ? i : first_local + i - sinks;
+        const int slot = streaming ? b * kv.ring + ring_slot(lp, p) : b * kv.max_pages + p;
+        const int from = ring ? kv.ring_table[(size_t)b * kv.ring + ring_slot(lp, p)] : kv.page_table[(size_t)b * kv.max_pages + p];
+        if (threadIdx.x == 0 && rank == 0) {
+            if (streaming)
+                to.ring_table[slot] = slot;
+            else
+                to.table[slot] = slot;
+        }
+        const int chunk = threadIdx.x % 16, row0 = threadIdx.x / 16;
+#pragma unroll
+        for (int side = 0; side < 2; ++side) {
+            const unsigned char* pool = reinterpret_cast<const unsigned char*>(side ? (ring ? kv.v_stream : kv.v_pool) : (ring ? kv.k_stream : kv.k_pool));
+            const unsigned char* slab = pool + (size_t)from * page_bytes + slab_in_page;
+            uint16_t* dst = (side ? (streaming ? to.v_ring : to.v) : (streaming ? to.k_ring : to.k)) + ((size_t)slot * heads + rank) * kTile * kHeadDim;
+            uint2 codes[4];
+            uint32_t sz[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int row = row0 + 16 * u;
+                const unsigned char* src = slab + row * kRowBytes + chunk * BITS;
+                if constexpr (BITS == 8)
+                    codes[u] = *reinterpret_cast<const uint2*>(src);
+                else
+                    codes[u] = make_uint2(*reinterpret_cast<const uint32_t*>(src), 0u);
+                sz[u] = reinterpret_cast<const uint32_t*>(slab + kTile * kRowBytes)[row];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)  // (rows past the end of the cache may hold anything: nobody reads them)
+                *reinterpret_cast<uint4*>(dst + (row0 + 16 * u) * kHeadDim + chunk * 8) = dequantise8<T, BITS>(codes[u], sz[u]);
+        }
+    }
+}
+
 // ---- host side -----------------------------------------------------------------------------------
 
 int count_streaming(const LayerParams& lp) {
@@ -1467,13 +1530,15 @@ bool may_cut(const LayerParams& lp, const PrefillRows& rows) {
            (long long)rows.total * dense * lp.group < (long long)num_compute_units() * kPairs * kTile;
 }
 
+constexpr float kWeight[4] = {4.f, 1.f, 1.f, 1.f};  // of the guesses
+
 // scratch: the launch may cut dense walks into pieces, so many that its workgroups are about one, two ... rounds of the chip.
-PrefillShape choose_shape(const LayerParams& lp, const PrefillRows& rows, bool quant, bool scratch, bool halves = true) {
+PrefillShape choose_shape(const LayerParams& lp, const PrefillRows& rows, bool quant, bool scratch, bool halves = true,
+                          float* times = nullptr) {
     constexpr PrefillShape kShapes[] = {{1, {false, false}, false, false, 0}, {1, {false, false}, true, false, 0},
                                         {2, {true, true}, true, false, 0},    {2, {true, true}, false, false, 0},
                                         {2, {true, false}, false, false, 0},  {4, {true, true}, false, false, 0}};
     constexpr int kCount = (int)(sizeof(kShapes) / sizeof(kShapes[0])), kRounds = 4;
-    constexpr float kWeight[4] = {4.f, 1.f, 1.f, 1.f};
     const int n_stream = count_streaming(lp), heads[2] = {lp.Hkv - n_stream, n_stream};
     const int units_per_xcd = std::max(1, num_compute_units() / kXcds);
     const bool prompt = rows.history_pages < 0, exact = prompt && (long long)rows.batch * rows.longest == rows.total;
@@ -1521,6 +1586,8 @@ PrefillShape choose_shape(const LayerParams& lp, const PrefillRows& rows, bool q
         }
         if (i == 0 || score < best_score) best = i, best_score = score;
     }
+    if (times)
+        for (int g = 0; g < guesses; ++g) times[g] = time[best][g] / (exact ? 1 : 2);
     PrefillShape shape = kShapes[best < kCount ? best : 0];
     if (best >= kCount) {
         shape.pieces = pieces[best - kCount];
@@ -1547,13 +1614,47 @@ PrefillRows chunk_rows(int batch, int total_new, int max_new_per_seq, int pages)
     return {batch, total_new, max_new_per_seq, std::max(0, pages - max_new_per_seq / kTile)};
 }
 
-// The shape of a launch that has this much scratch.
-PrefillShape shape_within(const LayerParams& lp, const PrefillRows& rows, bool quant, const void* scratch, size_t bytes) {
-    if (scratch && bytes > 0 && may_cut(lp, rows)) {
-        const PrefillShape shape = choose_shape(lp, rows, quant, true);
-        if (pieces_bytes(lp, shape) <= bytes) return shape;
+// Bytes of ExpandedPages, each array on a multiple of 256.
+constexpr size_t kMostExpanded = (size_t)1 << 30;
+size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
+struct ExpandedSizes {
+    size_t pool, ring, table, ring_table;
+    size_t all() const { return 2 * pool + 2 * ring + table + ring_table; }
+};
+ExpandedSizes expanded_sizes(const LayerParams& lp, int batch, int max_pages) {
+    const size_t slab = (size_t)kTile * kHeadDim * 2, n_stream = count_streaming(lp), ring = lp.sink_pages + lp.local_pages;
+    return {align256((size_t)batch * max_pages * (lp.Hkv - n_stream) * slab), align256((size_t)batch * ring * n_stream * slab),
+            align256((size_t)batch * max_pages * sizeof(int)), align256((size_t)batch * ring * sizeof(int))};
+}
+
+// How a launch over pages goes about its work, and the scratch it takes.
+struct ChunkPlan {
+    bool expand;  // quantised pages are turned into 16-bit ones first
+    PrefillShape shape;
+    size_t bytes;
+};
+// pages: width of the page table, or what max_seqlen leaves of it.
+ChunkPlan plan_chunk(const LayerParams& lp, const PrefillRows& rows, int pages, bool quant, bool scratch) {
+    if (!scratch) return {false, choose_shape(lp, rows, quant, false), 0};
+    const bool cut = may_cut(lp, rows);
+    const int dense = lp.Hkv - count_streaming(lp);
+    // Dequantising once takes the whole chip 13 ns a tile and head, doing it in the walk 1.8 ns a workgroup of it: eight workgroups.
+    const bool many = quant && dense > 0 && rows.history_pages >= 2 * kLeastSpanTiles && (long long)rows.total * lp.group >= 8LL * kPairs * kTile * rows.batch &&
+                      expanded_sizes(lp, rows.batch, pages).all() <= kMostExpanded;
+    if (!cut && !many) return {false, choose_shape(lp, rows, quant, false), 0};
+    float times[2][4];
+    const PrefillShape as_is = choose_shape(lp, rows, quant, cut, true, times[0]);
+    const ChunkPlan plan = {false, as_is, pieces_bytes(lp, as_is)};
+    if (!many) return plan;
+    const PrefillShape expanded = choose_shape(lp, rows, false, cut, true, times[1]);
+    constexpr float kTileUs = 0.013f, kExpandUs = 3.f;
+    float score[2] = {0.f, 0.f}, history = (float)rows.history_pages;
+    for (int g = 0; g < 4; ++g, history *= 0.25f) {
+        score[0] += kWeight[g];
+        score[1] += kWeight[g] * (times[1][g] + kExpandUs + kTileUs * history * rows.batch * dense) / times[0][g];
     }
-    return choose_shape(lp, rows, quant, false);
+    if (score[1] >= score[0]) return plan;
+    return {true, expanded, expanded_sizes(lp, rows.batch, pages).all() + pieces_bytes(lp, expanded)};
 }
 
 // How a listed mask is walked: by merged lists of four query tiles of a head, or by the caller's rows as they are, for a head
@@ -1772,12 +1873,47 @@ hipError_t launch_prefill_paged(const LayerParams& lp, const PagedParams& kv, co
     a.pg.v_new = reinterpret_cast<const uint16_t*>(v_new);
     a.stream = stream;
     const int pages = max_seqlen > 0 ? std::min(kv.max_pages, (max_seqlen - 1) / kTile + 1) : kv.max_pages;
-    const PrefillShape shape =
-        shape_within(lp, chunk_rows(kv.batch, total_new, max_new_per_seq, pages), kv.kv_bits != 16, workspace, workspace_bytes);
-    a.sched = make_schedule(lp, shape, max_new_per_seq, total_new, true, kv.batch);
-    if (kv.kv_bits == 8) return launch_chunk<T, 8>(a, shape, workspace);
-    if (kv.kv_bits == 4) return launch_chunk<T, 4>(a, shape, workspace);
-    return launch_chunk<T, 16>(a, shape, workspace);
+    const PrefillRows rows = chunk_rows(kv.batch, total_new, max_new_per_seq, pages);
+    ChunkPlan plan = plan_chunk(lp, rows, pages, kv.kv_bits != 16, workspace && workspace_bytes > 0);
+    if (plan.bytes > workspace_bytes) plan = plan_chunk(lp, rows, pages, kv.kv_bits != 16, false);
+    a.sched = make_schedule(lp, plan.shape, max_new_per_seq, total_new, true, kv.batch);
+    if (plan.expand) {
+        const ExpandedSizes size = expanded_sizes(lp, kv.batch, kv.max_pages);
+        unsigned char* at = reinterpret_cast<unsigned char*>(workspace);
+        auto take = [&](size_t bytes) {
+            unsigned char* p = at;
+            at += bytes;
+            return p;
+        };
+        ExpandedPages to;
+        to.k = reinterpret_cast<uint16_t*>(take(size.pool));
+        to.v = reinterpret_cast<uint16_t*>(take(size.pool));
+        to.k_ring = reinterpret_cast<uint16_t*>(take(size.ring));
+        to.v_ring = reinterpret_cast<uint16_t*>(take(size.ring));
+        to.table = reinterpret_cast<int*>(take(size.table));
+        to.ring_table = reinterpret_cast<int*>(take(size.ring_table));
+        workspace = at;
+        const dim3 grid(std::min(pages, 64), lp.Hkv, kv.batch);
+        if (kv.kv_bits == 8)
+            hipLaunchKernelGGL((expand_pages_kernel<T, 8>), grid, dim3(256), 0, stream, lp, kv, to);
+        else
+            hipLaunchKernelGGL((expand_pages_kernel<T, 4>), grid, dim3(256), 0, stream, lp, kv, to);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        PagedParams& pages16 = a.pg.kv;
+        pages16.k_pool = to.k;
+        pages16.v_pool = to.v;
+        pages16.page_table = to.table;
+        pages16.pool_heads = lp.Hkv - kv.stream_heads;
+        pages16.k_stream = kv.stream_heads ? to.k_ring : nullptr;
+        pages16.v_stream = kv.stream_heads ? to.v_ring : nullptr;
+        pages16.ring_table = to.ring_table;
+        pages16.kv_bits = 16;
+        return launch_chunk<T, 16>(a, plan.shape, workspace);
+    }
+    if (kv.kv_bits == 8) return launch_chunk<T, 8>(a, plan.shape, workspace);
+    if (kv.kv_bits == 4) return launch_chunk<T, 4>(a, plan.shape, workspace);
+    return launch_chunk<T, 16>(a, plan.shape, workspace);
 }
 
 }  // namespace
@@ -1797,8 +1933,7 @@ void prefill_shape(const LayerParams& lp, int batch, int total_rows, int max_row
 }
 
 size_t chunk_scratch_bytes(const LayerParams& lp, int batch, int total_rows, int max_rows, int pages, int kv_bits) {
-    const PrefillRows rows = chunk_rows(batch, total_rows, max_rows, pages);
-    return may_cut(lp, rows) ? pieces_bytes(lp, choose_shape(lp, rows, kv_bits != 16, true)) : 0;
+    return plan_chunk(lp, chunk_rows(batch, total_rows, max_rows, pages), pages, kv_bits != 16, true).bytes;
 }
 
 size_t paged_prefill_workspace_bytes(const LayerParams& lp, int batch, int max_pages) {
