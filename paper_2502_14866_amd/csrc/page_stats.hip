@@ -61,13 +61,96 @@ __global__ __launch_bounds__(kWave* kMaxLogical) void page_stats_kernel(LayerPar
     }
 }
 
+// Smaller and larger of two pairs of fp16.  (Written out: ahead of the compiler's own forms goes an instruction per operand that
+// quiets signalling not-a-numbers, which these do themselves.)
+__device__ __forceinline__ half2_t pk_min(half2_t a, half2_t b) {
+    half2_t r;
+    asm("v_pk_min_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ half2_t pk_max(half2_t a, half2_t b) {
+    half2_t r;
+    asm("v_pk_max_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
+// Smallest and largest of eight values (f: the same as numbers).
+template <class T> __device__ __forceinline__ void range8(const uint32_t (&)[4], const float (&f)[8], float& lo, float& hi) {
+    lo = hi = f[0];
+#pragma unroll
+    for (int i = 1; i < 8; ++i) {
+        lo = fminf(lo, f[i]);
+        hi = fmaxf(hi, f[i]);
+    }
+}
+template <> __device__ __forceinline__ void range8<F16>(const uint32_t (&w)[4], const float (&)[8], float& lo, float& hi) {
+    half2_t l = __builtin_bit_cast(half2_t, w[0]), h = l;
+#pragma unroll
+    for (int i = 1; i < 4; ++i) {
+        const half2_t x = __builtin_bit_cast(half2_t, w[i]);
+        l = pk_min(l, x);
+        h = pk_max(h, x);
+    }
+    lo = fminf((float)l[0], (float)l[1]);
+    hi = fmaxf((float)h[0], (float)h[1]);
+}
+
+// Running channel-wise maximum and minimum of rows, eight channels to a lane.
+template <class T> struct RowRange {
+    float hi[8], lo[8];
+    __device__ __forceinline__ RowRange() {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            hi[i] = -INFINITY;
+            lo[i] = INFINITY;
+        }
+    }
+    __device__ __forceinline__ void add(const uint4& x) {
+        const uint32_t w[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            hi[2 * i] = fmaxf(hi[2 * i], Elem<T>::lo(w[i]));
+            lo[2 * i] = fminf(lo[2 * i], Elem<T>::lo(w[i]));
+            hi[2 * i + 1] = fmaxf(hi[2 * i + 1], Elem<T>::hi(w[i]));
+            lo[2 * i + 1] = fminf(lo[2 * i + 1], Elem<T>::hi(w[i]));
+        }
+    }
+    __device__ __forceinline__ float largest(int i) const { return hi[i]; }
+    __device__ __forceinline__ float smallest(int i) const { return lo[i]; }
+};
+template <> struct RowRange<F16> {
+    half2_t hi[4], lo[4];
+    __device__ __forceinline__ RowRange() {
+        const _Float16 inf = (_Float16)INFINITY;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            hi[i] = half2_t{(_Float16)-inf, (_Float16)-inf};
+            lo[i] = half2_t{inf, inf};
+        }
+    }
+    __device__ __forceinline__ void add(const uint4& x) {
+        const uint32_t w[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            hi[i] = pk_max(hi[i], __builtin_bit_cast(half2_t, w[i]));
+            lo[i] = pk_min(lo[i], __builtin_bit_cast(half2_t, w[i]));
+        }
+    }
+    __device__ __forceinline__ float largest(int i) const { return (float)hi[i / 2][i % 2]; }
+    __device__ __forceinline__ float smallest(int i) const { return (float)lo[i / 2][i % 2]; }
+};
+
 // Asymmetric quantisation of one token row held by the 16 lanes of a DPP row, eight features per lane
-// (Sec. 3.2: scale factor and zero point of a token are stored next to its features), to codes 0 .. LEVELS:
-//   zero = fp16(min), scale = fp16((max - zero) / LEVELS), code = clamp(rint((x - zero) / scale), 0, LEVELS),
-// every step in IEEE fp32 (true divisions) so that the codes do not depend on the machine.  Yields the
-// lane's eight codes and the token's (scale, zero) pair as two fp16 in one word.
-template <class T, int LEVELS>
-__device__ __forceinline__ void quantize_row(const uint4& x, uint32_t (&c)[8], uint32_t& scale_zero) {
+// (Sec. 3.2: scale factor and zero point of a token are stored next to its features), to codes 0 .. levels = 2^BITS - 1:
+//   zero = fp16(min), scale = fp16((max - zero) / levels), code = clamp(rint((x - zero) / scale), 0, levels),
+// every step rounded as IEEE fp32 does, divisions too, so that the codes do not depend on the machine.
+// Yields the lane's eight codes and the token's (scale, zero) pair as two fp16 in one word.
+// The codes come packed as the pages keep them: 8 bits, one byte each, channels in order; 4 bits, byte j of the word holding
+// channel j in its low and channel 4 + j in its high half, so that masking out either half leaves four codes in the byte lanes
+// the 8-bit path uses.
+template <class T, int BITS>
+__device__ __forceinline__ void quantize_row(const uint4& x, uint2& packed, uint32_t& scale_zero) {
+    constexpr float kLevels = (float)((1 << BITS) - 1);
     const uint32_t w[4] = {x.x, x.y, x.z, x.w};
     float f[8];
 #pragma unroll
@@ -75,12 +158,8 @@ __device__ __forceinline__ void quantize_row(const uint4& x, uint32_t (&c)[8], u
         f[2 * i] = Elem<T>::lo(w[i]);
         f[2 * i + 1] = Elem<T>::hi(w[i]);
     }
-    float lo = f[0], hi = f[0];
-#pragma unroll
-    for (int i = 1; i < 8; ++i) {
-        lo = fminf(lo, f[i]);
-        hi = fmaxf(hi, f[i]);
-    }
+    float lo, hi;
+    range8<T>(w, f, lo, hi);
     lo = fminf(lo, dpp_f<kDppXor1>(lo));
     hi = fmaxf(hi, dpp_f<kDppXor1>(hi));
     lo = fminf(lo, dpp_f<kDppXor2>(lo));
@@ -92,42 +171,48 @@ __device__ __forceinline__ void quantize_row(const uint4& x, uint32_t (&c)[8], u
     constexpr float kBig = 65504.f;  // largest finite fp16
     const _Float16 zero_h = (_Float16)fminf(fmaxf(lo, -kBig), kBig);
     const float zero = (float)zero_h;
-    const _Float16 scale_h = (_Float16)fminf((hi - zero) / (float)LEVELS, kBig);
+    // (hi - zero) / levels: the product with the rounded reciprocal, corrected by its remainder, is the correctly rounded quotient
+    // (for 15 and 255 with every one of the 2^23 significands); an infinite range leaves no number here and the largest scale
+    // below, as the quotient would.
+    constexpr float kInverse = 1.f / kLevels;
+    const float range = hi - zero, q = range * kInverse;
+    const _Float16 scale_h = (_Float16)fminf(__builtin_fmaf(__builtin_fmaf(-q, kLevels, range), kInverse, q), kBig);
     const float scale = (float)scale_h;
     // code = rint of the fp32 quotient.  An IEEE division is some ten instructions, and eight of them per lane and row were
     // most of the write-back of quantised pages.  The product with the reciprocal is within 3 units in the last place of
     // the quotient, which for quotients up to 256 is less than 1e-4, so the two round to the same whole number unless the
     // product lies that close to a half.  That is two quotients in ten thousand, one lane in 600 (of eight quotients) and
-    // one wavefront in ten (of 512), which then divides.
+    // one wavefront in ten (of 512), which then divides.  (Where the product is not a number or not finite, neither is the
+    // quotient.)
     const float inv = __builtin_amdgcn_rcpf(scale);
-    float t[8];
-    bool close = false;
+    float t[8], off = 0.f;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const float x = (f[i] - zero) * inv;
-        t[i] = __builtin_rintf(x);
-        close |= !(fabsf(x - t[i]) < 0.4999f);  // also where the product is not a number
+    for (int i = 0; i < 8; i += 2) {
+        const float a = (f[i] - zero) * inv, b = (f[i + 1] - zero) * inv;
+        t[i] = __builtin_rintf(a);
+        t[i + 1] = __builtin_rintf(b);
+        off = fmaxf(fmaxf(off, fabsf(a - t[i])), fabsf(b - t[i + 1]));
     }
-    if (close) {
+    if (off >= 0.4999f) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) t[i] = __builtin_rintf((f[i] - zero) / scale);
     }
+    const float top = scale > 0.f ? kLevels : 0.f;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const float u = fminf(fmaxf(t[i], 0.f), (float)LEVELS);
-        c[i] = scale > 0.f ? (uint32_t)u : 0u;
-    }
+    for (int i = 0; i < 8; ++i) t[i] = __builtin_amdgcn_fmed3f(t[i], 0.f, top);  // 0 where there is no number
+    auto bytes4 = [](float a, float b, float c, float d) {
+        uint32_t u = __builtin_amdgcn_cvt_pk_u8_f32(a, 0, 0u);
+        u = __builtin_amdgcn_cvt_pk_u8_f32(b, 1, u);
+        u = __builtin_amdgcn_cvt_pk_u8_f32(c, 2, u);
+        return (uint32_t)__builtin_amdgcn_cvt_pk_u8_f32(d, 3, u);
+    };
+    if constexpr (BITS == 8)
+        packed = make_uint2(bytes4(t[0], t[1], t[2], t[3]), bytes4(t[4], t[5], t[6], t[7]));
+    else
+        packed = make_uint2(bytes4(__builtin_fmaf(t[4], 16.f, t[0]), __builtin_fmaf(t[5], 16.f, t[1]),
+                                   __builtin_fmaf(t[6], 16.f, t[2]), __builtin_fmaf(t[7], 16.f, t[3])), 0u);
     const half2_t sz = {scale_h, zero_h};
     scale_zero = __builtin_bit_cast(uint32_t, sz);
-}
-// One byte per code, features in order.
-__device__ __forceinline__ uint2 pack_codes8(const uint32_t (&c)[8]) {
-    return make_uint2(c[0] | (c[1] << 8) | (c[2] << 16) | (c[3] << 24), c[4] | (c[5] << 8) | (c[6] << 16) | (c[7] << 24));
-}
-// Two codes per byte: byte j of the word holds feature j in its low and feature 4 + j in its high half, so
-// that masking out either half leaves four codes in the byte lanes the 8-bit path uses.
-__device__ __forceinline__ uint32_t pack_codes4(const uint32_t (&c)[8]) {
-    return (c[0] | (c[4] << 4)) | ((c[1] | (c[5] << 4)) << 8) | ((c[2] | (c[6] << 4)) << 16) | ((c[3] | (c[7] << 4)) << 24);
 }
 
 // KV write-back with the statistics updated in the same pass (Sec. 3.2, Sec. 3.5.2): one workgroup per
@@ -172,52 +257,53 @@ __global__ __launch_bounds__(kWave* kMaxLogical) void append_kv_kernel(LayerPara
     kdst += ph * slab_chunks(lp.NP, BITS);
     vdst += ph * slab_chunks(lp.NP, BITS);
 
-    float vmax[8], vmin[8];
+    RowRange<T> range;
+    // Sixteen rows (a logical page, as a rule) at a time, all of them requested before the first is worked on.
+    constexpr int kRows = 4;  // per lane row
+    for (int tb = t0; tb < t1; tb += 4 * kRows) {
+        uint4 x[kRows], y[kRows];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        vmax[i] = -INFINITY;
-        vmin[i] = INFINITY;
-    }
-    for (int t = t0 + r; t < t1; t += 4) {
-        const size_t src = ((size_t)(src0 + t - s) * lp.Hkv + hk) * (kHeadDim / 8) + c;
-        const uint4 x = k_new[src];
-        const uint4 y = v_new[src];
-        const int slot = t - p * lp.NP;
-        if (BITS == 16) {
-            const size_t dst = (size_t)slot * (kHeadDim / 8) + c;
-            kdst[dst] = x;
-            vdst[dst] = y;
-        } else {
-            uint32_t ksz, vsz, kc[8], vc[8];
-            quantize_row<T, (1 << BITS) - 1>(x, kc, ksz);
-            quantize_row<T, (1 << BITS) - 1>(y, vc, vsz);
-            if (BITS == 8) {
-                reinterpret_cast<uint2*>(kdst)[(size_t)slot * (kHeadDim / 8) + c] = pack_codes8(kc);
-                reinterpret_cast<uint2*>(vdst)[(size_t)slot * (kHeadDim / 8) + c] = pack_codes8(vc);
-            } else {
-                reinterpret_cast<uint32_t*>(kdst)[(size_t)slot * (kHeadDim / 8) + c] = pack_codes4(kc);
-                reinterpret_cast<uint32_t*>(vdst)[(size_t)slot * (kHeadDim / 8) + c] = pack_codes4(vc);
-            }
-            if (c == 0) {  // the pairs follow the page's code rows
-                reinterpret_cast<uint32_t*>(kdst + lp.NP * (kHeadDim * BITS / 128))[slot] = ksz;
-                reinterpret_cast<uint32_t*>(vdst + lp.NP * (kHeadDim * BITS / 128))[slot] = vsz;
-            }
+        for (int u = 0; u < kRows; ++u) {
+            const int t = min(tb + 4 * u + r, t1 - 1);
+            const size_t src = ((size_t)(src0 + t - s) * lp.Hkv + hk) * (kHeadDim / 8) + c;
+            x[u] = k_new[src];
+            y[u] = v_new[src];
         }
-        const uint32_t w[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float a = Elem<T>::lo(w[i]), bb = Elem<T>::hi(w[i]);
-            vmax[2 * i] = fmaxf(vmax[2 * i], a);
-            vmin[2 * i] = fminf(vmin[2 * i], a);
-            vmax[2 * i + 1] = fmaxf(vmax[2 * i + 1], bb);
-            vmin[2 * i + 1] = fminf(vmin[2 * i + 1], bb);
+        for (int u = 0; u < kRows; ++u) {
+            const int t = tb + 4 * u + r;
+            if (t >= t1) continue;
+            const int slot = t - p * lp.NP;
+            const size_t dst = (size_t)slot * (kHeadDim / 8) + c;
+            if constexpr (BITS == 16) {
+                kdst[dst] = x[u];
+                vdst[dst] = y[u];
+            } else {
+                uint32_t ksz, vsz;
+                uint2 kc, vc;
+                quantize_row<T, BITS>(x[u], kc, ksz);
+                quantize_row<T, BITS>(y[u], vc, vsz);
+                if constexpr (BITS == 8) {
+                    reinterpret_cast<uint2*>(kdst)[dst] = kc;
+                    reinterpret_cast<uint2*>(vdst)[dst] = vc;
+                } else {
+                    reinterpret_cast<uint32_t*>(kdst)[dst] = kc.x;
+                    reinterpret_cast<uint32_t*>(vdst)[dst] = vc.x;
+                }
+                if (c == 0) {  // the pairs follow the page's code rows
+                    reinterpret_cast<uint32_t*>(kdst + lp.NP * (kHeadDim * BITS / 128))[slot] = ksz;
+                    reinterpret_cast<uint32_t*>(vdst + lp.NP * (kHeadDim * BITS / 128))[slot] = vsz;
+                }
+            }
+            range.add(x[u]);
         }
     }
     if (streaming) return;  // streaming heads are never scored
+    float vmax[8], vmin[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-        vmax[i] = rows4_max(vmax[i]);
-        vmin[i] = rows4_min(vmin[i]);
+        vmax[i] = rows4_max(range.largest(i));
+        vmin[i] = rows4_min(range.smallest(i));
     }
     if (r == 0) {
         uint4* st = reinterpret_cast<uint4*>(kv.stats) + ((ph * lp.g + j) * 2) * (kHeadDim / 8);
@@ -272,12 +358,13 @@ __global__ __launch_bounds__(256) void append_token_kernel(LayerParams lp, Paged
     if (BITS == 16) {
         dst[(size_t)slot * (kHeadDim / 8) + c] = x;
     } else {
-        uint32_t sz, code[8];
-        quantize_row<T, (1 << BITS) - 1>(x, code, sz);
+        uint32_t sz;
+        uint2 code;
+        quantize_row<T, BITS == 16 ? 8 : BITS>(x, code, sz);
         if (BITS == 8)
-            reinterpret_cast<uint2*>(dst)[(size_t)slot * (kHeadDim / 8) + c] = pack_codes8(code);
+            reinterpret_cast<uint2*>(dst)[(size_t)slot * (kHeadDim / 8) + c] = code;
         else
-            reinterpret_cast<uint32_t*>(dst)[(size_t)slot * (kHeadDim / 8) + c] = pack_codes4(code);
+            reinterpret_cast<uint32_t*>(dst)[(size_t)slot * (kHeadDim / 8) + c] = code.x;
         if (c == 0) reinterpret_cast<uint32_t*>(dst + lp.NP * (kHeadDim * BITS / 128))[slot] = sz;
     }
     if (!with_stats) return;
