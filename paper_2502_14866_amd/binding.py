@@ -1,4 +1,5 @@
-"""ctypes binding of liblserve.so: argument marshalling only, every step runs in the HIP kernels."""
+"""Binding of liblserve.so: argument marshalling only, every step runs in the HIP kernels.  The three calls of a decode step are
+marshalled natively (csrc/py_calls.cpp), the others by ctypes."""
 from __future__ import annotations
 
 import ctypes
@@ -12,6 +13,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 # LSERVE_LIBRARY points at another build of the same library (e.g. an instrumented one)
 _LIB_PATH = os.environ.get("LSERVE_LIBRARY") or os.path.join(_HERE, "liblserve.so")
 _lib = None
+_calls = None
 
 LSERVE_CALL_BUILD_PAGE_STATS = 0
 LSERVE_CALL_SELECT_PAGES = 1
@@ -133,6 +135,22 @@ def load_library():
     return _lib
 
 
+def _native():
+    """The native calls, bound to the loaded library."""
+    global _calls
+    if _calls is None:
+        lib = load_library()
+        try:
+            from . import _calls as calls
+        except ImportError as e:
+            raise ImportError("the binding's native calls (_calls.so) are missing: build them with "
+                              "`python -m paper_2502_14866_amd.build` (or __graft_entry__.build())") from e
+        calls.bind(*(ctypes.cast(f, ctypes.c_void_p).value
+                     for f in (lib.lserve_append_kv, lib.lserve_select_pages, lib.lserve_sparse_decode)))
+        _calls = calls
+    return _calls
+
+
 @dataclass
 class AttnDesc:
     """Mirror of lserve_attn_desc."""
@@ -154,6 +172,8 @@ class AttnDesc:
             self.num_q_heads, self.num_kv_heads, self.head_dim, self.page_size, self.logical_page_size,
             {torch.float16: 0, torch.bfloat16: 1}.get(self.dtype, -1), self.sink_tokens, self.local_tokens,
             ctypes.cast(self._flags, ctypes.POINTER(ctypes.c_uint8)), float(self.sm_scale))
+
+        self._address = ctypes.addressof(self._c)
 
     def c(self):
         return ctypes.byref(self._c)
@@ -187,9 +207,9 @@ class PagedKV:
         return ctypes.byref(self._c)
 
 
-# A decode step of a small batch is four calls of some ten microseconds of GPU work each, so the marshalling is kept to
-# what a call cannot do without: addresses travel as plain integers (the argument types make pointers of them), and the
-# current stream is asked for as a handle, without the stream object around it.
+# A decode step of a small batch is two or three calls of some ten microseconds of GPU work each, so the marshalling is kept to
+# what a call cannot do without: addresses travel as plain integers (the argument types make pointers of them), the
+# current stream is asked for as a handle, without the stream object around it, and the calls of the step itself are native.
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     if t is None:
         return None
@@ -241,19 +261,16 @@ def lserve_build_page_stats(desc: AttnDesc, kv: PagedKV, start_pos: Optional[tor
 
 def lserve_append_kv(desc: AttnDesc, kv: PagedKV, k_new: torch.Tensor, v_new: torch.Tensor, cu_new: torch.Tensor,
                      start_pos: torch.Tensor, max_new_per_seq: int, stream=None) -> None:
-    _check(load_library().lserve_append_kv(desc.c(), kv.c(), _ptr(k_new), _ptr(v_new), _ptr(cu_new), _ptr(start_pos),
-                                           max_new_per_seq, _stream(stream)), "lserve_append_kv")
+    _check((_calls or _native()).append(desc._address, kv, k_new, v_new, cu_new, start_pos, max_new_per_seq,
+                                        _stream(stream)), "lserve_append_kv")
 
 
 def lserve_select_pages(desc: AttnDesc, kv: PagedKV, q: torch.Tensor, budget_tokens: int,
                         sel_pages: torch.Tensor, sel_count: torch.Tensor, sel_seq_len: torch.Tensor,
                         scores_out: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None,
                         stream=None, stats_valid_len: Optional[torch.Tensor] = None) -> None:
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(load_library().lserve_select_pages(desc.c(), kv.c(), _ptr(q), budget_tokens, _ptr(stats_valid_len),
-                                              _ptr(sel_pages),
-                                              _ptr(sel_count), _ptr(sel_seq_len), _ptr(scores_out),
-                                              _ptr(workspace), ws_bytes, _stream(stream)), "lserve_select_pages")
+    _check((_calls or _native()).select(desc._address, kv, q, budget_tokens, stats_valid_len, sel_pages, sel_count, sel_seq_len,
+                                        scores_out, workspace, _stream(stream)), "lserve_select_pages")
 
 
 def lserve_chunk_scratch_bytes(desc: AttnDesc, batch: int, total_new: int, max_new_per_seq: int, pages: int,
@@ -357,11 +374,8 @@ def lserve_sparse_decode(desc: AttnDesc, kv: PagedKV, q: torch.Tensor, sel_pages
                          sel_count: Optional[torch.Tensor], sel_seq_len: Optional[torch.Tensor],
                          out: torch.Tensor, lse_out: Optional[torch.Tensor] = None,
                          workspace: Optional[torch.Tensor] = None, stream=None) -> None:
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    sel_stride = 0 if sel_pages is None else sel_pages.shape[-1]
-    _check(load_library().lserve_sparse_decode(desc.c(), kv.c(), _ptr(q), _ptr(sel_pages), _ptr(sel_count),
-                                               _ptr(sel_seq_len), sel_stride, _ptr(out), _ptr(lse_out),
-                                               _ptr(workspace), ws_bytes, _stream(stream)), "lserve_sparse_decode")
+    _check((_calls or _native()).decode(desc._address, kv, q, sel_pages, sel_count, sel_seq_len, out, lse_out, workspace,
+                                        _stream(stream)), "lserve_sparse_decode")
 
 
 def lserve_sparse_decode_noalloc(desc: AttnDesc, kv: PagedKV, q: torch.Tensor, sel_pages: Optional[torch.Tensor],

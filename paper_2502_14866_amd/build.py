@@ -1,4 +1,4 @@
-"""Builds liblserve.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree."""
+"""Builds liblserve.so (HIP kernels + C ABI) for gfx950 with hipcc, and the binding's native calls with g++, in-tree."""
 from __future__ import annotations
 
 import os
@@ -10,6 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD_DIR = os.path.join(HERE, "_build")
 LIB_PATH = os.path.join(HERE, "liblserve.so")
+CALLS_PATH = os.path.join(HERE, "_calls.so")  # the binding's native marshalling (host code only)
 
 SOURCES = ["lserve_api.hip", "page_stats.hip", "select_pages.hip", "sparse_decode.hip", "sparse_prefill.hip"]
 
@@ -38,11 +39,32 @@ def _compile(src: str, extra=()) -> str:
     return obj
 
 
+def _build_calls() -> str:
+    """py_calls.cpp against the Python and torch headers of this interpreter."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+
+    includes = [f"-I{d}" for d in cpp_extension.include_paths() + [sysconfig.get_paths()["include"]]]
+    libs = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *includes,
+           os.path.join(CSRC, "py_calls.cpp"), "-o", CALLS_PATH,
+           f"-L{libs}", f"-Wl,-rpath,{libs}", "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"{cmd[0]} failed for py_calls.cpp:\n{res.stderr[-4000:]}")
+    return CALLS_PATH
+
+
 def build_library(verbose: bool = False, extra_flags=()) -> str:
     """Compile every HIP source and link the shared library; always rebuilds."""
     os.makedirs(BUILD_DIR, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as pool:
+    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as pool:
+        calls = pool.submit(_build_calls)
         objs = list(pool.map(lambda s: _compile(s, extra_flags), SOURCES))
+        calls.result()
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB_PATH, *objs]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
