@@ -281,9 +281,9 @@ __device__ __forceinline__ BlockOrder block_order(const int* cu_seqlens, const i
 // nearly equal length, worked on by a workgroup each.  A piece leaves its unnormalised outputs, maxima and sums in
 // PrefillPieces::partials, and fold_pieces_kernel puts the pieces of a block together.  The span is the smallest that needs no
 // more pieces than the launch has workgroups for; every workgroup works it out from the lengths, which the host does not know.
-// Measured, whole walks in the best shape and pieces: 512 tokens over 32768, 32 / 8 heads, 372 and 161 us (7 pieces to a block:
-// 74 steps of 1.85 us with every compute unit at work, then 10 us to put 29 MB of pieces together); 17 over 42116, twice, 436 and
-// 65; 108 over 73893, 32 / 16 heads, 976 and 259.  Prompts are not cut: one of 4096 tokens takes 119 us whole and 124 or more in any
+// Measured, whole walks in the best shape and pieces: 512 tokens over 32768, 32 / 8 heads, 373 and 171 us (13 for the streaming
+// heads, see streams_apart; 8 pieces to a block: 65 steps of 1.85 us with every compute unit at work, then 11 us to put 33 MB of
+// pieces together); 17 over 42116, twice, 441 and 79; 108 over 73893, 32 / 16 heads, 982 and 267.  Prompts are not cut: one of 4096 tokens takes 119 us whole and 124 or more in any
 // number of pieces, one of 8192 313 and 340, because what they gain in balance (42 steps a compute unit where the longest walk has
 // 64) goes into the starts of the pieces and into putting them together.
 // A position in the launch stands for a piece: last pieces first (none is shorter than half a span), then the last but one,
@@ -1493,22 +1493,26 @@ float launch_time(const LayerParams& lp, const PrefillRows& rows, float history,
 }
 
 // The same with dense walks in up to `pieces` pieces per XCD (see PiecePlan): the time of a piece beside its steps, of
-// putting pieces together, and of a step where every compute unit is at work on keys of its own.  Fitted to 95 drawn chunks: the
-// pieces taken come to 0.60 of the time of whole walks over one half of them and 0.81 over the other, the best to 0.57 and 0.79.
+// putting pieces together, and of a step where every compute unit is at work on keys of its own.  Fitted to 95 drawn chunks with
+// streaming heads in the launch: the pieces taken came to 0.60 of the time of whole walks over one half of them and 0.81 over the
+// other, the best to 0.57 and 0.79.  In a launch of their own streaming heads cost 13 us more, and histories of less than some 10000
+// tokens stay whole (60 tokens over 3115, six times, 64 us where pieces took 45; 219 over 6972, 8 bits, 163 and 60).
 constexpr float kPieceUs = 0.5f, kFoldLaunchUs = 1.f, kFoldPieceUs = 0.15f, kCutStep = 1.07f;
 float cut_launch_time(const LayerParams& lp, const PrefillRows& rows, float history, const ClassCost (&c)[2], int units_per_xcd,
-                      float pieces) {
+                      float pieces, bool streams_apart) {
     const ClassWalks w[2] = {class_walks(lp, rows, history, c[0], 0), class_walks(lp, rows, history, c[1], 1)};
     const float work = c[0].count * w[0].mid;
     const float alike = w[0].hi / std::max(1.f, (float)(int)(pieces / c[0].count)), apart = work / (pieces - 0.5f * c[0].count);
     const float span = std::min(w[0].hi, std::max((float)kLeastSpanTiles, std::max(apart, apart + (alike - apart) * w[0].lo / w[0].hi)));
     const float count = std::max(c[0].count, std::min(pieces, work / span + 0.5f * c[0].count));
     const float longest = c[0].start + kCutStep * c[0].step * span + kPieceUs;
-    float t = std::max(longest, w[1].longest);
-    if (count + c[1].count > units_per_xcd) {
-        const float even = (count * (c[0].start + kPieceUs) + work * kCutStep * c[0].step + c[1].count * w[1].mean) / units_per_xcd;
-        t = std::max(t, even + std::max(kTailOfStream * w[1].longest, 0.3f * longest));
+    const float streams = streams_apart ? 0.f : c[1].count, last = streams_apart ? 0.f : w[1].longest;
+    float t = std::max(longest, last);
+    if (count + streams > units_per_xcd) {
+        const float even = (count * (c[0].start + kPieceUs) + work * kCutStep * c[0].step + streams * w[1].mean) / units_per_xcd;
+        t = std::max(t, even + std::max(kTailOfStream * last, 0.3f * longest));
     }
+    if (streams_apart) t += std::max(w[1].longest, c[1].count * w[1].mean / units_per_xcd) + kLaunchUs;  // a launch of their own
     return t + kLaunchUs + kFoldLaunchUs + kFoldPieceUs * count;
 }
 
@@ -1522,6 +1526,7 @@ float cut_launch_time(const LayerParams& lp, const PrefillRows& rows, float hist
 // sixteenth and a sixty-fourth of it (490 chunks: 1.5 % over the best shape with a tight table and 2.2 % with one 32 times as
 // wide; by the length of the table alone 1.1 and 3.3 %, and up to half the speed lost).  Where the number of blocks is an
 // estimate, near the end of a round of workgroups, so is the time: the mean of a few blocks less and a few more.
+
 // May it pay to cut the walks of these chunks into pieces?  A first look, for the host's time: not where the history is short
 // or whole walks fill the chip.
 bool may_cut(const LayerParams& lp, const PrefillRows& rows) {
@@ -1529,6 +1534,12 @@ bool may_cut(const LayerParams& lp, const PrefillRows& rows) {
     return dense > 0 && rows.batch <= kOrderedSeqs && rows.history_pages >= 3 * kLeastSpanTiles &&
            (long long)rows.total * dense * lp.group < (long long)num_compute_units() * kPairs * kTile;
 }
+
+// Where dense walks are cut, which is by workgroups of one slice, streaming heads keep the slices that the launch has with whole
+// walks, in a launch of their own if these are several.  Each slice rounds its weights relative to a maximum of its own, so
+// that many of the largest weights of a row are exact, which over the few keys of a streaming head tells: against 64 bits 2.78e-3
+// with four slices and 2.84e-3 with one (512 tokens over 32768, bf16; dense heads 2.99e-3 whole in four slices and 2.97e-3 in pieces).
+bool streams_apart(const LayerParams& lp, const PrefillShape& whole) { return whole.slices > 1 && lp.streaming_mask != 0; }
 
 constexpr float kWeight[4] = {4.f, 1.f, 1.f, 1.f};  // of the guesses
 
@@ -1549,12 +1560,15 @@ PrefillShape choose_shape(const LayerParams& lp, const PrefillRows& rows, bool q
     // pieces per (KV head, group of query heads), and per XCD, of launches of one, two ... rounds (0: not to be had)
     int pieces[kRounds] = {};
     float per_xcd[kRounds] = {};
+    PrefillShape whole = {1, {false, false}, false, false, 0};
+    if (scratch) whole = choose_shape(lp, rows, quant, false, false);
+    const bool apart = streams_apart(lp, whole);
     if (scratch) {
         const ClassCost dense = class_cost(lp, kShapes[0], rows, 0, heads[0], quant, 0, 0.f), stream = class_cost(lp, kShapes[0], rows, 1, heads[1], quant, -1, 0.f);
         const int per_block = lp.group / heads_per_block(lp, kShapes[0], 0), block = kTile * dense.qtiles;
         const long long blocks = std::min((long long)rows.batch * ((rows.longest + block - 1) / block + 1), (long long)rows.total / block + 2LL * rows.batch);
         for (int r = 0; r < kRounds; ++r) {
-            const int room = (r + 1) * units_per_xcd - (int)stream.count;
+            const int room = (r + 1) * units_per_xcd - (apart ? 0 : (int)stream.count);
             const int n = kXcds % heads[0] == 0 ? room / per_block * (kXcds / heads[0]) : room * kXcds / (heads[0] * per_block);
             if (room <= 0 || n < blocks + blocks / 4 || n > kMostPieces) continue;
             pieces[r] = n;
@@ -1567,11 +1581,11 @@ PrefillShape choose_shape(const LayerParams& lp, const PrefillRows& rows, bool q
             if (i < kCount ? i >= count : pieces[i - kCount] == 0) continue;
             const PrefillShape& shape = kShapes[i < kCount ? i : 0];
             const ClassCost c[2] = {class_cost(lp, shape, rows, 0, heads[0], quant, exact ? 0 : side, spread),
-                                    class_cost(lp, shape, rows, 1, heads[1], quant, exact ? 0 : side, spread)};
+                                    class_cost(lp, i >= kCount && apart ? whole : shape, rows, 1, heads[1], quant, exact ? 0 : side, spread)};
             float history = prompt ? 0.f : (float)rows.history_pages;
             for (int g = 0; g < guesses; ++g, history *= 0.25f)
                 time[i][g] += i < kCount ? launch_time(lp, rows, history, c, units_per_xcd)
-                                         : cut_launch_time(lp, rows, history, c, units_per_xcd, per_xcd[i - kCount]);
+                                         : cut_launch_time(lp, rows, history, c, units_per_xcd, per_xcd[i - kCount], apart);
         }
     }
     int best = 0;
@@ -1632,19 +1646,21 @@ struct ChunkPlan {
     bool expand;  // quantised pages are turned into 16-bit ones first
     PrefillShape shape;
     size_t bytes;
+    PrefillShape whole;  // of the streaming heads, if dense walks are cut
 };
 // pages: width of the page table, or what max_seqlen leaves of it.
 ChunkPlan plan_chunk(const LayerParams& lp, const PrefillRows& rows, int pages, bool quant, bool scratch) {
-    if (!scratch) return {false, choose_shape(lp, rows, quant, false), 0};
+    if (!scratch) return {false, choose_shape(lp, rows, quant, false), 0, {}};
     const bool cut = may_cut(lp, rows);
     const int dense = lp.Hkv - count_streaming(lp);
     // Dequantising once takes the whole chip 13 ns a tile and head, doing it in the walk 1.8 ns a workgroup of it: eight workgroups.
     const bool many = quant && dense > 0 && rows.history_pages >= 2 * kLeastSpanTiles && (long long)rows.total * lp.group >= 8LL * kPairs * kTile * rows.batch &&
                       expanded_sizes(lp, rows.batch, pages).all() <= kMostExpanded;
-    if (!cut && !many) return {false, choose_shape(lp, rows, quant, false), 0};
+    const PrefillShape whole = choose_shape(lp, rows, quant, false);
+    if (!cut && !many) return {false, whole, 0, whole};
     float times[2][4];
     const PrefillShape as_is = choose_shape(lp, rows, quant, cut, true, times[0]);
-    const ChunkPlan plan = {false, as_is, pieces_bytes(lp, as_is)};
+    const ChunkPlan plan = {false, as_is, pieces_bytes(lp, as_is), whole};
     if (!many) return plan;
     const PrefillShape expanded = choose_shape(lp, rows, false, cut, true, times[1]);
     constexpr float kTileUs = 0.013f, kExpandUs = 3.f;
@@ -1654,7 +1670,7 @@ ChunkPlan plan_chunk(const LayerParams& lp, const PrefillRows& rows, int pages, 
         score[1] += kWeight[g] * (times[1][g] + kExpandUs + kTileUs * history * rows.batch * dense) / times[0][g];
     }
     if (score[1] >= score[0]) return plan;
-    return {true, expanded, expanded_sizes(lp, rows.batch, pages).all() + pieces_bytes(lp, expanded)};
+    return {true, expanded, expanded_sizes(lp, rows.batch, pages).all() + pieces_bytes(lp, expanded), whole};
 }
 
 // How a listed mask is walked: by merged lists of four query tiles of a head, or by the caller's rows as they are, for a head
@@ -1749,7 +1765,7 @@ struct PrefillLaunch {
     const LayerParams* lp;
     const uint16_t *q, *k, *v;
     const int* cu_seqlens;
-    int batch, total_tokens;
+    int batch, total_tokens, max_rows;
     uint16_t* out;
     float* lse_out;
     PrefillSchedule sched;
@@ -1786,13 +1802,27 @@ hipError_t launch_half(const PrefillLaunch& a) {
     return hipGetLastError();
 }
 
-// A launch over pages, in pieces if that is the shape.
+// A launch of whole walks over pages.
 template <class T, int BITS>
-hipError_t launch_chunk(PrefillLaunch& a, const PrefillShape& shape, void* scratch) {
+hipError_t launch_whole(const PrefillLaunch& a, const PrefillShape& shape) {
     if constexpr (BITS == 16) {
         if (shape.half) return launch_half<T, kPaged>(a);
     }
-    if (!shape.pieces) return launch_slices<T, kPaged, BITS>(a, shape.slices);
+    return launch_slices<T, kPaged, BITS>(a, shape.slices);
+}
+
+// A launch over pages, in pieces if that is the shape.
+template <class T, int BITS>
+hipError_t launch_chunk(PrefillLaunch& a, const ChunkPlan& plan, void* scratch) {
+    if (!plan.shape.pieces) return launch_whole<T, BITS>(a, plan.shape);
+    if (streams_apart(*a.lp, plan.whole)) {
+        PrefillLaunch s = a;
+        s.sched = make_schedule(*a.lp, plan.whole, a.max_rows, a.total_tokens, true, a.batch);
+        s.sched.cls[0].items_per_xcd = 0;
+        a.sched.cls[1].items_per_xcd = 0;
+        const hipError_t e = launch_whole<T, BITS>(s, plan.whole);
+        if (e != hipSuccess) return e;
+    }
     a.sched.pieces.partials = reinterpret_cast<float*>(scratch);
     const HeadClass& dense = a.sched.cls[0];
     hipLaunchKernelGGL((prefill_pieces_kernel<T, BITS>), dim3(kXcds * (dense.items_per_xcd + a.sched.cls[1].items_per_xcd)),
@@ -1866,6 +1896,7 @@ hipError_t launch_prefill_paged(const LayerParams& lp, const PagedParams& kv, co
     a.cu_seqlens = cu_q;
     a.batch = kv.batch;
     a.total_tokens = total_new;
+    a.max_rows = max_new_per_seq;
     a.out = reinterpret_cast<uint16_t*>(out);
     a.lse_out = lse_out;
     a.pg.kv = kv;
@@ -1909,11 +1940,11 @@ hipError_t launch_prefill_paged(const LayerParams& lp, const PagedParams& kv, co
         pages16.v_stream = kv.stream_heads ? to.v_ring : nullptr;
         pages16.ring_table = to.ring_table;
         pages16.kv_bits = 16;
-        return launch_chunk<T, 16>(a, plan.shape, workspace);
+        return launch_chunk<T, 16>(a, plan, workspace);
     }
-    if (kv.kv_bits == 8) return launch_chunk<T, 8>(a, plan.shape, workspace);
-    if (kv.kv_bits == 4) return launch_chunk<T, 4>(a, plan.shape, workspace);
-    return launch_chunk<T, 16>(a, plan.shape, workspace);
+    if (kv.kv_bits == 8) return launch_chunk<T, 8>(a, plan, workspace);
+    if (kv.kv_bits == 4) return launch_chunk<T, 4>(a, plan, workspace);
+    return launch_chunk<T, 16>(a, plan, workspace);
 }
 
 }  // namespace

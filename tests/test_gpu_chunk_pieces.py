@@ -1,6 +1,6 @@
 """Chunks over histories long enough that their dense walks are cut into pieces (lserve_sparse_prefill_chunk_scratch): every form
 of cache, groups of heads that fill a workgroup or not, batches whose sequences differ in everything, sampled rows against the
-oracle, and the call without scratch beside it."""
+oracle, and the call without scratch beside it, whose streaming heads have the same bits."""
 import pytest
 import torch
 
@@ -9,15 +9,15 @@ import test_gpu_paged_shapes as paged
 pytestmark = pytest.mark.gpu
 
 CASES = [  # heads, KV heads, history, new tokens
-    (32, 8, (3000,), (1,)),                                  # one row
-    (32, 8, (4032,), (64,)),                                 # whole tiles
-    (32, 8, (4100, 4100), (190, 190)),                       # alike, off the tiles
-    (8, 8, (5000,), (300,)),                                 # no groups: a block is four tiles
-    (12, 2, (2500, 70), (130, 65)),                          # six heads per group: two of them and two tiles to a block
-    (12, 4, (0, 6000, 3, 700), (200, 17, 0, 64)),            # idle and empty sequences beside a long one
-    (64, 8, (2900,), (77,)),                                 # eight heads per group: two workgroups to a block
+    (32, 8, (12000,), (1,)),                                 # one row
+    (32, 8, (12096,), (64,)),                                # whole tiles
+    (32, 8, (14100, 14100), (190, 190)),                     # alike, off the tiles
+    (8, 8, (12000,), (300,)),                                # no groups: a block is four tiles
+    (12, 2, (13500, 70), (130, 65)),                         # six heads per group: two of them and two tiles to a block
+    (12, 4, (0, 22000, 3, 700), (200, 17, 0, 64)),           # idle and empty sequences beside a long one
+    (64, 8, (14900,), (77,)),                                # eight heads per group: two workgroups to a block
     # two sequences to some lanes, most of them idle (16-bit pages stay with whole walks)
-    (4, 2, tuple(977 * i % 6000 for i in range(66)), tuple(3 * int(i % 23 == 0) for i in range(66))),
+    (4, 2, tuple(977 * i % 600 + 40000 * int(i == 46) for i in range(66)), tuple(3 * int(i % 23 == 0) for i in range(66))),
 ]
 
 
@@ -48,12 +48,12 @@ def test_paged_prefill_in_pieces_repeats_itself_and_agrees_with_whole_walks():
     L.load_library()
     dev = torch.device("cuda:0")
     g = torch.Generator(device=dev).manual_seed(7)
-    n, new = 9000, 100
+    n, new = 20000, 100
     rnd = lambda *s: torch.randn(s, generator=g, device=dev).to(torch.float16)
-    k, v, q = rnd(141, 8, 64, 128), rnd(141, 8, 64, 128), rnd(new, 32, 128)
+    k, v, q = rnd(313, 8, 64, 128), rnd(313, 8, 64, 128), rnd(new, 32, 128)
     desc = L.AttnDesc(32, 8, [1, 1, 1, 1, 0, 0, 0, 0])
     i32 = lambda a: torch.tensor(a, dtype=torch.int32, device=dev)
-    kv = L.PagedKV(k, v, None, torch.randperm(141, generator=g, device=dev).to(torch.int32).reshape(1, -1), i32([n]))
+    kv = L.PagedKV(k, v, None, torch.randperm(313, generator=g, device=dev).to(torch.int32).reshape(1, -1), i32([n]))
     outs = []
     for i in range(6):
         out, lse = torch.full_like(q, float("nan")), torch.full((32, new), float("nan"), device=dev)
@@ -63,6 +63,9 @@ def test_paged_prefill_in_pieces_repeats_itself_and_agrees_with_whole_walks():
     torch.cuda.synchronize()
     for out, lse in outs[1:5]:
         assert torch.equal(out, outs[0][0]) and torch.equal(lse, outs[0][1])
+    # streaming heads keep the slices of the launch without scratch
+    assert torch.equal(outs[5][0][:, :16], outs[0][0][:, :16]) and torch.equal(outs[5][1][:16], outs[0][1][:16])
+    assert not torch.equal(outs[5][1][16:], outs[0][1][16:])
     # weights and outputs are rounded to fp16 on both sides: 2^-11 of the largest output twice
     assert (outs[5][0].float() - outs[0][0].float()).abs().max() <= 2 ** -10 * outs[0][0].float().abs().max()
     assert (outs[5][1] - outs[0][1]).abs().max() <= 1e-5 * outs[0][1].abs().max()
