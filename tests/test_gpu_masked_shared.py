@@ -1,5 +1,5 @@
-"""Masked prefill where two heads of a group share a workgroup and, if they have a mask in common, its rows (two key slices):
-masks given to the heads of a group in every way, streaming groups with listed masks, against the oracle."""
+"""Masked prefill by half workgroups (and, in the last case, by key slices): two heads of a group share one if they have a mask in
+common.  Masks given to the heads of a group in every way, streaming groups with listed masks, groups of odd size, against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -25,6 +25,7 @@ ROWS = {
     (16, 4, (1000, 65, 1), ("gaps",), [-1, 0, 0, -1, 0, 0, 0, 0, 0, -1, -1, -1, -1, 0, -1, 0]),  # one mask or none
     (64, 8, (1300,), ("few", "other", "gaps"), [(5 * h + h // 7) % 4 - 1 for h in range(64)]),    # four pairs to a group
     (24, 4, (2100, 700), ("other", "few", "gaps"), [(h * h) % 3 for h in range(24)]),             # three, listed masks on streaming heads
+    (24, 8, (2500, 70), ("few",), [-1] * 7 + [0] * 17),                                            # three heads to a group
     (4, 2, (3100,), ("few",), [0, 0, 0, 0]),
 ])
 def test_two_heads_to_a_row(dtype, heads, kv_heads, lengths, masks, head_mask):
