@@ -172,11 +172,12 @@ __device__ __forceinline__ void quantize_row(const uint4& x, uint2& packed, uint
     const _Float16 zero_h = (_Float16)fminf(fmaxf(lo, -kBig), kBig);
     const float zero = (float)zero_h;
     // (hi - zero) / levels: the product with the rounded reciprocal, corrected by its remainder, is the correctly rounded quotient
-    // (for 15 and 255 with every one of the 2^23 significands); an infinite range leaves no number here and the largest scale
-    // below, as the quotient would.
+    // (for 15 and 255 with every one of the 2^23 significands); an infinite range, whose remainder is not a number, is its own
+    // quotient (of either sign: rows of nothing but -inf have -inf - zero).
     constexpr float kInverse = 1.f / kLevels;
     const float range = hi - zero, q = range * kInverse;
-    const _Float16 scale_h = (_Float16)fminf(__builtin_fmaf(__builtin_fmaf(-q, kLevels, range), kInverse, q), kBig);
+    const float quotient = fabsf(range) == INFINITY ? range : __builtin_fmaf(__builtin_fmaf(-q, kLevels, range), kInverse, q);
+    const _Float16 scale_h = (_Float16)fminf(quotient, kBig);
     const float scale = (float)scale_h;
     // code = rint of the fp32 quotient.  An IEEE division is some ten instructions, and eight of them per lane and row were
     // most of the write-back of quantised pages.  The product with the reciprocal is within 3 units in the last place of
