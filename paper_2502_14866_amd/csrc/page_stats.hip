@@ -61,8 +61,10 @@ __global__ __launch_bounds__(kWave* kMaxLogical) void page_stats_kernel(LayerPar
     }
 }
 
-// Smaller and larger of two pairs of fp16.  (Written out: ahead of the compiler's own forms goes an instruction per operand that
-// quiets signalling not-a-numbers, which these do themselves.)
+// Smaller and larger of two pairs of fp16, and a pair with its signalling not-a-numbers quieted.  The first two return the other
+// operand for a quiet not-a-number, but the quieted one itself for a signalling one, which would drop what the range held before:
+// what comes from memory goes through quiet() first.  (Written out: ahead of the compiler's own forms goes such an instruction per
+// operand, results of the forms themselves among them, where one per loaded pair will do.)
 __device__ __forceinline__ half2_t pk_min(half2_t a, half2_t b) {
     half2_t r;
     asm("v_pk_min_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
@@ -72,6 +74,10 @@ __device__ __forceinline__ half2_t pk_max(half2_t a, half2_t b) {
     half2_t r;
     asm("v_pk_max_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
     return r;
+}
+__device__ __forceinline__ half2_t quiet(uint32_t w) {
+    const half2_t x = __builtin_bit_cast(half2_t, w);
+    return pk_max(x, x);
 }
 
 // Smallest and largest of eight values (f: the same as numbers).
@@ -84,10 +90,10 @@ template <class T> __device__ __forceinline__ void range8(const uint32_t (&)[4],
     }
 }
 template <> __device__ __forceinline__ void range8<F16>(const uint32_t (&w)[4], const float (&)[8], float& lo, float& hi) {
-    half2_t l = __builtin_bit_cast(half2_t, w[0]), h = l;
+    half2_t l = quiet(w[0]), h = l;
 #pragma unroll
     for (int i = 1; i < 4; ++i) {
-        const half2_t x = __builtin_bit_cast(half2_t, w[i]);
+        const half2_t x = quiet(w[i]);
         l = pk_min(l, x);
         h = pk_max(h, x);
     }
@@ -132,8 +138,9 @@ template <> struct RowRange<F16> {
         const uint32_t w[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            hi[i] = pk_max(hi[i], __builtin_bit_cast(half2_t, w[i]));
-            lo[i] = pk_min(lo[i], __builtin_bit_cast(half2_t, w[i]));
+            const half2_t v = quiet(w[i]);
+            hi[i] = pk_max(hi[i], v);
+            lo[i] = pk_min(lo[i], v);
         }
     }
     __device__ __forceinline__ float largest(int i) const { return (float)hi[i / 2][i % 2]; }

@@ -11,6 +11,7 @@ from test_gpu_quant import _unpack_rows
 pytestmark = pytest.mark.gpu
 
 INF = float("inf")
+SIGNALLING = {"fp16": 0x7d01, "bf16": 0x7fa1}  # quiet bit clear
 
 
 def _rows(dtype):
@@ -104,3 +105,16 @@ def _check(x, bits, dtype, one_by_one):
 @pytest.mark.parametrize("dtype", ["fp16", "bf16"])
 def test_rows_with_infinities_and_not_a_numbers(dtype, bits, one_by_one):
     _check(_rows(dtype), bits, dtype, one_by_one)
+
+
+@pytest.mark.parametrize("one_by_one", [False, True])
+@pytest.mark.parametrize("dtype,bits", [("fp16", 16), ("fp16", 8), ("fp16", 4), ("bf16", 16)])
+def test_signalling_not_a_numbers_do_not_drop_what_came_before(dtype, bits, one_by_one):
+    """The extremes of a row in front of one in the same lane, those of a channel in rows above one."""
+    x = torch.randn((23, 128), generator=torch.Generator().manual_seed(8)).to(_rows(dtype).dtype)
+    x[0, 40], x[0, 41], x[3, 8], x[3, 9], x[5, 126], x[2, :] = -50.0, 60.0, -70.0, 80.0, 90.0, -33.0
+    raw = x.view(torch.int16)
+    for r, c in [(0, 42), (0, 43), (3, 10), (3, 15), (5, 127), (6, 7), (16, 100), (20, 100)] + [(6, c) for c in range(64, 96)]:
+        raw[r, c] = SIGNALLING[dtype] if c % 2 else SIGNALLING[dtype] - 0x8000
+    raw[22] = SIGNALLING[dtype]
+    _check(x, bits, dtype, one_by_one)
