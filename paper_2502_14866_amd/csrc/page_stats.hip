@@ -223,14 +223,6 @@ __device__ __forceinline__ void quantize_row(const uint4& x, uint2& packed, uint
     scale_zero = __builtin_bit_cast(uint32_t, sz);
 }
 
-// A row on its way to its page, past the last-level cache: a write-back is as many bytes in as out, and what comes in has been
-// written just before.  (65536 tokens of 16 bits, 8 KV heads, 537 MB: 118 -> 96 us; loads past the cache as well 109, and 5 us
-// slower where the rows are in it: 35K tokens into 4-bit pages 52 -> 58.)
-__device__ __forceinline__ void store_streaming(uint4* p, const uint4& x) {
-    typedef uint32_t words __attribute__((ext_vector_type(4)));
-    __builtin_nontemporal_store(words{x.x, x.y, x.z, x.w}, reinterpret_cast<words*>(p));
-}
-
 // KV write-back with the statistics updated in the same pass (Sec. 3.2, Sec. 3.5.2): one workgroup per
 // (physical page touched by the new tokens, KV head, sequence), one wavefront per logical page.  New
 // rows are copied into both pools with 16-byte accesses; for non-streaming heads the wave folds the
@@ -292,8 +284,8 @@ __global__ __launch_bounds__(kWave* kMaxLogical) void append_kv_kernel(LayerPara
             const int slot = t - p * lp.NP;
             const size_t dst = (size_t)slot * (kHeadDim / 8) + c;
             if constexpr (BITS == 16) {
-                store_streaming(kdst + dst, x[u]);
-                store_streaming(vdst + dst, y[u]);
+                kdst[dst] = x[u];
+                vdst[dst] = y[u];
             } else {
                 uint32_t ksz, vsz;
                 uint2 kc, vc;
