@@ -436,6 +436,15 @@ int lserve_probe_prefill_shape(const lserve_attn_desc *desc, int32_t batch, int3
                                int32_t pages, int32_t kv_bits, int32_t *shape);
 
 /*
+ * The same for lserve_sparse_prefill_masked with a mask of these sizes.
+ *   walk       HOST, out: 0: the lists of four neighbouring query tiles are merged and walked together; 1: the caller's rows are
+ *              walked one by one, in four key slices; 2: likewise in one slice, for two heads of a group where they have a
+ *              mask in common.  Rows of 0 and 2 have the same bits.
+ */
+int lserve_probe_mask_walk(const lserve_attn_desc *desc, int32_t batch, int32_t total_tokens, int32_t max_seqlen,
+                           int32_t num_masks, int32_t rows_per_mask, int32_t nnz, int32_t *walk);
+
+/*
  * Bytes of device workspace a call needs (Sec. 3.6 / 3.5.2 calls keep partial results there).
  *   batch, max_pages_per_seq: as in lserve_paged_kv (ignored for prefill)
  *   sel_stride_or_budget_pages: K for select, sel_stride for decode (ignored otherwise)

@@ -26,6 +26,7 @@ from .binding import (  # noqa: F401
     lserve_init,
     lserve_last_hip_error,
     lserve_probe_decode_read,
+    lserve_probe_mask_walk,
     lserve_probe_prefill_shape,
     lserve_select_pages,
     lserve_sparse_decode,

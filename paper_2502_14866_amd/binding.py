@@ -41,6 +41,7 @@ EXPORTED_SYMBOLS = (
     "lserve_sparse_decode_noalloc",
     "lserve_probe_decode_read",
     "lserve_probe_prefill_shape",
+    "lserve_probe_mask_walk",
 )
 
 
@@ -126,6 +127,8 @@ def load_library():
         lib.lserve_probe_decode_read.restype = ctypes.c_int
         lib.lserve_probe_prefill_shape.argtypes = [dp, i32, i32, i32, i32, i32, ctypes.POINTER(i32)]
         lib.lserve_probe_prefill_shape.restype = ctypes.c_int
+        lib.lserve_probe_mask_walk.argtypes = [dp, i32, i32, i32, i32, i32, i32, ctypes.POINTER(i32)]
+        lib.lserve_probe_mask_walk.restype = ctypes.c_int
         lib.lserve_init.argtypes = []
         lib.lserve_init.restype = ctypes.c_int
         for name in ("lserve_build_page_stats", "lserve_select_pages", "lserve_sparse_prefill",
@@ -401,3 +404,12 @@ def lserve_probe_prefill_shape(desc: AttnDesc, batch: int, total_rows: int, max_
     _check(load_library().lserve_probe_prefill_shape(desc.c(), batch, total_rows, max_rows, pages, kv_bits, shape),
            "lserve_probe_prefill_shape")
     return tuple(shape)
+
+
+def lserve_probe_mask_walk(desc: AttnDesc, batch: int, total_tokens: int, max_seqlen: int, num_masks: int, rows_per_mask: int,
+                           nnz: int) -> int:
+    """How a masked prefill walks its lists: 0 merged, 1 by rows in four key slices, 2 by rows in half workgroups."""
+    walk = ctypes.c_int32()
+    _check(load_library().lserve_probe_mask_walk(desc.c(), batch, total_tokens, max_seqlen, num_masks, rows_per_mask, nnz,
+                                                 ctypes.byref(walk)), "lserve_probe_mask_walk")
+    return walk.value

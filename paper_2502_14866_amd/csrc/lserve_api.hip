@@ -336,6 +336,19 @@ int lserve_probe_prefill_shape(const lserve_attn_desc* desc, int32_t batch, int3
     return LSERVE_OK;
 }
 
+int lserve_probe_mask_walk(const lserve_attn_desc* desc, int32_t batch, int32_t total_tokens, int32_t max_seqlen,
+                           int32_t num_masks, int32_t rows_per_mask, int32_t nnz, int32_t* walk) {
+    LayerParams lp;
+    const int rc = make_layer(desc, &lp);
+    if (rc) return rc;
+    if (!walk || batch <= 0 || total_tokens <= 0 || max_seqlen <= 0 || max_seqlen > total_tokens || num_masks <= 0 ||
+        rows_per_mask <= 0 || nnz < 0)
+        return LSERVE_ERR_INVALID_ARG;
+    if (lp.NP != 64) return LSERVE_ERR_UNSUPPORTED;
+    *walk = mask_walk(lp, batch, total_tokens, max_seqlen, num_masks, rows_per_mask, nnz);
+    return LSERVE_OK;
+}
+
 size_t lserve_paged_prefill_workspace_bytes(const lserve_attn_desc* desc, int32_t batch, int32_t max_pages_per_seq) {
     LayerParams lp;
     if (make_layer(desc, &lp) != LSERVE_OK || batch <= 0 || max_pages_per_seq <= 0) return 0;
