@@ -41,6 +41,7 @@ EXPORTED_SYMBOLS = (
     "lserve_sparse_decode_noalloc",
     "lserve_probe_decode_read",
     "lserve_probe_prefill_shape",
+    "lserve_probe_prefill_plan",
     "lserve_probe_mask_walk",
 )
 
@@ -127,6 +128,8 @@ def load_library():
         lib.lserve_probe_decode_read.restype = ctypes.c_int
         lib.lserve_probe_prefill_shape.argtypes = [dp, i32, i32, i32, i32, i32, ctypes.POINTER(i32)]
         lib.lserve_probe_prefill_shape.restype = ctypes.c_int
+        lib.lserve_probe_prefill_plan.argtypes = [dp, i32, i32, i32, i32, i32, i32, ctypes.POINTER(i32)]
+        lib.lserve_probe_prefill_plan.restype = ctypes.c_int
         lib.lserve_probe_mask_walk.argtypes = [dp, i32, i32, i32, i32, i32, i32, ctypes.POINTER(i32)]
         lib.lserve_probe_mask_walk.restype = ctypes.c_int
         lib.lserve_init.argtypes = []
@@ -404,6 +407,16 @@ def lserve_probe_prefill_shape(desc: AttnDesc, batch: int, total_rows: int, max_
     _check(load_library().lserve_probe_prefill_shape(desc.c(), batch, total_rows, max_rows, pages, kv_bits, shape),
            "lserve_probe_prefill_shape")
     return tuple(shape)
+
+
+def lserve_probe_prefill_plan(desc: AttnDesc, batch: int, total_rows: int, max_rows: int, pages: int = 0, kv_bits: int = 16,
+                              scratch: bool = True) -> dict:
+    """The rest of it: key ranges of a dense and of a streaming head's rows, half workgroups, pieces, streaming heads in a launch of
+    their own, expanded pages."""
+    plan = (ctypes.c_int32 * 6)()
+    _check(load_library().lserve_probe_prefill_plan(desc.c(), batch, total_rows, max_rows, pages, kv_bits, int(scratch), plan),
+           "lserve_probe_prefill_plan")
+    return dict(zip(("dense", "streaming", "half", "pieces", "apart", "expand"), plan))
 
 
 def lserve_probe_mask_walk(desc: AttnDesc, batch: int, total_tokens: int, max_seqlen: int, num_masks: int, rows_per_mask: int,

@@ -30,6 +30,9 @@ int num_compute_units();
 // of prompts with pages = 0, else of chunks whose sequences have up to `pages` pages of keys.
 void prefill_shape(const LayerParams& lp, int batch, int total_rows, int max_rows, int pages, int kv_bits, int (&out)[4]);
 
+// The rest of it (lserve_probe_prefill_plan).
+void prefill_plan(const LayerParams& lp, int batch, int total_rows, int max_rows, int pages, int kv_bits, bool scratch, int (&out)[6]);
+
 // How a launch under a listed mask walks it (lserve_probe_mask_walk).
 int mask_walk(const LayerParams& lp, int batch, int total_tokens, int max_seqlen, int masks, int rows_per_mask, int nnz);
 

@@ -336,6 +336,20 @@ int lserve_probe_prefill_shape(const lserve_attn_desc* desc, int32_t batch, int3
     return LSERVE_OK;
 }
 
+int lserve_probe_prefill_plan(const lserve_attn_desc* desc, int32_t batch, int32_t total_rows, int32_t max_rows, int32_t pages,
+                              int32_t kv_bits, int32_t scratch, int32_t* plan) {
+    LayerParams lp;
+    const int rc = make_layer(desc, &lp);
+    if (rc) return rc;
+    if (!plan || batch <= 0 || total_rows <= 0 || max_rows <= 0 || max_rows > total_rows || pages < 0) return LSERVE_ERR_INVALID_ARG;
+    if (kv_bits != 0 && kv_bits != 16 && kv_bits != 8 && kv_bits != 4) return LSERVE_ERR_INVALID_ARG;
+    if (lp.NP != 64) return LSERVE_ERR_UNSUPPORTED;
+    int out[6];
+    prefill_plan(lp, batch, total_rows, max_rows, pages, kv_bits == 0 ? 16 : kv_bits, scratch != 0, out);
+    for (int i = 0; i < 6; ++i) plan[i] = out[i];
+    return LSERVE_OK;
+}
+
 int lserve_probe_mask_walk(const lserve_attn_desc* desc, int32_t batch, int32_t total_tokens, int32_t max_seqlen,
                            int32_t num_masks, int32_t rows_per_mask, int32_t nnz, int32_t* walk) {
     LayerParams lp;

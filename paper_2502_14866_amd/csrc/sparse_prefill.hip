@@ -151,6 +151,7 @@ struct HeadClass {
 struct PrefillPieces {
     float* partials;  // kPieceFloats for every piece, pieces of a (KV head, group of query heads) next to each other
     int target;       // pieces of a (KV head, group of query heads) in the launch, at most
+    int least;        // of a block
 };
 struct PrefillSchedule {
     HeadClass cls[2];  // dense, streaming
@@ -286,6 +287,8 @@ __device__ __forceinline__ BlockOrder block_order(const int* cu_seqlens, const i
 // pieces together); 17 over 42116, twice, 441 and 79; 108 over 73893, 32 / 16 heads, 982 and 267.  Prompts are not cut: one of 4096 tokens takes 119 us whole and 124 or more in any
 // number of pieces, one of 8192 313 and 340, because what they gain in balance (42 steps a compute unit where the longest walk has
 // 64) goes into the starts of the pieces and into putting them together.
+// No block is fewer pieces than the key slices it has without scratch (PrefillPieces::least), however short its walk: the weights of
+// a row are rounded to 16 bits relative to the maximum of their piece or slice, and fewer of these make the error larger.
 // A position in the launch stands for a piece: last pieces first (none is shorter than half a span), then the last but one,
 // and so on, each kind farthest block first; whole blocks of less than a span come at the end.
 constexpr int kLeastSpanTiles = 8;  // key tiles: a piece costs about three steps of its own
@@ -303,23 +306,26 @@ __device__ __forceinline__ int divide(int x, int y, float reciprocal) {
 }
 
 struct PiecePlan {
-    int span, total;
-    // pieces of x blocks at the start of a sequence
-    static __device__ __forceinline__ int prefix(int x, int span, float reciprocal) {
+    int span, least, total;  // total: 0 where not even the smallest number of pieces has room (lengths beyond the stated bounds)
+    // pieces of block x, and of the x blocks at the start of a sequence
+    __device__ __forceinline__ int pieces_of(int x) const { return max(least, divide(x, span, __builtin_amdgcn_rcpf((float)span)) + 1); }
+    __device__ __forceinline__ int prefix(int x, float reciprocal) const {
         const int k = divide(x, span, reciprocal), r = x - k * span;
-        return span * (k * (k + 1) / 2) + r * (k + 1);
+        return k < least ? least * x : span * (k * (k + 1) / 2 + least * (least - 1) / 2) + r * (k + 1);
     }
-    static __device__ __forceinline__ int pieces_of_batch(const BlockOrder& o, int span) {
+    // blocks have a piece of this number from here on
+    __device__ __forceinline__ int level(int piece) const { return piece < least ? 0 : piece * span; }
+    __device__ __forceinline__ int pieces_of_batch(const BlockOrder& o) const {
         const float rec = __builtin_amdgcn_rcpf((float)span);
-        if (o.alike) return __builtin_amdgcn_readfirstlane(o.batch * min(prefix(o.hi0, span, rec) - prefix(o.lo0, span, rec), kManyPieces));
+        if (o.alike) return __builtin_amdgcn_readfirstlane(o.batch * min(prefix(o.hi0, rec) - prefix(o.lo0, rec), kManyPieces));
         int count = 0;
-        o.each([&](int g, int n) { count += n > 0 ? min(prefix(o.s.hi[g], span, rec) - prefix(o.s.lo[g], span, rec), kManyPieces) : 0; });
+        o.each([&](int g, int n) { count += n > 0 ? min(prefix(o.s.hi[g], rec) - prefix(o.s.lo[g], rec), kManyPieces) : 0; });
         return wave_count(count);
     }
-    static __device__ __forceinline__ PiecePlan make(const BlockOrder& o, int target, int least) {
-        // A walk of x is ceil(x / span) pieces: with a sum of w over n blocks, at least w / span in all and less than
-        // w / span + n.  (fp32 sums, so one to spare on either side.)
-        const int blocks = o.at_or_past(0);
+    static __device__ __forceinline__ PiecePlan make(const BlockOrder& o, const PrefillPieces& p, int least_span) {
+        // A walk of x is ceil(x / span) pieces, or `least`: with a sum of w over n blocks, at least w / span in all and less than
+        // w / span + least n.  (fp32 sums, so one to spare on either side.)
+        const int blocks = p.least * o.at_or_past(0);
         float w = 0.f;
         if (o.alike) {
             w = 0.5f * (float)o.batch * (float)(o.hi0 - o.lo0) * (float)(o.hi0 + o.lo0 + 1);
@@ -327,25 +333,29 @@ struct PiecePlan {
             o.each([&](int g, int n) { w += 0.5f * (float)n * (float)(o.s.hi[g] + o.s.lo[g] + 1); });
             w = rows4_sum(row16_sum(w));
         }
-        int low = max(least, (int)(w * __builtin_amdgcn_rcpf((float)target)) - 1) - 1;
-        int high = target > blocks ? (int)min(1e6f, w * __builtin_amdgcn_rcpf((float)(target - blocks))) + 2 : 1 << 20;
+        int low = max(least_span, (int)(w * __builtin_amdgcn_rcpf((float)p.target)) - 1) - 1;
+        int high = p.target > blocks ? (int)min(1e6f, w * __builtin_amdgcn_rcpf((float)(p.target - blocks))) + 2 : 1 << 20;
         low = __builtin_amdgcn_readfirstlane(low);
         high = __builtin_amdgcn_readfirstlane(max(min(high, max(o.top(), 1)), low + 1));
+        PiecePlan plan = {0, p.least, 0};
         while (high - low > 1) {
-            const int mid = (low + high) / 2;
-            if (pieces_of_batch(o, mid) <= target)
-                high = mid;
+            plan.span = (low + high) / 2;
+            if (plan.pieces_of_batch(o) <= p.target)
+                high = plan.span;
             else
-                low = mid;
+                low = plan.span;
         }
-        return {high, pieces_of_batch(o, high)};
+        plan.span = high;
+        plan.total = plan.pieces_of_batch(o);
+        if (plan.total > p.target) plan.total = 0;
+        return plan;
     }
     // Position `rank` of the launch, below `total`: which piece it is of which block in the order of blocks, and the slot of
     // the piece.
     __device__ __forceinline__ void find(const BlockOrder& o, int& rank, int& piece, int& slot) const {
         int before = total;  // pieces with numbers up to the one looked at
-        for (piece = __builtin_amdgcn_readfirstlane(divide(o.top() - 1, span, __builtin_amdgcn_rcpf((float)span))); piece > 0; --piece) {
-            const int n = o.at_or_past(piece * span);
+        for (piece = __builtin_amdgcn_readfirstlane(pieces_of(o.top() - 1)) - 1; piece > 0; --piece) {
+            const int n = o.at_or_past(level(piece));
             before -= n;
             if (rank < n) break;
             rank -= n;
@@ -513,16 +523,16 @@ __device__ __forceinline__ void prefill_workgroup(
         if (heads_per_block == 1) return;
         rank -= blocks;
     }
-    int piece = 0, pieces = 1, slot = 0, span = 0x7fffffff;  // of a cut walk: which piece of how many, and where it goes
+    int piece = 0, pieces = 1, slot = 0;  // of a cut walk: which piece of how many, and where it goes
+    PiecePlan plan = {0x7fffffff, 1, 0};
     if (second ? sched.cls[1].ordered : sched.cls[0].ordered) {
         const BlockOrder order =
             block_order(cu_seqlens, PAGED ? pg.kv.seq_lens : nullptr, PAGED && pg.k_new, batch, kTileLog2 + qtiles_log2);
         if (CUT && !second) {
-            const PiecePlan plan = PiecePlan::make(order, sched.pieces.target, kLeastSpanTiles >> qtiles_log2);
+            plan = PiecePlan::make(order, sched.pieces, kLeastSpanTiles >> qtiles_log2);
             if (rank >= plan.total) return;
             plan.find(order, rank, piece, slot);
             slot += (hidx * (lp.group / heads_per_block) + hg) * sched.pieces.target;
-            span = plan.span;
         }
         if (!order.find(rank, b, qblk)) return;
         // All of it comes out of lane arithmetic.  Left in a vector register, the block's position takes the length of the
@@ -532,7 +542,7 @@ __device__ __forceinline__ void prefill_workgroup(
         qblk = __builtin_amdgcn_readfirstlane(qblk);
         if (CUT) {
             piece = __builtin_amdgcn_readfirstlane(piece);
-            pieces = qblk >= span ? __builtin_amdgcn_readfirstlane(divide(qblk, span, __builtin_amdgcn_rcpf((float)span)) + 1) : 1;
+            if (!second) pieces = __builtin_amdgcn_readfirstlane(plan.pieces_of(qblk));
             slot = pieces > 1 ? slot : -1;
             asm volatile("" : "+v"(slot));  // wanted at the very end: a vector register, of which there are some left
         }
@@ -1217,10 +1227,10 @@ __global__ __launch_bounds__(256) void fold_pieces_kernel(LayerParams lp, const 
     const int wave = blockIdx.x % kPrefillWaves, rank = blockIdx.x / kPrefillWaves, hidx = blockIdx.y, hg = blockIdx.z;
     const int hk = (int)(hc.kv_head[hidx / 4] >> (8 * (hidx % 4))) & 0xff;
     const BlockOrder order = block_order(cu_seqlens, seq_lens, alongside, batch, kTileLog2 + hc.qtiles_log2);
-    const PiecePlan plan = PiecePlan::make(order, sched.pieces.target, kLeastSpanTiles >> hc.qtiles_log2);
+    const PiecePlan plan = PiecePlan::make(order, sched.pieces, kLeastSpanTiles >> hc.qtiles_log2);
     int b, qblk;
-    if (!order.find(rank, b, qblk)) return;
-    const int pieces = __builtin_amdgcn_readfirstlane(divide(qblk, plan.span, __builtin_amdgcn_rcpf((float)plan.span))) + 1;
+    if (plan.total == 0 || !order.find(rank, b, qblk)) return;
+    const int pieces = __builtin_amdgcn_readfirstlane(plan.pieces_of(qblk));
     if (pieces == 1) return;
     const int start = cu_seqlens[b], fresh = cu_seqlens[b + 1] - start;
     const int len = seq_lens[b] + (alongside ? fresh : 0), first = len - fresh;
@@ -1246,7 +1256,7 @@ __global__ __launch_bounds__(256) void fold_pieces_kernel(LayerParams lp, const 
             ml[u] = reinterpret_cast<const float2*>(src + 16 * kWave)[n];
 #pragma unroll
             for (int g4 = 0; g4 < 4; ++g4) x[u][g4] = src[(db * 4 + g4) * kWave + lane];
-            if (p + u + 1 < pieces) before += order.at_or_past((p + u) * plan.span);  // past the end: the last piece again, unused
+            if (p + u + 1 < pieces) before += order.at_or_past(plan.level(p + u));  // past the end: the last piece again, unused
         }
         float m_new = m;
 #pragma unroll
@@ -1362,6 +1372,7 @@ struct PrefillShape {
     bool one_head;
     bool half;   // workgroups of two units, two to a compute unit
     int pieces;  // of dense walks per (KV head, group of query heads), at most (PrefillPieces::target); 0: whole walks
+    int least;   // of a block (PrefillPieces::least)
 };
 
 // The queries of a launch as far as the host knows them.
@@ -1369,6 +1380,9 @@ struct PrefillRows {
     int batch, total, longest;
     int history_pages;  // bound of the key tiles in front of them, of every sequence; -1: none (a prompt)
 };
+
+// Key ranges, each with a maximum of its own, in which the sums of a row are taken.
+int slices_of(const PrefillShape& shape, int cls) { return shape.fold[cls] ? shape.slices : 1; }
 
 int units_of(const PrefillShape& shape, int cls) {
     return shape.half ? kPairs / 2 : shape.fold[cls] ? kPairs / shape.slices : kPairs;
@@ -1499,12 +1513,12 @@ float launch_time(const LayerParams& lp, const PrefillRows& rows, float history,
 // tokens stay whole (60 tokens over 3115, six times, 64 us where pieces took 45; 219 over 6972, 8 bits, 163 and 60).
 constexpr float kPieceUs = 0.5f, kFoldLaunchUs = 1.f, kFoldPieceUs = 0.15f, kCutStep = 1.07f;
 float cut_launch_time(const LayerParams& lp, const PrefillRows& rows, float history, const ClassCost (&c)[2], int units_per_xcd,
-                      float pieces, bool streams_apart) {
+                      float pieces, int least, bool streams_apart) {
     const ClassWalks w[2] = {class_walks(lp, rows, history, c[0], 0), class_walks(lp, rows, history, c[1], 1)};
     const float work = c[0].count * w[0].mid;
     const float alike = w[0].hi / std::max(1.f, (float)(int)(pieces / c[0].count)), apart = work / (pieces - 0.5f * c[0].count);
     const float span = std::min(w[0].hi, std::max((float)kLeastSpanTiles, std::max(apart, apart + (alike - apart) * w[0].lo / w[0].hi)));
-    const float count = std::max(c[0].count, std::min(pieces, work / span + 0.5f * c[0].count));
+    const float count = std::max(least * c[0].count, std::min(pieces, work / span + 0.5f * c[0].count));
     const float longest = c[0].start + kCutStep * c[0].step * span + kPieceUs;
     const float streams = streams_apart ? 0.f : c[1].count, last = streams_apart ? 0.f : w[1].longest;
     float t = std::max(longest, last);
@@ -1543,12 +1557,15 @@ bool streams_apart(const LayerParams& lp, const PrefillShape& whole) { return wh
 
 constexpr float kWeight[4] = {4.f, 1.f, 1.f, 1.f};  // of the guesses
 
-// scratch: the launch may cut dense walks into pieces, so many that its workgroups are about one, two ... rounds of the chip.
-PrefillShape choose_shape(const LayerParams& lp, const PrefillRows& rows, bool quant, bool scratch, bool halves = true,
-                          float* times = nullptr) {
-    constexpr PrefillShape kShapes[] = {{1, {false, false}, false, false, 0}, {1, {false, false}, true, false, 0},
-                                        {2, {true, true}, true, false, 0},    {2, {true, true}, false, false, 0},
-                                        {2, {true, false}, false, false, 0},  {4, {true, true}, false, false, 0}};
+// The shape of a launch: of whole walks, or with `cut` also in pieces, so many that its workgroups are about one, two ... rounds
+// of the chip.
+// uncut: the shape of the same call without scratch.  Streaming heads keep it where dense walks are cut, and no row's sums are taken in
+// fewer key ranges than there.
+PrefillShape choose_shape(const LayerParams& lp, const PrefillRows& rows, bool quant, const PrefillShape* uncut = nullptr, bool cut = false,
+                          bool halves = true, float* times = nullptr) {
+    constexpr PrefillShape kShapes[] = {{1, {false, false}, false, false, 0, 1}, {1, {false, false}, true, false, 0, 1},
+                                        {2, {true, true}, true, false, 0, 1},    {2, {true, true}, false, false, 0, 1},
+                                        {2, {true, false}, false, false, 0, 1},  {4, {true, true}, false, false, 0, 1}};
     constexpr int kCount = (int)(sizeof(kShapes) / sizeof(kShapes[0])), kRounds = 4;
     const int n_stream = count_streaming(lp), heads[2] = {lp.Hkv - n_stream, n_stream};
     const int units_per_xcd = std::max(1, num_compute_units() / kXcds);
@@ -1560,13 +1577,12 @@ PrefillShape choose_shape(const LayerParams& lp, const PrefillRows& rows, bool q
     // pieces per (KV head, group of query heads), and per XCD, of launches of one, two ... rounds (0: not to be had)
     int pieces[kRounds] = {};
     float per_xcd[kRounds] = {};
-    PrefillShape whole = {1, {false, false}, false, false, 0};
-    if (scratch) whole = choose_shape(lp, rows, quant, false, false);
-    const bool apart = streams_apart(lp, whole);
-    if (scratch) {
+    const bool apart = cut && streams_apart(lp, *uncut);
+    const int least = cut ? slices_of(*uncut, 0) : 1;
+    if (cut) {
         const ClassCost dense = class_cost(lp, kShapes[0], rows, 0, heads[0], quant, 0, 0.f), stream = class_cost(lp, kShapes[0], rows, 1, heads[1], quant, -1, 0.f);
         const int per_block = lp.group / heads_per_block(lp, kShapes[0], 0), block = kTile * dense.qtiles;
-        const long long blocks = std::min((long long)rows.batch * ((rows.longest + block - 1) / block + 1), (long long)rows.total / block + 2LL * rows.batch);
+        const long long blocks = least * std::min((long long)rows.batch * ((rows.longest + block - 1) / block + 1), (long long)rows.total / block + 2LL * rows.batch);
         for (int r = 0; r < kRounds; ++r) {
             const int room = (r + 1) * units_per_xcd - (apart ? 0 : (int)stream.count);
             const int n = kXcds % heads[0] == 0 ? room / per_block * (kXcds / heads[0]) : room * kXcds / (heads[0] * per_block);
@@ -1575,43 +1591,51 @@ PrefillShape choose_shape(const LayerParams& lp, const PrefillRows& rows, bool q
             per_xcd[r] = (float)(n * heads[0] * per_block) / kXcds;
         }
     }
+    auto allowed = [&](int i) {
+        if (i >= kCount) return pieces[i - kCount] > 0;
+        if (i >= count) return false;
+        for (int c = 0; c < 2; ++c)
+            if (uncut && heads[c] > 0 && slices_of(kShapes[i], c) < slices_of(*uncut, c)) return false;
+        return true;
+    };
     float time[kCount + kRounds][4] = {};
     for (int side = exact ? 0 : -1; side <= 1; side += 2) {
         for (int i = 0; i < kCount + kRounds; ++i) {
             if (i < kCount ? i >= count : pieces[i - kCount] == 0) continue;
             const PrefillShape& shape = kShapes[i < kCount ? i : 0];
             const ClassCost c[2] = {class_cost(lp, shape, rows, 0, heads[0], quant, exact ? 0 : side, spread),
-                                    class_cost(lp, i >= kCount && apart ? whole : shape, rows, 1, heads[1], quant, exact ? 0 : side, spread)};
+                                    class_cost(lp, i >= kCount && apart ? *uncut : shape, rows, 1, heads[1], quant, exact ? 0 : side, spread)};
             float history = prompt ? 0.f : (float)rows.history_pages;
             for (int g = 0; g < guesses; ++g, history *= 0.25f)
                 time[i][g] += i < kCount ? launch_time(lp, rows, history, c, units_per_xcd)
-                                         : cut_launch_time(lp, rows, history, c, units_per_xcd, per_xcd[i - kCount], apart);
+                                         : cut_launch_time(lp, rows, history, c, units_per_xcd, per_xcd[i - kCount], least, apart);
         }
     }
-    int best = 0;
+    int best = -1;
     float best_score = 0.f;
     for (int i = 0; i < kCount + kRounds; ++i) {
-        if (i < kCount ? i >= count : pieces[i - kCount] == 0) continue;
+        if (!allowed(i)) continue;
         float score = 0.f;
         for (int g = 0; g < guesses; ++g) {
-            float least = time[0][g];
-            for (int k = 1; k < count; ++k) least = std::min(least, time[k][g]);
-            score += kWeight[g] * time[i][g] / least;
+            float fastest = time[0][g];
+            for (int k = 1; k < count; ++k) fastest = std::min(fastest, time[k][g]);
+            score += kWeight[g] * time[i][g] / fastest;
         }
-        if (i == 0 || score < best_score) best = i, best_score = score;
+        if (best < 0 || score < best_score) best = i, best_score = score;
     }
     if (times)
         for (int g = 0; g < guesses; ++g) times[g] = time[best][g] / (exact ? 1 : 2);
     PrefillShape shape = kShapes[best < kCount ? best : 0];
     if (best >= kCount) {
         shape.pieces = pieces[best - kCount];
+        shape.least = least;
     } else if (halves && shape.slices == 1 && !quant) {
         // The same walks by half workgroups (see prefill_half_kernel): the same sums in the same order, so the results are of
         // the shape they were.  Over 160 batches of prompts half workgroups took 0.72 to 0.95 of the time where a dense walk is up to
         // 30 tiles long on average, 0.84 to 1.01 up to 60, 0.92 to 1.03 beyond.  (Quantised pages are dequantised by every
         // workgroup for itself, and half workgroups are twice as many.)
         constexpr float kHalfWalkTiles = 60.f;
-        const PrefillShape half = {1, {false, false}, false, true, 0};
+        const PrefillShape half = {1, {false, false}, false, true, 0, 1};
         const ClassCost dense = class_cost(lp, half, rows, 0, heads[0], quant, 0, 0.f);
         if (class_walks(lp, rows, prompt ? 0.f : (float)rows.history_pages, dense, 0).mid <= kHalfWalkTiles) shape = half;
     }
@@ -1646,23 +1670,23 @@ struct ChunkPlan {
     bool expand;  // quantised pages are turned into 16-bit ones first
     PrefillShape shape;
     size_t bytes;
-    PrefillShape whole;  // of the streaming heads, if dense walks are cut
+    PrefillShape uncut;  // without scratch; also of the streaming heads, if dense walks are cut
 };
-// pages: width of the page table, or what max_seqlen leaves of it.
-ChunkPlan plan_chunk(const LayerParams& lp, const PrefillRows& rows, int pages, bool quant, bool scratch) {
-    if (!scratch) return {false, choose_shape(lp, rows, quant, false), 0, {}};
+// width: of the page table (and of the table of the expanded pages).
+ChunkPlan plan_chunk(const LayerParams& lp, const PrefillRows& rows, int width, bool quant, bool scratch) {
+    const PrefillShape uncut = choose_shape(lp, rows, quant);
+    if (!scratch) return {false, uncut, 0, uncut};
     const bool cut = may_cut(lp, rows);
     const int dense = lp.Hkv - count_streaming(lp);
     // Dequantising once takes the whole chip 13 ns a tile and head, doing it in the walk 1.8 ns a workgroup of it: eight workgroups.
     const bool many = quant && dense > 0 && rows.history_pages >= 2 * kLeastSpanTiles && (long long)rows.total * lp.group >= 8LL * kPairs * kTile * rows.batch &&
-                      expanded_sizes(lp, rows.batch, pages).all() <= kMostExpanded;
-    const PrefillShape whole = choose_shape(lp, rows, quant, false);
-    if (!cut && !many) return {false, whole, 0, whole};
+                      expanded_sizes(lp, rows.batch, width).all() <= kMostExpanded;
+    if (!cut && !many) return {false, uncut, 0, uncut};
     float times[2][4];
-    const PrefillShape as_is = choose_shape(lp, rows, quant, cut, true, times[0]);
-    const ChunkPlan plan = {false, as_is, pieces_bytes(lp, as_is), whole};
+    const PrefillShape as_is = choose_shape(lp, rows, quant, &uncut, cut, true, times[0]);
+    const ChunkPlan plan = {false, as_is, pieces_bytes(lp, as_is), uncut};
     if (!many) return plan;
-    const PrefillShape expanded = choose_shape(lp, rows, false, cut, true, times[1]);
+    const PrefillShape expanded = choose_shape(lp, rows, false, &uncut, cut, true, times[1]);
     constexpr float kTileUs = 0.013f, kExpandUs = 3.f;
     float score[2] = {0.f, 0.f}, history = (float)rows.history_pages;
     for (int g = 0; g < 4; ++g, history *= 0.25f) {
@@ -1670,7 +1694,7 @@ ChunkPlan plan_chunk(const LayerParams& lp, const PrefillRows& rows, int pages, 
         score[1] += kWeight[g] * (times[1][g] + kExpandUs + kTileUs * history * rows.batch * dense) / times[0][g];
     }
     if (score[1] >= score[0]) return plan;
-    return {true, expanded, expanded_sizes(lp, rows.batch, pages).all() + pieces_bytes(lp, expanded), whole};
+    return {true, expanded, expanded_sizes(lp, rows.batch, width).all() + pieces_bytes(lp, expanded), uncut};
 }
 
 // How a listed mask is walked: by merged lists of four query tiles of a head, or by the caller's rows as they are, for a head
@@ -1726,7 +1750,7 @@ MaskWalk choose_mask_walk(const LayerParams& lp, int batch, int total_tokens, in
 PrefillSchedule make_schedule(const LayerParams& lp, const PrefillShape& shape, int max_rows, int total_rows, bool any_start,
                               int batch, bool single_rows = false) {
     PrefillSchedule sched;
-    sched.pieces = {nullptr, shape.pieces};
+    sched.pieces = {nullptr, shape.pieces, shape.least};
     for (int c = 0; c < 2; ++c) {
         HeadClass& hc = sched.cls[c];
         hc.fold = shape.fold[c];
@@ -1823,12 +1847,12 @@ hipError_t launch_whole(const PrefillLaunch& a, const PrefillShape& shape) {
 template <class T, int BITS>
 hipError_t launch_chunk(PrefillLaunch& a, const ChunkPlan& plan, void* scratch) {
     if (!plan.shape.pieces) return launch_whole<T, BITS>(a, plan.shape);
-    if (streams_apart(*a.lp, plan.whole)) {
+    if (streams_apart(*a.lp, plan.uncut)) {
         PrefillLaunch s = a;
-        s.sched = make_schedule(*a.lp, plan.whole, a.max_rows, a.total_tokens, true, a.batch);
+        s.sched = make_schedule(*a.lp, plan.uncut, a.max_rows, a.total_tokens, true, a.batch);
         s.sched.cls[0].items_per_xcd = 0;
         a.sched.cls[1].items_per_xcd = 0;
-        const hipError_t e = launch_whole<T, BITS>(s, plan.whole);
+        const hipError_t e = launch_whole<T, BITS>(s, plan.uncut);
         if (e != hipSuccess) return e;
     }
     a.sched.pieces.partials = reinterpret_cast<float*>(scratch);
@@ -1861,7 +1885,7 @@ hipError_t launch_prefill(const LayerParams& lp, const void* q, const void* k, c
     a.lse_out = lse_out;
     a.stream = stream;
     if (!mask) {
-        const PrefillShape shape = choose_shape(lp, {batch, total_tokens, max_seqlen, -1}, false, false);
+        const PrefillShape shape = choose_shape(lp, {batch, total_tokens, max_seqlen, -1}, false);
         a.sched = make_schedule(lp, shape, max_seqlen, total_tokens, false, batch);
         if (shape.half) return launch_half<T, kPlain>(a);
         return launch_slices<T, kPlain, 16>(a, shape.slices);
@@ -1874,11 +1898,11 @@ hipError_t launch_prefill(const LayerParams& lp, const void* q, const void* k, c
     mk.rows_per_mask = mask->rows_per_mask;
     const MaskWalk walk = choose_mask_walk(lp, batch, total_tokens, max_seqlen, mask->num_masks, mask->rows_per_mask, mask->nnz);
     if (walk == kRowHalves) {
-        a.sched = make_schedule(lp, {1, {false, false}, false, true, 0}, max_seqlen, total_tokens, false, batch, true);
+        a.sched = make_schedule(lp, {1, {false, false}, false, true, 0, 1}, max_seqlen, total_tokens, false, batch, true);
         return launch_half<T, kMasked>(a);
     }
     if (walk == kRowSlices) {
-        a.sched = make_schedule(lp, {4, {true, true}, true, false, 0}, max_seqlen, total_tokens, false, batch);
+        a.sched = make_schedule(lp, {4, {true, true}, true, false, 0, 1}, max_seqlen, total_tokens, false, batch);
         return launch_slices<T, kMasked, 16>(a, 4);
     }
     mk.blocks_per_seq = mask_blocks(max_seqlen);
@@ -1888,7 +1912,7 @@ hipError_t launch_prefill(const LayerParams& lp, const void* q, const void* k, c
                        (size_t)align16(max_tiles), stream, mk, cu_seqlens, batch);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    a.sched = make_schedule(lp, {1, {false, false}, true, false, 0}, max_seqlen, total_tokens, false, batch);
+    a.sched = make_schedule(lp, {1, {false, false}, true, false, 0, 1}, max_seqlen, total_tokens, false, batch);
     return launch_slices<T, kMasked, 16>(a, 1);
 }
 
@@ -1911,8 +1935,8 @@ hipError_t launch_prefill_paged(const LayerParams& lp, const PagedParams& kv, co
     a.stream = stream;
     const int pages = max_seqlen > 0 ? std::min(kv.max_pages, (max_seqlen - 1) / kTile + 1) : kv.max_pages;
     const PrefillRows rows = chunk_rows(kv.batch, total_new, max_new_per_seq, pages);
-    ChunkPlan plan = plan_chunk(lp, rows, pages, kv.kv_bits != 16, workspace && workspace_bytes > 0);
-    if (plan.bytes > workspace_bytes) plan = plan_chunk(lp, rows, pages, kv.kv_bits != 16, false);
+    ChunkPlan plan = plan_chunk(lp, rows, kv.max_pages, kv.kv_bits != 16, workspace && workspace_bytes > 0);
+    if (plan.bytes > workspace_bytes) plan = plan_chunk(lp, rows, kv.max_pages, kv.kv_bits != 16, false);
     a.sched = make_schedule(lp, plan.shape, max_new_per_seq, total_new, true, kv.batch);
     if (plan.expand) {
         const ExpandedSizes size = expanded_sizes(lp, kv.batch, kv.max_pages);
@@ -1961,12 +1985,27 @@ hipError_t preload_prefill_kernels() {
 }
 
 void prefill_shape(const LayerParams& lp, int batch, int total_rows, int max_rows, int pages, int kv_bits, int (&out)[4]) {
-    const PrefillShape shape = pages > 0 ? choose_shape(lp, chunk_rows(batch, total_rows, max_rows, pages), kv_bits != 16, false, false)
-                                         : choose_shape(lp, {batch, total_rows, max_rows, -1}, false, false, false);
+    const PrefillRows rows = pages > 0 ? chunk_rows(batch, total_rows, max_rows, pages) : PrefillRows{batch, total_rows, max_rows, -1};
+    const PrefillShape shape = choose_shape(lp, rows, pages > 0 && kv_bits != 16, nullptr, false, false);
     out[0] = shape.slices;
     out[1] = shape.fold[0];
     out[2] = shape.fold[1];
     out[3] = shape.one_head;
+}
+
+void prefill_plan(const LayerParams& lp, int batch, int total_rows, int max_rows, int pages, int kv_bits, bool scratch, int (&out)[6]) {
+    ChunkPlan plan = {};
+    if (pages > 0)
+        plan = plan_chunk(lp, chunk_rows(batch, total_rows, max_rows, pages), pages, kv_bits != 16, scratch);
+    else
+        plan.shape = plan.uncut = choose_shape(lp, {batch, total_rows, max_rows, -1}, false);
+    const bool apart = plan.shape.pieces && streams_apart(lp, plan.uncut);
+    out[0] = plan.shape.pieces ? plan.shape.least : slices_of(plan.shape, 0);
+    out[1] = slices_of(apart ? plan.uncut : plan.shape, 1);
+    out[2] = plan.shape.half;
+    out[3] = plan.shape.pieces;
+    out[4] = apart;
+    out[5] = plan.expand;
 }
 
 int mask_walk(const LayerParams& lp, int batch, int total_tokens, int max_seqlen, int masks, int rows_per_mask, int nnz) {

@@ -14,7 +14,7 @@ CASES = [  # heads, KV heads, history, new tokens
     (32, 8, (14100, 14100), (190, 190)),                     # alike, off the tiles
     (8, 8, (12000,), (300,)),                                # no groups: a block is four tiles
     (12, 2, (13500, 70), (130, 65)),                         # six heads per group: two of them and two tiles to a block
-    (12, 4, (0, 22000, 3, 700), (200, 17, 0, 64)),           # idle and empty sequences beside a long one
+    (12, 4, (0, 26000, 3, 700), (200, 17, 0, 64)),           # idle and empty sequences beside a long one
     (64, 8, (14900,), (77,)),                                # eight heads per group: two workgroups to a block
     # two sequences to some lanes, most of them idle (16-bit pages stay with whole walks)
     (4, 2, tuple(977 * i % 600 + 40000 * int(i == 46) for i in range(66)), tuple(3 * int(i % 23 == 0) for i in range(66))),
