@@ -1307,9 +1307,10 @@ struct ExpandedPages {
 };
 
 // One workgroup per KV head, sequence and share of its pages; bound by memory (a slab of 8192 codes is 8.5 KB to read and 16 KB to
-// write).
+// write).  Sequences without new tokens are left alone: nobody reads their pages, and their tables need not lead anywhere.
 template <class T, int BITS>
-__global__ __launch_bounds__(256) void expand_pages_kernel(LayerParams lp, PagedParams kv, ExpandedPages to) {
+__global__ __launch_bounds__(256) void expand_pages_kernel(LayerParams lp, PagedParams kv, const int* __restrict__ cu_new, ExpandedPages to) {
+    if (cu_new[blockIdx.z + 1] <= cu_new[blockIdx.z]) return;
     const int hk = blockIdx.y, b = blockIdx.z, cached = kv.seq_lens[b], pages = ceil_div(cached, kTile);
     const bool streaming = (lp.streaming_mask >> hk) & 1ull, ring = in_stream_pool(lp, kv, hk);
     const int heads = streaming ? kv.stream_heads : lp.Hkv - kv.stream_heads;
@@ -1956,9 +1957,9 @@ hipError_t launch_prefill_paged(const LayerParams& lp, const PagedParams& kv, co
         workspace = at;
         const dim3 grid(std::min(pages, 64), lp.Hkv, kv.batch);
         if (kv.kv_bits == 8)
-            hipLaunchKernelGGL((expand_pages_kernel<T, 8>), grid, dim3(256), 0, stream, lp, kv, to);
+            hipLaunchKernelGGL((expand_pages_kernel<T, 8>), grid, dim3(256), 0, stream, lp, kv, cu_q, to);
         else
-            hipLaunchKernelGGL((expand_pages_kernel<T, 4>), grid, dim3(256), 0, stream, lp, kv, to);
+            hipLaunchKernelGGL((expand_pages_kernel<T, 4>), grid, dim3(256), 0, stream, lp, kv, cu_q, to);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         PagedParams& pages16 = a.pg.kv;

@@ -39,3 +39,19 @@ def test_chunks_over_expanded_pages(case, dtype, bits, two_way, monkeypatch):
     pages = max(-(-(h + n) // 64) for h, n in zip(hist, fresh))
     dense = hkv - hkv // 2
     assert used[0] is not None and used[0].numel() >= len(hist) * pages * dense * 2 * 64 * 128 * 2
+
+
+@pytest.mark.parametrize("two_way", [False, True])
+def test_sequences_without_new_tokens_are_not_expanded(two_way, monkeypatch):
+    import paper_2502_14866_amd.binding as B
+
+    heads, hkv, hist, fresh = CASES[3]
+    idle = fresh.index(0)
+    used, take = [], B._chunk_scratch
+    monkeypatch.setattr(B, "_chunk_scratch", lambda *args: used.append(take(*args).fill_(0xff)) or used[-1])
+    monkeypatch.setattr(paged, "CASES", [(heads, hkv, hist, fresh, {8: None, 4: None})])
+    paged.test_chunks_in_every_launch_shape(0, "fp16", 8, two_way)
+    pages = max(-(-(h + n) // 64) for h, n in zip(hist, fresh))
+    per_seq = pages * (hkv - hkv // 2) * 64 * 128 * 2
+    k = used[0][:len(hist) * per_seq].reshape(len(hist), per_seq).cpu()
+    assert (k[idle] == 0xff).all() and all((k[b] != 0xff).any() for b in range(len(hist)) if b != idle)
