@@ -258,9 +258,8 @@ int lserve_sparse_prefill(const lserve_attn_desc *desc, const void *q, const voi
  *   max_new_per_seq  host bound of n_b (> 0); max_seqlen host bound of L_b (the launch is laid out for walks of up to
  *                this length, or of max_pages_per_seq where that is shorter: a bound far too wide costs time)
  *   out          device [total_new][H][D]; lse_out device [H][total_new] fp32 or NULL
- *   workspace    none needed: lserve_paged_prefill_workspace_bytes() is 0 (keys and values are read from the pages as
- *                they are), NULL is accepted.  With lserve_chunk_scratch_bytes(...) or more, of any contents, a chunk over
- *                a long history is shared out over more of the chip
+ *   workspace    unused: lserve_paged_prefill_workspace_bytes() is 0 (keys and values are read from the pages as
+ *                they are); NULL is accepted
  */
 int lserve_sparse_prefill_paged(const lserve_attn_desc *desc, const lserve_paged_kv *kv, const void *q,
                                 const int32_t *cu_q, int32_t total_new, int32_t max_new_per_seq,
@@ -269,6 +268,16 @@ int lserve_sparse_prefill_paged(const lserve_attn_desc *desc, const lserve_paged
 
 size_t lserve_paged_prefill_workspace_bytes(const lserve_attn_desc *desc, int32_t batch,
                                             int32_t max_pages_per_seq);
+
+/*
+ * The same with scratch of lserve_chunk_scratch_bytes(...) or more (device, any contents; NULL or less: done without), with which a
+ * chunk over a long history is shared out over more of the chip.  The scratch is written: calls that may run at the same time
+ * need one each.
+ */
+int lserve_sparse_prefill_paged_scratch(const lserve_attn_desc *desc, const lserve_paged_kv *kv, const void *q,
+                                        const int32_t *cu_q, int32_t total_new, int32_t max_new_per_seq,
+                                        int32_t max_seqlen, void *out, float *lse_out, void *scratch,
+                                        size_t scratch_bytes, void *stream);
 
 /*
  * Chunked prefill in the order of the prefill flow (Sec. 3.2: attention over the new tokens first, then their K / V
@@ -297,7 +306,10 @@ int lserve_sparse_prefill_chunk(const lserve_attn_desc *desc, const lserve_paged
                                 const void *k_new, const void *v_new, const int32_t *cu_new, int32_t total_new,
                                 int32_t max_new_per_seq, void *out, float *lse_out, void *stream);
 
-/* The same with scratch of lserve_chunk_scratch_bytes(...) (device, any contents; NULL or less: done without). */
+/*
+ * The same with scratch of lserve_chunk_scratch_bytes(...) or more (device, any contents; NULL or less: done without).  The scratch is
+ * written: calls that may run at the same time need one each.
+ */
 int lserve_sparse_prefill_chunk_scratch(const lserve_attn_desc *desc, const lserve_paged_kv *kv, const void *q,
                                         const void *k_new, const void *v_new, const int32_t *cu_new,
                                         int32_t total_new, int32_t max_new_per_seq, void *out, float *lse_out,
@@ -310,7 +322,7 @@ int lserve_sparse_prefill_chunk_scratch(const lserve_attn_desc *desc, const lser
  * by every workgroup; with scratch it is turned into 16-bit pages once (up to 1 GiB of them; wider tables are left as they
  * are).
  *   total_new, max_new_per_seq: as in the call
- *   pages      width of the page table; for lserve_sparse_prefill_paged min(width, ceil(max_seqlen / 64))
+ *   pages      width of the page table; for lserve_sparse_prefill_paged_scratch min(width, ceil(max_seqlen / 64))
  */
 size_t lserve_chunk_scratch_bytes(const lserve_attn_desc *desc, int32_t batch, int32_t total_new, int32_t max_new_per_seq,
                                   int32_t pages, int32_t kv_bits);

@@ -29,7 +29,6 @@ EXPORTED_SYMBOLS = (
     "lserve_sparse_prefill_masked",
     "lserve_sparse_prefill_paged",
     "lserve_sparse_prefill_chunk",
-    "lserve_sparse_prefill_chunk_scratch",
     "lserve_chunk_scratch_bytes",
     "lserve_paged_prefill_workspace_bytes",
     "lserve_masked_prefill_workspace_bytes",
@@ -109,6 +108,8 @@ def load_library():
         lib.lserve_masked_prefill_workspace_bytes.restype = ctypes.c_size_t
         lib.lserve_sparse_prefill_paged.argtypes = [dp, kp, vp, vp, i32, i32, i32, vp, vp, vp, sz, vp]
         lib.lserve_sparse_prefill_paged.restype = ctypes.c_int
+        lib.lserve_sparse_prefill_paged_scratch.argtypes = [dp, kp, vp, vp, i32, i32, i32, vp, vp, vp, sz, vp]
+        lib.lserve_sparse_prefill_paged_scratch.restype = ctypes.c_int
         lib.lserve_sparse_prefill_chunk.argtypes = [dp, kp, vp, vp, vp, vp, i32, i32, vp, vp, vp]
         lib.lserve_sparse_prefill_chunk.restype = ctypes.c_int
         lib.lserve_sparse_prefill_chunk_scratch.argtypes = [dp, kp, vp, vp, vp, vp, i32, i32, vp, vp, vp, sz, vp]
@@ -356,14 +357,12 @@ def lserve_sparse_prefill_paged(desc: AttnDesc, kv: PagedKV, q: torch.Tensor, cu
                                 max_new_per_seq: int, max_seqlen: int, out: torch.Tensor,
                                 lse_out: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None,
                                 stream=None) -> None:
-    if workspace is None and max_seqlen > 0:
-        pages = min(kv.page_table.shape[1], (max_seqlen - 1) // 64 + 1)
-        workspace = _chunk_scratch(desc, q, cu_q.shape[0] - 1, max_new_per_seq, pages, 16, stream)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(load_library().lserve_sparse_prefill_paged(desc.c(), kv.c(), _ptr(q), _ptr(cu_q), q.shape[0],
-                                                      max_new_per_seq, max_seqlen, _ptr(out), _ptr(lse_out),
-                                                      _ptr(workspace), ws_bytes, _stream(stream)),
-           "lserve_sparse_prefill_paged")
+    _ptr(workspace)  # unused by the call, contiguous all the same
+    pages = min(kv.page_table.shape[1], (max_seqlen - 1) // 64 + 1)
+    scratch = _chunk_scratch(desc, q, cu_q.shape[0] - 1, max_new_per_seq, pages, 16, stream)
+    _check(load_library().lserve_sparse_prefill_paged_scratch(
+        desc.c(), kv.c(), _ptr(q), _ptr(cu_q), q.shape[0], max_new_per_seq, max_seqlen, _ptr(out), _ptr(lse_out), _ptr(scratch),
+        0 if scratch is None else scratch.numel(), _stream(stream)), "lserve_sparse_prefill_paged")
 
 
 def lserve_sparse_prefill_chunk(desc: AttnDesc, kv: PagedKV, q: torch.Tensor, k_new: torch.Tensor, v_new: torch.Tensor,

@@ -262,9 +262,10 @@ int lserve_sparse_prefill_masked(const lserve_attn_desc* desc, const lserve_bloc
                         workspace_bytes, stream);
 }
 
-int lserve_sparse_prefill_paged(const lserve_attn_desc* desc, const lserve_paged_kv* kv, const void* q,
-                                const int32_t* cu_q, int32_t total_new, int32_t max_new_per_seq, int32_t max_seqlen,
-                                void* out, float* lse_out, void* workspace, size_t workspace_bytes, void* stream) {
+namespace {
+int prefill_paged_impl(const lserve_attn_desc* desc, const lserve_paged_kv* kv, const void* q, const int32_t* cu_q,
+                       int32_t total_new, int32_t max_new_per_seq, int32_t max_seqlen, void* out, float* lse_out,
+                       const void* workspace, void* scratch, size_t scratch_bytes, void* stream) {
     LayerParams lp;
     PagedParams pp;
     int rc = make_layer(desc, &lp);
@@ -277,13 +278,26 @@ int lserve_sparse_prefill_paged(const lserve_attn_desc* desc, const lserve_paged
     if (!q || !cu_q || !out) return LSERVE_ERR_INVALID_ARG;
     if (total_new <= 0 || max_new_per_seq <= 0 || max_new_per_seq > total_new || max_seqlen < max_new_per_seq)
         return LSERVE_ERR_INVALID_ARG;
-    if (!aligned16(q) || !aligned16(cu_q) || !aligned16(out) || !aligned16(lse_out) || !aligned16(workspace))
+    if (!aligned16(q) || !aligned16(cu_q) || !aligned16(out) || !aligned16(lse_out) || !aligned16(workspace) || !aligned16(scratch))
         return LSERVE_ERR_INVALID_ARG;
-    const size_t need = paged_prefill_workspace_bytes(lp, pp.batch, pp.max_pages);
-    if (need > 0 && (!workspace || workspace_bytes < need)) return LSERVE_ERR_WORKSPACE;
     hipError_t e = launch_sparse_prefill_paged(desc->dtype, lp, pp, q, nullptr, nullptr, cu_q, total_new, max_new_per_seq,
-                                               max_seqlen, out, lse_out, workspace, workspace_bytes, (hipStream_t)stream);
+                                               max_seqlen, out, lse_out, scratch, scratch_bytes, (hipStream_t)stream);
     return e == hipSuccess ? LSERVE_OK : fail_hip(e);
+}
+}  // namespace
+
+int lserve_sparse_prefill_paged(const lserve_attn_desc* desc, const lserve_paged_kv* kv, const void* q,
+                                const int32_t* cu_q, int32_t total_new, int32_t max_new_per_seq, int32_t max_seqlen,
+                                void* out, float* lse_out, void* workspace, size_t workspace_bytes, void* stream) {
+    (void)workspace_bytes;  // none needed, none used
+    return prefill_paged_impl(desc, kv, q, cu_q, total_new, max_new_per_seq, max_seqlen, out, lse_out, workspace, nullptr, 0, stream);
+}
+
+int lserve_sparse_prefill_paged_scratch(const lserve_attn_desc* desc, const lserve_paged_kv* kv, const void* q,
+                                        const int32_t* cu_q, int32_t total_new, int32_t max_new_per_seq, int32_t max_seqlen,
+                                        void* out, float* lse_out, void* scratch, size_t scratch_bytes, void* stream) {
+    return prefill_paged_impl(desc, kv, q, cu_q, total_new, max_new_per_seq, max_seqlen, out, lse_out, nullptr, scratch,
+                              scratch_bytes, stream);
 }
 
 int lserve_sparse_prefill_chunk(const lserve_attn_desc* desc, const lserve_paged_kv* kv, const void* q, const void* k_new,

@@ -69,3 +69,34 @@ def test_paged_prefill_in_pieces_repeats_itself_and_agrees_with_whole_walks():
     # weights and outputs are rounded to fp16 on both sides: 2^-11 of the largest output twice
     assert (outs[5][0].float() - outs[0][0].float()).abs().max() <= 2 ** -10 * outs[0][0].float().abs().max()
     assert (outs[5][1] - outs[0][1]).abs().max() <= 1e-5 * outs[0][1].abs().max()
+
+
+def test_the_workspace_of_paged_prefill_is_not_used():
+    """Callers may hand one to calls on several streams: however large, it is left as it is."""
+    import ctypes
+
+    import paper_2502_14866_amd as L
+    from paper_2502_14866_amd.binding import lserve_chunk_scratch_bytes
+
+    lib = L.load_library()
+    dev = torch.device("cuda:0")
+    g = torch.Generator(device=dev).manual_seed(9)
+    n, new = 20000, 100
+    rnd = lambda *s: torch.randn(s, generator=g, device=dev).to(torch.float16)
+    k, v, q = rnd(313, 8, 64, 128), rnd(313, 8, 64, 128), rnd(new, 32, 128)
+    desc = L.AttnDesc(32, 8, [1, 1, 1, 1, 0, 0, 0, 0])
+    i32 = lambda a: torch.tensor(a, dtype=torch.int32, device=dev)
+    kv, cu = L.PagedKV(k, v, None, torch.arange(313, device=dev).to(torch.int32).reshape(1, -1), i32([n])), i32([0, new])
+    need = lserve_chunk_scratch_bytes(desc, 1, new, new, 313)
+    assert need > 0
+    ws = torch.full((2 * need,), 0x5a, dtype=torch.uint8, device=dev)
+    outs = [torch.empty_like(q) for _ in range(4)]
+    L.lserve_sparse_prefill_paged(desc, kv, q, cu, new, n, outs[0], None, ws)
+    L.lserve_sparse_prefill_paged(desc, kv, q, cu, new, n, outs[1])
+    stream = torch.cuda.current_stream().cuda_stream
+    for out, size in ((outs[2], ws.numel()), (outs[3], 0)):  # the entry point in C
+        assert lib.lserve_sparse_prefill_paged(desc.c(), kv.c(), q.data_ptr(), cu.data_ptr(), new, new, n, out.data_ptr(), None,
+                                               ws.data_ptr() if size else None, ctypes.c_size_t(size), stream) == 0
+    torch.cuda.synchronize()
+    assert (ws == 0x5a).all()
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[2], outs[3])
