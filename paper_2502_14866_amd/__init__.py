@@ -23,6 +23,7 @@ from .binding import (  # noqa: F401
     lserve_sparse_prefill_paged,
     lserve_sparse_prefill_chunk,
     lserve_build_page_stats,
+    lserve_chunk_scratch_bytes,
     lserve_init,
     lserve_last_hip_error,
     lserve_probe_decode_read,

@@ -2,8 +2,10 @@
 marshalled natively (csrc/py_calls.cpp), the others by ctypes."""
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import os
+import warnings
 from dataclasses import dataclass
 from typing import Optional, Sequence
 
@@ -285,19 +287,44 @@ def lserve_chunk_scratch_bytes(desc: AttnDesc, batch: int, total_new: int, max_n
     return int(load_library().lserve_chunk_scratch_bytes(desc.c(), batch, total_new, max_new_per_seq, pages, kv_bits))
 
 
+def _capture_has_a_pool() -> bool:
+    """Under capture: do allocations come from a pool that the graph keeps (torch.cuda.graph), or from the one whose memory is handed
+    on after the call and would be somebody else's when the graph is replayed (a capture begun by other means)?"""
+    probe = torch.empty((16,), dtype=torch.uint8, device="cuda")
+    for segment in torch.cuda.memory_snapshot():
+        if segment["address"] <= probe.data_ptr() < segment["address"] + segment["total_size"]:
+            return tuple(segment.get("segment_pool_id", (0, 0))) != (0, 0)
+    return False
+
+
 def _chunk_scratch(desc: AttnDesc, q: torch.Tensor, batch: int, max_new_per_seq: int, pages: int, kv_bits: int,
                    stream) -> Optional[torch.Tensor]:
-    """Scratch for a call on chunks, from torch's allocator, which hands freed memory on in the order of the stream it was
-    taken on: only for calls on the current stream, and not under capture, where an allocation may not be allowed."""
-    if stream is not None or not q.is_cuda:
-        return None
+    """Scratch for a call on chunks, from torch's allocator, which hands freed memory on in the order of the stream it was taken on:
+    it is taken on the stream of the call."""
     need = lserve_chunk_scratch_bytes(desc, batch, q.shape[0], max_new_per_seq, pages, kv_bits)
-    if need == 0 or torch.cuda.is_current_stream_capturing():
+    if need == 0 or not q.is_cuda:
         return None
-    try:
-        return torch.empty((need,), dtype=torch.uint8, device=q.device)
-    except torch.cuda.OutOfMemoryError:
-        return None
+    handle = _stream(stream)
+    on_stream = contextlib.nullcontext()
+    if handle != _stream(None):
+        if isinstance(stream, torch.cuda.Stream):
+            on_stream = torch.cuda.stream(stream)
+        elif handle == 0:
+            on_stream = torch.cuda.stream(torch.cuda.default_stream(q.device))
+        elif handle < 16:  # the runtime's names for streams are not addresses, as which torch would take them
+            return None
+        else:
+            on_stream = torch.cuda.stream(torch.cuda.ExternalStream(handle, device=q.device))
+    with on_stream:
+        if torch.cuda.is_current_stream_capturing() and not _capture_has_a_pool():
+            return None
+        try:
+            return torch.empty((need,), dtype=torch.uint8, device="cuda")
+        except torch.cuda.OutOfMemoryError:
+            warnings.warn(f"no memory for the {need} bytes of scratch of a call on chunks: it goes without, which is slower and adds "
+                          "up in another order; scratch= takes memory of the caller's, an empty tensor for none",
+                          RuntimeWarning, stacklevel=3)
+            return None
 
 
 def lserve_sparse_prefill(desc: AttnDesc, q: torch.Tensor, k: torch.Tensor, v: torch.Tensor,
@@ -356,22 +383,33 @@ def lserve_paged_prefill_workspace_bytes(desc: AttnDesc, batch: int, max_pages_p
 def lserve_sparse_prefill_paged(desc: AttnDesc, kv: PagedKV, q: torch.Tensor, cu_q: torch.Tensor,
                                 max_new_per_seq: int, max_seqlen: int, out: torch.Tensor,
                                 lse_out: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None,
-                                stream=None) -> None:
-    _ptr(workspace)  # unused by the call, contiguous all the same
-    pages = min(kv.page_table.shape[1], (max_seqlen - 1) // 64 + 1)
-    scratch = _chunk_scratch(desc, q, cu_q.shape[0] - 1, max_new_per_seq, pages, 16, stream)
+                                stream=None, scratch: Optional[torch.Tensor] = None) -> None:
+    """workspace is not used.  scratch: see lserve_sparse_prefill_chunk; lserve_chunk_scratch_bytes with
+    pages = min(page_table.shape[1], ceil(max_seqlen / 64))."""
+    _ptr(workspace)  # unused, and contiguous all the same
+    if scratch is None:
+        pages = min(kv.page_table.shape[1], (max_seqlen - 1) // 64 + 1)
+        scratch = _chunk_scratch(desc, q, cu_q.shape[0] - 1, max_new_per_seq, pages, 16, stream)
     _check(load_library().lserve_sparse_prefill_paged_scratch(
         desc.c(), kv.c(), _ptr(q), _ptr(cu_q), q.shape[0], max_new_per_seq, max_seqlen, _ptr(out), _ptr(lse_out), _ptr(scratch),
-        0 if scratch is None else scratch.numel(), _stream(stream)), "lserve_sparse_prefill_paged")
+        0 if scratch is None else scratch.numel() * scratch.element_size(), _stream(stream)), "lserve_sparse_prefill_paged")
 
 
 def lserve_sparse_prefill_chunk(desc: AttnDesc, kv: PagedKV, q: torch.Tensor, k_new: torch.Tensor, v_new: torch.Tensor,
                                 cu_new: torch.Tensor, max_new_per_seq: int, out: torch.Tensor,
-                                lse_out: Optional[torch.Tensor] = None, stream=None) -> None:
-    scratch = _chunk_scratch(desc, q, cu_new.shape[0] - 1, max_new_per_seq, kv.page_table.shape[1], kv.kv_bits, stream)
+                                lse_out: Optional[torch.Tensor] = None, stream=None,
+                                scratch: Optional[torch.Tensor] = None) -> None:
+    """scratch: device memory of lserve_chunk_scratch_bytes(desc, batch, q.shape[0], max_new_per_seq, page_table.shape[1], kv_bits)
+    bytes or more, not shared with work in flight; too little of it, an empty tensor for instance: the call does without.  None: taken
+    from torch's allocator for the call (up to 1 GiB of expanded pages, by the width of the page table, and some ten MB of pieces),
+    on whatever stream it goes to and from the graph's own pool under torch.cuda.graph, so that the same call gives the same bits
+    everywhere.  A call goes without, slower and with sums in another order, where torch is out of memory (a RuntimeWarning says
+    so) and in a capture begun by other means than torch.cuda.graph."""
+    if scratch is None:
+        scratch = _chunk_scratch(desc, q, cu_new.shape[0] - 1, max_new_per_seq, kv.page_table.shape[1], kv.kv_bits, stream)
     _check(load_library().lserve_sparse_prefill_chunk_scratch(
         desc.c(), kv.c(), _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(cu_new), q.shape[0], max_new_per_seq, _ptr(out),
-        _ptr(lse_out), _ptr(scratch), 0 if scratch is None else scratch.numel(), _stream(stream)),
+        _ptr(lse_out), _ptr(scratch), 0 if scratch is None else scratch.numel() * scratch.element_size(), _stream(stream)),
         "lserve_sparse_prefill_chunk")
 
 

@@ -42,7 +42,7 @@ def test_chunks_in_pieces(case, dtype, bits, two_way, monkeypatch):
 
 
 def test_paged_prefill_in_pieces_repeats_itself_and_agrees_with_whole_walks():
-    """Five times on the same data with scratch: the same bits; without (another stream argument): the same but for rounding."""
+    """Five times on the same data with scratch: the same bits; without (an empty one): the same but for rounding."""
     import paper_2502_14866_amd as L
 
     L.load_library()
@@ -58,7 +58,7 @@ def test_paged_prefill_in_pieces_repeats_itself_and_agrees_with_whole_walks():
     for i in range(6):
         out, lse = torch.full_like(q, float("nan")), torch.full((32, new), float("nan"), device=dev)
         L.lserve_sparse_prefill_paged(desc, kv, q, i32([0, new]), new, n, out, lse,
-                                      stream=torch.cuda.current_stream() if i == 5 else None)
+                                      scratch=torch.empty((0,), dtype=torch.uint8, device=dev) if i == 5 else None)
         outs.append((out, lse))
     torch.cuda.synchronize()
     for out, lse in outs[1:5]:
