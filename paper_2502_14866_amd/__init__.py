@@ -1,8 +1,8 @@
 """MI355X-native unified block-sparse attention path of LServe (arxiv 2502.14866).
 
 The product is the C-ABI library `liblserve.so` (include/lserve.h).  This package is a thin
-ctypes binding with the same entry-point names; it only marshals arguments.  PyTorch supplies
-device memory and streams.  There is no CPU fallback: if the library has not been built the
+binding with the same entry-point names; it only marshals arguments (the three calls of a decode
+step natively, the others by ctypes).  PyTorch supplies device memory and streams.  There is no CPU fallback: if the library has not been built the
 calls raise.
 """
 from .binding import (  # noqa: F401

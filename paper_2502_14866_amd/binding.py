@@ -144,18 +144,47 @@ def load_library():
     return _lib
 
 
+class _CtypesCalls:
+    """The native calls by ctypes, where the extension is not there or not of this torch; desc as its address."""
+
+    @staticmethod
+    def append(desc, kv, k_new, v_new, cu_new, start_pos, max_new_per_seq, stream):
+        return load_library().lserve_append_kv(_CAttnDesc.from_address(desc), kv.c(), _ptr(k_new), _ptr(v_new), _ptr(cu_new),
+                                               _ptr(start_pos), max_new_per_seq, stream)
+
+    @staticmethod
+    def select(desc, kv, q, budget_tokens, stats_valid_len, sel_pages, sel_count, sel_seq_len, scores_out, workspace, stream):
+        ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+        return load_library().lserve_select_pages(_CAttnDesc.from_address(desc), kv.c(), _ptr(q), budget_tokens,
+                                                  _ptr(stats_valid_len), _ptr(sel_pages), _ptr(sel_count), _ptr(sel_seq_len),
+                                                  _ptr(scores_out), _ptr(workspace), ws_bytes, stream)
+
+    @staticmethod
+    def decode(desc, kv, q, sel_pages, sel_count, sel_seq_len, out, lse_out, workspace, stream):
+        ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+        sel_stride = 0 if sel_pages is None else sel_pages.shape[-1]
+        return load_library().lserve_sparse_decode(_CAttnDesc.from_address(desc), kv.c(), _ptr(q), _ptr(sel_pages),
+                                                   _ptr(sel_count), _ptr(sel_seq_len), sel_stride, _ptr(out), _ptr(lse_out),
+                                                   _ptr(workspace), ws_bytes, stream)
+
+
 def _native():
-    """The native calls, bound to the loaded library."""
+    """The native calls, bound to the loaded library; without the extension (only the library was built, or it was built with another
+    torch or Python) the same by ctypes, some five microseconds a call slower."""
     global _calls
     if _calls is None:
         lib = load_library()
         try:
             from . import _calls as calls
+
+            if calls.torch_version != torch.__version__:
+                raise ImportError(f"_calls was built with torch {calls.torch_version}, this is {torch.__version__}")
+            calls.bind(*(ctypes.cast(f, ctypes.c_void_p).value
+                         for f in (lib.lserve_append_kv, lib.lserve_select_pages, lib.lserve_sparse_decode)))
         except ImportError as e:
-            raise ImportError("the binding's native calls (_calls.so) are missing: build them with "
-                              "`python -m paper_2502_14866_amd.build` (or __graft_entry__.build())") from e
-        calls.bind(*(ctypes.cast(f, ctypes.c_void_p).value
-                     for f in (lib.lserve_append_kv, lib.lserve_select_pages, lib.lserve_sparse_decode)))
+            warnings.warn(f"the binding's native calls are missing ({e}): decode steps are marshalled by ctypes; build them with "
+                          "`python -m paper_2502_14866_amd.build` (or __graft_entry__.build())", RuntimeWarning, stacklevel=3)
+            calls = _CtypesCalls
         _calls = calls
     return _calls
 

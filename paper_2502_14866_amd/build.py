@@ -4,13 +4,15 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD_DIR = os.path.join(HERE, "_build")
 LIB_PATH = os.path.join(HERE, "liblserve.so")
-CALLS_PATH = os.path.join(HERE, "_calls.so")  # the binding's native marshalling (host code only)
+# the binding's native marshalling (host code only), under a name that other versions of Python do not take for theirs
+CALLS_PATH = os.path.join(HERE, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 SOURCES = ["lserve_api.hip", "page_stats.hip", "select_pages.hip", "sparse_decode.hip", "sparse_prefill.hip"]
 
@@ -41,15 +43,13 @@ def _compile(src: str, extra=()) -> str:
 
 def _build_calls() -> str:
     """py_calls.cpp against the Python and torch headers of this interpreter."""
-    import sysconfig
-
     import torch
     from torch.utils import cpp_extension
 
     includes = [f"-I{d}" for d in cpp_extension.include_paths() + [sysconfig.get_paths()["include"]]]
     libs = os.path.join(os.path.dirname(torch.__file__), "lib")
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *includes,
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DLSERVE_TORCH="{torch.__version__}"', *includes,
            os.path.join(CSRC, "py_calls.cpp"), "-o", CALLS_PATH,
            f"-L{libs}", f"-Wl,-rpath,{libs}", "-ltorch_python", "-ltorch_cpu", "-lc10"]
     res = subprocess.run(cmd, capture_output=True, text=True)

@@ -36,9 +36,10 @@ template <class P = void> P* address(const at::Tensor* t) {
 }
 template <class P = void> P* address(PyObject* o) { return address<P>(tensor_or_null(o)); }
 
-long long number(PyObject* o) {
-    const long long x = PyLong_AsLongLong(o);
-    if (x == -1 && PyErr_Occurred()) throw PythonError();
+// (the low bits, as ctypes takes them)
+unsigned long long number(PyObject* o) {
+    const unsigned long long x = PyLong_AsUnsignedLongLongMask(o);
+    if (x == (unsigned long long)-1 && PyErr_Occurred()) throw PythonError();
     return x;
 }
 int32_t number32(PyObject* o) { return (int32_t)number(o); }
@@ -176,5 +177,10 @@ PyMODINIT_FUNC PyInit__calls() {
                                              "pool_heads", "k_pool_stream", "v_pool_stream", "ring_table", "kv_bits"};
     for (int i = 0; i < kNames; ++i)
         if (!(names[i] = PyUnicode_InternFromString(spelled[i]))) return nullptr;
-    return PyModule_Create(&module);
+    PyObject* m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "torch_version", LSERVE_TORCH) < 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
 }
