@@ -1206,7 +1206,7 @@ __global__ __launch_bounds__(kPrefillThreads, 512 / kPrefillThreads) void prefil
 // Half workgroups: one does not have a compute unit to itself, so that its start and end, 5 us in which nothing else of it is under
 // way, and the time its wavefronts wait for each other at the end of a step go to the other's steps; short walks gain most, and
 // where heads of a group keep different tiles (listed masks) two share a walk more often than four.  It stages every tile for half
-// as many rows, which long walks pay for.  Whole and half, us: ten prompts of 327 tokens, 32 / 32 heads, 47 and 34; 16 of 527, 32 / 16,
+// as many rows, which long walks pay for (see halves_are_quicker).  Whole and half, us: ten prompts of 327 tokens, 32 / 32 heads, 47 and 34; 16 of 527, 32 / 16,
 // 108 and 87; one of 4096, 32 / 8, 121 and 108; 16 of 77 .. 3001, 213 and 208; 65536, 15690 and 16220.
 template <class T, int MODE>
 __global__ __launch_bounds__(kPrefillThreads / 2, 2) void prefill_half_kernel(
@@ -1556,6 +1556,35 @@ bool may_cut(const LayerParams& lp, const PrefillRows& rows) {
 // with four slices and 2.84e-3 with one (512 tokens over 32768, bf16; dense heads 2.99e-3 whole in four slices and 2.97e-3 in pieces).
 bool streams_apart(const LayerParams& lp, const PrefillShape& whole) { return whole.slices > 1 && lp.streaming_mask != 0; }
 
+// Are half workgroups (see prefill_half_kernel) quicker than the whole ones of a shape of one slice?  (Not over quantised pages, which
+// every workgroup dequantises for itself: half ones are twice as many.)  Measured over 850 batches, half as a part of whole: 0.64 to
+// 1.08 where a dense walk is up to 60 tiles long on average, 0.92 to 1.03 beyond; and up to 60 whole ones are as quick or quicker
+// where (the last two, and of the second what is said of four heads, over prompts only)
+//   - a dense walk is a single tile and whole workgroups have tiles of one head for units (1.02 to 1.16: 51 tokens, 32 / 16 heads, 6.3 and
+//     7.2 us): most of the time is the way of that tile into LDS, on which a half workgroup has half the wavefronts;
+//   - whole workgroups of four heads, or of four tiles of one, fill the chip just once with walks of some tiles (1.0 to 1.04: eight of
+//     231, 32 / 8 heads, 17.1 and 17.4; 0.96 to 1.1: four of 385, 32 / 32, 20.4 and 22.4, four chunks of 165 over 173 15.8 and 17.6; with walks
+//     of up to two tiles 0.87 to 0.95, of seven and more 0.80 to 0.98);
+//   - those of four heads fill it twice with walks of two tiles (0.90 to 1.6: 16 of 128, 64 / 8 heads, 30 and 48, of 123 27.6 and 25.8);
+//   - no two heads read the same keys and walks are not short in more than 16 rounds (0.98 to 1.07: 18 of 3001, 32 / 32 heads, 1352 and
+//     1447).
+bool halves_are_quicker(const LayerParams& lp, const PrefillRows& rows, const PrefillShape& whole) {
+    const int n_stream = count_streaming(lp), heads[2] = {lp.Hkv - n_stream, n_stream};
+    const PrefillShape half = {1, {false, false}, false, true, 0, 1};
+    const ClassWalks walks = class_walks(lp, rows, (float)std::max(0, rows.history_pages), class_cost(lp, half, rows, 0, heads[0], false, 0, 0.f), 0);
+    if (walks.mid > 60.f) return false;
+    const bool prompt = rows.history_pages < 0, fours = lp.group % 4 == 0, single = lp.group % 2 != 0;
+    if (walks.hi <= 1.f && whole.one_head) return false;
+    float rounds = 0.f;
+    for (int c = 0; c < 2; ++c) rounds += class_cost(lp, whole, rows, c, heads[c], false, 0, 0.f).count;
+    rounds /= std::max(1, num_compute_units() / kXcds);
+    if (single && rounds > 0.8f && rounds <= 1.f && walks.mid >= 2.9f && walks.mid <= 6.5f) return false;
+    if (!prompt) return true;
+    if (fours && rounds > 0.875f && rounds <= 1.f && walks.mid >= 2.2f && walks.mid <= 6.f) return false;
+    if (fours && rounds > 1.75f && rounds <= 2.f && walks.mid >= 1.4f && walks.hi <= 2.f) return false;
+    return !(single && rounds > 16.f && walks.mid > 20.f);
+}
+
 constexpr float kWeight[4] = {4.f, 1.f, 1.f, 1.f};  // of the guesses
 
 // The shape of a launch: of whole walks, or with `cut` also in pieces, so many that its workgroups are about one, two ... rounds
@@ -1630,15 +1659,9 @@ PrefillShape choose_shape(const LayerParams& lp, const PrefillRows& rows, bool q
     if (best >= kCount) {
         shape.pieces = pieces[best - kCount];
         shape.least = least;
-    } else if (halves && shape.slices == 1 && !quant) {
-        // The same walks by half workgroups (see prefill_half_kernel): the same sums in the same order, so the results are of
-        // the shape they were.  Over 160 batches of prompts half workgroups took 0.72 to 0.95 of the time where a dense walk is up to
-        // 30 tiles long on average, 0.84 to 1.01 up to 60, 0.92 to 1.03 beyond.  (Quantised pages are dequantised by every
-        // workgroup for itself, and half workgroups are twice as many.)
-        constexpr float kHalfWalkTiles = 60.f;
-        const PrefillShape half = {1, {false, false}, false, true, 0, 1};
-        const ClassCost dense = class_cost(lp, half, rows, 0, heads[0], quant, 0, 0.f);
-        if (class_walks(lp, rows, prompt ? 0.f : (float)rows.history_pages, dense, 0).mid <= kHalfWalkTiles) shape = half;
+    } else if (halves && shape.slices == 1 && !quant && halves_are_quicker(lp, rows, shape)) {
+        // the same walks by half workgroups: the same sums in the same order, so the results are of the shape they were
+        shape = {1, {false, false}, false, true, 0, 1};
     }
     return shape;
 }

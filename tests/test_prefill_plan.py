@@ -58,3 +58,29 @@ def test_arguments():
             B.lserve_probe_prefill_plan(desc, *bad)
     with pytest.raises(LserveError):
         B.lserve_probe_prefill_plan(L.AttnDesc(8, 2, [1, 0], page_size=32), 1, 10, 10)
+
+
+# (heads, KV heads, sequences of one length): half workgroups or whole ones, whichever took less time
+@pytest.mark.parametrize("heads,kv_heads,batch,length,half", [
+    (32, 8, 1, 4096, 1),     # 109 us by half workgroups, 121 by whole ones
+    (32, 32, 10, 327, 1),    # 34 and 47
+    (32, 16, 1, 51, 0),      # 7.2 and 6.3: one tile
+    (32, 8, 4, 64, 0),       # 7.8 and 6.8
+    (32, 32, 1, 51, 1),      # 6.2 and 6.4
+    (64, 8, 16, 128, 0),     # 48 and 30: two full rounds of walks of two tiles
+    (64, 8, 16, 70, 1),      # 19 and 22
+    (64, 8, 13, 215, 1),     # 41 and 49
+    (32, 8, 4, 399, 0),      # 22.3 and 21.2: one full round of some tiles each
+    (32, 8, 8, 231, 0),      # 17.4 and 17.1
+    (32, 8, 16, 123, 1),     # 13.8 and 15.6
+    (32, 8, 2, 1024, 1),     # 32 and 38
+    (32, 32, 4, 385, 0),     # 22.4 and 20.4
+    (32, 32, 6, 385, 1),     # 30 and 35
+    (32, 32, 18, 3001, 0),   # 1447 and 1352: 27 rounds, no groups
+    (32, 32, 21, 1888, 1),   # 767 and 785
+    (32, 32, 5, 3017, 1),    # 362 and 371
+    (32, 8, 1, 65536, 0),    # 16.2 ms and 15.7
+])
+def test_half_workgroups_where_they_are_quicker(heads, kv_heads, batch, length, half):
+    desc = L.AttnDesc(heads, kv_heads, [1] * (kv_heads // 2) + [0] * (kv_heads // 2))
+    assert B.lserve_probe_prefill_plan(desc, batch, batch * length, length)["half"] == half
