@@ -1842,10 +1842,13 @@ hipError_t launch_slices(const PrefillLaunch& a, int slices) {
             return hipGetLastError();
         }
     }
-    if (slices == 2)
-        LSERVE_PREFILL_SLICES(2);
-    else
-        LSERVE_PREFILL_SLICES(1);
+    if constexpr (MODE != kMasked) {  // listed masks: one or four
+        if (slices == 2) {
+            LSERVE_PREFILL_SLICES(2);
+            return hipGetLastError();
+        }
+    }
+    LSERVE_PREFILL_SLICES(1);
 #undef LSERVE_PREFILL_SLICES
     return hipGetLastError();
 }

@@ -57,7 +57,7 @@ def test_decode_kernels_leave_room_for_two_workgroups(kernels):
 
 def test_prefill_kernels_use_no_scratch(kernels):
     found = [k for name, k in kernels.items() if "sparse_prefill_kernel" in name]
-    assert len(found) == 2 * (3 + 3 + 3 + 2 + 2)  # types, slices of each of the five kinds
+    assert len(found) == 2 * (3 + 2 + 3 + 2 + 2)  # types, slices over prompts, listed masks, pages of 16, 8 and 4 bits
     assert all(k[".private_segment_fixed_size"] == 0 and k[".vgpr_count"] <= 256 for k in found)
 
 
