@@ -13,13 +13,36 @@ CASES = [  # heads, KV heads, history, new tokens
     (12, 4, (1700, 2000, 64), (1500, 0, 2000)),   # an idle sequence; sink and local pages are all there is
     (64, 8, (2047,), (400,)),
     (8, 1, (3001,), (300,)),                      # no streaming head
+    (32, 8, (4400, 4100), (2500, 2600)),          # whole workgroups in one slice over the 16-bit pages
+    # dense walks over the 16-bit pages cut into pieces, streaming heads in a launch of their own
+    (32, 8, (16001,), (512,)),
+    (8, 2, (30000,), (1500,)),
+    (12, 4, (30001,), (900,)),                    # groups of three
+    (16, 4, (20001, 3000), (900, 300)),           # sequences of different lengths
 ]
+PIECES = (5, 7, 8, 9, 10)
+
+
+def _scratch(desc, heads, hkv, hist, fresh, bits, sink, local):
+    """The plan, and the scratch it takes: expanded pages, ring and tables, then the pieces."""
+    import paper_2502_14866_amd as L
+
+    pages = max(-(-(h + n) // 64) for h, n in zip(hist, fresh))
+    plan = L.lserve_probe_prefill_plan(desc, len(hist), sum(fresh), max(fresh), pages, bits)
+    streaming, ring = hkv // 2, sink // 64 + local // 64
+    whole = lambda x: -(-x // 256) * 256
+    slab, b, group = 64 * 128 * 2, len(hist), heads // hkv
+    per_block = 4 if group % 4 == 0 else 2 if group % 2 == 0 else 1
+    expanded = (2 * whole(b * pages * (hkv - streaming) * slab) + 2 * whole(b * ring * streaming * slab) + whole(4 * b * pages)
+                + whole(4 * b * ring))
+    return plan, expanded, plan["pieces"] * (hkv - streaming) * (group // per_block) * 8 * (32 * 128 + 64) * 4
 
 
 @pytest.mark.parametrize("dtype,bits", [("fp16", 8), ("bf16", 8), ("fp16", 4), ("bf16", 4)])
 @pytest.mark.parametrize("two_way", [False, True])
 @pytest.mark.parametrize("case", range(len(CASES)))
 def test_chunks_over_expanded_pages(case, dtype, bits, two_way, monkeypatch):
+    import paper_2502_14866_amd as L
     import paper_2502_14866_amd.binding as B
 
     heads, hkv, hist, fresh = CASES[case]
@@ -36,9 +59,10 @@ def test_chunks_over_expanded_pages(case, dtype, bits, two_way, monkeypatch):
     monkeypatch.setattr(B, "_chunk_scratch", recorded)
     monkeypatch.setattr(paged, "CASES", [(heads, hkv, hist, fresh, {8: None, 4: None})])
     paged.test_chunks_in_every_launch_shape(0, dtype, bits, two_way)
-    pages = max(-(-(h + n) // 64) for h, n in zip(hist, fresh))
-    dense = hkv - hkv // 2
-    assert used[0] is not None and used[0].numel() >= len(hist) * pages * dense * 2 * 64 * 128 * 2
+    desc = L.AttnDesc(heads, hkv, [1 if h < hkv // 2 else 0 for h in range(hkv)], sink_tokens=paged.SINK, local_tokens=paged.LOCAL)
+    plan, expanded, pieces = _scratch(desc, heads, hkv, hist, fresh, bits, paged.SINK, paged.LOCAL)
+    assert plan["expand"] and bool(plan["pieces"]) == (case in PIECES) and plan["apart"] == (case in PIECES and hkv > 1)
+    assert len(used) == 1 and used[0].numel() == expanded + pieces
 
 
 @pytest.mark.parametrize("two_way", [False, True])

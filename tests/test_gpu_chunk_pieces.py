@@ -24,6 +24,7 @@ CASES = [  # heads, KV heads, history, new tokens
 @pytest.mark.parametrize("dtype,bits,two_way", [("fp16", 16, False), ("bf16", 16, True), ("bf16", 8, False), ("fp16", 4, True)])
 @pytest.mark.parametrize("case", range(len(CASES)))
 def test_chunks_in_pieces(case, dtype, bits, two_way, monkeypatch):
+    import paper_2502_14866_amd as L
     import paper_2502_14866_amd.binding as B
 
     heads, hkv, hist, fresh = CASES[case]
@@ -38,7 +39,17 @@ def test_chunks_in_pieces(case, dtype, bits, two_way, monkeypatch):
     monkeypatch.setattr(B, "_chunk_scratch", recorded)
     monkeypatch.setattr(paged, "CASES", [(heads, hkv, hist, fresh, {16: None, 8: None, 4: None})])
     paged.test_chunks_in_every_launch_shape(0, dtype, bits, two_way)
-    assert len(used) == 1 and (used[0] is not None or (bits == 16 and len(hist) > 64))
+    desc = L.AttnDesc(heads, hkv, [1 if h < hkv // 2 else 0 for h in range(hkv)], sink_tokens=paged.SINK, local_tokens=paged.LOCAL)
+    pages = max(-(-(h + n) // 64) for h, n in zip(hist, fresh))
+    plan = L.lserve_probe_prefill_plan(desc, len(hist), sum(fresh), max(fresh), pages, bits)
+    assert len(used) == 1 and not plan["expand"]
+    if bits == 16 and len(hist) > 64:
+        assert used[0] is None and not plan["pieces"]
+    else:
+        group = heads // hkv
+        per_block = 4 if group % 4 == 0 else 2 if group % 2 == 0 else 1
+        assert plan["pieces"] and plan["apart"]
+        assert used[0].numel() == plan["pieces"] * (hkv - hkv // 2) * (group // per_block) * 8 * (32 * 128 + 64) * 4
 
 
 def test_paged_prefill_in_pieces_repeats_itself_and_agrees_with_whole_walks():

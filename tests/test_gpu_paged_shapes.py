@@ -53,8 +53,13 @@ def _sample(fresh, per_seq, seed):
     return np.asarray(tok, dtype=np.int32)
 
 
-CASES = [  # heads, KV heads, history, new tokens, {bits: (slices, dense folded, streaming folded, units are query tiles)}
-    (32, 8, (101, 333), (1500, 1500), {16: (1, 0, 0, 0), 8: (1, 0, 0, 0), 4: (1, 0, 0, 0)}),
+# heads, KV heads, history, new tokens, {bits: (slices, dense folded, streaming folded, units are query tiles)}; "half": the launch over 16
+# bits is by half workgroups; "expand": that over quantised pages goes over expanded ones
+CASES = [
+    (32, 8, (101, 333), (1500, 1500), {16: (1, 0, 0, 0), 8: (1, 0, 0, 0), 4: (1, 0, 0, 0), "half": 1, "expand": 0}),
+    # whole workgroups in one slice: four heads to one, and four tiles
+    (32, 8, (4400, 4100), (2500, 2600), {16: (1, 0, 0, 0), 8: (1, 0, 0, 0), 4: (1, 0, 0, 0), "half": 0, "expand": 1}),
+    (24, 8, (6001, 6000), (1500, 2000), {16: (1, 0, 0, 0), 8: (1, 0, 0, 0), 4: (1, 0, 0, 0), "half": 0, "expand": 1}),
     (32, 8, (1500,), (4096,), {16: (2, 1, 0, 0), 8: (1, 0, 0, 1), 4: (1, 0, 0, 1)}),
     (32, 8, (1500, 37), (700, 2200), {16: (2, 1, 0, 0), 8: (2, 1, 0, 0), 4: (2, 1, 0, 0)}),
     (32, 8, (101, 0), (300, 1200), {16: (2, 1, 1, 0), 8: (2, 1, 1, 0), 4: (2, 1, 1, 0)}),
@@ -84,6 +89,9 @@ def test_chunks_in_every_launch_shape(case, dtype, bits, two_way):
     desc = L.AttnDesc(heads, hkv, w.streaming_flags(), dtype=w.torch_dtype, sink_tokens=SINK, local_tokens=LOCAL)
     if shapes[bits] is not None:
         assert L.lserve_probe_prefill_shape(desc, B, sum(fresh), max(fresh), pages, bits) == shapes[bits]
+    if "half" in shapes:
+        plan = L.lserve_probe_prefill_plan(desc, B, sum(fresh), max(fresh), pages, bits)
+        assert plan["half"] == (shapes["half"] and bits == 16) and plan["expand"] == (shapes["expand"] and bits != 16)
     s_pages, w_pages = SINK // NP, LOCAL // NP
     g = torch.Generator().manual_seed(case)
     table = torch.randperm(B * pages, generator=g).to(torch.int32).reshape(B, pages)
