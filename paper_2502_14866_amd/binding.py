@@ -430,7 +430,7 @@ def lserve_sparse_prefill_chunk(desc: AttnDesc, kv: PagedKV, q: torch.Tensor, k_
                                 scratch: Optional[torch.Tensor] = None) -> None:
     """scratch: device memory of lserve_chunk_scratch_bytes(desc, batch, q.shape[0], max_new_per_seq, page_table.shape[1], kv_bits)
     bytes or more, not shared with work in flight; too little of it, an empty tensor for instance: the call does without.  None: taken
-    from torch's allocator for the call (up to 1 GiB of expanded pages, by the width of the page table, and some ten MB of pieces),
+    from torch's allocator for the call (up to 1 GiB of expanded pages, by the width of the page table, and 34 to 136 MB of pieces),
     on whatever stream it goes to and from the graph's own pool under torch.cuda.graph, so that the same call gives the same bits
     everywhere.  A call goes without, slower and with sums in another order, where torch is out of memory (a RuntimeWarning says
     so) and in a capture begun by other means than torch.cuda.graph."""

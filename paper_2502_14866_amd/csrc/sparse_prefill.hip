@@ -282,11 +282,11 @@ __device__ __forceinline__ BlockOrder block_order(const int* cu_seqlens, const i
 // nearly equal length, worked on by a workgroup each.  A piece leaves its unnormalised outputs, maxima and sums in
 // PrefillPieces::partials, and fold_pieces_kernel puts the pieces of a block together.  The span is the smallest that needs no
 // more pieces than the launch has workgroups for; every workgroup works it out from the lengths, which the host does not know.
-// Measured, whole walks in the best shape and pieces: 512 tokens over 32768, 32 / 8 heads, 373 and 171 us (13 for the streaming
+// Measured, whole walks in the best shape and pieces: 512 tokens over 32768, 32 / 8 heads, 365 and 176 us (13 for the streaming
 // heads, see streams_apart; 8 pieces to a block: 65 steps of 1.85 us with every compute unit at work, then 11 us to put 33 MB of
-// pieces together); 17 over 42116, twice, 441 and 79; 108 over 73893, 32 / 16 heads, 982 and 267.  Prompts are not cut: one of 4096 tokens takes 119 us whole and 124 or more in any
-// number of pieces, one of 8192 313 and 340, because what they gain in balance (42 steps a compute unit where the longest walk has
-// 64) goes into the starts of the pieces and into putting them together.
+// pieces together); 17 over 42116, twice, 441 and 79; 108 over 73893, 32 / 16 heads, 982 and 267.  Prompts are not cut: one of 4096
+// tokens takes 119 us whole and 124 or more in any number of pieces, one of 8192 313 and 340, because what they gain in balance (42
+// steps a compute unit where the longest walk has 64) goes into the starts of the pieces and into putting them together.
 // No block is fewer pieces than the key slices it has without scratch (PrefillPieces::least), however short its walk: the weights of
 // a row are rounded to 16 bits relative to the maximum of their piece or slice, and fewer of these make the error larger.
 // A position in the launch stands for a piece: last pieces first (none is shorter than half a span), then the last but one,
@@ -1298,7 +1298,7 @@ __global__ __launch_bounds__(256) void fold_pieces_kernel(LayerParams lp, const 
 // A chunk of many rows has every tile of a quantised history dequantised by every workgroup that walks it, next to the softmax
 // in the vector pipe: a step takes 2.21 us where 16-bit pages take 1.75.  With scratch for it the history is dequantised once,
 // into pages of the layer's type, and the chunk then walks those: the same values, rounded the same way.  Two chunks of 1500 and
-// 2048 tokens over 24001 of 8 bits, 32 / 8 heads: 930 -> 830 us, 40 of them for 98 MB of pages; 859 over 8966, five times, 64 / 8
+// 2048 tokens over 24001 of 8 bits, 32 / 8 heads: 949 -> 849 us, 27 of them for 98 MB of pages; 859 over 8966, five times, 64 / 8
 // heads: 672 -> 573; 1392 over 1055 of 4 bits, twice: 93 -> 83.
 struct ExpandedPages {
     uint16_t *k, *v;            // [batch][max_pages][dense heads][64][D]
