@@ -1531,17 +1531,6 @@ float cut_launch_time(const LayerParams& lp, const PrefillRows& rows, float hist
     return t + kLaunchUs + kFoldLaunchUs + kFoldPieceUs * count;
 }
 
-// The shape of a launch.  Measured with one / two / four slices: 512 new tokens over a history of 32768, 849 / 520 / 363 us;
-// 2635 over 45405, 1229 / 1480 / 1513 us (one round of workgroups, or two of half the length at more per step); one prompt of
-// 4096 tokens, 119 / 116 / 146 us; of 65536, 15.4 / 17.6 / 21.6 ms.  Heads or query tiles as units of one slice: 5 sequences of
-// 7 .. 123 tokens, 12.4 and 9.3 us (fewer wavefronts at work on a compute unit); 8 of 100 .. 1500, 60 and 73 us.
-// The history of a chunk is not known on the host.  It may be as long as the page table allows, which a caller that
-// allocates what it needs sees to, or far shorter, in a table as wide as the longest context: the shape is the one that on
-// average costs least over what it could have been for histories of that length (counted four times), a quarter, a
-// sixteenth and a sixty-fourth of it (490 chunks: 1.5 % over the best shape with a tight table and 2.2 % with one 32 times as
-// wide; by the length of the table alone 1.1 and 3.3 %, and up to half the speed lost).  Where the number of blocks is an
-// estimate, near the end of a round of workgroups, so is the time: the mean of a few blocks less and a few more.
-
 // May it pay to cut the walks of these chunks into pieces?  A first look, for the host's time: not where the history is short
 // or whole walks fill the chip.
 bool may_cut(const LayerParams& lp, const PrefillRows& rows) {
@@ -1557,21 +1546,26 @@ bool may_cut(const LayerParams& lp, const PrefillRows& rows) {
 bool streams_apart(const LayerParams& lp, const PrefillShape& whole) { return whole.slices > 1 && lp.streaming_mask != 0; }
 
 // Are half workgroups (see prefill_half_kernel) quicker than the whole ones of a shape of one slice?  (Not over quantised pages, which
-// every workgroup dequantises for itself: half ones are twice as many.)  Measured over 850 batches, half as a part of whole: 0.64 to
+// every workgroup dequantises for itself: half ones are twice as many.)  Measured over 1000 batches, half as a part of whole: 0.64 to
 // 1.08 where a dense walk is up to 60 tiles long on average, 0.92 to 1.03 beyond; and up to 60 whole ones are as quick or quicker
-// where (the last two, and of the second what is said of four heads, over prompts only)
+// where (over prompts only but for the first, the second by tiles of one head, and the last)
 //   - a dense walk is a single tile and whole workgroups have tiles of one head for units (1.02 to 1.16: 51 tokens, 32 / 16 heads, 6.3 and
 //     7.2 us): most of the time is the way of that tile into LDS, on which a half workgroup has half the wavefronts;
 //   - whole workgroups of four heads, or of four tiles of one, fill the chip just once with walks of some tiles (1.0 to 1.04: eight of
 //     231, 32 / 8 heads, 17.1 and 17.4; 0.96 to 1.1: four of 385, 32 / 32, 20.4 and 22.4, four chunks of 165 over 173 15.8 and 17.6; with walks
 //     of up to two tiles 0.87 to 0.95, of seven and more 0.80 to 0.98);
 //   - those of four heads fill it twice with walks of two tiles (0.90 to 1.6: 16 of 128, 64 / 8 heads, 30 and 48, of 123 27.6 and 25.8);
-//   - no two heads read the same keys and walks are not short in more than 16 rounds (0.98 to 1.07: 18 of 3001, 32 / 32 heads, 1352 and
-//     1447).
+//   - they fill it once and a half to twice without a streaming head, whose short walks would fill the gaps (0.98 to 1.06: two of 2000, 32 / 8
+//     heads, 82.5 and 87.7);
+//   - there are more dense KV heads than XCDs, each of which then works on several heads' keys at a time, in many rounds (0.98 to 1.28: 18 of
+//     3001, 32 / 32 heads, 16 of them streaming 1352 and 1447, none 1880 and 2400; 64 of 500, none streaming, 370 and 401; 16 chunks of
+//     1000 over 500, none streaming, 458 and 499).
 bool halves_are_quicker(const LayerParams& lp, const PrefillRows& rows, const PrefillShape& whole) {
     const int n_stream = count_streaming(lp), heads[2] = {lp.Hkv - n_stream, n_stream};
     const PrefillShape half = {1, {false, false}, false, true, 0, 1};
-    const ClassWalks walks = class_walks(lp, rows, (float)std::max(0, rows.history_pages), class_cost(lp, half, rows, 0, heads[0], false, 0, 0.f), 0);
+    const int cls = heads[0] > 0 ? 0 : 1;  // (of the dense heads, if there are any)
+    const ClassWalks walks =
+        class_walks(lp, rows, (float)std::max(0, rows.history_pages), class_cost(lp, half, rows, cls, heads[cls], false, 0, 0.f), cls);
     if (walks.mid > 60.f) return false;
     const bool prompt = rows.history_pages < 0, fours = lp.group % 4 == 0, single = lp.group % 2 != 0;
     if (walks.hi <= 1.f && whole.one_head) return false;
@@ -1579,16 +1573,27 @@ bool halves_are_quicker(const LayerParams& lp, const PrefillRows& rows, const Pr
     for (int c = 0; c < 2; ++c) rounds += class_cost(lp, whole, rows, c, heads[c], false, 0, 0.f).count;
     rounds /= std::max(1, num_compute_units() / kXcds);
     if (single && rounds > 0.8f && rounds <= 1.f && walks.mid >= 2.9f && walks.mid <= 6.5f) return false;
-    if (!prompt) return true;
+    const float together = heads[0] > kXcds ? rounds * (float)heads[0] : 0.f;
+    if (!prompt) return together <= 280.f;
     if (fours && rounds > 0.875f && rounds <= 1.f && walks.mid >= 2.2f && walks.mid <= 6.f) return false;
     if (fours && rounds > 1.75f && rounds <= 2.f && walks.mid >= 1.4f && walks.hi <= 2.f) return false;
-    return !(single && rounds > 16.f && walks.mid > 20.f);
+    if (n_stream == 0 && rounds > 1.4f && rounds <= 2.05f && walks.mid >= 12.f && walks.mid <= 32.f) return false;
+    return together <= 256.f || (together <= 400.f && walks.mid <= 20.f);
 }
 
 constexpr float kWeight[4] = {4.f, 1.f, 1.f, 1.f};  // of the guesses
 
-// The shape of a launch: of whole walks, or with `cut` also in pieces, so many that its workgroups are about one, two ... rounds
-// of the chip.
+// The shape of a launch.  Measured with one / two / four slices: 512 new tokens over a history of 32768, 849 / 520 / 363 us;
+// 2635 over 45405, 1229 / 1480 / 1513 us (one round of workgroups, or two of half the length at more per step); one prompt of
+// 4096 tokens, 119 / 116 / 146 us; of 65536, 15.4 / 17.6 / 21.6 ms.  Heads or query tiles as units of one slice: 5 sequences of
+// 7 .. 123 tokens, 12.4 and 9.3 us (fewer wavefronts at work on a compute unit); 8 of 100 .. 1500, 60 and 73 us.
+// The history of a chunk is not known on the host.  It may be as long as the page table allows, which a caller that
+// allocates what it needs sees to, or far shorter, in a table as wide as the longest context: the shape is the one that on
+// average costs least over what it could have been for histories of that length (counted four times), a quarter, a
+// sixteenth and a sixty-fourth of it (490 chunks: 1.5 % over the best shape with a tight table and 2.2 % with one 32 times as
+// wide; by the length of the table alone 1.1 and 3.3 %, and up to half the speed lost).  Where the number of blocks is an
+// estimate, near the end of a round of workgroups, so is the time: the mean of a few blocks less and a few more.
+// cut: pieces too, so many that the workgroups of the launch are about one, two ... rounds of the chip.
 // uncut: the shape of the same call without scratch.  Streaming heads keep it where dense walks are cut, and no row's sums are taken in
 // fewer key ranges than there.
 PrefillShape choose_shape(const LayerParams& lp, const PrefillRows& rows, bool quant, const PrefillShape* uncut = nullptr, bool cut = false,

@@ -84,3 +84,24 @@ def test_arguments():
 def test_half_workgroups_where_they_are_quicker(heads, kv_heads, batch, length, half):
     desc = L.AttnDesc(heads, kv_heads, [1] * (kv_heads // 2) + [0] * (kv_heads // 2))
     assert B.lserve_probe_prefill_plan(desc, batch, batch * length, length)["half"] == half
+
+
+@pytest.mark.parametrize("heads,kv_heads,batch,length,half", [  # no streaming head
+    (32, 32, 18, 3001, 0),   # 2400 us and 1880: more dense heads than XCDs, in many rounds
+    (32, 32, 64, 500, 0),    # 401 and 370
+    (32, 16, 18, 3001, 0),   # 2033 and 1853
+    (32, 16, 16, 2000, 1),   # 741 and 760
+    (32, 32, 4, 2000, 1),    # 175 and 184
+    (32, 8, 16, 2000, 1),    # 684 and 702
+    (32, 8, 2, 2000, 0),     # 87.7 and 82.5: two rounds of long walks
+    (32, 8, 1, 2500, 1),     # 69 and 79
+])
+def test_half_workgroups_without_streaming_heads(heads, kv_heads, batch, length, half):
+    desc = L.AttnDesc(heads, kv_heads, [0] * kv_heads)
+    assert B.lserve_probe_prefill_plan(desc, batch, batch * length, length)["half"] == half
+
+
+def test_half_workgroups_of_streaming_heads_alone():
+    desc = L.AttnDesc(32, 8, [1] * 8)
+    assert B.lserve_probe_prefill_plan(desc, 8, 16000, 2000)["half"] == 1  # 204 us and 220
+    assert B.lserve_probe_prefill_plan(desc, 1, 51, 51)["half"] == 0       # 7.5 and 6.7
