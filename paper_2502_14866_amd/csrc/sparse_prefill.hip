@@ -31,6 +31,7 @@ namespace {
 
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf168_t __attribute__((ext_vector_type(8)));
+typedef float float4_t __attribute__((ext_vector_type(4)));
 typedef float float16_t __attribute__((ext_vector_type(16)));
 
 constexpr int kTileLog2 = 6;
@@ -80,10 +81,16 @@ template <> struct Mfma<F16> {
     static __device__ __forceinline__ float16_t run(uint4 a, uint4 b, float16_t c) {
         return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8_t, a), __builtin_bit_cast(half8_t, b), c, 0, 0, 0);
     }
+    static __device__ __forceinline__ float4_t run16(uint4 a, uint4 b, float4_t c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a), __builtin_bit_cast(half8_t, b), c, 0, 0, 0);
+    }
 };
 template <> struct Mfma<BF16> {
     static __device__ __forceinline__ float16_t run(uint4 a, uint4 b, float16_t c) {
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf168_t, a), __builtin_bit_cast(bf168_t, b), c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ float4_t run16(uint4 a, uint4 b, float4_t c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf168_t, a), __builtin_bit_cast(bf168_t, b), c, 0, 0, 0);
     }
 };
 
@@ -657,9 +664,12 @@ __device__ __forceinline__ void prefill_workgroup(
     for (int db = 0; db < 4; ++db)
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[db][i] = 0.f;
-    float m_run = -INFINITY, l_run = 0.f;  // running maximum (scaled, base 2) and sum of this lane's query row
-    // The score products start from -m_run instead of 0 (the accumulator input of the first product), so a
-    // tile whose maxima do not exceed the running ones needs no subtraction before exp2; 0 while m_run = -inf.
+    // Reference of this lane's query row, in units of the unscaled products, and the sum of its weights relative to it.  The
+    // reference is a maximum of the row's scores, but not always the latest (see weights_and_values).
+    float m_run = -INFINITY, l_run = 0.f;
+    int unset = 1;  // some row of the wave has no reference yet
+    // The score products start from -m_run instead of 0 (the accumulator input of the first product), so that scores come
+    // relative to it at no cost; 0 while m_run = -inf.
     float16_t neg_m;
 #pragma unroll
     for (int i = 0; i < 16; ++i) neg_m[i] = 0.f;
@@ -851,18 +861,7 @@ __device__ __forceinline__ void prefill_workgroup(
 #pragma unroll
         for (int kk = 0; kk < 8; ++kk)
             asm volatile("" : "+v"(qreg[kk].x), "+v"(qreg[kk].y), "+v"(qreg[kk].z), "+v"(qreg[kk].w));
-        // The softmax scale (times log2 e) goes into Q once, so the scores leave the matrix pipe ready for
-        // exp2.  The extra rounding of Q to 16 bit moves a logit by about 2^-9 (bf16) or 2^-11 (fp16) of its
-        // size times 0.13, an order below the rounding of the softmax weights themselves.
-#pragma unroll
-        for (int kk = 0; kk < 8; ++kk) {
-            uint32_t* w = reinterpret_cast<uint32_t*>(&qreg[kk]);
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                w[i] = Elem<T>::pack(Elem<T>::lo(w[i]) * lp.sm_scale_log2, Elem<T>::hi(w[i]) * lp.sm_scale_log2);
-        }
     }
-
 
     // loop-invariant operand offsets of this lane inside a stage (its slice's tile)
     int koff[8], voff[4];
@@ -942,44 +941,88 @@ __device__ __forceinline__ void prefill_workgroup(
                 }
         }
     };
-    // online softmax of this lane's query row (its keys are split between the two lane halves), then O^T += V^T P^T
+    // Selects a lane's own row in the sums of weights: see below.
+    const uint32_t own_row = ((lane % 16) / 4 - lane / 16) % 2 == 0 ? Ones<T>::pair : 0u;
+    // Softmax of this lane's query row (its keys are split between the two lane halves), then O^T += V^T P^T.
+    //
+    // Weights are exp2(scale (score - reference)), and the reference stays what it is until the weights of some row of the wave add
+    // up to kMostWeight in a tile: below that nothing overflows (fp16 ends at 65504), and weights above 1 have the bits of those below.
+    // So no maximum stands between the products and the exponentials, and most tiles need none: a tile is 32 multiplications, 32
+    // exponentials and 16 conversions per lane, where a running maximum took a chain of 16 in front of them and, whenever the maximum of
+    // one of the wave's 32 rows moved (three of four tiles among a walk's first 64), 112 instructions to rescale.  The scale meets the
+    // fp32 products, and the queries stay as they are: scaled and rounded in front of the products they save the multiplications, which
+    // gains 0.1 % over 26 prompts and chunks, and lose a quarter of the precision (against 64 bits, 16 of 77 .. 3001 in bf16: 2.00e-3;
+    // with rounded queries 2.55e-3, with the running maximum 2.50e-3).  An fma of product, scale and reference instead of the
+    // accumulator input and a multiplication: 7 % slower at 65536 tokens.  Running maximum and this, on one box: 65536 tokens 15.68 and 15.08
+    // ms, 4096 111 and 105 us, 12345 under a mask 319 and 295, 512 over 32768 174 and 158, two of 2642, 64 / 8 heads, 192 and 177.
+    constexpr float kMostWeight = 4096.f;
     auto weights_and_values = [&](float16_t (&s)[2], const unsigned char* vs) {
-        float mx = fmaxf(s[0][0], s[1][0]);
+        uint4 pb[2][2];  // P^T packed to 16 bit: [key block][16-key step]
+        float sum;
+        int moved = unset;
+        asm volatile("" : "+s"(moved));  // (opaque, or the second round becomes a copy of the first that costs 20 registers)
+#pragma clang loop unroll(disable)
+        for (;;) {
+            if (moved) {  // the reference becomes the maximum so far: subtract and rescale
+                float mx = fmaxf(s[0][0], s[1][0]);
 #pragma unroll
-        for (int i = 1; i < 16; ++i) mx = __builtin_fmaxf(__builtin_fmaxf(mx, s[0][i]), s[1][i]);  // v_max3_f32
-        mx = halves_max(mx);  // relative to the running maximum (to 0 before the first kept tile)
-        if (__any(mx > 0.f || m_run == -INFINITY)) {  // some row's maximum moved: subtract and rescale
-            const float m_base = m_run == -INFINITY ? 0.f : m_run;
-            const float m_new = fmaxf(m_run, m_base + mx);
-            const float delta = m_new - m_base;                         // 0 for rows whose maximum stayed
-            const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);  // exp2(-inf) = 0 on the first tile
-            l_run *= alpha;
+                for (int i = 1; i < 16; ++i) mx = __builtin_fmaxf(__builtin_fmaxf(mx, s[0][i]), s[1][i]);  // v_max3_f32
+                mx = halves_max(mx);  // relative to the reference (to 0 before the first kept tile)
+                const float m_base = m_run == -INFINITY ? 0.f : m_run;
+                const float m_new = fmaxf(m_run, m_base + mx);
+                const bool none = m_new == -INFINITY;                // nothing but -inf so far
+                const float delta = none ? 0.f : m_new - m_base;     // 0 for rows whose maximum stayed
+                const float alpha = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_run - m_new) * lp.sm_scale_log2);
+                l_run *= alpha;
 #pragma unroll
-            for (int db = 0; db < 4; ++db)
+                for (int db = 0; db < 4; ++db)
 #pragma unroll
-                for (int i = 0; i < 16; ++i) acc[db][i] *= alpha;
+                    for (int i = 0; i < 16; ++i) acc[db][i] *= alpha;
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) s[kb][i] -= delta;
+                m_run = m_new;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) neg_m[i] = none ? 0.f : -m_new;
+                unset = __builtin_amdgcn_readfirstlane(__any(none));
+            }
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) {
+                float pf[16];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) pf[i] = __builtin_amdgcn_exp2f(s[kb][i] * lp.sm_scale_log2);
+                pb[kb][0] = pack8<T>(pf);
+                pb[kb][1] = pack8<T>(pf + 8);
+            }
+            // Row sums of the rounded weights, the same values the second product uses.
+            if (moved) {
+                sum = 0.f;
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb) {
+                    const uint32_t w[8] = {pb[kb][0].x, pb[kb][0].y, pb[kb][0].z, pb[kb][0].w,
+                                           pb[kb][1].x, pb[kb][1].y, pb[kb][1].z, pb[kb][1].w};
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) sum = Elem<T>::dot2(w[u], Ones<T>::pair, sum);
+                }
+                sum = halves_sum(sum);
+                break;
+            }
+            // In most tiles by four products of 16 x 16 x 32 (0.7 % quicker).  Read as the 32 x 16 operand of such a product, P^T has
+            // query c and query 16 + c in its column c, the one in the first and third eight keys, the other in the second and
+            // fourth; ones in those of row r's choice leave every lane with the sum of its own query.  A weight that is infinite or not
+            // a number spoils the sum of the other query too: then as above.
+            float4_t sums = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                for (int i = 0; i < 16; ++i) s[kb][i] -= delta;
-            m_run = m_new;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) neg_m[i] = -m_new;
+                for (int j = 0; j < 2; ++j) sums = Mfma<T>::run16(make_uint4(own_row, own_row, own_row, own_row), pb[kb][j], sums);
+            sum = sums[0];
+            if (!__any(!(sum < kMostWeight))) break;
+            moved = 1;
+            asm volatile("" : "+s"(moved));
         }
-        uint4 pb[2][2];  // P^T packed to 16 bit: [key block][16-key step]
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
-            float pf[16];
-#pragma unroll
-            for (int i = 0; i < 16; ++i) pf[i] = __builtin_amdgcn_exp2f(s[kb][i]);
-            pb[kb][0] = pack8<T>(pf);
-            pb[kb][1] = pack8<T>(pf + 8);
-            // row sum from the rounded weights, the same values the second product uses
-            const uint32_t w[8] = {pb[kb][0].x, pb[kb][0].y, pb[kb][0].z, pb[kb][0].w,
-                                   pb[kb][1].x, pb[kb][1].y, pb[kb][1].z, pb[kb][1].w};
-#pragma unroll
-            for (int u = 0; u < 8; ++u) l_run = Elem<T>::dot2(w[u], Ones<T>::pair, l_run);
-        }
+        l_run += sum;
         // O^T += V^T * P^T, 16 keys per instruction; operand reads run one step ahead
 #pragma unroll
         for (int step = 0; step < 4; ++step) {
@@ -1095,7 +1138,8 @@ __device__ __forceinline__ void prefill_workgroup(
 
     if (CUT) slot = __builtin_amdgcn_readfirstlane(slot);
     // ---- epilogue: lane (n, half) holds O^T[d][q] for d = 32 db + 8 (i / 4) + 4 half + i % 4
-    const float lt = halves_sum(l_run);
+    const float lt = l_run;
+    m_run *= lp.sm_scale_log2;
     const int pos = iq * kTile + row0 + n;
     const int row = pos - first;
     if (CUT && slot >= 0) {  // a piece: as the lanes hold it, 1 KiB at a time
