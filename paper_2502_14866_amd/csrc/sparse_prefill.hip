@@ -1156,19 +1156,38 @@ __device__ __forceinline__ void prefill_workgroup(
     }
     if (!fold) {
         if (!wave_has_rows) return;
-        if (pos >= len || pos < first) return;
         const float inv = lt > 0.f ? 1.f / lt : 0.f;  // a row that keeps nothing (possible with a listed mask) gives 0
-        uint16_t* dst = out + ((size_t)(start + row) * lp.H + h) * kHeadDim;
+        // The rows go out through LDS (the tiles are done with: the loop ended on a barrier), 8 KiB to a wave, chunks permuted as in a K
+        // tile, so that sixteen lanes store a row.  As the lanes hold them, 16 bytes of 32 rows to an instruction, the stores of a
+        // workgroup kept the address path, which also brings in the tiles of the compute unit's other workgroup, busy for 1 us: 16
+        // prompts of 77 .. 3001 tokens 191 -> 177 us, of 123 14.8 -> 12.9, ten of 105, 32 / 16 heads, 12.2 -> 9.8.
+        constexpr int kRowsBytes = 32 * kHeadDim * 2, kPerArray = SL * kKTileBytes / kRowsBytes;
+        unsigned char* const arrays[4] = {k_lds0, v_lds0, k_lds1, v_lds1};
+        static_assert(kWaves <= (kOneStage ? 2 : 4) * kPerArray, "room for the rows of every wave");
+        unsigned char* room = arrays[0];
+#pragma unroll
+        for (int i = 1; i < ceil_div(kWaves, kPerArray); ++i)
+            if (wave / kPerArray == i) room = arrays[i];
+        room += wave % kPerArray * kRowsBytes;
 #pragma unroll
         for (int db = 0; db < 4; ++db)
 #pragma unroll
             for (int g4 = 0; g4 < 4; ++g4) {
-                const int d = db * 32 + 8 * g4 + 4 * half;
                 uint2 w;
                 w.x = Elem<T>::pack(acc[db][4 * g4] * inv, acc[db][4 * g4 + 1] * inv);
                 w.y = Elem<T>::pack(acc[db][4 * g4 + 2] * inv, acc[db][4 * g4 + 3] * inv);
-                *reinterpret_cast<uint2*>(dst + d) = w;
+                *reinterpret_cast<uint2*>(room + n * kKRowBytes + k_chunk_pos(n, db * 4 + g4) * 16 + 8 * half) = w;
             }
+        asm volatile("" ::: "memory");  // LDS serves a wave in order, if the compiler asks in order
+        const int r4 = lane / 16, pos4 = pos - n + r4;  // of the first of the lane's rows, four apart
+        uint16_t* dst = out + ((size_t)(start + pos4 - first) * lp.H + h) * kHeadDim + lane % 16 * 8;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const uint4 w = *reinterpret_cast<const uint4*>(room + (4 * i + r4) * kKRowBytes + k_chunk_pos(4 * i + r4, lane % 16) * 16);
+            if (pos4 + 4 * i < len && pos4 + 4 * i >= first)
+                *reinterpret_cast<uint4*>(dst + (ptrdiff_t)(4 * i) * lp.H * kHeadDim) = w;
+        }
+        if (pos >= len || pos < first) return;
         if (lse_out && half == 0)
             lse_out[(size_t)h * total_tokens + start + row] = lt > 0.f ? (m_run + __builtin_amdgcn_logf(lt)) * kLn2 : -INFINITY;
     } else if constexpr (SL > 1) {
@@ -1188,7 +1207,6 @@ __device__ __forceinline__ void prefill_workgroup(
         if (half == 0) fold_ml[wave][n] = make_float2(m_run, lt);
         __syncthreads();
         if (!wave_has_rows) return;
-        if (pos >= len || pos < first) return;
         const int peer0 = unit * SL * 2 + wave % 2;  // wave of slice 0 with the same rows; slice i is 2 i waves on
         float2 ml[SL];
         float m_all = -INFINITY;
@@ -1204,11 +1222,16 @@ __device__ __forceinline__ void prefill_workgroup(
             l_all = __builtin_fmaf(ml[i].y, f[i], l_all);
         }
         const float inv = l_all > 0.f ? 1.f / l_all : 0.f;
-        uint16_t* dst = out + ((size_t)(start + row) * lp.H + h) * kHeadDim;
+        // Finished rows, 64 bytes of a channel block, take the place of the first slice's contribution to the block and are stored
+        // from there, four lanes to a row (only this wave reads what the slices left of this block for these rows).
+        const int r4 = lane / 4, pos4 = pos - n + r4;
+        uint16_t* dst = out + ((size_t)(start + pos4 - first) * lp.H + h) * kHeadDim + lane % 4 * 8;
 #pragma unroll
         for (int u = 0; u < 4 / SL; ++u) {
             const int db = slice * (4 / SL) + u;
-            const float4* from = db == 0 ? room[0] : db == 1 ? room[1] : db == 2 ? room[2] : room[3];
+            float4* from = db == 0 ? room[0] : db == 1 ? room[1] : db == 2 ? room[2] : room[3];
+            unsigned char* rows = reinterpret_cast<unsigned char*>(from + peer0 * 4 * kWave);
+            uint2 done[4];
 #pragma unroll
             for (int g4 = 0; g4 < 4; ++g4) {
                 float o[4] = {0.f, 0.f, 0.f, 0.f};
@@ -1220,11 +1243,21 @@ __device__ __forceinline__ void prefill_workgroup(
                     o[2] = __builtin_fmaf(x.z, f[i], o[2]);
                     o[3] = __builtin_fmaf(x.w, f[i], o[3]);
                 }
-                const int d = db * 32 + 8 * g4 + 4 * half;
-                *reinterpret_cast<uint2*>(dst + d) =
-                    make_uint2(Elem<T>::pack(o[0] * inv, o[1] * inv), Elem<T>::pack(o[2] * inv, o[3] * inv));
+                done[g4] = make_uint2(Elem<T>::pack(o[0] * inv, o[1] * inv), Elem<T>::pack(o[2] * inv, o[3] * inv));
+            }
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int g4 = 0; g4 < 4; ++g4)
+                *reinterpret_cast<uint2*>(rows + n * 64 + (g4 ^ (n / 4 % 4)) * 16 + 8 * half) = done[g4];
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const uint4 w = *reinterpret_cast<const uint4*>(rows + (16 * i + r4) * 64 + (lane % 4 ^ (r4 / 4 % 4)) * 16);
+                if (pos4 + 16 * i < len && pos4 + 16 * i >= first)
+                    *reinterpret_cast<uint4*>(dst + (ptrdiff_t)(16 * i) * lp.H * kHeadDim + db * 32) = w;
             }
         }
+        if (pos >= len || pos < first) return;
         if (lse_out && slice == 0 && half == 0)
             lse_out[(size_t)h * total_tokens + start + row] =
                 l_all > 0.f ? (m_all + __builtin_amdgcn_logf(l_all)) * kLn2 : -INFINITY;
@@ -1325,14 +1358,24 @@ __global__ __launch_bounds__(256) void fold_pieces_kernel(LayerParams lp, const 
         }
         m = m_new;
     }
-    if (pos >= len || pos < first) return;
-    const int row = pos - first;
     const float inv = l > 0.f ? 1.f / l : 0.f;
-    uint16_t* dst = out + ((size_t)(start + row) * lp.H + h) * kHeadDim + db * 32 + 4 * half;
+    // 64 bytes of each row, stored by four lanes each
+    __shared__ __attribute__((aligned(16))) unsigned char rows[4][32 * 64];
 #pragma unroll
     for (int g4 = 0; g4 < 4; ++g4)
-        *reinterpret_cast<uint2*>(dst + 8 * g4) = make_uint2(Elem<T>::pack(o[4 * g4] * inv, o[4 * g4 + 1] * inv),
-                                                             Elem<T>::pack(o[4 * g4 + 2] * inv, o[4 * g4 + 3] * inv));
+        *reinterpret_cast<uint2*>(rows[db] + n * 64 + (g4 ^ (n / 4 % 4)) * 16 + 8 * half) =
+            make_uint2(Elem<T>::pack(o[4 * g4] * inv, o[4 * g4 + 1] * inv), Elem<T>::pack(o[4 * g4 + 2] * inv, o[4 * g4 + 3] * inv));
+    asm volatile("" ::: "memory");
+    const int r4 = lane / 4, pos4 = pos - n + r4;
+    uint16_t* dst = out + ((size_t)(start + pos4 - first) * lp.H + h) * kHeadDim + db * 32 + lane % 4 * 8;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const uint4 w = *reinterpret_cast<const uint4*>(rows[db] + (16 * i + r4) * 64 + (lane % 4 ^ (r4 / 4 % 4)) * 16);
+        if (pos4 + 16 * i < len && pos4 + 16 * i >= first)
+            *reinterpret_cast<uint4*>(dst + (ptrdiff_t)(16 * i) * lp.H * kHeadDim) = w;
+    }
+    if (pos >= len || pos < first) return;
+    const int row = pos - first;
     if (lse_out && db == 0 && half == 0)
         lse_out[(size_t)h * total_tokens + start + row] = l > 0.f ? (m + __builtin_amdgcn_logf(l)) * kLn2 : -INFINITY;
 }
