@@ -833,7 +833,10 @@ __device__ __forceinline__ void prefill_workgroup(
     int ph_nx2 = QUANT && it_first + 2 * stride < n_visit ? page_of(e_nx2 & kTileMask) : 0;
     // the first tiles travel while the queries are fetched
     if (it_first < n_visit) {
-        fetch(kBoth, k_lds0, v_lds0, e_cur & kTileMask, ph_first);
+        if constexpr (kOneStage)
+            fetch(kOnlyK, k_lds0, v_lds0, e_cur & kTileMask, ph_first);
+        else
+            fetch(kBoth, k_lds0, v_lds0, e_cur & kTileMask, ph_first);
         fetch_codes(kOnlyK, staged_k, e_cur & kTileMask, ph_first);
         fetch_codes(kOnlyV, staged_v, e_cur & kTileMask, ph_first);
     }
@@ -851,13 +854,36 @@ __device__ __forceinline__ void prefill_workgroup(
     // ---- Q^T operand: lane (n, half) holds Q[row][16 kk + 8 half .. + 8]
     uint4 qreg[8];
     {
-        const int row = min(max(iq * kTile + row0 + n, first), len - 1) - first;
-        const uint4* src = reinterpret_cast<const uint4*>(q + ((size_t)(start + row) * lp.H + h) * kHeadDim);
+        // By direct loads into LDS where it has room (the second stage; of a single one V's part, whose first tile comes after), a row
+        // to sixteen lanes: 16 bytes of 32 rows to an instruction, as the lanes want them, keep the address path busy twice as long.
+        // One prompt of 1024 tokens 21.9 -> 20.5 us, of 3200 80.1 -> 74.7, 16 of 123 12.4 -> 11.3, of 77 .. 3001 177 -> 172.  (Whole
+        // workgroups of one slice have half the room, and lose 2 to 3 % on long walks with more.)
+        constexpr int kRowsBytes = 32 * kHeadDim * 2, kPerArray = (kOneStage ? SL * kVTileBytes : kSpare) / kRowsBytes;
+        if constexpr (kWaves <= (kOneStage ? 1 : 2) * kPerArray) {
+            unsigned char* const room = (kOneStage ? v_lds0 : wave < kPerArray ? k_lds1 : v_lds1) + wave % kPerArray * kRowsBytes;
+            // rows without a query (in front of the chunk, past the end) read the nearest one
+            const int top = min(max(iq * kTile + row0, first), len - 1);
+            const unsigned long long rows = uniform64((unsigned long long)(q + ((size_t)(start + top - first) * lp.H + h) * kHeadDim));
+            const unsigned q_row_bytes = (unsigned)__builtin_amdgcn_readfirstlane(lp.H * kHeadDim * 2);
 #pragma unroll
-        for (int kk = 0; kk < 8; ++kk) qreg[kk] = src[kk * 2 + half];
+            for (int i = 0; i < 8; ++i) {
+                const int r = 4 * i + lane / 16, at = min(max(iq * kTile + row0 + r, first), len - 1) - top;
+                dma_load16(rows, (unsigned)at * q_row_bytes + k_chunk_pos(r, lane % 16) * 16,
+                           __builtin_amdgcn_readfirstlane(lds_address(room) + i * 1024));
+            }
+            dma_wait();
+#pragma unroll
+            for (int kk = 0; kk < 8; ++kk)
+                qreg[kk] = *reinterpret_cast<const uint4*>(room + n * kKRowBytes + k_chunk_pos(n, kk * 2 + half) * 16);
+        } else {
+            const int row = min(max(iq * kTile + row0 + n, first), len - 1) - first;
+            const uint4* src = reinterpret_cast<const uint4*>(q + ((size_t)(start + row) * lp.H + h) * kHeadDim);
+#pragma unroll
+            for (int kk = 0; kk < 8; ++kk) qreg[kk] = src[kk * 2 + half];
+        }
         // Pin the loads here.  Left alone the compiler sinks them to the loop entry, and because the
         // memory counter completes in order every tile's first product would then wait for that
-        // tile's K / V prefetch.
+        // tile's K / V prefetch.  (And the place in LDS is given to other waves' tiles after the next barrier.)
 #pragma unroll
         for (int kk = 0; kk < 8; ++kk)
             asm volatile("" : "+v"(qreg[kk].x), "+v"(qreg[kk].y), "+v"(qreg[kk].z), "+v"(qreg[kk].w));
@@ -1114,6 +1140,7 @@ __device__ __forceinline__ void prefill_workgroup(
             tile_step(it_first + (st + 1) * stride, k_lds1, v_lds1, k_lds0, v_lds0);
         }
     } else {
+        if (it_first < n_visit) fetch(kOnlyV, k_lds0, v_lds0, e_cur & kTileMask, ph_first);  // the queries have left its place
         // K of the next step is requested once every wave has its scores of this one, V once every wave is done with it
         for (int st = 0; st < steps; ++st) {
             const int it = it_first + st * stride;
