@@ -844,8 +844,12 @@ __device__ __forceinline__ const uint4* pointer_of_lane(const uint4* p, int lane
                                           (unsigned)__builtin_amdgcn_readlane((int)x, lane));
 }
 
+// Quantised pages: two wavefronts to a SIMD is what the compiler is told to plan for, and what the launch has (kBlocksPerCU).  Left alone
+// it keeps registers down for more, and puts the unpacking of codes and their products in an order that takes longer: 64 sequences of 9K
+// .. 24K over 4-bit pages, four steps, 209 -> 193 us, 57 of 290 .. 6691 over 8-bit ones 193 -> 171, eight heads to a group, 16 of 30000,
+// 116 -> 105.  16-bit rows gain nothing and over pages of 32 tokens lose 4 %; for three wavefronts the quantised kernels spill.
 template <class T, int N, int NP, int BITS>
-__global__ __launch_bounds__(kDecodeThreads) void sparse_decode_kernel(
+__global__ __launch_bounds__(kDecodeThreads, BITS != 16 ? 2 : 1) void sparse_decode_kernel(
     LayerParams lp, PagedParams kv, DecodePlan plan, const uint4* __restrict__ q, const int* __restrict__ sel_pages,
     const int* __restrict__ sel_count, const int* __restrict__ sel_seq_len, int sel_stride,
     uint16_t* __restrict__ out, float* __restrict__ lse_out, float* __restrict__ part_o, float* __restrict__ part_ml,
