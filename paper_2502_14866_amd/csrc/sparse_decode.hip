@@ -2,10 +2,10 @@
 // its index table -- the selector's list (plus pages newer than the selection) for dense heads,
 // sink + local pages for streaming heads.  Both kinds run in one launch.
 //
-// The work is GEMV-shaped (n <= 8 query rows per KV head) and bound by HBM bandwidth, so there is
-// no MFMA here for 16-bit pages: each page is a 2 * N_P * 256-byte contiguous K / V slab read with 16-byte loads
-// (16 lanes per token row), dot products use packed 16-bit dot instructions with fp32
-// accumulation, and the softmax is kept online per wavefront.
+// The work is GEMV-shaped (n <= 8 query rows per KV head) and bound by HBM bandwidth: each page is a 2 * N_P * 256-byte
+// contiguous K / V slab read with 16-byte loads (16 lanes per token row).  Scores come from small matrix products or, without a
+// group and over small pages, from packed 16-bit dot instructions (see scores_by_matrix), values are weighted in fp32, and the
+// softmax is kept online per wavefront.
 //
 // Work distribution: a launch is only a few thousand pages, far too few for the hardware scheduler
 // to even out, so the page lists of all (sequence, KV head) pairs are laid end to end and cut into
@@ -21,6 +21,7 @@
 // token, stored after the page's rows).  The kernel is the same with the slab loads and the per-page
 // arithmetic swapped (template parameter BITS); see quantised_quarter_page.
 #include <algorithm>
+#include <type_traits>
 
 #include "kernels.h"
 
@@ -87,6 +88,11 @@ template <int NP> struct KeyMap {
     static constexpr int ITS = NP / 16;                              // 16-byte loads per lane and slab
 };
 
+// 16-bit rows: are the scores taken on the matrix cores (matrix_quarter_page)?  Not without a group, where the vector form is as quick
+// (32 sequences of 4096 .. 131072, 32 / 32 heads, 657 and 671 us a pass), nor for two heads over pages of 128 tokens (30 of 300 .. 9000,
+// 32 / 16 heads, 302 and 308); a quarter of a smaller page has fewer tokens than a product has columns.
+constexpr bool scores_by_matrix(int n, int np) { return np == 64 ? n >= 2 : np == 128 && n >= 3; }
+
 template <int NP, int BITS> struct Slabs;
 template <int NP> struct Slabs<NP, 16> {
     uint4 k[KeyMap<NP>::ITS], v[KeyMap<NP>::ITS];
@@ -117,9 +123,17 @@ template <class V> __device__ __forceinline__ V load_at(const uint4* slab, unsig
     return *reinterpret_cast<const V*>(reinterpret_cast<const char*>(slab) + lane_bytes + constant_bytes);
 }
 
-template <int NP>
+template <int N, int NP>
 __device__ __forceinline__ void load_k(Slabs<NP, 16>& s, const uint4* kslab, int tok0, int lane, unsigned live) {
     using M = KeyMap<NP>;
+    if constexpr (scores_by_matrix(N, NP)) {  // lane (t, g): the chunks g, g + 4 ... of token t, as the products take them
+        const unsigned at = (unsigned)((tok0 + lane % 16) * (kHeadDim / 8) + lane / 16) * 16u & live;
+#pragma unroll
+        for (int ps = 0; ps < M::PASSES; ++ps)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) s.k[4 * ps + j] = load_at<uint4>(kslab, at, (ps * 16 * (kHeadDim / 8) + 4 * j) * 16u);
+        return;
+    }
     const unsigned at = (unsigned)((tok0 + lane / M::LPT) * (kHeadDim / 8) + lane % M::LPT) * 16u & live;
 #pragma unroll
     for (int ps = 0; ps < M::PASSES; ++ps)
@@ -135,7 +149,7 @@ __device__ __forceinline__ void load_v(Slabs<NP, 16>& s, const uint4* vslab, int
     for (int it = 0; it < KeyMap<NP>::ITS; ++it) s.v[it] = load_at<uint4>(vslab, at, 4 * it * kHeadDim * 2u);
 }
 
-__device__ __forceinline__ void load_k(Slabs<64, 4>& s, const uint4* kslab, int tok0, int lane, unsigned live) {
+template <int N> __device__ __forceinline__ void load_k(Slabs<64, 4>& s, const uint4* kslab, int tok0, int lane, unsigned live) {
     const int tok = tok0 + lane % 16;
     s.k[0] = load_at<uint4>(kslab, (unsigned)(tok * (kHeadDim / 32) + lane / 16) * 16u & live, 0);
     s.ksz = load_at<uint32_t>(kslab + 64 * (kHeadDim / 32), (unsigned)tok * 4u & live, 0);
@@ -146,7 +160,7 @@ __device__ __forceinline__ void load_v(Slabs<64, 4>& s, const uint4* vslab, int 
     for (int it = 0; it < 4; ++it) s.v[it] = load_at<uint32_t>(vslab, at, it * kHeadDim / 2u);
     s.vsz = load_at<uint32_t>(vslab + 64 * (kHeadDim / 32), (unsigned)(tok0 + lane % 16) * 4u & live, 0);
 }
-__device__ __forceinline__ void load_k(Slabs<64, 8>& s, const uint4* kslab, int tok0, int lane, unsigned live) {
+template <int N> __device__ __forceinline__ void load_k(Slabs<64, 8>& s, const uint4* kslab, int tok0, int lane, unsigned live) {
     const int tok = tok0 + lane % 16;
     const unsigned at = (unsigned)(tok * (kHeadDim / 16) + lane / 16) * 16u & live;
 #pragma unroll
@@ -202,6 +216,27 @@ template <int N> struct WaveState<N, 16> {
     }
 };
 
+// 16-bit rows with scores from the matrix cores: lane (t, g) keeps the softmax of heads g and g + 4 as over quantised pages, the
+// outputs are those of the vector form.
+template <int N> struct MatrixState {
+    static constexpr int kHeadsPerLane = (N + 3) / 4;
+    float m[kHeadsPerLane], l[kHeadsPerLane], o[N][8];
+    uint4 q[4];
+    __device__ __forceinline__ void reset() {
+#pragma unroll
+        for (int j = 0; j < kHeadsPerLane; ++j) {
+            m[j] = -INFINITY;
+            l[j] = 0.f;
+        }
+#pragma unroll
+        for (int hh = 0; hh < N; ++hh)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) o[hh][i] = 0.f;
+    }
+};
+template <int N, int NP, int BITS>
+using StateOf = std::conditional_t<BITS == 16 && scores_by_matrix(N, NP), MatrixState<N>, WaveState<N, BITS>>;
+
 constexpr int p_row(int n) { return n <= 4 ? 4 : 8; }  // floats per token row of the weight buffer
 
 // Sum over the LPT lanes that share a token; every one of them receives the total.
@@ -218,6 +253,37 @@ __device__ __forceinline__ float wave_max_of_quads(float x) {
     x = fmaxf(x, dpp_f<kDppHalfMirror>(x));
     x = fmaxf(x, dpp_f<kDppMirror>(x));
     return rows4_max(x);
+}
+
+// Adds weights * values of a quarter page to the outputs: four rows to a pass, sixteen lanes to a row.
+template <class T, int N, int NP>
+__device__ __forceinline__ void add_values(float (&o)[N][8], const float* p_lds, const Slabs<NP, 16>& cur, int valid, int tok0, int r) {
+    using M = KeyMap<NP>;
+    constexpr int PR = p_row(N);
+    const bool tail = valid < NP;
+#pragma unroll
+    for (int it = 0; it < M::ITS; ++it) {
+        uint4 vv = cur.v[it];
+        if (tail && tok0 + 4 * it + r >= valid) vv = make_uint4(0, 0, 0, 0);  // slots past the end may hold anything
+        const uint32_t vw[4] = {vv.x, vv.y, vv.z, vv.w};
+        float pv[PR];
+#pragma unroll
+        for (int x4 = 0; x4 < PR / 4; ++x4) {
+            const float4 t4 = *reinterpret_cast<const float4*>(p_lds + (4 * it + r) * PR + 4 * x4);
+            pv[4 * x4] = t4.x;
+            pv[4 * x4 + 1] = t4.y;
+            pv[4 * x4 + 2] = t4.z;
+            pv[4 * x4 + 3] = t4.w;
+        }
+#pragma unroll
+        for (int hh = 0; hh < N; ++hh) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                o[hh][2 * i] = __builtin_fmaf(pv[hh], Elem<T>::lo(vw[i]), o[hh][2 * i]);
+                o[hh][2 * i + 1] = __builtin_fmaf(pv[hh], Elem<T>::hi(vw[i]), o[hh][2 * i + 1]);
+            }
+        }
+    }
 }
 
 // One quarter page.  q_lds: [N][16] 16-byte chunks of the group's queries; p_lds: this wave's
@@ -288,36 +354,89 @@ __device__ __forceinline__ void process_quarter_page(WaveState<N, 16>& st, const
         }
     }
     __builtin_amdgcn_wave_barrier();
+    add_values<T, N, NP>(st.o, p_lds, cur, valid, tok0, r);
+    __builtin_amdgcn_wave_barrier();
+}
+
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+typedef __bf16 bf168_t __attribute__((ext_vector_type(8)));
+template <class T> __device__ __forceinline__ floatx4_t mfma_16x16x32(uint4 a, uint4 b, floatx4_t c) {
+    if constexpr (std::is_same<T, F16>::value)
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a), __builtin_bit_cast(half8_t, b), c, 0, 0, 0);
+    else
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf168_t, a), __builtin_bit_cast(bf168_t, b), c, 0, 0, 0);
+}
+
+// One quarter page of 16-bit rows under a group of heads, scores from the matrix cores: Q (heads x 128) * K^T (128 x tokens), four
+// v_mfma_f32_16x16x32 per sixteen tokens, with the heads in the rows that quantised_quarter_page has them in.  A lane then has the
+// score of one token under one head in four instead of a quarter of it under every head: an exponential, a maximum over sixteen lanes
+// and a sum per four heads, where packed dot products took 16 instructions and three cross-lane sums and maxima per head, and the queries are
+// operands in registers.  Weights stay in fp32 and meet the values in the vector pipe as before, so sums are as exact as they were.
+// The vector instructions bounded this path under large groups and the latency of a page under small ones.  Passes of four steps, us: 16
+// sequences of 32768, 32 / 8 heads, 155.6 -> 152.0; of 16384, 64 / 8 heads, 186 -> 154, over pages of 128 tokens (eight of 20000) 167 -> 133; four
+// of 262144 108 -> 104, one of 4000 59.3 -> 57.4; 57 of 290 .. 6691 337 -> 282.
+template <class T, int N, int NP>
+__device__ __forceinline__ void matrix_quarter_page(MatrixState<N>& st, float* p_lds, Slabs<NP, 16>& cur, int valid, int tok0,
+                                                    int lane, float scale_log2) {
+    constexpr int HPL = MatrixState<N>::kHeadsPerLane, PASSES = NP / 64, PR = p_row(N);
+    const int t = lane % 16, g = lane / 16;
+    floatx4_t s[PASSES];
 #pragma unroll
-    for (int it = 0; it < M::ITS; ++it) {
-        uint4 vv = cur.v[it];
-        if (tail && tok0 + 4 * it + r >= valid) vv = make_uint4(0, 0, 0, 0);  // slots past the end may hold anything
-        const uint32_t vw[4] = {vv.x, vv.y, vv.z, vv.w};
-        float pv[PR];
+    for (int ps = 0; ps < PASSES; ++ps) {
+        s[ps] = floatx4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int x4 = 0; x4 < PR / 4; ++x4) {
-            const float4 t4 = *reinterpret_cast<const float4*>(p_lds + (4 * it + r) * PR + 4 * x4);
-            pv[4 * x4] = t4.x;
-            pv[4 * x4 + 1] = t4.y;
-            pv[4 * x4 + 2] = t4.z;
-            pv[4 * x4 + 3] = t4.w;
+        for (int j = 0; j < 4; ++j) s[ps] = mfma_16x16x32<T>(st.q[j], cur.k[4 * ps + j], s[ps]);
+    }
+    const bool tail = valid < NP;
+    float x[HPL][PASSES], pm[HPL];
+    bool moved = false;
+#pragma unroll
+    for (int j = 0; j < HPL; ++j) {
+#pragma unroll
+        for (int ps = 0; ps < PASSES; ++ps) {
+            x[j][ps] = tail && tok0 + 16 * ps + t >= valid ? -INFINITY : s[ps][j] * scale_log2;
+            pm[j] = ps == 0 ? x[j][ps] : fmaxf(pm[j], x[j][ps]);
+        }
+        pm[j] = fmaxf(pm[j], dpp_f<kDppXor1>(pm[j]));
+        pm[j] = fmaxf(pm[j], dpp_f<kDppXor2>(pm[j]));
+        pm[j] = fmaxf(pm[j], dpp_f<kDppHalfMirror>(pm[j]));
+        pm[j] = fmaxf(pm[j], dpp_f<kDppMirror>(pm[j]));
+        moved |= pm[j] > st.m[j];
+    }
+    if (__any(moved)) {
+        float alpha[HPL];
+#pragma unroll
+        for (int j = 0; j < HPL; ++j) {
+            const float m_new = fmaxf(st.m[j], pm[j]);
+            alpha[j] = m_new > st.m[j] ? __builtin_amdgcn_exp2f(st.m[j] - m_new) : 1.f;
+            st.m[j] = m_new;
+            st.l[j] *= alpha[j];
         }
 #pragma unroll
         for (int hh = 0; hh < N; ++hh) {
+            const float a = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, alpha[hh / 4]), 16 * (hh % 4)));
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                st.o[hh][2 * i] = __builtin_fmaf(pv[hh], Elem<T>::lo(vw[i]), st.o[hh][2 * i]);
-                st.o[hh][2 * i + 1] = __builtin_fmaf(pv[hh], Elem<T>::hi(vw[i]), st.o[hh][2 * i + 1]);
-            }
+            for (int i = 0; i < 8; ++i) st.o[hh][i] *= a;
         }
     }
+#pragma unroll
+    for (int j = 0; j < HPL; ++j) {
+        const float m_safe = st.m[j] == -INFINITY ? 0.f : st.m[j];
+#pragma unroll
+        for (int ps = 0; ps < PASSES; ++ps) {
+            const float p = __builtin_amdgcn_exp2f(x[j][ps] - m_safe);
+            st.l[j] += p;
+            p_lds[(16 * ps + t) * PR + 4 * j + g] = p;
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+    add_values<T, N, NP>(st.o, p_lds, cur, valid, tok0, g);
     __builtin_amdgcn_wave_barrier();
 }
 
 constexpr float kCodeUnit = 0x1p-24f;  // value of the fp16 number whose bits are 1
 
 typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
-typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 
 // The same over a quantised quarter page, on the matrix cores.  With k = code * scale + zero the logit of a token is
 //   q . k = scale * (q . code) + zero * sum(q),
@@ -465,10 +584,21 @@ __device__ __forceinline__ void load_query_operands(WaveState<N, BITS>& st, cons
     for (int j = 0; j < HPL; ++j) st.q_sum[j] = q_sum[min(g + 4 * j, N - 1)];
 }
 
+template <int N>
+__device__ __forceinline__ void load_query_operands(MatrixState<N>& st, const uint4* q_lds, const float*, int lane) {
+    constexpr int HPL = MatrixState<N>::kHeadsPerLane;
+    const int t = lane % 16, g = lane / 16;
+    const int head = min(t / 4 + 4 * (t % 4 < HPL ? t % 4 : 0), N - 1);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) st.q[j] = q_lds[head * 16 + 4 * j + g];
+}
+
 template <class T, int N, int NP, int BITS>
-__device__ __forceinline__ void process_quarter(WaveState<N, BITS>& st, const uint4* q_lds, float* p_lds,
+__device__ __forceinline__ void process_quarter(StateOf<N, NP, BITS>& st, const uint4* q_lds, float* p_lds,
                                                 Slabs<NP, BITS>& cur, int valid, int tok0, int lane, float scale_log2) {
-    if constexpr (BITS == 16)
+    if constexpr (BITS == 16 && scores_by_matrix(N, NP))
+        matrix_quarter_page<T, N, NP>(st, p_lds, cur, valid, tok0, lane, scale_log2);
+    else if constexpr (BITS == 16)
         process_quarter_page<T, N, NP>(st, q_lds, p_lds, cur, valid, tok0, lane, scale_log2);
     else
         quantised_quarter_page<N, BITS>(st, p_lds, cur, valid, tok0, lane, scale_log2);
@@ -565,6 +695,24 @@ __device__ __forceinline__ void deposit_wave(WaveState<N, 16>& st, DecodeShared<
         if (lane == 0) sm.m[wave][hh] = st.m[hh];
     }
 }
+template <int N, int NP>
+__device__ __forceinline__ void deposit_wave(MatrixState<N>& st, DecodeShared<N, NP>& sm, int wave, int lane) {
+    const int t = lane % 16, g = lane / 16;
+#pragma unroll
+    for (int j = 0; j < MatrixState<N>::kHeadsPerLane; ++j) {
+        const float l = row16_sum(st.l[j]);
+        if (t == 0 && g + 4 * j < N) {
+            sm.m[wave][g + 4 * j] = st.m[j];
+            sm.l[wave][g + 4 * j] = l;
+        }
+    }
+#pragma unroll
+    for (int hh = 0; hh < N; ++hh)
+#pragma unroll
+        for (int q = 0; q < 2; ++q)  // lane (r, c) receives channel 8 c + 4 q + r
+            sm.o[wave][hh][8 * t + 4 * q + g] =
+                rows4_sum_scatter(st.o[hh][4 * q], st.o[hh][4 * q + 1], st.o[hh][4 * q + 2], st.o[hh][4 * q + 3]);
+}
 // Quantised pages: the outputs are whole already and take their unit here, the sums are added over the sixteen tokens.
 template <int N, int NP, int BITS>
 __device__ __forceinline__ void deposit_wave(WaveState<N, BITS>& st, DecodeShared<N, NP>& sm, int wave, int lane) {
@@ -591,7 +739,7 @@ __device__ __forceinline__ void deposit_wave(WaveState<N, BITS>& st, DecodeShare
 // Folds the four waves of the workgroup, and writes either
 // the final rows (out / lse) or a partial (part_o / part_ml).  Must be called by all 256 threads.
 template <class T, int N, int NP, int BITS>
-__device__ __forceinline__ void flush_block(WaveState<N, BITS>& st, DecodeShared<N, NP>& sm, bool final_result, int H,
+__device__ __forceinline__ void flush_block(StateOf<N, NP, BITS>& st, DecodeShared<N, NP>& sm, bool final_result, int H,
                                             int b, int hk, uint16_t* out, float* lse_out, float* part_o,
                                             float* part_ml, size_t part_slot) {
     deposit_wave(st, sm, threadIdx.x / kWave, threadIdx.x % kWave);
@@ -778,7 +926,7 @@ __device__ __forceinline__ void fold_list(DecodeShared<N, NP>& sm, int list, int
 // agent-scope accesses with a wait for the stores in between; no cache-wide fence (a device-scope fence here was
 // measured at three times the whole kernel: it writes back and invalidates the L2).  Called by all threads.
 template <class T, int N, int NP, int BITS>
-__device__ __forceinline__ void end_piece(WaveState<N, BITS>& st, DecodeShared<N, NP>& sm, const DecodePlan& plan, int blk,
+__device__ __forceinline__ void end_piece(StateOf<N, NP, BITS>& st, DecodeShared<N, NP>& sm, const DecodePlan& plan, int blk,
                                           int lo, int hi, int list, int len, int H, int Hkv,
                                           unsigned long long streaming_mask, uint16_t* out,
                                           float* lse_out, float* part_o, float* part_ml, unsigned* arrivals) {
@@ -817,7 +965,7 @@ __device__ __forceinline__ void end_piece(WaveState<N, BITS>& st, DecodeShared<N
             cur_b = list / lp.Hkv;                                                                                   \
             cur_hk = list % lp.Hkv;                                                                                  \
             stage_query<T, N, NP, BITS>(sm, q, cur_b, lp.H, cur_hk, list, q_ahead);                                  \
-            if constexpr (BITS != 16) load_query_operands<N, BITS>(st, sm.q, sm.q_sum, lane);                        \
+            if constexpr (BITS != 16 || scores_by_matrix(N, NP)) load_query_operands(st, sm.q, sm.q_sum, lane);            \
             st.reset();                                                                                              \
         }                                                                                                            \
         process_quarter<T, N, NP, BITS>(st, sm.q, sm.p[wave], CUR, __builtin_amdgcn_readlane(my_left, (IDX)), tok0, lane, lp.sm_scale_log2); \
@@ -830,7 +978,7 @@ __device__ __forceinline__ void end_piece(WaveState<N, BITS>& st, DecodeShared<N
                 const int ephys = kv.page_table[(size_t)cur_b * kv.max_pages + epos];                                \
                 const uint4 *ke, *ve;                                                                                \
                 slab_of(ephys, cur_hk, ke, ve);                                                                      \
-                load_k(CUR, ke, tok0, lane, ~0u);                                                                     \
+                load_k<N>(CUR, ke, tok0, lane, ~0u);                                                                     \
                 load_v(CUR, ve, tok0, r, c, lane, ~0u);                                                                \
                 process_quarter<T, N, NP, BITS>(st, sm.q, sm.p[wave], CUR, L - epos * NP, tok0, lane, lp.sm_scale_log2);\
             }                                                                                                        \
@@ -848,8 +996,10 @@ __device__ __forceinline__ const uint4* pointer_of_lane(const uint4* p, int lane
 // it keeps registers down for more, and puts the unpacking of codes and their products in an order that takes longer: 64 sequences of 9K
 // .. 24K over 4-bit pages, four steps, 209 -> 193 us, 57 of 290 .. 6691 over 8-bit ones 193 -> 171, eight heads to a group, 16 of 30000,
 // 116 -> 105.  16-bit rows gain nothing and over pages of 32 tokens lose 4 %; for three wavefronts the quantised kernels spill.
+// Pages of 128 tokens take a few registers more than there are for two wavefronts, which the compiler only gives up if told (57 of
+// 290 .. 6691 tokens 360 and 288 us); under six and more heads it would have to spill.
 template <class T, int N, int NP, int BITS>
-__global__ __launch_bounds__(kDecodeThreads, BITS != 16 ? 2 : 1) void sparse_decode_kernel(
+__global__ __launch_bounds__(kDecodeThreads, BITS != 16 || (NP == 128 && N >= 3 && N <= 5) ? 2 : 1) void sparse_decode_kernel(
     LayerParams lp, PagedParams kv, DecodePlan plan, const uint4* __restrict__ q, const int* __restrict__ sel_pages,
     const int* __restrict__ sel_count, const int* __restrict__ sel_seq_len, int sel_stride,
     uint16_t* __restrict__ out, float* __restrict__ lse_out, float* __restrict__ part_o, float* __restrict__ part_ml,
@@ -897,7 +1047,7 @@ __global__ __launch_bounds__(kDecodeThreads, BITS != 16 ? 2 : 1) void sparse_dec
     q_ahead.list = -4;  // matches no list
     q_ahead.x[0] = q_ahead.x[1] = make_uint4(0, 0, 0, 0);
 
-    WaveState<N, BITS> st;
+    StateOf<N, NP, BITS> st;
     int cur_list = -1, cur_b = 0, cur_hk = 0, cur_len = 0;
     // with every head streaming there is no selection: the loads below then read a valid word of the lengths
     const int* sel_table = sel_pages ? sel_pages : kv.seq_lens;
@@ -981,7 +1131,7 @@ __global__ __launch_bounds__(kDecodeThreads, BITS != 16 ? 2 : 1) void sparse_dec
             {
                 const uint4 *k0, *v0;
                 slabs_of(__builtin_ctzll(todo), k0, v0);
-                load_k(cur, k0, tok0, lane, ~0u);
+                load_k<N>(cur, k0, tok0, lane, ~0u);
                 load_v(cur, v0, tok0, r, c, lane, ~0u);
             }
             while (todo) {
@@ -990,7 +1140,7 @@ __global__ __launch_bounds__(kDecodeThreads, BITS != 16 ? 2 : 1) void sparse_dec
                 if (todo) {
                     const uint4 *k1, *v1;
                     slabs_of(__builtin_ctzll(todo), k1, v1);
-                    load_k(nxt, k1, tok0, lane, ~0u);
+                    load_k<N>(nxt, k1, tok0, lane, ~0u);
                     load_v(nxt, v1, tok0, r, c, lane, ~0u);
                 }
                 take_turn();
@@ -1012,7 +1162,7 @@ __global__ __launch_bounds__(kDecodeThreads, BITS != 16 ? 2 : 1) void sparse_dec
                 ahead &= ahead - 1;
                 const uint4 *k1, *v1;
                 slabs_of(nx, k1, v1);
-                load_k(dst, k1, tok0, lane, live);
+                load_k<N>(dst, k1, tok0, lane, live);
                 load_v(dst, v1, tok0, r, c, lane, live);
             };
             constexpr int kStages = 2;
