@@ -453,7 +453,7 @@ int lserve_probe_prefill_shape(const lserve_attn_desc *desc, int32_t batch, int3
  *   plan       HOST, [6] out: key ranges, each with a running maximum of its own, in which the sums of a dense head's row are
  *              taken, at least (its slices, or the pieces of its walk); the same of a streaming head's; 1 if the workgroups are half
  *              ones; the most pieces of a (KV head, group of query heads) where dense walks are cut into pieces, else 0; 1 if
- *              streaming heads are then a launch of their own; 1 if quantised pages are first turned into 16-bit ones
+ *              streaming heads are then in the launch that puts pieces together; 1 if quantised pages are first turned into 16-bit ones
  */
 int lserve_probe_prefill_plan(const lserve_attn_desc *desc, int32_t batch, int32_t total_rows, int32_t max_rows,
                               int32_t pages, int32_t kv_bits, int32_t scratch, int32_t *plan);

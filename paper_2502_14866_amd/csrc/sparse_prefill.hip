@@ -289,9 +289,9 @@ __device__ __forceinline__ BlockOrder block_order(const int* cu_seqlens, const i
 // nearly equal length, worked on by a workgroup each.  A piece leaves its unnormalised outputs, maxima and sums in
 // PrefillPieces::partials, and fold_pieces_kernel puts the pieces of a block together.  The span is the smallest that needs no
 // more pieces than the launch has workgroups for; every workgroup works it out from the lengths, which the host does not know.
-// Measured, whole walks in the best shape and pieces: 512 tokens over 32768, 32 / 8 heads, 365 and 176 us (13 for the streaming
-// heads, see streams_apart; 8 pieces to a block: 65 steps of 1.85 us with every compute unit at work, then 11 us to put 33 MB of
-// pieces together); 17 over 42116, twice, 441 and 79; 108 over 73893, 32 / 16 heads, 982 and 267.  Prompts are not cut: one of 4096
+// Measured, whole walks in the best shape and pieces: 512 tokens over 32768, 32 / 8 heads, 338 and 144 us (8 pieces to a
+// block: 65 steps of 1.75 us with every compute unit at work, then 14 us to put 33 MB of pieces together, next to the streaming
+// heads, see streams_apart); 17 over 42116, twice, 441 and 79; 108 over 73893, 32 / 16 heads, 982 and 267.  Prompts are not cut: one of 4096
 // tokens takes 119 us whole and 124 or more in any number of pieces, one of 8192 313 and 340, because what they gain in balance (42
 // steps a compute unit where the longest walk has 64) goes into the starts of the pieces and into putting them together.
 // No block is fewer pieces than the key slices it has without scratch (PrefillPieces::least), however short its walk: the weights of
@@ -1320,15 +1320,15 @@ __global__ __launch_bounds__(kPrefillThreads / 2, 2) void prefill_half_kernel(
     prefill_workgroup<T, MODE, 16, 1, kHalf>(lp, q, k, v, cu_seqlens, batch, out, lse_out, total_tokens, sched, mk, pg);
 }
 
-// Puts the pieces of cut walks together.  One workgroup per block and wavefront of its workgroups, one wavefront per 32
+// Puts the pieces of cut walks together: four wavefronts per block and wavefront of its workgroups, one per 32
 // channels, which reads 4 KiB of every piece, kBatch pieces at a time.
 template <class T>
-__global__ __launch_bounds__(256) void fold_pieces_kernel(LayerParams lp, const int* __restrict__ cu_seqlens, const int* __restrict__ seq_lens,
-                                                          int alongside, int batch, uint16_t* __restrict__ out, float* __restrict__ lse_out,
-                                                          int total_tokens, PrefillSchedule sched) {
+__device__ __forceinline__ void fold_block(const LayerParams& lp, const int* __restrict__ cu_seqlens, const int* __restrict__ seq_lens,
+                                           int alongside, int batch, uint16_t* __restrict__ out, float* __restrict__ lse_out,
+                                           int total_tokens, const PrefillSchedule& sched, int wave, int rank, int hidx, int hg, int thread,
+                                           unsigned char (&rows)[4][32 * 64]) {
     constexpr int kBatch = 8;
     const HeadClass& hc = sched.cls[0];
-    const int wave = blockIdx.x % kPrefillWaves, rank = blockIdx.x / kPrefillWaves, hidx = blockIdx.y, hg = blockIdx.z;
     const int hk = (int)(hc.kv_head[hidx / 4] >> (8 * (hidx % 4))) & 0xff;
     const BlockOrder order = block_order(cu_seqlens, seq_lens, alongside, batch, kTileLog2 + hc.qtiles_log2);
     const PiecePlan plan = PiecePlan::make(order, sched.pieces, kLeastSpanTiles >> hc.qtiles_log2);
@@ -1339,7 +1339,7 @@ __global__ __launch_bounds__(256) void fold_pieces_kernel(LayerParams lp, const 
     const int start = cu_seqlens[b], fresh = cu_seqlens[b + 1] - start;
     const int len = seq_lens[b] + (alongside ? fresh : 0), first = len - fresh;
     const int lane = threadIdx.x % kWave, n = lane % 32, half = lane / 32;
-    const int db = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int db = __builtin_amdgcn_readfirstlane(thread / kWave);
     const int unit = wave / 2;
     const int h = hk * lp.group + hg * hc.heads_per_block + (unit >> hc.qtiles_log2);
     const int pos = ((qblk << hc.qtiles_log2) + (unit & ((1 << hc.qtiles_log2) - 1))) * kTile + wave % 2 * 32 + n;
@@ -1387,7 +1387,6 @@ __global__ __launch_bounds__(256) void fold_pieces_kernel(LayerParams lp, const 
     }
     const float inv = l > 0.f ? 1.f / l : 0.f;
     // 64 bytes of each row, stored by four lanes each
-    __shared__ __attribute__((aligned(16))) unsigned char rows[4][32 * 64];
 #pragma unroll
     for (int g4 = 0; g4 < 4; ++g4)
         *reinterpret_cast<uint2*>(rows[db] + n * 64 + (g4 ^ (n / 4 % 4)) * 16 + 8 * half) =
@@ -1405,6 +1404,37 @@ __global__ __launch_bounds__(256) void fold_pieces_kernel(LayerParams lp, const 
     const int row = pos - first;
     if (lse_out && db == 0 && half == 0)
         lse_out[(size_t)h * total_tokens + start + row] = l > 0.f ? (m + __builtin_amdgcn_logf(l)) * kLn2 : -INFINITY;
+}
+
+template <class T>
+__global__ __launch_bounds__(256) void fold_pieces_kernel(LayerParams lp, const int* __restrict__ cu_seqlens, const int* __restrict__ seq_lens,
+                                                          int alongside, int batch, uint16_t* __restrict__ out, float* __restrict__ lse_out,
+                                                          int total_tokens, PrefillSchedule sched) {
+    __shared__ __attribute__((aligned(16))) unsigned char rows[4][32 * 64];
+    fold_block<T>(lp, cu_seqlens, seq_lens, alongside, batch, out, lse_out, total_tokens, sched, blockIdx.x % kPrefillWaves,
+                  blockIdx.x / kPrefillWaves, blockIdx.y, blockIdx.z, threadIdx.x, rows);
+}
+
+// The same next to the streaming heads of the call, where these are not in the launch of the pieces (see streams_apart): neither
+// fills the chip, and both are mostly latency.  First the workgroups of the streaming heads, `streams` deals them out, then those that fold, two
+// of fold_block's side by side.  Two launches of 13 and 11 us were 10 us longer: 512 tokens over 32768
+// 154 -> 144 us, 128 over 20000 of 8 bits 78 -> 71.
+template <class T, int BITS, int SL>
+__global__ __launch_bounds__(kPrefillThreads, 512 / kPrefillThreads) void fold_and_streams_kernel(
+    LayerParams lp, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+    const int* __restrict__ cu_seqlens, int batch, uint16_t* __restrict__ out, float* __restrict__ lse_out, int total_tokens,
+    PrefillSchedule streams, PrefillMask mk, PrefillPaged pg, PrefillSchedule sched) {
+    const int i = blockIdx.x - kXcds * streams.cls[1].items_per_xcd;
+    if (i < 0) {
+        prefill_workgroup<T, kPaged, BITS, SL, kWhole>(lp, q, k, v, cu_seqlens, batch, out, lse_out, total_tokens, streams, mk, pg);
+        return;
+    }
+    __shared__ __attribute__((aligned(16))) unsigned char rows[2][4][32 * 64];
+    constexpr int kPerBlock = kPrefillWaves / 2;
+    const int side = __builtin_amdgcn_readfirstlane(threadIdx.x / 256), of_head = sched.cls[0].blocks * kPerBlock;
+    const int at = i % of_head, head = i / of_head;
+    fold_block<T>(lp, cu_seqlens, pg.kv.seq_lens, pg.k_new != nullptr, batch, out, lse_out, total_tokens, sched,
+                  at % kPerBlock * 2 + side, at / kPerBlock, head % sched.cls[0].heads, head / sched.cls[0].heads, threadIdx.x % 256, rows[side]);
 }
 
 // ---- quantised history as 16-bit pages ------------------------------------------------------------
@@ -1622,11 +1652,13 @@ float launch_time(const LayerParams& lp, const PrefillRows& rows, float history,
 }
 
 // The same with dense walks in up to `pieces` pieces per XCD (see PiecePlan): the time of a piece beside its steps, of
-// putting pieces together, and of a step where every compute unit is at work on keys of its own.  Fitted to 95 drawn chunks with
-// streaming heads in the launch: the pieces taken came to 0.60 of the time of whole walks over one half of them and 0.81 over the
-// other, the best to 0.57 and 0.79.  In a launch of their own streaming heads cost 13 us more, and histories of less than some 10000
-// tokens stay whole (60 tokens over 3115, six times, 64 us where pieces took 45; 219 over 6972, 8 bits, 163 and 60).
-constexpr float kPieceUs = 0.5f, kFoldLaunchUs = 1.f, kFoldPieceUs = 0.15f, kCutStep = 1.07f;
+// putting pieces together, and of a step where every compute unit is at work on keys of its own: fitted to 95 drawn chunks with
+// streaming heads in the launch.  kStreamsBeside: what streaming heads in the launch that puts pieces together add, as a part of the
+// estimate for a launch of theirs, fitted to 152 chunks over 300 .. 131000 tokens of history (130 of them drawn), measured whole and in one to
+// four rounds of pieces, behind tables of their length and of eight times as much: the shapes taken cost 4 % over the best ones on average.
+// In a launch of its own, which cost 13 us, 9 %: histories of less than some 10000 tokens stayed whole (31 tokens over 5931 of 4 bits, three times, 128 us
+// whole and 56 in pieces; 219 over 6972 of 8, twice, 157 and 78; 256 over 20000, four times, 289 and 205).
+constexpr float kPieceUs = 0.5f, kFoldLaunchUs = 1.f, kFoldPieceUs = 0.15f, kCutStep = 1.07f, kStreamsBeside = 0.7f;
 float cut_launch_time(const LayerParams& lp, const PrefillRows& rows, float history, const ClassCost (&c)[2], int units_per_xcd,
                       float pieces, int least, bool streams_apart) {
     const ClassWalks w[2] = {class_walks(lp, rows, history, c[0], 0), class_walks(lp, rows, history, c[1], 1)};
@@ -1641,7 +1673,7 @@ float cut_launch_time(const LayerParams& lp, const PrefillRows& rows, float hist
         const float even = (count * (c[0].start + kPieceUs) + work * kCutStep * c[0].step + streams * w[1].mean) / units_per_xcd;
         t = std::max(t, even + std::max(kTailOfStream * last, 0.3f * longest));
     }
-    if (streams_apart) t += std::max(w[1].longest, c[1].count * w[1].mean / units_per_xcd) + kLaunchUs;  // a launch of their own
+    if (streams_apart) t += kStreamsBeside * std::max(w[1].longest, c[1].count * w[1].mean / units_per_xcd);
     return t + kLaunchUs + kFoldLaunchUs + kFoldPieceUs * count;
 }
 
@@ -1654,7 +1686,7 @@ bool may_cut(const LayerParams& lp, const PrefillRows& rows) {
 }
 
 // Where dense walks are cut, which is by workgroups of one slice, streaming heads keep the slices that the launch has with whole
-// walks, in a launch of their own if these are several.  Each slice rounds its weights relative to a maximum of its own, so
+// walks, next to the fold, in its launch, if these are several.  Each slice rounds its weights relative to a maximum of its own, so
 // that many of the largest weights of a row are exact, which over the few keys of a streaming head tells: against 64 bits 2.78e-3
 // with four slices and 2.84e-3 with one (512 tokens over 32768, bf16; dense heads 2.99e-3 whole in four slices and 2.97e-3 in pieces).
 bool streams_apart(const LayerParams& lp, const PrefillShape& whole) { return whole.slices > 1 && lp.streaming_mask != 0; }
@@ -1993,25 +2025,34 @@ hipError_t launch_whole(const PrefillLaunch& a, const PrefillShape& shape) {
 template <class T, int BITS>
 hipError_t launch_chunk(PrefillLaunch& a, const ChunkPlan& plan, void* scratch) {
     if (!plan.shape.pieces) return launch_whole<T, BITS>(a, plan.shape);
-    if (streams_apart(*a.lp, plan.uncut)) {
-        PrefillLaunch s = a;
-        s.sched = make_schedule(*a.lp, plan.uncut, a.max_rows, a.total_tokens, true, a.batch);
-        s.sched.cls[0].items_per_xcd = 0;
-        a.sched.cls[1].items_per_xcd = 0;
-        const hipError_t e = launch_whole<T, BITS>(s, plan.uncut);
-        if (e != hipSuccess) return e;
-    }
     a.sched.pieces.partials = reinterpret_cast<float*>(scratch);
+    const bool apart = streams_apart(*a.lp, plan.uncut);
+    if (apart) a.sched.cls[1].items_per_xcd = 0;
     const HeadClass& dense = a.sched.cls[0];
     hipLaunchKernelGGL((prefill_pieces_kernel<T, BITS>), dim3(kXcds * (dense.items_per_xcd + a.sched.cls[1].items_per_xcd)),
                        dim3(kPrefillThreads), 0, a.stream, *a.lp, a.q, a.k, a.v, a.cu_seqlens, a.batch, a.out, a.lse_out, a.total_tokens,
                        a.sched, a.mk, a.pg);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((fold_pieces_kernel<T>), dim3(dense.blocks * kPrefillWaves, dense.heads, a.lp->group / dense.heads_per_block), dim3(256),
-                       0, a.stream, *a.lp, a.cu_seqlens, a.pg.kv.seq_lens, a.pg.k_new != nullptr, a.batch, a.out, a.lse_out, a.total_tokens,
-                       a.sched);
-    return hipGetLastError();
+    const int heads = dense.heads * (a.lp->group / dense.heads_per_block);
+    if (!apart) {
+        hipLaunchKernelGGL((fold_pieces_kernel<T>), dim3(dense.blocks * kPrefillWaves, dense.heads, a.lp->group / dense.heads_per_block), dim3(256),
+                           0, a.stream, *a.lp, a.cu_seqlens, a.pg.kv.seq_lens, a.pg.k_new != nullptr, a.batch, a.out, a.lse_out, a.total_tokens,
+                           a.sched);
+        return hipGetLastError();
+    }
+    PrefillSchedule streams = make_schedule(*a.lp, plan.uncut, a.max_rows, a.total_tokens, true, a.batch);
+    streams.cls[0].items_per_xcd = 0;
+    const int grid = kXcds * streams.cls[1].items_per_xcd + dense.blocks * (kPrefillWaves / 2) * heads;
+    auto launch = [&](auto slices) {
+        hipLaunchKernelGGL((fold_and_streams_kernel<T, BITS, decltype(slices)::value>), dim3(grid), dim3(kPrefillThreads), 0, a.stream, *a.lp, a.q,
+                           a.k, a.v, a.cu_seqlens, a.batch, a.out, a.lse_out, a.total_tokens, streams, a.mk, a.pg, a.sched);
+        return hipGetLastError();
+    };
+    if constexpr (BITS == 16) {
+        if (plan.uncut.slices == 4) return launch(std::integral_constant<int, 4>{});
+    }
+    return launch(std::integral_constant<int, 2>{});
 }
 
 template <class T>
