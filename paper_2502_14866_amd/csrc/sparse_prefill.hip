@@ -163,6 +163,7 @@ struct PrefillPieces {
 struct PrefillSchedule {
     HeadClass cls[2];  // dense, streaming
     PrefillPieces pieces;
+    int compute_units;  // of the device
 };
 
 // Decodes workgroup `li` of XCD `xcd` inside a class of workgroups, `n` of them per (KV head, query block): KV head hk (the
@@ -223,14 +224,56 @@ struct BlockOrder {
         each([&](int g, int n) { t = max(t, n > 0 ? s.hi[g] : 0); });
         return __builtin_amdgcn_readfirstlane((int)wave_max((float)t));
     }
+    // find() for batches of up to sixteen sequences that differ, which a row of lanes holds: each of the four rows counts at a
+    // level of its own, so that a round, of half the instructions, leaves a fifth of the levels instead of half of them.  The search is a
+    // third of a half workgroup's start (2.4 us of 7 where lengths differ, 1.0 where not): 16 prompts of 77 .. 3001 tokens 173 -> 169 us,
+    // six of 100 .. 3000, 64 / 8 heads, 182 -> 177, nine of 108 .. 2283 112 -> 108.
+    __device__ __forceinline__ bool find_few(int rank, int& b, int& qblk) const {
+        auto everywhere = [](int x) {  // row 0 in all four rows
+            const swap_pair_t p = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)x, false, false);
+            const unsigned u = p[0];
+            const swap_pair_t q = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+            return (int)q[0];
+        };
+        const int lo = everywhere(s.lo[0]), hi = everywhere(s.hi[0]), row = threadIdx.x % kWave / 16;
+        float t = lo < hi ? (float)hi : 0.f;
+        t = fmaxf(t, dpp_f<kDppXor1>(t));
+        t = fmaxf(t, dpp_f<kDppXor2>(t));
+        t = fmaxf(t, dpp_f<kDppHalfMirror>(t));
+        t = fmaxf(t, dpp_f<kDppMirror>(t));
+        int below = 0, above = __builtin_amdgcn_readfirstlane((int)t), past = 0;  // past: blocks at `above` or past it
+        int step = (above + 3) / 4, at = row * step;
+        for (bool begun = false;; begun = true) {
+            const float count = row16_sum((float)max(hi - max(lo, at), 0));
+            const unsigned long long more = __ballot(count > (float)rank) & 0x0001000100010001ull;
+            const int k = __popcll(more);  // levels with more than `rank` blocks at or past them
+            if (!begun && k == 0) return false;
+            const int first = begun ? below + step : 0;  // the level of row 0
+            if (first + k * step < above && k < 4) {
+                above = first + k * step;
+                past = (int)__builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, count), 16 * k));
+            }
+            if (k > 0) below = first + (k - 1) * step;
+            if (above - below <= 1) break;
+            step = (above - below + 4) / 5;
+            at = below + (row + 1) * step;
+        }
+        const bool member = threadIdx.x % kWave < 16 && lo <= below && below < hi;
+        const unsigned long long members = __ballot(member), lower = (1ull << (threadIdx.x % kWave)) - 1ull;
+        b = __builtin_ctzll(__ballot(member && __popcll(members & lower) == rank - past));
+        qblk = below;
+        return true;
+    }
     // The rank-th block of the batch; false past the last one.
-    __device__ __forceinline__ bool find(int rank, int& b, int& qblk) const {
+    // FEW: see find_few; the other kernels, whose workgroups are fewer and longer, do without the code.
+    template <bool FEW = false> __device__ __forceinline__ bool find(int rank, int& b, int& qblk) const {
         if (alike) {
             const int level = batch == 1 ? rank : rank / batch;
             b = rank - level * batch;
             qblk = hi0 - 1 - level;
             return qblk >= lo0;
         }
+        if (FEW && batch <= 16) return find_few(rank, b, qblk);
         if (rank >= at_or_past(0)) return false;
         int below = 0, above = top();
         while (above - below > 1) {  // largest level with more than `rank` blocks at or past it
@@ -472,15 +515,15 @@ enum PrefillMode { kPlain = 0, kMasked = 1, kPaged = 2 };
 // history) then has SL times the workgroups, each with a walk SL times shorter, for SL times the staging per step
 // (see choose_shape).
 // KIND: kCut: the dense walks come in pieces (see PiecePlan); kHalf: a workgroup of four wavefronts and two units, two of them to
-// a compute unit.
-enum WorkgroupKind { kWhole = 0, kCut = 1, kHalf = 2 };
+// a compute unit; kHasty: the same with the first workgroup of every compute unit in front (see longest_walk_decides).
+enum WorkgroupKind { kWhole = 0, kCut = 1, kHalf = 2, kHasty = 3 };
 template <class T, int MODE, int BITS, int SL, int KIND>
 __device__ __forceinline__ void prefill_workgroup(
     const LayerParams& lp, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int* __restrict__ cu_seqlens, int batch, uint16_t* __restrict__ out,
     float* __restrict__ lse_out, int total_tokens, const PrefillSchedule& sched, const PrefillMask& mk, const PrefillPaged& pg) {
     constexpr bool MASKED = MODE == kMasked, PAGED = MODE == kPaged, QUANT = BITS != 16;
-    constexpr bool CUT = KIND == kCut, HALF = KIND == kHalf, ROWS = MASKED && (SL > 1 || HALF);  // ROWS: lists are the caller's rows
+    constexpr bool CUT = KIND == kCut, HALF = KIND == kHalf || KIND == kHasty, ROWS = MASKED && (SL > 1 || HALF);  // ROWS: lists are the caller's rows
     constexpr int kWaves = HALF ? kPrefillWaves / 2 : kPrefillWaves;
     static_assert(!CUT || (SL == 1 && PAGED), "chunks");
     static_assert(!HALF || SL == 1, "two units share a walk");
@@ -541,7 +584,7 @@ __device__ __forceinline__ void prefill_workgroup(
             plan.find(order, rank, piece, slot);
             slot += (hidx * (lp.group / heads_per_block) + hg) * sched.pieces.target;
         }
-        if (!order.find(rank, b, qblk)) return;
+        if (!order.find<HALF>(rank, b, qblk)) return;
         // All of it comes out of lane arithmetic.  Left in a vector register, the block's position takes the length of the
         // walk, the key tile of every step and the page look-ups there with it, and each branch on them runs under a mask of
         // lanes (a step of one slice 1.71 us, 1.65 with all in scalar registers: 512 tokens over 32768).
@@ -667,6 +710,7 @@ __device__ __forceinline__ void prefill_workgroup(
     // Reference of this lane's query row, in units of the unscaled products, and the sum of its weights relative to it.  The
     // reference is a maximum of the row's scores, but not always the latest (see weights_and_values).
     float m_run = -INFINITY, l_run = 0.f;
+    const bool first_on_unit = KIND == kHasty && (int)blockIdx.x < sched.compute_units;
     int unset = 1;  // some row of the wave has no reference yet
     // The score products start from -m_run instead of 0 (the accumulator input of the first product), so that scores come
     // relative to it at no cost; 0 while m_run = -inf.
@@ -930,7 +974,10 @@ __device__ __forceinline__ void prefill_workgroup(
     // S^T for the 64 keys of a tile, two blocks of 32 keys.  All operand reads of a block are issued before its
     // products so that LDS latency is paid once, and the two blocks' accumulation chains alternate in the matrix pipe.
     auto scores = [&](float16_t (&s)[2], const unsigned char* ks, bool diagonal) {
-        __builtin_amdgcn_s_setprio(2);  // products first: the other wavefront of the SIMD fills in with softmax work
+        if (KIND == kHasty && first_on_unit)
+            __builtin_amdgcn_s_setprio(3);
+        else
+            __builtin_amdgcn_s_setprio(2);  // products first: the other wavefront of the SIMD fills in with softmax work
         uint4 ka[8][2];
 #pragma unroll
         for (int kk = 0; kk < 8; ++kk)
@@ -952,7 +999,10 @@ __device__ __forceinline__ void prefill_workgroup(
             __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         }
         __builtin_amdgcn_sched_group_barrier(0x008, kAhead, 0);
-        __builtin_amdgcn_s_setprio(0);
+        if (KIND == kHasty && first_on_unit)
+            __builtin_amdgcn_s_setprio(2);
+        else
+            __builtin_amdgcn_s_setprio(0);
         if (diagonal) {  // causal mask inside the diagonal tile
             // (opaque, or the 32 comparisons are hoisted out of the loop into 64 scalar registers, and what the loop
             // does need is then read back from spilled lanes in every step)
@@ -1134,6 +1184,8 @@ __device__ __forceinline__ void prefill_workgroup(
     }
     __syncthreads();
     if constexpr (!kOneStage) {
+        // (where the loop starts within 64 bytes of code moves half workgroups by up to 2 % either way)
+        if constexpr (HALF) asm volatile(".p2align 6");
         for (int st = 0; st < steps; st += 2) {
             tile_step(it_first + st * stride, k_lds0, v_lds0, k_lds1, v_lds1);
             if (st + 1 >= steps) break;
@@ -1318,6 +1370,15 @@ __global__ __launch_bounds__(kPrefillThreads / 2, 2) void prefill_half_kernel(
     const int* __restrict__ cu_seqlens, int batch, uint16_t* __restrict__ out,
     float* __restrict__ lse_out, int total_tokens, PrefillSchedule sched, PrefillMask mk, PrefillPaged pg) {
     prefill_workgroup<T, MODE, 16, 1, kHalf>(lp, q, k, v, cu_seqlens, batch, out, lse_out, total_tokens, sched, mk, pg);
+}
+
+// (a kernel of its own: the choice in every tile, or merely other code in front of the loop, moves the others by 1 to 3 %)
+template <class T>
+__global__ __launch_bounds__(kPrefillThreads / 2, 2) void prefill_hasty_kernel(
+    LayerParams lp, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+    const int* __restrict__ cu_seqlens, int batch, uint16_t* __restrict__ out,
+    float* __restrict__ lse_out, int total_tokens, PrefillSchedule sched, PrefillMask mk, PrefillPaged pg) {
+    prefill_workgroup<T, kPlain, 16, 1, kHasty>(lp, q, k, v, cu_seqlens, batch, out, lse_out, total_tokens, sched, mk, pg);
 }
 
 // Puts the pieces of cut walks together: four wavefronts per block and wavefront of its workgroups, one per 32
@@ -1926,6 +1987,7 @@ PrefillSchedule make_schedule(const LayerParams& lp, const PrefillShape& shape, 
                               int batch, bool single_rows = false) {
     PrefillSchedule sched;
     sched.pieces = {nullptr, shape.pieces, shape.least};
+    sched.compute_units = num_compute_units();
     for (int c = 0; c < 2; ++c) {
         HeadClass& hc = sched.cls[c];
         hc.fold = shape.fold[c];
@@ -2055,6 +2117,17 @@ hipError_t launch_chunk(PrefillLaunch& a, const ChunkPlan& plan, void* scratch) 
     return launch(std::integral_constant<int, 2>{});
 }
 
+// Does a launch of half workgroups last as long as its longest walk?  With about two dense workgroups to a compute unit, dealt out
+// longest first, the longest walk of all shares its unit from beginning to end, with one half as long and then with streaming heads, at 1.7
+// us a step where it would take 1.0 alone, and the chip runs empty around it (one prompt of 4096 tokens: 64 steps where an even share is
+// 42).  The first workgroup of every unit then has a higher wave priority throughout.  4096 tokens 103 -> 98 us, 4300 110 -> 104, 4200 of 32 / 16
+// heads 105 -> 100, 3900 of 32 / 32 94 -> 91.  Walks of fewer tiles lose 1 to 3 % (1600 tokens, 64 / 8 heads: 44.2 and 45.3), and so do launches
+// of more workgroups, whose units have other long walks to fill up with (4900 of 32 / 32, 2.4 to a unit, 123 and 126).
+bool longest_walk_decides(const PrefillSchedule& sched, int tiles) {
+    const long long n = (long long)kXcds * sched.cls[0].items_per_xcd, units = sched.compute_units;
+    return tiles >= 48 && 4 * n > 5 * units && 4 * n <= 9 * units;
+}
+
 template <class T>
 hipError_t launch_prefill(const LayerParams& lp, const void* q, const void* k, const void* v, const int* cu_seqlens,
                           int batch, int total_tokens, int max_seqlen, void* out, float* lse_out, void* workspace,
@@ -2074,6 +2147,12 @@ hipError_t launch_prefill(const LayerParams& lp, const void* q, const void* k, c
     if (!mask) {
         const PrefillShape shape = choose_shape(lp, {batch, total_tokens, max_seqlen, -1}, false);
         a.sched = make_schedule(lp, shape, max_seqlen, total_tokens, false, batch);
+        if (shape.half && longest_walk_decides(a.sched, max_tiles)) {
+            hipLaunchKernelGGL((prefill_hasty_kernel<T>), dim3(kXcds * (a.sched.cls[0].items_per_xcd + a.sched.cls[1].items_per_xcd)),
+                               dim3(kPrefillThreads / 2), 0, stream, lp, a.q, a.k, a.v, cu_seqlens, batch, a.out, lse_out, total_tokens,
+                               a.sched, a.mk, a.pg);
+            return hipGetLastError();
+        }
         if (shape.half) return launch_half<T, kPlain>(a);
         return launch_slices<T, kPlain, 16>(a, shape.slices);
     }
