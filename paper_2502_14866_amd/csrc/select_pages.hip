@@ -25,6 +25,38 @@ __device__ __forceinline__ unsigned orderable(float s) {
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+// Max and min rows of a logical page of `cnt` tokens, from its keys: this lane's eight channels.
+template <class T> __device__ __forceinline__ void rebuild_rows(const uint4* __restrict__ keys, int cnt, uint4& mx, uint4& mn) {
+    float vmax[8], vmin[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        vmax[i] = -INFINITY;
+        vmin[i] = INFINITY;
+    }
+    for (int t0 = 0; t0 < cnt; t0 += 8) {  // eight rows requested together
+        uint4 x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            x[u] = keys[(size_t)min(t0 + u, cnt - 1) * (kHeadDim / 8)];  // a repeated row changes nothing
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const uint32_t w[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float a = Elem<T>::lo(w[i]), d = Elem<T>::hi(w[i]);
+                vmax[2 * i] = fmaxf(vmax[2 * i], a);
+                vmin[2 * i] = fminf(vmin[2 * i], a);
+                vmax[2 * i + 1] = fmaxf(vmax[2 * i + 1], d);
+                vmin[2 * i + 1] = fminf(vmin[2 * i + 1], d);
+            }
+        }
+    }
+    mx = make_uint4(Elem<T>::pack(vmax[0], vmax[1]), Elem<T>::pack(vmax[2], vmax[3]),
+                    Elem<T>::pack(vmax[4], vmax[5]), Elem<T>::pack(vmax[6], vmax[7]));
+    mn = make_uint4(Elem<T>::pack(vmin[0], vmin[1]), Elem<T>::pack(vmin[2], vmin[3]),
+                    Elem<T>::pack(vmin[4], vmin[5]), Elem<T>::pack(vmin[6], vmin[7]));
+}
+
 // GMAX: upper bound of the logical pages per physical page (4 or kMaxLogical), sizes the row registers.
 template <class T, int N, int GMAX>
 __global__ __launch_bounds__(kScoreThreads) void page_score_kernel(LayerParams lp, PagedParams kv,
@@ -97,35 +129,7 @@ __global__ __launch_bounds__(kScoreThreads) void page_score_kernel(LayerParams l
             if (j < n_log && min(lo + lp.NL, L) > fresh_below) {
                 const uint4* keys = reinterpret_cast<const uint4*>(kv.k_pool) +
                                     (ph * lp.NP + (lo - p * lp.NP)) * (kHeadDim / 8) + c;
-                float vmax[8], vmin[8];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    vmax[i] = -INFINITY;
-                    vmin[i] = INFINITY;
-                }
-                const int cnt = min(lp.NL, L - lo);
-                for (int t0 = 0; t0 < cnt; t0 += 8) {  // eight rows requested together
-                    uint4 x[8];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u)
-                        x[u] = keys[(size_t)min(t0 + u, cnt - 1) * (kHeadDim / 8)];  // a repeated row changes nothing
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const uint32_t w[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const float a = Elem<T>::lo(w[i]), d = Elem<T>::hi(w[i]);
-                            vmax[2 * i] = fmaxf(vmax[2 * i], a);
-                            vmin[2 * i] = fminf(vmin[2 * i], a);
-                            vmax[2 * i + 1] = fmaxf(vmax[2 * i + 1], d);
-                            vmin[2 * i + 1] = fminf(vmin[2 * i + 1], d);
-                        }
-                    }
-                }
-                mx[j] = make_uint4(Elem<T>::pack(vmax[0], vmax[1]), Elem<T>::pack(vmax[2], vmax[3]),
-                                   Elem<T>::pack(vmax[4], vmax[5]), Elem<T>::pack(vmax[6], vmax[7]));
-                mn[j] = make_uint4(Elem<T>::pack(vmin[0], vmin[1]), Elem<T>::pack(vmin[2], vmin[3]),
-                                   Elem<T>::pack(vmin[4], vmin[5]), Elem<T>::pack(vmin[6], vmin[7]));
+                rebuild_rows<T>(keys, min(lp.NL, L - lo), mx[j], mn[j]);
                 st[(size_t)(j * 2) * (kHeadDim / 8) + c] = mx[j];
                 st[(size_t)(j * 2 + 1) * (kHeadDim / 8) + c] = mn[j];
             }
@@ -482,6 +486,37 @@ __global__ __launch_bounds__(kWave* WAVES) void topk_pages_ballot_kernel(LayerPa
         for (int i = P + tid; i < kv.max_pages; i += kWave * WAVES) user_scores[(size_t)list * kv.max_pages + i] = 0.f;
 }
 
+// The whole of a selector run whose budget covers the page table, and with it every sequence: lists are all pages, and of the
+// statistics only what is out of date is rebuilt, as page_score_kernel would.  One launch for two: a pass of four steps on one sequence of 4000 tokens
+// 58.7 -> 55.8 us, on eight of 3000 91.7 -> 88.6.  One workgroup per list and sixteen logical pages, counted from the first that is out of date.
+constexpr int kMostLogical = 16384;  // of a list: what is out of date may be all of them or, as a rule, a few
+template <class T>
+__global__ __launch_bounds__(256) void select_all_kernel(LayerParams lp, PagedParams kv, int K, const int* __restrict__ stats_valid_len,
+                                                         int* __restrict__ sel_pages, int* __restrict__ sel_count, int* __restrict__ sel_seq_len) {
+    const int list = blockIdx.x, b = list / lp.Hkv, hk = list % lp.Hkv, tid = threadIdx.x;
+    const int L = kv.seq_lens[b], fresh_below = stats_valid_len ? stats_valid_len[b] : L;
+    const bool streaming = (lp.streaming_mask >> hk) & 1ull;
+    if (blockIdx.y == 0) {
+        const int count = streaming ? 0 : min(ceil_div(L, lp.NP), K);
+        for (int i = tid; i < K; i += 256) sel_pages[(size_t)list * K + i] = i < count ? i : -1;
+        if (tid == 0) {
+            sel_count[list] = count;
+            if (hk == 0) sel_seq_len[b] = L;
+        }
+    }
+    const int logical = max(fresh_below, 0) / lp.NL + blockIdx.y * 16 + tid / 16, c = tid % 16;
+    const int lo = logical * lp.NL;
+    const int p = lo / lp.NP;
+    if (streaming || fresh_below >= L || lo >= L || p >= kv.max_pages) return;
+    const int j = (lo - p * lp.NP) / lp.NL;
+    const size_t ph = (size_t)kv.page_table[(size_t)b * kv.max_pages + p] * kv.pool_heads + pool_rank(lp, kv, hk, false);
+    uint4 mx, mn;
+    rebuild_rows<T>(reinterpret_cast<const uint4*>(kv.k_pool) + (ph * lp.NP + (lo - p * lp.NP)) * (kHeadDim / 8) + c, min(lp.NL, L - lo), mx, mn);
+    uint4* st = reinterpret_cast<uint4*>(kv.stats) + (ph * lp.g + j) * 2 * (kHeadDim / 8);
+    st[c] = mx;
+    st[kHeadDim / 8 + c] = mn;
+}
+
 template <class T>
 hipError_t launch_score(const LayerParams& lp, const PagedParams& kv, const void* q, const int* stats_valid_len,
                         float* scores, int covered, const HeadList& selecting, hipStream_t stream) {
@@ -524,6 +559,14 @@ hipError_t launch_select_pages(int dtype, const LayerParams& lp, const PagedPara
                                const int* stats_valid_len, int budget_pages, int* sel_pages, int* sel_count, int* sel_seq_len,
                                float* scores, bool scores_is_user_buffer, const HeadList& selecting,
                                hipStream_t stream) {
+    if (!scores_is_user_buffer && kv.max_pages <= budget_pages && (long long)kv.max_pages * lp.g <= kMostLogical) {
+        const dim3 grid(kv.batch * lp.Hkv, stats_valid_len ? ceil_div(kv.max_pages * lp.g, 16) : 1);
+        if (dtype == 0)
+            hipLaunchKernelGGL(select_all_kernel<F16>, grid, dim3(256), 0, stream, lp, kv, budget_pages, stats_valid_len, sel_pages, sel_count, sel_seq_len);
+        else
+            hipLaunchKernelGGL(select_all_kernel<BF16>, grid, dim3(256), 0, stream, lp, kv, budget_pages, stats_valid_len, sel_pages, sel_count, sel_seq_len);
+        return hipGetLastError();
+    }
     if (selecting.count > 0) {
         const int covered = scores_is_user_buffer ? 0 : budget_pages;
         hipError_t e = dtype == 0 ? launch_score<F16>(lp, kv, q, stats_valid_len, scores, covered, selecting, stream)
