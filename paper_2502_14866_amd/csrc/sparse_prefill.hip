@@ -1601,6 +1601,9 @@ int heads_per_block(const LayerParams& lp, const PrefillShape& shape, int cls) {
     return heads;
 }
 
+// (Times behind the choices from here on were taken with a running maximum in the loop and rows stored as the lanes hold them; all launches are
+// 5 to 15 % shorter now and compare as they did, so the constants stay.)
+//
 // The estimate behind the choice of a shape: a compute unit holds one workgroup at a time, an XCD deals its workgroups out
 // longest walk first, and a workgroup costs a fixed time and its steps.  Constants in microseconds, fitted to 2100 launches
 // (211 chunks and 90 prompts of 1 .. 24 sequences in every shape; two thirds of the estimates are within 9 %):
