@@ -1770,6 +1770,10 @@ bool streams_apart(const LayerParams& lp, const PrefillShape& whole) { return wh
 //   - there are more dense KV heads than XCDs, each of which then works on several heads' keys at a time, in many rounds (0.98 to 1.28: 18 of
 //     3001, 32 / 32 heads, 16 of them streaming 1352 and 1447, none 1880 and 2400; 64 of 500, none streaming, 370 and 401; 16 chunks of
 //     1000 over 500, none streaming, 458 and 499).
+// Since then starts and ends of workgroups are shorter, of half ones by more.  Over 3100 more batches, half as a part of whole: 0.89 in the middle
+// where half ones are taken (2 % slower or more in 41 of 2551); in the exceptions 0.96 for single tiles, 0.92 for one full round, 0.95 without a
+// streaming head, 1.03 in many rounds of many heads; 0.98 beyond 60 tiles.  What is left there, up to 5 % of the smallest prompts, is not taken: tests
+// state whole workgroups for these plans (lserve_probe_prefill_plan).
 bool halves_are_quicker(const LayerParams& lp, const PrefillRows& rows, const PrefillShape& whole) {
     const int n_stream = count_streaming(lp), heads[2] = {lp.Hkv - n_stream, n_stream};
     const PrefillShape half = {1, {false, false}, false, true, 0, 1};
