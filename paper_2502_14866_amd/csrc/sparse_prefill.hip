@@ -1021,8 +1021,8 @@ __device__ __forceinline__ void prefill_workgroup(
     const uint32_t own_row = ((lane % 16) / 4 - lane / 16) % 2 == 0 ? Ones<T>::pair : 0u;
     // Softmax of this lane's query row (its keys are split between the two lane halves), then O^T += V^T P^T.
     //
-    // Weights are exp2(scale (score - reference)), and the reference stays what it is until the weights of some row of the wave add
-    // up to kMostWeight in a tile: below that nothing overflows (fp16 ends at 65504), and weights above 1 have the bits of those below.
+    // Weights are exp2(scale (score - reference)), and a row's reference stays what it is until its weights in a tile add
+    // up to kMostWeight: below that nothing overflows (fp16 ends at 65504), and weights above 1 have the bits of those below.
     // So no maximum stands between the products and the exponentials, and most tiles need none: a tile is 32 multiplications, 32
     // exponentials and 16 conversions per lane, where a running maximum took a chain of 16 in front of them and, whenever the maximum of
     // one of the wave's 32 rows moved (three of four tiles among a walk's first 64), 112 instructions to rescale.  The scale meets the
@@ -1031,24 +1031,31 @@ __device__ __forceinline__ void prefill_workgroup(
     // with rounded queries 2.55e-3, with the running maximum 2.50e-3).  An fma of product, scale and reference instead of the
     // accumulator input and a multiplication: 7 % slower at 65536 tokens.  Running maximum and this, on one box: 65536 tokens 15.68 and 15.08
     // ms, 4096 111 and 105 us, 12345 under a mask 319 and 295, 512 over 32768 174 and 158, two of 2642, 64 / 8 heads, 192 and 177.
+    //
+    // Each row goes by its own weights, and a sum is taken the same way in every round, so the other rows of the wavefront, which a
+    // chunk that begins or ends inside 32 rows has others of, leave no trace in a row's bits (nor in the time: 65536 tokens 15.01 and 14.94
+    // ms with one decision for the wavefront and with this, 16 of 77 .. 3001 178.6 and 178.1 us).
     constexpr float kMostWeight = 4096.f;
+    const uint4 own_rows = make_uint4(own_row, own_row, own_row, own_row);
     auto weights_and_values = [&](float16_t (&s)[2], const unsigned char* vs) {
         uint4 pb[2][2];  // P^T packed to 16 bit: [key block][16-key step]
         float sum;
         int moved = unset;
+        unsigned long long over = 0;  // lanes of the rows whose weights add up to too much in this tile
         asm volatile("" : "+s"(moved));  // (opaque, or the second round becomes a copy of the first that costs 20 registers)
 #pragma clang loop unroll(disable)
         for (;;) {
-            if (moved) {  // the reference becomes the maximum so far: subtract and rescale
+            if (moved) {  // the reference of rows over the bound, or without one, becomes the maximum so far: subtract and rescale
                 float mx = fmaxf(s[0][0], s[1][0]);
 #pragma unroll
                 for (int i = 1; i < 16; ++i) mx = __builtin_fmaxf(__builtin_fmaxf(mx, s[0][i]), s[1][i]);  // v_max3_f32
                 mx = halves_max(mx);  // relative to the reference (to 0 before the first kept tile)
-                const float m_base = m_run == -INFINITY ? 0.f : m_run;
-                const float m_new = fmaxf(m_run, m_base + mx);
-                const bool none = m_new == -INFINITY;                // nothing but -inf so far
-                const float delta = none ? 0.f : m_new - m_base;     // 0 for rows whose maximum stayed
-                const float alpha = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_run - m_new) * lp.sm_scale_log2);
+                const bool first_one = m_run == -INFINITY, stays = !first_one && !(over >> lane & 1);
+                const float m_base = first_one ? 0.f : m_run;
+                const float m_new = stays ? m_run : fmaxf(m_run, m_base + mx);
+                const bool none = m_new == -INFINITY;  // nothing but -inf so far
+                const float delta = none || stays ? 0.f : m_new - m_base;
+                const float alpha = stays ? 1.f : first_one ? 0.f : __builtin_amdgcn_exp2f((m_run - m_new) * lp.sm_scale_log2);
                 l_run *= alpha;
 #pragma unroll
                 for (int db = 0; db < 4; ++db)
@@ -1071,30 +1078,43 @@ __device__ __forceinline__ void prefill_workgroup(
                 pb[kb][0] = pack8<T>(pf);
                 pb[kb][1] = pack8<T>(pf + 8);
             }
-            // Row sums of the rounded weights, the same values the second product uses.
-            if (moved) {
-                sum = 0.f;
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb) {
-                    const uint32_t w[8] = {pb[kb][0].x, pb[kb][0].y, pb[kb][0].z, pb[kb][0].w,
-                                           pb[kb][1].x, pb[kb][1].y, pb[kb][1].z, pb[kb][1].w};
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) sum = Elem<T>::dot2(w[u], Ones<T>::pair, sum);
-                }
-                sum = halves_sum(sum);
-                break;
-            }
-            // In most tiles by four products of 16 x 16 x 32 (0.7 % quicker).  Read as the 32 x 16 operand of such a product, P^T has
-            // query c and query 16 + c in its column c, the one in the first and third eight keys, the other in the second and
-            // fourth; ones in those of row r's choice leave every lane with the sum of its own query.  A weight that is infinite or not
-            // a number spoils the sum of the other query too: then as above.
+            // Row sums of the rounded weights, the same values the second product uses, by four products of 16 x 16 x 32 (0.7 %
+            // quicker than sixteen dot products).  Read as the 32 x 16 operand of such a product, P^T has query c and query 16 + c in its
+            // column c, the one in the first and third eight keys, the other in the second and fourth; ones in those of row r's choice
+            // leave every lane with the sum of its own query.
             float4_t sums = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                for (int j = 0; j < 2; ++j) sums = Mfma<T>::run16(make_uint4(own_row, own_row, own_row, own_row), pb[kb][j], sums);
+                for (int j = 0; j < 2; ++j) sums = Mfma<T>::run16(own_rows, pb[kb][j], sums);
             sum = sums[0];
             if (!__any(!(sum < kMostWeight))) break;
+            // A weight that is infinite or not a number spoils the sum of the other query of its column: once more without the rows
+            // that have one.
+            float own = 0.f;
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) {
+                const uint32_t w[8] = {pb[kb][0].x, pb[kb][0].y, pb[kb][0].z, pb[kb][0].w,
+                                       pb[kb][1].x, pb[kb][1].y, pb[kb][1].z, pb[kb][1].w};
+#pragma unroll
+                for (int u = 0; u < 8; ++u) own = Elem<T>::dot2(w[u], Ones<T>::pair, own);
+            }
+            own = halves_sum(own);
+            const bool finite = own < INFINITY;
+            sums = float4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    __builtin_amdgcn_sched_barrier(0);  // one at a time, or all four copies are alive together
+                    const uint4 w = pb[kb][j];
+                    sums = Mfma<T>::run16(own_rows, make_uint4(finite ? w.x : 0u, finite ? w.y : 0u, finite ? w.z : 0u, finite ? w.w : 0u), sums);
+                }
+            __builtin_amdgcn_sched_barrier(0);
+            sum = finite ? sums[0] : own;
+            if (over) break;  // rows that still are over the bound are not numbers
+            over = __ballot(!(sum < kMostWeight));
+            if (!over) break;
             moved = 1;
             asm volatile("" : "+s"(moved));
         }
