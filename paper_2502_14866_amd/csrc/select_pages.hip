@@ -9,6 +9,8 @@
 // fp32 score: lists of up to 8192 candidates from registers, on ballots alone; longer ones from memory
 // with a 4-pass radix select.  Both emit in index order, so the output is ascending and ties resolve
 // to the lower page index.
+#include <algorithm>
+
 #include "kernels.h"
 
 namespace lserve {
@@ -488,8 +490,8 @@ __global__ __launch_bounds__(kWave* WAVES) void topk_pages_ballot_kernel(LayerPa
 
 // The whole of a selector run whose budget covers the page table, and with it every sequence: lists are all pages, and of the
 // statistics only what is out of date is rebuilt, as page_score_kernel would.  One launch for two: a pass of four steps on one sequence of 4000 tokens
-// 58.7 -> 55.8 us, on eight of 3000 91.7 -> 88.6.  One workgroup per list and sixteen logical pages, counted from the first that is out of date.
-constexpr int kMostLogical = 16384;  // of a list: what is out of date may be all of them or, as a rule, a few
+// 58.7 -> 55.8 us, on eight of 3000 91.7 -> 88.6.  gridDim.y workgroups to a list share out its logical pages from the first that is out of
+// date, sixteen to a turn.
 template <class T>
 __global__ __launch_bounds__(256) void select_all_kernel(LayerParams lp, PagedParams kv, int K, const int* __restrict__ stats_valid_len,
                                                          int* __restrict__ sel_pages, int* __restrict__ sel_count, int* __restrict__ sel_seq_len) {
@@ -504,17 +506,32 @@ __global__ __launch_bounds__(256) void select_all_kernel(LayerParams lp, PagedPa
             if (hk == 0) sel_seq_len[b] = L;
         }
     }
-    const int logical = max(fresh_below, 0) / lp.NL + blockIdx.y * 16 + tid / 16, c = tid % 16;
-    const int lo = logical * lp.NL;
-    const int p = lo / lp.NP;
-    if (streaming || fresh_below >= L || lo >= L || p >= kv.max_pages) return;
-    const int j = (lo - p * lp.NP) / lp.NL;
-    const size_t ph = (size_t)kv.page_table[(size_t)b * kv.max_pages + p] * kv.pool_heads + pool_rank(lp, kv, hk, false);
-    uint4 mx, mn;
-    rebuild_rows<T>(reinterpret_cast<const uint4*>(kv.k_pool) + (ph * lp.NP + (lo - p * lp.NP)) * (kHeadDim / 8) + c, min(lp.NL, L - lo), mx, mn);
-    uint4* st = reinterpret_cast<uint4*>(kv.stats) + (ph * lp.g + j) * 2 * (kHeadDim / 8);
-    st[c] = mx;
-    st[kHeadDim / 8 + c] = mn;
+    if (streaming || fresh_below >= L) return;
+    const int end = min(ceil_div(L, lp.NL), kv.max_pages * lp.g), c = tid % 16, rank = pool_rank(lp, kv, hk, false), step = gridDim.y * 16;
+    const int* pages = kv.page_table + (size_t)b * kv.max_pages;
+    int logical = max(fresh_below, 0) / lp.NL + blockIdx.y * 16 + tid / 16;
+    int page = logical < end ? pages[logical / lp.g] : 0;
+    for (; logical < end; logical += step) {
+        const int lo = logical * lp.NL, p = logical / lp.g, j = logical - p * lp.g;
+        const size_t ph = (size_t)page * kv.pool_heads + rank;
+        if (logical + step < end) page = pages[(logical + step) / lp.g];  // requested a turn ahead
+        uint4 mx, mn;
+        rebuild_rows<T>(reinterpret_cast<const uint4*>(kv.k_pool) + (ph * lp.NP + j * lp.NL) * (kHeadDim / 8) + c, min(lp.NL, L - lo), mx, mn);
+        uint4* st = reinterpret_cast<uint4*>(kv.stats) + (ph * lp.g + j) * 2 * (kHeadDim / 8);
+        st[c] = mx;
+        st[kHeadDim / 8 + c] = mn;
+    }
+}
+
+// Is a selector run that launch?  Up to kMostLogical logical pages to a list; `share` workgroups to a list: as a rule a few tokens are out of
+// date, which the first finds, but all may be, so as many as the chip holds (kSelectAllBlocks) and a list has work for.
+constexpr int kMostLogical = 16384, kSelectAllBlocks = 2048;
+bool selects_all(const LayerParams& lp, const PagedParams& kv, int budget_pages) {
+    return kv.max_pages <= budget_pages && (long long)kv.max_pages * lp.g <= kMostLogical;
+}
+int select_all_share(const LayerParams& lp, const PagedParams& kv) {
+    const long long lists = (long long)kv.batch * lp.Hkv;
+    return (int)std::max(1LL, std::min((long long)ceil_div(kv.max_pages * lp.g, 16), kSelectAllBlocks / lists));
 }
 
 template <class T>
@@ -559,8 +576,8 @@ hipError_t launch_select_pages(int dtype, const LayerParams& lp, const PagedPara
                                const int* stats_valid_len, int budget_pages, int* sel_pages, int* sel_count, int* sel_seq_len,
                                float* scores, bool scores_is_user_buffer, const HeadList& selecting,
                                hipStream_t stream) {
-    if (!scores_is_user_buffer && kv.max_pages <= budget_pages && (long long)kv.max_pages * lp.g <= kMostLogical) {
-        const dim3 grid(kv.batch * lp.Hkv, stats_valid_len ? ceil_div(kv.max_pages * lp.g, 16) : 1);
+    if (!scores_is_user_buffer && selects_all(lp, kv, budget_pages)) {
+        const dim3 grid(kv.batch * lp.Hkv, stats_valid_len ? select_all_share(lp, kv) : 1);
         if (dtype == 0)
             hipLaunchKernelGGL(select_all_kernel<F16>, grid, dim3(256), 0, stream, lp, kv, budget_pages, stats_valid_len, sel_pages, sel_count, sel_seq_len);
         else

@@ -45,3 +45,35 @@ def test_budget_covers_the_table(dtype, page, logical, two_way):
         for x, y in zip(got[a], got[b]):
             assert torch.equal(x.view(torch.uint8), y.view(torch.uint8))
     assert not torch.equal(got[0][3], got[2][3])  # some were out of date
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("batch,pages", [(100, 33), (683, 9)])
+def test_more_work_than_workgroups_to_share_it_out(dtype, batch, pages):
+    """So many lists that a workgroup takes several turns over the logical pages of its own, of which all, some or none are out of date."""
+    import paper_2502_14866_amd as L
+
+    L.load_library()
+    dev, hkv = torch.device("cuda:0"), 3
+    g = torch.Generator().manual_seed(batch)
+    lens = torch.randint(1, pages * 64 + 1, (batch,), generator=g).to(torch.int32)
+    lens[0] = pages * 64
+    valid = (lens * torch.rand(batch, generator=g) * (torch.arange(batch) % 3)).to(torch.int32).to(dev)
+    table = torch.randperm(batch * pages, generator=g).to(torch.int32).reshape(batch, pages).to(dev)
+    k = torch.randn((batch * pages, hkv, 64, 128), generator=torch.Generator(device=dev).manual_seed(1), device=dev, dtype=dtype)
+    q = torch.zeros((batch, 2 * hkv, 128), dtype=dtype, device=dev)
+    desc = L.AttnDesc(2 * hkv, hkv, [0, 1, 0], dtype=dtype)
+    got = []
+    for width in (pages, 4 * pages):
+        wide = torch.cat([table, torch.zeros((batch, width - pages), dtype=torch.int32, device=dev)], 1).contiguous()
+        stats = torch.full((batch * pages, hkv, 4, 2, 128), 7.0, dtype=dtype, device=dev)
+        kv = L.PagedKV(k, k, stats, wide, lens.to(dev))
+        sel = torch.full((batch, hkv, pages), -7, dtype=torch.int32, device=dev)
+        cnt, at = torch.full((batch, hkv), -7, dtype=torch.int32, device=dev), torch.full((batch,), -7, dtype=torch.int32, device=dev)
+        ws = torch.empty((L.lserve_workspace_bytes(L.LSERVE_CALL_SELECT_PAGES, desc, batch, width, pages, 0),), dtype=torch.uint8, device=dev)
+        L.lserve_select_pages(desc, kv, q, pages * 64, sel, cnt, at, None, ws, stats_valid_len=valid)
+        torch.cuda.synchronize()
+        got.append((sel, cnt, at, stats))
+    for x, y in zip(*got):
+        assert torch.equal(x.view(torch.uint8), y.view(torch.uint8))
+    assert (got[0][3] != 7.0).any()
