@@ -1021,8 +1021,8 @@ __device__ __forceinline__ void prefill_workgroup(
     const uint32_t own_row = ((lane % 16) / 4 - lane / 16) % 2 == 0 ? Ones<T>::pair : 0u;
     // Softmax of this lane's query row (its keys are split between the two lane halves), then O^T += V^T P^T.
     //
-    // Weights are exp2(scale (score - reference)), and a row's reference stays what it is until its weights in a tile add
-    // up to kMostWeight: below that nothing overflows (fp16 ends at 65504), and weights above 1 have the bits of those below.
+    // Weights are exp2(scale (score - reference)), and a row's reference stays what it is until its weights in a tile add up
+    // to kMostWeight: below that nothing overflows (fp16 ends at 65504), and weights above 1 have the bits of those below.
     // So no maximum stands between the products and the exponentials, and most tiles need none: a tile is 32 multiplications, 32
     // exponentials and 16 conversions per lane, where a running maximum took a chain of 16 in front of them and, whenever the maximum of
     // one of the wave's 32 rows moved (three of four tiles among a walk's first 64), 112 instructions to rescale.  The scale meets the
@@ -1034,8 +1034,10 @@ __device__ __forceinline__ void prefill_workgroup(
     //
     // Each row goes by its own weights, and a sum is taken the same way in every round, so the other rows of the wavefront, which a
     // chunk that begins or ends inside 32 rows has others of, leave no trace in a row's bits (nor in the time: 65536 tokens 15.01 and 14.94
-    // ms with one decision for the wavefront and with this, 16 of 77 .. 3001 178.6 and 178.1 us).
-    constexpr float kMostWeight = 4096.f;
+    // ms with one decision for the wavefront and with this, 16 of 77 .. 3001 178.6 and 178.1 us).  What is left of moving references is paid for by loud keys: keys that grow along the sequence to
+    // three times their size, running maximum and this, us, 4096 tokens 114.9 and 107.8, 16384 1197 and 1075; to twelve times 113.7 and 121.1
+    // in bf16, whose bound is passed once in a while only, 112.7 and 130.0 in fp16.  A row in 37 not a number: 109.9 and 100.0.
+    constexpr float kMostWeight = std::is_same<T, F16>::value ? 0x1p15f : 0x1p30f;
     const uint4 own_rows = make_uint4(own_row, own_row, own_row, own_row);
     auto weights_and_values = [&](float16_t (&s)[2], const unsigned char* vs) {
         uint4 pb[2][2];  // P^T packed to 16 bit: [key block][16-key step]
@@ -1050,7 +1052,7 @@ __device__ __forceinline__ void prefill_workgroup(
 #pragma unroll
                 for (int i = 1; i < 16; ++i) mx = __builtin_fmaxf(__builtin_fmaxf(mx, s[0][i]), s[1][i]);  // v_max3_f32
                 mx = halves_max(mx);  // relative to the reference (to 0 before the first kept tile)
-                const bool first_one = m_run == -INFINITY, stays = !first_one && !(over >> lane & 1);
+                const bool first_one = m_run == -INFINITY, stays = !first_one && !__builtin_amdgcn_inverse_ballot_w64(over);
                 const float m_base = first_one ? 0.f : m_run;
                 const float m_new = stays ? m_run : fmaxf(m_run, m_base + mx);
                 const bool none = m_new == -INFINITY;  // nothing but -inf so far
@@ -1091,28 +1093,41 @@ __device__ __forceinline__ void prefill_workgroup(
             if (!__any(!(sum < kMostWeight))) break;
             // A weight that is infinite or not a number spoils the sum of the other query of its column: once more without the rows
             // that have one.
-            float own = 0.f;
+            if (__any(!(sum < INFINITY))) {
+                float own = 0.f;
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb) {
-                const uint32_t w[8] = {pb[kb][0].x, pb[kb][0].y, pb[kb][0].z, pb[kb][0].w,
-                                       pb[kb][1].x, pb[kb][1].y, pb[kb][1].z, pb[kb][1].w};
+                for (int kb = 0; kb < 2; ++kb) {
+                    const uint32_t w[8] = {pb[kb][0].x, pb[kb][0].y, pb[kb][0].z, pb[kb][0].w,
+                                           pb[kb][1].x, pb[kb][1].y, pb[kb][1].z, pb[kb][1].w};
 #pragma unroll
-                for (int u = 0; u < 8; ++u) own = Elem<T>::dot2(w[u], Ones<T>::pair, own);
-            }
-            own = halves_sum(own);
-            const bool finite = own < INFINITY;
-            sums = float4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    __builtin_amdgcn_sched_barrier(0);  // one at a time, or all four copies are alive together
-                    const uint4 w = pb[kb][j];
-                    sums = Mfma<T>::run16(own_rows, make_uint4(finite ? w.x : 0u, finite ? w.y : 0u, finite ? w.z : 0u, finite ? w.w : 0u), sums);
+                    for (int u = 0; u < 8; ++u) own = Elem<T>::dot2(w[u], Ones<T>::pair, own);
                 }
-            __builtin_amdgcn_sched_barrier(0);
-            sum = finite ? sums[0] : own;
-            if (over) break;  // rows that still are over the bound are not numbers
+                own = halves_sum(own);
+                const bool finite = own < INFINITY;
+                sums = float4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        __builtin_amdgcn_sched_barrier(0);  // one at a time, or all four copies are alive together
+                        const uint4 w = pb[kb][j];
+                        sums = Mfma<T>::run16(own_rows, make_uint4(finite ? w.x : 0u, finite ? w.y : 0u, finite ? w.z : 0u, finite ? w.w : 0u), sums);
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+                sum = finite ? sums[0] : own;
+                if (over) {
+                    // Not finite by its own maximum either: a row that is not a number, and its sum says so for good.  Its queries give way to
+                    // zeros, so that it holds up no more tiles.
+                    m_run = finite ? m_run : 0.f;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) neg_m[i] = finite ? neg_m[i] : 0.f;
+#pragma unroll
+                    for (int kk = 0; kk < 8; ++kk)
+                        qreg[kk] = make_uint4(finite ? qreg[kk].x : 0u, finite ? qreg[kk].y : 0u, finite ? qreg[kk].z : 0u, finite ? qreg[kk].w : 0u);
+                    unset = __builtin_amdgcn_readfirstlane(__any(m_run == -INFINITY));
+                }
+            }
+            if (over) break;
             over = __ballot(!(sum < kMostWeight));
             if (!over) break;
             moved = 1;
