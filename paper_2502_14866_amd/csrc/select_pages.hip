@@ -490,15 +490,16 @@ __global__ __launch_bounds__(kWave* WAVES) void topk_pages_ballot_kernel(LayerPa
 
 // The whole of a selector run whose budget covers the page table, and with it every sequence: lists are all pages, and of the
 // statistics only what is out of date is rebuilt, as page_score_kernel would.  One launch for two: a pass of four steps on one sequence of 4000 tokens
-// 58.7 -> 55.8 us, on eight of 3000 91.7 -> 88.6.  gridDim.y workgroups to a list share out its logical pages from the first that is out of
-// date, sixteen to a turn.
+// 58.7 -> 55.8 us, on eight of 3000 91.7 -> 88.6.  gridDim.z workgroups to a list share out its logical pages from the first that is out of
+// date, sixteen to a turn; the first of every list, which as a rule has all there is to do, come first.
 template <class T>
 __global__ __launch_bounds__(256) void select_all_kernel(LayerParams lp, PagedParams kv, int K, const int* __restrict__ stats_valid_len,
                                                          int* __restrict__ sel_pages, int* __restrict__ sel_count, int* __restrict__ sel_seq_len) {
-    const int list = blockIdx.x, b = list / lp.Hkv, hk = list % lp.Hkv, tid = threadIdx.x;
+    // (heads in turn: a workgroup's number says which XCD it goes to, and streaming heads have no statistics)
+    const int b = blockIdx.y, turn = blockIdx.z, hk = (blockIdx.x + b + turn) % lp.Hkv, list = b * lp.Hkv + hk, tid = threadIdx.x;
     const int L = kv.seq_lens[b], fresh_below = stats_valid_len ? stats_valid_len[b] : L;
     const bool streaming = (lp.streaming_mask >> hk) & 1ull;
-    if (blockIdx.y == 0) {
+    if (turn == 0) {
         const int count = streaming ? 0 : min(ceil_div(L, lp.NP), K);
         for (int i = tid; i < K; i += 256) sel_pages[(size_t)list * K + i] = i < count ? i : -1;
         if (tid == 0) {
@@ -507,24 +508,28 @@ __global__ __launch_bounds__(256) void select_all_kernel(LayerParams lp, PagedPa
         }
     }
     if (streaming || fresh_below >= L) return;
-    const int end = min(ceil_div(L, lp.NL), kv.max_pages * lp.g), c = tid % 16, rank = pool_rank(lp, kv, hk, false), step = gridDim.y * 16;
+    const int nl = __builtin_ctz(lp.NL), g = __builtin_ctz(lp.g);  // both divide the page, a power of two
+    const int end = min((L + lp.NL - 1) >> nl, kv.max_pages << g), c = tid % 16, rank = pool_rank(lp, kv, hk, false), step = gridDim.z * 16;
     const int* pages = kv.page_table + (size_t)b * kv.max_pages;
-    int logical = max(fresh_below, 0) / lp.NL + blockIdx.y * 16 + tid / 16;
-    int page = logical < end ? pages[logical / lp.g] : 0;
+    int logical = (max(fresh_below, 0) >> nl) + turn * 16 + tid / 16;
+    int page = logical < end ? pages[logical >> g] : 0;
     for (; logical < end; logical += step) {
-        const int lo = logical * lp.NL, p = logical / lp.g, j = logical - p * lp.g;
+        const int lo = logical << nl, j = logical & (lp.g - 1);
         const size_t ph = (size_t)page * kv.pool_heads + rank;
-        if (logical + step < end) page = pages[(logical + step) / lp.g];  // requested a turn ahead
+        if (logical + step < end) page = pages[(logical + step) >> g];  // requested a turn ahead
         uint4 mx, mn;
-        rebuild_rows<T>(reinterpret_cast<const uint4*>(kv.k_pool) + (ph * lp.NP + j * lp.NL) * (kHeadDim / 8) + c, min(lp.NL, L - lo), mx, mn);
+        rebuild_rows<T>(reinterpret_cast<const uint4*>(kv.k_pool) + (ph * lp.NP + (j << nl)) * (kHeadDim / 8) + c, min(lp.NL, L - lo), mx, mn);
         uint4* st = reinterpret_cast<uint4*>(kv.stats) + (ph * lp.g + j) * 2 * (kHeadDim / 8);
         st[c] = mx;
         st[kHeadDim / 8 + c] = mn;
     }
 }
 
-// Is a selector run that launch?  Up to kMostLogical logical pages to a list; `share` workgroups to a list: as a rule a few tokens are out of
-// date, which the first finds, but all may be, so as many as the chip holds (kSelectAllBlocks) and a list has work for.
+// Is a selector run that launch?  Up to kMostLogical logical pages to a list.  As a rule a few tokens are out of date, which a list's first
+// workgroup finds, but all may be: as many to a list as it has work for and the chip has room for (kSelectAllBlocks; one for every sixteen
+// logical pages of the table, as it was at first, cost batches more than the scan and the ranking).  By scan and ranking, by a workgroup for
+// every sixteen, and now, us, four tokens out of date: one sequence of 63 pages, 8 heads, 5.6, 3.3 and 3.3; 16 of 64 5.8, 3.3 and 3.5; 64 of
+// 96 7.3, 8.7 and 4.0; 32 of 96, 32 heads, 10.6, 15.4 and 4.2; 32 of 2048 14.7, 69 and 3.9; all out of date, 64 of 64, 57, 61 and 48.
 constexpr int kMostLogical = 16384, kSelectAllBlocks = 2048;
 bool selects_all(const LayerParams& lp, const PagedParams& kv, int budget_pages) {
     return kv.max_pages <= budget_pages && (long long)kv.max_pages * lp.g <= kMostLogical;
@@ -577,7 +582,7 @@ hipError_t launch_select_pages(int dtype, const LayerParams& lp, const PagedPara
                                float* scores, bool scores_is_user_buffer, const HeadList& selecting,
                                hipStream_t stream) {
     if (!scores_is_user_buffer && selects_all(lp, kv, budget_pages)) {
-        const dim3 grid(kv.batch * lp.Hkv, stats_valid_len ? select_all_share(lp, kv) : 1);
+        const dim3 grid(lp.Hkv, kv.batch, stats_valid_len ? select_all_share(lp, kv) : 1);
         if (dtype == 0)
             hipLaunchKernelGGL(select_all_kernel<F16>, grid, dim3(256), 0, stream, lp, kv, budget_pages, stats_valid_len, sel_pages, sel_count, sel_seq_len);
         else
