@@ -159,6 +159,7 @@ struct PrefillPieces {
     float* partials;  // kPieceFloats for every piece, pieces of a (KV head, group of query heads) next to each other
     int target;       // pieces of a (KV head, group of query heads) in the launch, at most
     int least;        // of a block
+    int short_blocks; // a batch whose sequences have no more blocks than this is left to whole walks (see fold_and_streams_kernel)
 };
 struct PrefillSchedule {
     HeadClass cls[2];  // dense, streaming
@@ -521,7 +522,8 @@ template <class T, int MODE, int BITS, int SL, int KIND>
 __device__ __forceinline__ void prefill_workgroup(
     const LayerParams& lp, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int* __restrict__ cu_seqlens, int batch, uint16_t* __restrict__ out,
-    float* __restrict__ lse_out, int total_tokens, const PrefillSchedule& sched, const PrefillMask& mk, const PrefillPaged& pg) {
+    float* __restrict__ lse_out, int total_tokens, const PrefillSchedule& sched, const PrefillMask& mk, const PrefillPaged& pg,
+    int number) {  // of the workgroup in the launch
     constexpr bool MASKED = MODE == kMasked, PAGED = MODE == kPaged, QUANT = BITS != 16;
     constexpr bool CUT = KIND == kCut, HALF = KIND == kHalf || KIND == kHasty, ROWS = MASKED && (SL > 1 || HALF);  // ROWS: lists are the caller's rows
     constexpr int kWaves = HALF ? kPrefillWaves / 2 : kPrefillWaves;
@@ -557,8 +559,8 @@ __device__ __forceinline__ void prefill_workgroup(
 #endif
 
     // heaviest query blocks first; see HeadClass for the XCD-aware order
-    const int xcd = blockIdx.x % kXcds;
-    int li = blockIdx.x / kXcds, hidx, hk, hg, rank;
+    const int xcd = number % kXcds;
+    int li = number / kXcds, hidx, hk, hg, rank;
     const bool second = li >= sched.cls[0].items_per_xcd;
     if (second) li -= sched.cls[0].items_per_xcd;
     const int heads_per_block = second ? sched.cls[1].heads_per_block : sched.cls[0].heads_per_block;
@@ -579,6 +581,7 @@ __device__ __forceinline__ void prefill_workgroup(
         const BlockOrder order =
             block_order(cu_seqlens, PAGED ? pg.kv.seq_lens : nullptr, PAGED && pg.k_new, batch, kTileLog2 + qtiles_log2);
         if (CUT && !second) {
+            if (order.top() <= sched.pieces.short_blocks) return;
             plan = PiecePlan::make(order, sched.pieces, kLeastSpanTiles >> qtiles_log2);
             if (rank >= plan.total) return;
             plan.find(order, rank, piece, slot);
@@ -710,7 +713,7 @@ __device__ __forceinline__ void prefill_workgroup(
     // Reference of this lane's query row, in units of the unscaled products, and the sum of its weights relative to it.  The
     // reference is a maximum of the row's scores, but not always the latest (see weights_and_values).
     float m_run = -INFINITY, l_run = 0.f;
-    const bool first_on_unit = KIND == kHasty && (int)blockIdx.x < sched.compute_units;
+    const bool first_on_unit = KIND == kHasty && number < sched.compute_units;
     int unset = 1;  // some row of the wave has no reference yet
     // The score products start from -m_run instead of 0 (the accumulator input of the first product), so that scores come
     // relative to it at no cost; 0 while m_run = -inf.
@@ -1383,7 +1386,7 @@ __global__ __launch_bounds__(kPrefillThreads, 512 / kPrefillThreads) void sparse
     LayerParams lp, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int* __restrict__ cu_seqlens, int batch, uint16_t* __restrict__ out,
     float* __restrict__ lse_out, int total_tokens, PrefillSchedule sched, PrefillMask mk, PrefillPaged pg) {
-    prefill_workgroup<T, MODE, BITS, SL, kWhole>(lp, q, k, v, cu_seqlens, batch, out, lse_out, total_tokens, sched, mk, pg);
+    prefill_workgroup<T, MODE, BITS, SL, kWhole>(lp, q, k, v, cu_seqlens, batch, out, lse_out, total_tokens, sched, mk, pg, blockIdx.x);
 }
 // (a kernel of its own: the search for a piece takes scalar registers from the walk, 2 to 5 % of a launch of whole walks)
 template <class T, int BITS>
@@ -1391,7 +1394,7 @@ __global__ __launch_bounds__(kPrefillThreads, 512 / kPrefillThreads) void prefil
     LayerParams lp, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int* __restrict__ cu_seqlens, int batch, uint16_t* __restrict__ out,
     float* __restrict__ lse_out, int total_tokens, PrefillSchedule sched, PrefillMask mk, PrefillPaged pg) {
-    prefill_workgroup<T, kPaged, BITS, 1, kCut>(lp, q, k, v, cu_seqlens, batch, out, lse_out, total_tokens, sched, mk, pg);
+    prefill_workgroup<T, kPaged, BITS, 1, kCut>(lp, q, k, v, cu_seqlens, batch, out, lse_out, total_tokens, sched, mk, pg, blockIdx.x);
 }
 
 // Half workgroups: one does not have a compute unit to itself, so that its start and end, 5 us in which nothing else of it is under
@@ -1404,7 +1407,7 @@ __global__ __launch_bounds__(kPrefillThreads / 2, 2) void prefill_half_kernel(
     LayerParams lp, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int* __restrict__ cu_seqlens, int batch, uint16_t* __restrict__ out,
     float* __restrict__ lse_out, int total_tokens, PrefillSchedule sched, PrefillMask mk, PrefillPaged pg) {
-    prefill_workgroup<T, MODE, 16, 1, kHalf>(lp, q, k, v, cu_seqlens, batch, out, lse_out, total_tokens, sched, mk, pg);
+    prefill_workgroup<T, MODE, 16, 1, kHalf>(lp, q, k, v, cu_seqlens, batch, out, lse_out, total_tokens, sched, mk, pg, blockIdx.x);
 }
 
 // (a kernel of its own: the choice in every tile, or merely other code in front of the loop, moves the others by 1 to 3 %)
@@ -1413,20 +1416,19 @@ __global__ __launch_bounds__(kPrefillThreads / 2, 2) void prefill_hasty_kernel(
     LayerParams lp, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int* __restrict__ cu_seqlens, int batch, uint16_t* __restrict__ out,
     float* __restrict__ lse_out, int total_tokens, PrefillSchedule sched, PrefillMask mk, PrefillPaged pg) {
-    prefill_workgroup<T, kPlain, 16, 1, kHasty>(lp, q, k, v, cu_seqlens, batch, out, lse_out, total_tokens, sched, mk, pg);
+    prefill_workgroup<T, kPlain, 16, 1, kHasty>(lp, q, k, v, cu_seqlens, batch, out, lse_out, total_tokens, sched, mk, pg, blockIdx.x);
 }
 
 // Puts the pieces of cut walks together: four wavefronts per block and wavefront of its workgroups, one per 32
 // channels, which reads 4 KiB of every piece, kBatch pieces at a time.
 template <class T>
-__device__ __forceinline__ void fold_block(const LayerParams& lp, const int* __restrict__ cu_seqlens, const int* __restrict__ seq_lens,
-                                           int alongside, int batch, uint16_t* __restrict__ out, float* __restrict__ lse_out,
-                                           int total_tokens, const PrefillSchedule& sched, int wave, int rank, int hidx, int hg, int thread,
+__device__ __forceinline__ void fold_block(const LayerParams& lp, const BlockOrder& order, const int* __restrict__ cu_seqlens,
+                                           const int* __restrict__ seq_lens, int alongside, uint16_t* __restrict__ out,
+                                           float* __restrict__ lse_out, int total_tokens, const PrefillSchedule& sched, int wave, int rank, int hidx, int hg, int thread,
                                            unsigned char (&rows)[4][32 * 64]) {
     constexpr int kBatch = 8;
     const HeadClass& hc = sched.cls[0];
     const int hk = (int)(hc.kv_head[hidx / 4] >> (8 * (hidx % 4))) & 0xff;
-    const BlockOrder order = block_order(cu_seqlens, seq_lens, alongside, batch, kTileLog2 + hc.qtiles_log2);
     const PiecePlan plan = PiecePlan::make(order, sched.pieces, kLeastSpanTiles >> hc.qtiles_log2);
     int b, qblk;
     if (plan.total == 0 || !order.find(rank, b, qblk)) return;
@@ -1507,30 +1509,40 @@ __global__ __launch_bounds__(256) void fold_pieces_kernel(LayerParams lp, const 
                                                           int alongside, int batch, uint16_t* __restrict__ out, float* __restrict__ lse_out,
                                                           int total_tokens, PrefillSchedule sched) {
     __shared__ __attribute__((aligned(16))) unsigned char rows[4][32 * 64];
-    fold_block<T>(lp, cu_seqlens, seq_lens, alongside, batch, out, lse_out, total_tokens, sched, blockIdx.x % kPrefillWaves,
+    const BlockOrder order = block_order(cu_seqlens, seq_lens, alongside, batch, kTileLog2 + sched.cls[0].qtiles_log2);
+    fold_block<T>(lp, order, cu_seqlens, seq_lens, alongside, out, lse_out, total_tokens, sched, blockIdx.x % kPrefillWaves,
                   blockIdx.x / kPrefillWaves, blockIdx.y, blockIdx.z, threadIdx.x, rows);
 }
 
 // The same next to the streaming heads of the call, where these are not in the launch of the pieces (see streams_apart): neither
-// fills the chip, and both are mostly latency.  First the workgroups of the streaming heads, `streams` deals them out, then those that fold, two
+// fills the chip, and both are mostly latency.  First the workgroups of the streaming heads, `uncut` deals them out, then those that fold, two
 // of fold_block's side by side.  Two launches of 13 and 11 us were 10 us longer: 512 tokens over 32768
 // 154 -> 144 us, 128 over 20000 of 8 bits 78 -> 71.
+//
+// Pieces are chosen for histories that the page table has room for, and a table may be far wider than its sequences.  Where these are short
+// (PrefillPieces::short_blocks), the launch of the pieces ends at once and the workgroups that would fold walk the dense heads, as the
+// call without scratch does.
 template <class T, int BITS, int SL>
 __global__ __launch_bounds__(kPrefillThreads, 512 / kPrefillThreads) void fold_and_streams_kernel(
     LayerParams lp, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int* __restrict__ cu_seqlens, int batch, uint16_t* __restrict__ out, float* __restrict__ lse_out, int total_tokens,
-    PrefillSchedule streams, PrefillMask mk, PrefillPaged pg, PrefillSchedule sched) {
-    const int i = blockIdx.x - kXcds * streams.cls[1].items_per_xcd;
-    if (i < 0) {
-        prefill_workgroup<T, kPaged, BITS, SL, kWhole>(lp, q, k, v, cu_seqlens, batch, out, lse_out, total_tokens, streams, mk, pg);
+    PrefillSchedule uncut, PrefillMask mk, PrefillPaged pg, PrefillSchedule sched) {
+    const int dense = kXcds * uncut.cls[0].items_per_xcd, i = blockIdx.x - kXcds * uncut.cls[1].items_per_xcd;
+    BlockOrder order;
+    if (i >= 0) order = block_order(cu_seqlens, pg.kv.seq_lens, pg.k_new != nullptr, batch, kTileLog2 + sched.cls[0].qtiles_log2);
+    if (i < 0 || order.top() <= sched.pieces.short_blocks) {
+        if (i >= dense) return;
+        prefill_workgroup<T, kPaged, BITS, SL, kWhole>(lp, q, k, v, cu_seqlens, batch, out, lse_out, total_tokens, uncut, mk, pg,
+                                                       i < 0 ? (int)blockIdx.x + dense : i);
         return;
     }
     __shared__ __attribute__((aligned(16))) unsigned char rows[2][4][32 * 64];
     constexpr int kPerBlock = kPrefillWaves / 2;
     const int side = __builtin_amdgcn_readfirstlane(threadIdx.x / 256), of_head = sched.cls[0].blocks * kPerBlock;
-    const int at = i % of_head, head = i / of_head;
-    fold_block<T>(lp, cu_seqlens, pg.kv.seq_lens, pg.k_new != nullptr, batch, out, lse_out, total_tokens, sched,
-                  at % kPerBlock * 2 + side, at / kPerBlock, head % sched.cls[0].heads, head / sched.cls[0].heads, threadIdx.x % 256, rows[side]);
+    const int at = i % of_head, head = i / of_head, hg = head / sched.cls[0].heads;
+    if (hg * sched.cls[0].heads_per_block >= lp.group) return;
+    fold_block<T>(lp, order, cu_seqlens, pg.kv.seq_lens, pg.k_new != nullptr, out, lse_out, total_tokens, sched, at % kPerBlock * 2 + side,
+                  at / kPerBlock, head % sched.cls[0].heads, hg, threadIdx.x % 256, rows[side]);
 }
 
 // ---- quantised history as 16-bit pages ------------------------------------------------------------
@@ -1650,6 +1662,9 @@ constexpr float kStepWithoutRows = 0.78f;
 constexpr float kStartUs[2] = {5.2f, 5.8f}, kStartOfSlices[3] = {0.f, 0.5f, 0.55f}, kFoldUs = 0.44f, kLaunchUs = 2.2f;
 // past the even share of the work: a part of the last streaming walk, or of the longest dense one
 constexpr float kTailOfStream = 0.55f, kTailOfDense = 0.14f;
+
+// Blocks less or more than the mean, where their number is an estimate.
+float spread_of(const PrefillRows& rows) { return 0.4f * std::sqrt((float)rows.batch); }
 
 // One class of heads of a launch: workgroups per XCD and what they cost.
 struct ClassCost {
@@ -1830,6 +1845,26 @@ bool halves_are_quicker(const LayerParams& lp, const PrefillRows& rows, const Pr
     return together <= 256.f || (together <= 400.f && walks.mid <= 20.f);
 }
 
+// Key tiles of history up to which whole walks, after a launch of pieces that ends at once (4 to 6 us), are quicker than the pieces of
+// `shape`, by these estimates.  Up to some kWholeUs only: in a longer call that launch is little, and a wrong estimate much (one call in 60
+// was slower, by up to 1.7 times).  Measured, 900 chunks over 300 .. 131000 tokens that go in pieces, tables 1, 2, 4, 8 and 32 times as wide
+// as needed, time as a part of whole walks', always in pieces and now: 0.33, 0.42, 0.495, 0.53, 0.64 and 0.33, 0.42, 0.49, 0.51, 0.59, at worst
+// 2.2 and 1.4.  Seven of 2 to 17 tokens over 1214 of 8 bits, 64 / 8 heads, table eight times as wide: 78 and 62 us, whole 57.
+float whole_walks_until(const LayerParams& lp, const PrefillRows& rows, bool quant, const PrefillShape& uncut, const PrefillShape& shape) {
+    constexpr float kSkippedUs = 4.f, kCutShort = 1.1f, kWholeUs = 80.f;
+    const int n_stream = count_streaming(lp), heads[2] = {lp.Hkv - n_stream, n_stream}, units_per_xcd = std::max(1, num_compute_units() / kXcds);
+    const float spread = spread_of(rows), per_xcd = (float)(shape.pieces * heads[0] * (lp.group / heads_per_block(lp, shape, 0))) / kXcds;
+    const ClassCost whole[2] = {class_cost(lp, uncut, rows, 0, heads[0], quant, 0, spread), class_cost(lp, uncut, rows, 1, heads[1], quant, 0, spread)};
+    const ClassCost cut[2] = {class_cost(lp, shape, rows, 0, heads[0], quant, 0, spread), whole[1]};
+    float until = 0.f;
+    for (float history = 4.f; history <= (float)rows.history_pages; history *= 1.2f) {
+        const float t = launch_time(lp, rows, history, whole, units_per_xcd);
+        if (t > kWholeUs) break;
+        if (t + kSkippedUs < kCutShort * cut_launch_time(lp, rows, history, cut, units_per_xcd, per_xcd, shape.least, true)) until = history;
+    }
+    return until;
+}
+
 constexpr float kWeight[4] = {4.f, 1.f, 1.f, 1.f};  // of the guesses
 
 // The shape of a launch.  Measured with one / two / four slices: 512 new tokens over a history of 32768, 849 / 520 / 363 us;
@@ -1857,7 +1892,7 @@ PrefillShape choose_shape(const LayerParams& lp, const PrefillRows& rows, bool q
     // a walk of one or two tiles leaves nothing to share out; quantised pages are not built for four slices
     const int count = prompt && rows.longest <= 2 * kTile ? 2 : quant ? kCount - 1 : kCount;
     const int guesses = prompt ? 1 : 4;
-    const float spread = 0.4f * std::sqrt((float)rows.batch);
+    const float spread = spread_of(rows);
     // pieces per (KV head, group of query heads), and per XCD, of launches of one, two ... rounds (0: not to be had)
     int pieces[kRounds] = {};
     float per_xcd[kRounds] = {};
@@ -2028,7 +2063,7 @@ MaskWalk choose_mask_walk(const LayerParams& lp, int batch, int total_tokens, in
 PrefillSchedule make_schedule(const LayerParams& lp, const PrefillShape& shape, int max_rows, int total_rows, bool any_start,
                               int batch, bool single_rows = false) {
     PrefillSchedule sched;
-    sched.pieces = {nullptr, shape.pieces, shape.least};
+    sched.pieces = {nullptr, shape.pieces, shape.least, 0};
     sched.compute_units = num_compute_units();
     for (int c = 0; c < 2; ++c) {
         HeadClass& hc = sched.cls[c];
@@ -2077,6 +2112,7 @@ struct PrefillLaunch {
     const uint16_t *q, *k, *v;
     const int* cu_seqlens;
     int batch, total_tokens, max_rows;
+    PrefillRows rows;  // (of chunks)
     uint16_t* out;
     float* lse_out;
     PrefillSchedule sched;
@@ -2131,8 +2167,12 @@ hipError_t launch_chunk(PrefillLaunch& a, const ChunkPlan& plan, void* scratch) 
     if (!plan.shape.pieces) return launch_whole<T, BITS>(a, plan.shape);
     a.sched.pieces.partials = reinterpret_cast<float*>(scratch);
     const bool apart = streams_apart(*a.lp, plan.uncut);
-    if (apart) a.sched.cls[1].items_per_xcd = 0;
     const HeadClass& dense = a.sched.cls[0];
+    if (apart) {
+        a.sched.cls[1].items_per_xcd = 0;
+        const int until = (int)whole_walks_until(*a.lp, a.rows, BITS != 16, plan.uncut, plan.shape);
+        if (until > 0) a.sched.pieces.short_blocks = (until + ceil_div(a.max_rows, kTile)) >> dense.qtiles_log2;
+    }
     hipLaunchKernelGGL((prefill_pieces_kernel<T, BITS>), dim3(kXcds * (dense.items_per_xcd + a.sched.cls[1].items_per_xcd)),
                        dim3(kPrefillThreads), 0, a.stream, *a.lp, a.q, a.k, a.v, a.cu_seqlens, a.batch, a.out, a.lse_out, a.total_tokens,
                        a.sched, a.mk, a.pg);
@@ -2145,12 +2185,11 @@ hipError_t launch_chunk(PrefillLaunch& a, const ChunkPlan& plan, void* scratch) 
                            a.sched);
         return hipGetLastError();
     }
-    PrefillSchedule streams = make_schedule(*a.lp, plan.uncut, a.max_rows, a.total_tokens, true, a.batch);
-    streams.cls[0].items_per_xcd = 0;
-    const int grid = kXcds * streams.cls[1].items_per_xcd + dense.blocks * (kPrefillWaves / 2) * heads;
+    const PrefillSchedule uncut = make_schedule(*a.lp, plan.uncut, a.max_rows, a.total_tokens, true, a.batch);
+    const int grid = kXcds * uncut.cls[1].items_per_xcd + std::max(dense.blocks * (kPrefillWaves / 2) * heads, kXcds * uncut.cls[0].items_per_xcd);
     auto launch = [&](auto slices) {
         hipLaunchKernelGGL((fold_and_streams_kernel<T, BITS, decltype(slices)::value>), dim3(grid), dim3(kPrefillThreads), 0, a.stream, *a.lp, a.q,
-                           a.k, a.v, a.cu_seqlens, a.batch, a.out, a.lse_out, a.total_tokens, streams, a.mk, a.pg, a.sched);
+                           a.k, a.v, a.cu_seqlens, a.batch, a.out, a.lse_out, a.total_tokens, uncut, a.mk, a.pg, a.sched);
         return hipGetLastError();
     };
     if constexpr (BITS == 16) {
@@ -2242,7 +2281,7 @@ hipError_t launch_prefill_paged(const LayerParams& lp, const PagedParams& kv, co
     a.pg.v_new = reinterpret_cast<const uint16_t*>(v_new);
     a.stream = stream;
     const int pages = max_seqlen > 0 ? std::min(kv.max_pages, (max_seqlen - 1) / kTile + 1) : kv.max_pages;
-    const PrefillRows rows = chunk_rows(kv.batch, total_new, max_new_per_seq, pages);
+    const PrefillRows rows = a.rows = chunk_rows(kv.batch, total_new, max_new_per_seq, pages);
     ChunkPlan plan = plan_chunk(lp, rows, kv.max_pages, kv.kv_bits != 16, workspace && workspace_bytes > 0);
     if (plan.bytes > workspace_bytes) plan = plan_chunk(lp, rows, kv.max_pages, kv.kv_bits != 16, false);
     a.sched = make_schedule(lp, plan.shape, max_new_per_seq, total_new, true, kv.batch);
