@@ -526,8 +526,8 @@ __global__ __launch_bounds__(256) void select_all_kernel(LayerParams lp, PagedPa
 }
 
 // Is a selector run that launch?  Up to kMostLogical logical pages to a list.  As a rule a few tokens are out of date, which a list's first
-// workgroup finds, but all may be: as many to a list as it has work for and the chip has room for (kSelectAllBlocks; one for every sixteen
-// logical pages of the table, as it was at first, cost batches more than the scan and the ranking).  By scan and ranking, by a workgroup for
+// workgroup finds, but all may be: as many to a list as it has work for, up to kSelectAllBlocks in all (64 sequences of 96 pages, 8 heads: 3.6 us with
+// 2048, 4.2 with 1024, 4.7 with 4096; one for every sixteen logical pages of the table cost batches more than scan and ranking).  By scan and ranking, by a workgroup for
 // every sixteen, and now, us, four tokens out of date: one sequence of 63 pages, 8 heads, 5.6, 3.3 and 3.3; 16 of 64 5.8, 3.3 and 3.5; 64 of
 // 96 7.3, 8.7 and 4.0; 32 of 96, 32 heads, 10.6, 15.4 and 4.2; 32 of 2048 14.7, 69 and 3.9; all out of date, 64 of 64, 57, 61 and 48.
 constexpr int kMostLogical = 16384, kSelectAllBlocks = 2048;

@@ -63,9 +63,24 @@ def test_prefill_kernels_use_no_scratch(kernels):
 
 def test_half_prefill_workgroups_go_two_to_a_compute_unit(kernels):
     """Four wavefronts each, one to a SIMD, and no scratch; chunks in pieces: no scratch either."""
-    halves = [k for name, k in kernels.items() if "prefill_half_kernel" in name]
-    assert len(halves) == 2 * 3  # types, (prompts, listed masks, pages)
+    halves = [k for name, k in kernels.items() if "prefill_half_kernel" in name or "prefill_hasty_kernel" in name]
+    assert len(halves) == 2 * (3 + 1)  # types, (prompts, listed masks, pages) and prompts whose longest walk goes first
     assert all(k[".vgpr_count"] <= 256 and k[".group_segment_fixed_size"] <= 80 * 1024 for k in halves)
     pieces = [k for name, k in kernels.items() if "pieces_kernel" in name]
     assert len(pieces) == 2 * (3 + 1)  # types, widths of the pages and the kernel that puts pieces together
     assert all(k[".private_segment_fixed_size"] == 0 and k[".vgpr_count"] <= 256 for k in halves + pieces)
+
+
+def test_fold_and_streams_use_no_scratch(kernels):
+    """The body of a whole walk in slices and that which puts pieces together, in one kernel of eight wavefronts."""
+    both = [k for name, k in kernels.items() if "fold_and_streams_kernel" in name]
+    assert len(both) == 2 * (2 + 1 + 1)  # types, 16-bit pages in two and four slices, 8- and 4-bit pages in two
+    assert all(k[".private_segment_fixed_size"] == 0 and k[".vgpr_count"] <= 256 for k in both)
+    assert all(k[".group_segment_fixed_size"] <= 160 * 1024 for k in both)
+
+
+def test_selector_runs_of_one_launch_use_no_scratch(kernels):
+    """Five workgroups of four wavefronts to a compute unit at most: 102 registers each."""
+    found = [k for name, k in kernels.items() if "select_all_kernel" in name]
+    assert len(found) == 2
+    assert all(k[".private_segment_fixed_size"] == 0 and k[".vgpr_count"] <= 102 for k in found)
