@@ -450,13 +450,20 @@ int lserve_probe_prefill_shape(const lserve_attn_desc *desc, int32_t batch, int3
 /*
  * What else there is to such a launch; arguments as above.
  *   scratch    0: without; else with what lserve_chunk_scratch_bytes asks for (chunks)
- *   plan       HOST, [6] out: key ranges, each with a running maximum of its own, in which the sums of a dense head's row are
+ *   plan       HOST, [6] out: key ranges, each with a softmax reference of its own, in which the sums of a dense head's row are
  *              taken, at least (its slices, or the pieces of its walk); the same of a streaming head's; 1 if the workgroups are half
  *              ones; the most pieces of a (KV head, group of query heads) where dense walks are cut into pieces, else 0; 1 if
  *              streaming heads are then in the launch that puts pieces together; 1 if quantised pages are first turned into 16-bit ones
  */
 int lserve_probe_prefill_plan(const lserve_attn_desc *desc, int32_t batch, int32_t total_rows, int32_t max_rows,
                               int32_t pages, int32_t kv_bits, int32_t scratch, int32_t *plan);
+
+/*
+ * The same for prompts (lserve_sparse_prefill): *first (HOST, out) is 1 if the first workgroup of every compute unit, which has the longest
+ * walks, has the higher wave priority.  No bit depends on it.
+ */
+int lserve_probe_prefill_longest_first(const lserve_attn_desc *desc, int32_t batch, int32_t total_rows, int32_t max_rows,
+                                       int32_t *first);
 
 /*
  * The same for lserve_sparse_prefill_masked with a mask of these sizes.

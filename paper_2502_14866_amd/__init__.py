@@ -28,6 +28,7 @@ from .binding import (  # noqa: F401
     lserve_last_hip_error,
     lserve_probe_decode_read,
     lserve_probe_mask_walk,
+    lserve_probe_prefill_longest_first,
     lserve_probe_prefill_plan,
     lserve_probe_prefill_shape,
     lserve_select_pages,

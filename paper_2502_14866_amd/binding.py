@@ -43,6 +43,7 @@ EXPORTED_SYMBOLS = (
     "lserve_probe_decode_read",
     "lserve_probe_prefill_shape",
     "lserve_probe_prefill_plan",
+    "lserve_probe_prefill_longest_first",
     "lserve_probe_mask_walk",
 )
 
@@ -133,6 +134,8 @@ def load_library():
         lib.lserve_probe_prefill_shape.restype = ctypes.c_int
         lib.lserve_probe_prefill_plan.argtypes = [dp, i32, i32, i32, i32, i32, i32, ctypes.POINTER(i32)]
         lib.lserve_probe_prefill_plan.restype = ctypes.c_int
+        lib.lserve_probe_prefill_longest_first.argtypes = [dp, i32, i32, i32, ctypes.POINTER(i32)]
+        lib.lserve_probe_prefill_longest_first.restype = ctypes.c_int
         lib.lserve_probe_mask_walk.argtypes = [dp, i32, i32, i32, i32, i32, i32, ctypes.POINTER(i32)]
         lib.lserve_probe_mask_walk.restype = ctypes.c_int
         lib.lserve_init.argtypes = []
@@ -477,12 +480,20 @@ def lserve_probe_prefill_shape(desc: AttnDesc, batch: int, total_rows: int, max_
 
 def lserve_probe_prefill_plan(desc: AttnDesc, batch: int, total_rows: int, max_rows: int, pages: int = 0, kv_bits: int = 16,
                               scratch: bool = True) -> dict:
-    """The rest of it: key ranges of a dense and of a streaming head's rows, half workgroups, pieces, streaming heads in a launch of
-    their own, expanded pages."""
+    """The rest of it: key ranges of a dense and of a streaming head's rows, half workgroups, pieces, streaming heads in the launch
+    that puts pieces together, expanded pages."""
     plan = (ctypes.c_int32 * 6)()
     _check(load_library().lserve_probe_prefill_plan(desc.c(), batch, total_rows, max_rows, pages, kv_bits, int(scratch), plan),
            "lserve_probe_prefill_plan")
     return dict(zip(("dense", "streaming", "half", "pieces", "apart", "expand"), plan))
+
+
+def lserve_probe_prefill_longest_first(desc: AttnDesc, batch: int, total_rows: int, max_rows: int) -> bool:
+    """Prompts: has the first workgroup of every compute unit, with the longest walks, the higher wave priority?"""
+    first = ctypes.c_int32()
+    _check(load_library().lserve_probe_prefill_longest_first(desc.c(), batch, total_rows, max_rows, ctypes.byref(first)),
+           "lserve_probe_prefill_longest_first")
+    return bool(first.value)
 
 
 def lserve_probe_mask_walk(desc: AttnDesc, batch: int, total_tokens: int, max_seqlen: int, num_masks: int, rows_per_mask: int,

@@ -33,6 +33,9 @@ void prefill_shape(const LayerParams& lp, int batch, int total_rows, int max_row
 // The rest of it (lserve_probe_prefill_plan).
 void prefill_plan(const LayerParams& lp, int batch, int total_rows, int max_rows, int pages, int kv_bits, bool scratch, int (&out)[6]);
 
+// Prompts: does the first workgroup of every compute unit go first (lserve_probe_prefill_longest_first)?
+bool prefill_longest_first(const LayerParams& lp, int batch, int total_rows, int max_rows);
+
 // How a launch under a listed mask walks it (lserve_probe_mask_walk).
 int mask_walk(const LayerParams& lp, int batch, int total_tokens, int max_seqlen, int masks, int rows_per_mask, int nnz);
 

@@ -364,6 +364,16 @@ int lserve_probe_prefill_plan(const lserve_attn_desc* desc, int32_t batch, int32
     return LSERVE_OK;
 }
 
+int lserve_probe_prefill_longest_first(const lserve_attn_desc* desc, int32_t batch, int32_t total_rows, int32_t max_rows, int32_t* first) {
+    LayerParams lp;
+    const int rc = make_layer(desc, &lp);
+    if (rc) return rc;
+    if (!first || batch <= 0 || total_rows <= 0 || max_rows <= 0 || max_rows > total_rows) return LSERVE_ERR_INVALID_ARG;
+    if (lp.NP != 64) return LSERVE_ERR_UNSUPPORTED;
+    *first = prefill_longest_first(lp, batch, total_rows, max_rows);
+    return LSERVE_OK;
+}
+
 int lserve_probe_mask_walk(const lserve_attn_desc* desc, int32_t batch, int32_t total_tokens, int32_t max_seqlen,
                            int32_t num_masks, int32_t rows_per_mask, int32_t nnz, int32_t* walk) {
     LayerParams lp;

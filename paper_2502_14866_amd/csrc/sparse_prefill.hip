@@ -2203,7 +2203,10 @@ hipError_t launch_chunk(PrefillLaunch& a, const ChunkPlan& plan, void* scratch) 
 // us a step where it would take 1.0 alone, and the chip runs empty around it (one prompt of 4096 tokens: 64 steps where an even share is
 // 42).  The first workgroup of every unit then has a higher wave priority throughout.  4096 tokens 103 -> 98 us, 4300 110 -> 104, 4200 of 32 / 16
 // heads 105 -> 100, 3900 of 32 / 32 94 -> 91.  Walks of fewer tiles lose 1 to 3 % (1600 tokens, 64 / 8 heads: 44.2 and 45.3), and so do launches
-// of more workgroups, whose units have other long walks to fill up with (4900 of 32 / 32, 2.4 to a unit, 123 and 126).
+// of more workgroups, whose units have other long walks to fill up with (4900 of 32 / 32, 2.4 to a unit, 123 and 126).  At the edges, time
+// with priority as a part of that without, 28 prompts and batches of 32 query heads, half of the KV heads streaming: 55 tiles, 1.7
+// workgroups to a unit 0.96, 63 to 72 tiles, 2.25 to a unit 0.95 to 0.99; just outside 47 tiles, 2.2 1.02, 32 tiles, 2.0 1.00 to 1.01, 74 tiles, 2.3 0.97
+// to 0.98, 77 tiles, 2.4 0.98 and 1.015, 2.5 and more 1.01 to 1.04.  (Fewer than 1.7 to a unit go in key slices.)
 bool longest_walk_decides(const PrefillSchedule& sched, int tiles) {
     const long long n = (long long)kXcds * sched.cls[0].items_per_xcd, units = sched.compute_units;
     return tiles >= 48 && 4 * n > 5 * units && 4 * n <= 9 * units;
@@ -2353,6 +2356,11 @@ void prefill_plan(const LayerParams& lp, int batch, int total_rows, int max_rows
     out[3] = plan.shape.pieces;
     out[4] = apart;
     out[5] = plan.expand;
+}
+
+bool prefill_longest_first(const LayerParams& lp, int batch, int total_rows, int max_rows) {
+    const PrefillShape shape = choose_shape(lp, {batch, total_rows, max_rows, -1}, false);
+    return shape.half && longest_walk_decides(make_schedule(lp, shape, max_rows, total_rows, false, batch), ceil_div(max_rows, kTile));
 }
 
 int mask_walk(const LayerParams& lp, int batch, int total_tokens, int max_seqlen, int masks, int rows_per_mask, int nnz) {

@@ -105,3 +105,31 @@ def test_half_workgroups_of_streaming_heads_alone():
     desc = L.AttnDesc(32, 8, [1] * 8)
     assert B.lserve_probe_prefill_plan(desc, 8, 16000, 2000)["half"] == 1  # 204 us and 220
     assert B.lserve_probe_prefill_plan(desc, 1, 51, 51)["half"] == 0       # 7.5 and 6.7
+
+
+@pytest.mark.parametrize("heads,kv_heads,lengths,first", [
+    (32, 8, (4096,), 1),        # 104 us with priority, 109 without
+    (32, 8, (3500,), 1),        # 88.6 and 92.5
+    (32, 32, (3500,), 1),       # 84.4 and 88.1
+    (32, 8, (4600,), 1),        # 122.5 and 125.8: two and a quarter workgroups to a unit
+    (32, 8, (4609,), 0),
+    (32, 32, (4900,), 0),       # 136.8 and 134.8
+    (32, 8, (4000, 500), 1),    # 100.7 and 105.5
+    (32, 8, (3500, 1500), 0),   # 98.5 and 95.4
+    (32, 8, (2000, 2000), 0),   # 62.8 and 63.1: walks of 32 tiles
+    (16, 8, (3000,) * 3, 0),    # 90.0 and 88.4: of 47
+    (64, 8, (4096,), 0),        # 189.9 and 185.5
+    (32, 8, (3000,), 0),        # goes in key slices
+])
+def test_priority_where_the_longest_walk_decides(heads, kv_heads, lengths, first):
+    desc = L.AttnDesc(heads, kv_heads, [1] * (kv_heads // 2) + [0] * (kv_heads // 2))
+    assert B.lserve_probe_prefill_longest_first(desc, len(lengths), sum(lengths), max(lengths)) == first
+
+
+def test_priority_arguments():
+    desc = L.AttnDesc(8, 2, [1, 0])
+    for bad in ((0, 1, 1), (1, 0, 1), (1, 10, 11), (1, 10, 0)):
+        with pytest.raises(LserveError):
+            B.lserve_probe_prefill_longest_first(desc, *bad)
+    with pytest.raises(LserveError):
+        B.lserve_probe_prefill_longest_first(L.AttnDesc(8, 2, [1, 0], page_size=32), 1, 10, 10)
