@@ -336,8 +336,9 @@ __device__ __forceinline__ BlockOrder block_order(const int* cu_seqlens, const i
 // Measured, whole walks in the best shape and pieces: 512 tokens over 32768, 32 / 8 heads, 338 and 144 us (8 pieces to a
 // block: 65 steps of 1.75 us with every compute unit at work, then 14 us to put 33 MB of pieces together, next to the streaming
 // heads, see streams_apart); 17 over 42116, twice, 441 and 79; 108 over 73893, 32 / 16 heads, 982 and 267.  Prompts are not cut: one of 4096
-// tokens takes 119 us whole and 124 or more in any number of pieces, one of 8192 313 and 340, because what they gain in balance (42
-// steps a compute unit where the longest walk has 64) goes into the starts of the pieces and into putting them together.
+// tokens took 119 us whole and 124 or more in any number of pieces, one of 8192 313 and 340, because what they gained in balance (42
+// steps a compute unit where the longest walk has 64) went into the starts of the pieces and into putting them together (with a running
+// maximum and a launch of its own for the fold; not measured since, 4096 tokens take 102 us whole).
 // No block is fewer pieces than the key slices it has without scratch (PrefillPieces::least), however short its walk: the weights of
 // a row are rounded to 16 bits relative to the maximum of their piece or slice, and fewer of these make the error larger.
 // A position in the launch stands for a piece: last pieces first (none is shorter than half a span), then the last but one,
@@ -1400,8 +1401,8 @@ __global__ __launch_bounds__(kPrefillThreads, 512 / kPrefillThreads) void prefil
 // Half workgroups: one does not have a compute unit to itself, so that its start and end, 5 us in which nothing else of it is under
 // way, and the time its wavefronts wait for each other at the end of a step go to the other's steps; short walks gain most, and
 // where heads of a group keep different tiles (listed masks) two share a walk more often than four.  It stages every tile for half
-// as many rows, which long walks pay for (see halves_are_quicker).  Whole and half, us: ten prompts of 327 tokens, 32 / 32 heads, 47 and 34; 16 of 527, 32 / 16,
-// 108 and 87; one of 4096, 32 / 8, 121 and 108; 16 of 77 .. 3001, 213 and 208; 65536, 15690 and 16220.
+// as many rows, which long walks pay for (see halves_are_quicker).  Whole and half, us: ten prompts of 327 tokens, 32 / 32 heads, 40.6 and 31.8; 13 of 215, 64 / 8,
+// 42.0 and 35.6; one of 4096, 32 / 8, 117 and 111; two of 1024 34.1 and 30.8; 65536, 15500 and 16070.
 template <class T, int MODE>
 __global__ __launch_bounds__(kPrefillThreads / 2, 2) void prefill_half_kernel(
     LayerParams lp, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
@@ -1648,8 +1649,10 @@ int heads_per_block(const LayerParams& lp, const PrefillShape& shape, int cls) {
     return heads;
 }
 
-// (Times behind the choices from here on were taken with a running maximum in the loop and rows stored as the lanes hold them; all launches are
-// 5 to 15 % shorter now and compare as they did, so the constants stay.)
+// (The constants from here on were fitted to a loop with a running maximum and to rows stored as the lanes hold them.  Since then steps are 4
+// to 7 % shorter and starts and ends by up to a third, which these estimates weigh against each other: launches are 4 to 17 % shorter, those of
+// many starts by most.  The constants have not been fitted again; over 900 chunks behind tables 1 to 32 times as wide as needed the estimates are
+// now 1.01 to 1.04 of the time of whole walks and 1.00 to 1.06 of that of pieces, by geometric mean.)
 //
 // The estimate behind the choice of a shape: a compute unit holds one workgroup at a time, an XCD deals its workgroups out
 // longest walk first, and a workgroup costs a fixed time and its steps.  Constants in microseconds, fitted to 2100 launches
@@ -1820,10 +1823,12 @@ bool streams_apart(const LayerParams& lp, const PrefillShape& whole) { return wh
 //   - there are more dense KV heads than XCDs, each of which then works on several heads' keys at a time, in many rounds (0.98 to 1.28: 18 of
 //     3001, 32 / 32 heads, 16 of them streaming 1352 and 1447, none 1880 and 2400; 64 of 500, none streaming, 370 and 401; 16 chunks of
 //     1000 over 500, none streaming, 458 and 499).
-// Since then starts and ends of workgroups are shorter, of half ones by more.  Over 3100 more batches, half as a part of whole: 0.89 in the middle
-// where half ones are taken (2 % slower or more in 41 of 2551); in the exceptions 0.96 for single tiles, 0.92 for one full round, 0.95 without a
-// streaming head, 1.03 in many rounds of many heads; 0.98 beyond 60 tiles.  What is left there, up to 5 % of the smallest prompts, is not taken: tests
-// state whole workgroups for these plans (lserve_probe_prefill_plan).
+// All of these times are from a loop with a running maximum and rows stored as the lanes hold them.  Steps, starts and ends are shorter
+// now, starts and ends of half workgroups by most, and the lines have not been drawn again.  Over 3100 more batches, half as a part of whole: 0.89
+// on average where half ones are taken (2 % slower or more in 41 of 2551); in the exceptions 0.96 for single tiles, 0.92 for one full round,
+// 0.95 without a streaming head, 1.03 in many rounds of many heads; 0.98 beyond 60 tiles.  So whole ones are kept in the first three
+// exceptions at a loss of 4 to 8 %, and in many rounds of many heads the line lies too far out (21 of 1888, 32 / 32 heads, 632 whole
+// and 691 half).
 bool halves_are_quicker(const LayerParams& lp, const PrefillRows& rows, const PrefillShape& whole) {
     const int n_stream = count_streaming(lp), heads[2] = {lp.Hkv - n_stream, n_stream};
     const PrefillShape half = {1, {false, false}, false, true, 0, 1};
@@ -2020,7 +2025,7 @@ enum MaskWalk { kMergedRows = 0, kRowSlices = 1, kRowHalves = 2 };
 // but one fewer than there are masks are of one mask, whoever has which.  (Merged, slices, halves: 12345 tokens at density 0.3, 32 / 8
 // heads, two masks in turn, 473, 530 and 329 us; 6330 tokens, twice, at 0.08, 64 / 8 heads, 466, 702 and 399; 5101 tokens at 0.35,
 // 8 / 2 heads, slices 54 where merged lists take 119; 519 tokens, twice, at 0.4, 32 and 28; a pattern of 65536 tokens whose rows
-// agree, 24 and 16 ms.  A second launch that walked blocks of little common row by row gained 2 to 9 % over merged lists above 10000
+// agree, 24 and 16 ms: times of a loop with a running maximum, as are the constants below; 12345 tokens in halves take 295 now.  A second launch that walked blocks of little common row by row gained 2 to 9 % over merged lists above 10000
 // tokens and lost up to 30 % below.  Two heads to a row in two slices: 392 us at 12345 tokens, but 41 where halves take 47 at 2907,
 // twice, 8 / 2 heads; not kept for that.)
 MaskWalk choose_mask_walk(const LayerParams& lp, double tiles, double longest, double row, int masks) {
