@@ -31,12 +31,11 @@ def assert_attention_close(got: torch.Tensor, ref: np.ndarray, what: str = ""):
     return max_abs, max_rel
 
 
-# Log-sum-exp.  Decode keeps the query exact: 2e-3.  Prefill rounds the query times the softmax scale to the
-# storage type (unit roundoff u = 2^-11 for fp16, 2^-8 for bf16), which moves a logit of 128 N(0,1) products by
-# about 0.58 u (one sigma) and the log-sum-exp by at most the largest logit move: four sigma is 1.1e-3 for fp16
-# and 9e-3 for bf16, and the bound is that four-sigma figure (fp16 keeps the 2e-3 of the output bound).
+# Log-sum-exp.  Decode adds up weights in fp32: 2e-3.  Prefill adds up the weights as they are rounded to the storage type, each off by up to the
+# unit roundoff u of its value (2^-11 for fp16, 2^-8 for bf16), so the sum is off by u at most and its logarithm likewise.  Queries and
+# keys are exact; fp32 products of logits up to some hundreds, their exponentials and sums take 2e-4 more.
 LSE_TOL_DECODE = 2e-3
-LSE_TOL_PREFILL = {"fp16": 2e-3, "bf16": 9e-3}
+LSE_TOL_PREFILL = {"fp16": 2.0 ** -11 + 2e-4, "bf16": 2.0 ** -8 + 2e-4}
 
 # Largest errors seen by the assertions of the running test: (what, kind, max abs, max row-relative or 0).
 # tests/conftest.py prints them after each test so that a run's log records the margins, not only pass / fail.

@@ -14,7 +14,7 @@ CASES = [  # heads, KV heads, history, new tokens
     (64, 8, (2047,), (400,)),
     (8, 1, (3001,), (300,)),                      # no streaming head
     (32, 8, (4400, 4100), (2500, 2600)),          # whole workgroups in one slice over the 16-bit pages
-    # dense walks over the 16-bit pages cut into pieces, streaming heads in a launch of their own
+    # dense walks over the 16-bit pages cut into pieces, streaming heads in the launch that puts them together
     (32, 8, (16001,), (512,)),
     (8, 2, (30000,), (1500,)),
     (12, 4, (30001,), (900,)),                    # groups of three
