@@ -1094,7 +1094,7 @@ __device__ __forceinline__ void prefill_workgroup(
 #pragma unroll
                 for (int j = 0; j < 2; ++j) sums = Mfma<T>::run16(own_rows, pb[kb][j], sums);
             sum = sums[0];
-            if (!__any(!(sum < kMostWeight))) break;
+            if (__builtin_expect(!__any(!(sum < kMostWeight)), 1)) break;
             // A weight that is infinite or not a number spoils the sum of the other query of its column: once more without the rows
             // that have one.
             if (__any(!(sum < INFINITY))) {
