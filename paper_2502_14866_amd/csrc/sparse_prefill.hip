@@ -1223,8 +1223,6 @@ __device__ __forceinline__ void prefill_workgroup(
     }
     __syncthreads();
     if constexpr (!kOneStage) {
-        // (where the loop starts within 64 bytes of code moves half workgroups by up to 2 % either way)
-        if constexpr (HALF) asm volatile(".p2align 6");
         for (int st = 0; st < steps; st += 2) {
             tile_step(it_first + st * stride, k_lds0, v_lds0, k_lds1, v_lds1);
             if (st + 1 >= steps) break;
